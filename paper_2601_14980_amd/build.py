@@ -32,6 +32,7 @@ UNITS = {
     "kernels_batch.hip": [],
     "kernels_mfma.hip": [],
     "kernels_matvec.hip": [],
+    "kernels_rns.hip": [],
     "kernels_quant.hip": ["-ffp-contract=off"],
     "kernels_admm.hip": ["-ffp-contract=off"],
     "kernels_colsplit.hip": ["-ffp-contract=off"],

@@ -12,6 +12,8 @@
 #include "host_bn.hpp"
 #include "launch.hpp"
 #include "pc2_types.hpp"
+#include "rns_host.hpp"
+#include "rns_launch.hpp"
 
 using pc2h::Limbs;
 
@@ -30,6 +32,7 @@ struct pc2_ctx {
   int occ[pc2k::NUM_GEOS][pc2k::OP_COUNT] = {};    // workgroups per CU (0 = not queried)
   int tuned[pc2k::NUM_GEOS][pc2k::OP_COUNT] = {};  // autotuned windows (0 = none)
   int tuned_geo[pc2k::NUM_CLASSES] = {-1, -1, -1, -1, -1, -1, -1, -1, -1};  // encryption tile
+  int rocc[pc2k::RNS_NT][pc2k::RNS_NBMAX + 1] = {};  // RNS powering: workgroups per CU
 };
 
 struct pc2_runner {
@@ -122,6 +125,7 @@ struct pc2_pk {
   void* dev = nullptr;  // one allocation holding every constant
   pc2k::PkConst c{};
   pc2k::PkConst alt{};  // n^2 constants in the alternative tile (ALT_GEO[cls] >= 0)
+  pc2k::RnsKey rn{};    // modulo n^2, power n (T = 0: not on the RNS engine)
 };
 
 struct pc2_sk {
@@ -130,6 +134,8 @@ struct pc2_sk {
   void* dev = nullptr;
   pc2k::SkConst c{};
   bool crt_ok = false;  // p < 2 q: the key-holder encryption's inputs fit mod q^2
+  pc2k::RnsKey dec[2]{};  // modulo p^2, q^2: power s - 1, output times MA^-1
+  pc2k::RnsKey enc[2]{};  // ... power n mod s (s - 1), 1 + m n
 };
 
 namespace {
@@ -387,6 +393,96 @@ pc2k::PkConst pk_const_alt(const uint32_t* base, const PkOffsets& o, const pc2k:
   return a;
 }
 
+// ---------------------------------------------------------- RNS engine keys
+struct RnsOffsets {
+  int T = 0;
+  size_t E1, E2, c1, c2, kb, ka;
+  struct To { size_t P, add, m; int nhalf; } x, gm;
+  struct From { size_t C, D, O, N28, F; int S, nblk; double ntop_inv; } from;
+  size_t ops[5];
+};
+size_t add_aligned(DevBuf& buf, const std::vector<uint32_t>& w) {
+  while (buf.words.size() % 64) buf.words.push_back(0);  // 256 bytes
+  return buf.add(w);
+}
+RnsOffsets::To add_rns_to(DevBuf& buf, const pc2h::RnsToHost& h) {
+  return {add_aligned(buf, h.P), add_aligned(buf, h.add), add_aligned(buf, h.m), h.nhalf};
+}
+// Powers x^e modulo N (N of `tiles`), x of nhalf 16-bit halves; f2 != null: a
+// second input 1 + m f2 (m of mhalf halves) closes the product, else the
+// result leaves Montgomery form on output.  E2, c2, kb and ka depend on the
+// tile count alone: `same` (null: none) names a modulus whose copies to use.
+// T = 0 in the result: the engine does not take this modulus.
+RnsOffsets add_rns(DevBuf& buf, const Limbs& N, int T, const Limbs& e, int nhalf, const Limbs* f2,
+                   int mhalf, const RnsOffsets* same) {
+  RnsOffsets o;
+  if (T == 0) return o;
+  const pc2h::RnsBase& R = pc2h::rns_base(T);
+  std::vector<uint32_t> E1, c1;
+  if (!pc2h::rns_e1(R, N, &E1, &c1)) return o;
+  std::vector<uint32_t> prog[5];
+  for (int w = pc2k::SCHED_WMIN; w <= pc2k::SCHED_WMAX; ++w) {
+    prog[w - pc2k::SCHED_WMIN] = pc2h::rns_program(sliding_schedule(e, w), w, f2 != nullptr);
+    if (prog[w - pc2k::SCHED_WMIN].empty()) return o;
+  }
+  o.E1 = add_aligned(buf, E1);
+  o.c1 = add_aligned(buf, c1);
+  if (same && same->T == T) {
+    o.E2 = same->E2;
+    o.c2 = same->c2;
+    o.kb = same->kb;
+    o.ka = same->ka;
+  } else {
+    o.E2 = add_aligned(buf, R.E2);
+    o.c2 = add_aligned(buf, R.c2);
+    o.kb = add_aligned(buf, R.kb);
+    o.ka = add_aligned(buf, R.ka);
+  }
+  o.x = add_rns_to(buf, pc2h::rns_to(R, N, R.MA, nhalf, false));
+  if (f2) o.gm = add_rns_to(buf, pc2h::rns_to(R, N, *f2, mhalf, true));
+  const pc2h::RnsFromHost h = pc2h::rns_from(R, N, f2 == nullptr);
+  std::vector<uint32_t> F;
+  for (int64_t v : h.F) {
+    F.push_back((uint32_t)v);
+    F.push_back((uint32_t)((uint64_t)v >> 32));
+  }
+  o.from = {add_aligned(buf, h.C), add_aligned(buf, h.D), add_aligned(buf, h.O),
+            add_aligned(buf, h.N28), add_aligned(buf, F), h.S, h.nblk, h.ntop_inv};
+  for (int i = 0; i < 5; ++i) o.ops[i] = add_aligned(buf, prog[i]);
+  o.T = T;
+  return o;
+}
+pc2k::RnsTo rns_to_const(const uint32_t* base, const RnsOffsets::To& t) {
+  return {base + t.P, base + t.add, base + t.m, t.nhalf};
+}
+pc2k::RnsKey rns_const(const uint32_t* base, const RnsOffsets& o, int nw) {
+  pc2k::RnsKey k{};
+  if (o.T == 0) return k;
+  k.T = o.T;
+  k.M = {(const uint8_t*)(base + o.E1), (const uint8_t*)(base + o.E2),
+         (const int32_t*)(base + o.c1), (const int32_t*)(base + o.c2), base + o.kb, base + o.ka};
+  k.x = rns_to_const(base, o.x);
+  if (o.gm.nhalf) k.gm = rns_to_const(base, o.gm);
+  k.from = {base + o.from.C, base + o.from.D, base + o.from.O, base + o.from.N28,
+            (const int64_t*)(base + o.from.F), o.from.S, o.from.nblk, nw, o.from.ntop_inv};
+  for (int i = 0; i < 5; ++i) k.ops[i] = base + o.ops[i];
+  return k;
+}
+// Tile count of a modulus of a key of class cls, 0 below 1024-bit keys (where
+// the VALU engine's products are short) and for a modulus far below its
+// class's size (the output conversion reads its four top limbs).
+constexpr int RNS_MIN_CLASS = 5;
+int rns_tiles_for(int cls, const Limbs& N) {
+  const int bits = pc2h::bitlen(N);
+  return cls >= RNS_MIN_CLASS && bits >= 512 ? pc2h::rns_tiles(bits) : 0;
+}
+
+RnsOffsets add_rns_public(DevBuf& buf, const Limbs& n, int cls, int L) {
+  Limbs n2 = pc2h::mul(n, n);
+  pc2h::trim(n2);
+  return add_rns(buf, n2, rns_tiles_for(cls, n2), n, 2 * L, &n, 2 * L, nullptr);
+}
+
 struct HalfOffsets {
   ModOffsets s2;
   size_t s, e, sinv, H;
@@ -576,6 +672,80 @@ int prepare(pc2_ctx* ctx, int geo, int op, size_t count, int Ls, int L, pc2k::La
   return PC2_OK;
 }
 
+// ------------------------------------------------------------- RNS launches
+int rns_index(int T) {
+  for (int i = 0; i < pc2k::RNS_NT; ++i)
+    if (pc2k::RNS_T[i] == T) return i;
+  return 0;
+}
+// resident workgroups of k_rns_pow<T, nb> (0: not compiled)
+int rns_slots(pc2_ctx* ctx, int T, int nb) {
+  int& o = ctx->rocc[rns_index(T)][nb];
+  if (o == 0) {
+    const void* k = pc2k::rns_pow_kernel(T, nb);
+    int v = 0;
+    if (!k)
+      o = -1;
+    else if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k, pc2k::rns_pow_threads(T, nb),
+                                                          0) != hipSuccess || v <= 0)
+      o = 1;
+    else
+      o = v;
+  }
+  return o < 0 ? 0 : ctx->cus * o;
+}
+// The powering window: widest that pays for the exponent's length.
+int rns_window(const pc2_ctx* ctx, int T) { return ctx->window ? ctx->window : (T > 5 ? 6 : 5); }
+
+// Column blocks per workgroup for `count` elements of nmod moduli: the least
+// time by rounds of resident workgroups.
+struct RnsPlan {
+  int T = 0, nb = 0, grid = 0, w = 0;
+  size_t ngroups = 0, group_bytes = 0, table_bytes = 0;
+  size_t stage_bytes() const { return ngroups * group_bytes; }  // one input, one modulus
+};
+RnsPlan rns_plan_nb(pc2_ctx* ctx, int T, int nmod, size_t count, int nb, int w) {
+  RnsPlan p;
+  p.T = T;
+  p.nb = nb;
+  p.w = w;
+  p.ngroups = (count + 32 * nb - 1) / (32 * nb);
+  p.group_bytes = pc2k::rns_group_bytes(T, nb);
+  p.grid = (int)std::min<size_t>(p.ngroups * nmod, (size_t)rns_slots(ctx, T, nb));
+  p.table_bytes = (size_t)p.grid * ((size_t)1 << (w - 1)) * p.group_bytes;
+  return p;
+}
+RnsPlan rns_plan(pc2_ctx* ctx, int T, int nmod, size_t count) {
+  const int w = rns_window(ctx, T);
+  RnsPlan best;
+  double best_cost = 0;
+  for (int nb = 1; nb <= pc2k::RNS_NBMAX; ++nb) {
+    const int slots = rns_slots(ctx, T, nb);
+    if (!slots) continue;
+    RnsPlan p = rns_plan_nb(ctx, T, nmod, count, nb, w);
+    const size_t rounds = (p.ngroups * nmod + slots - 1) / slots;
+    const double per_cu = (double)slots / ctx->cus;  // workgroups that share a CU
+    const double cost = (double)rounds * (1.0 + per_cu * nb);
+    if (!best.T || cost < best_cost) {
+      best = p;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+// scratch of the RNS calls: the tables, then the per-chunk staging (256-byte
+// aligned parts)
+size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+size_t rns_encrypt_bytes(const RnsPlan& p) { return p.table_bytes + 2 * p.stage_bytes(); }
+size_t rns_decrypt_bytes(const RnsPlan& p, size_t chunk, int Ls, int nl2) {
+  return p.table_bytes + 2 * p.stage_bytes() + align256(chunk * 2 * (size_t)(nl2 + 1) * 4) +
+         align256(chunk * 2 * (size_t)(Ls + 1) * 4);
+}
+size_t rns_encrypt_sk_bytes(const RnsPlan& p, size_t chunk, int nl2) {
+  return p.table_bytes + 4 * p.stage_bytes() + align256(chunk * 2 * (size_t)(nl2 + 1) * 4);
+}
+
 // Largest scratch any data call under a key of class cls can need: every
 // operation and encryption tile, the widest window an option can select,
 // a device-filling grid and the largest per-call staging (DEC_CHUNK
@@ -605,6 +775,20 @@ size_t class_scratch_need(pc2_ctx* ctx, int cls, int L, int Ls, int nl2) {
   take(cls, pc2k::OP_FUSED_MFMA, fused_aux);
   take(cls, pc2k::OP_ENC_CRT, ch * 2 * (size_t)(nl2 + 1));
   (void)occupancy(ctx, cls, pc2k::OP_SUM);
+  if (cls >= RNS_MIN_CLASS) {  // the RNS engine, any tile count of the class's moduli
+    const pc2k::ClassGeo g = pc2k::CLASS_GEO[cls];
+    const int tn = pc2h::rns_tiles(64 * L), tp = pc2h::rns_tiles(g.pD * g.pK * g.pT - 2);
+    for (int T : pc2k::RNS_T)
+      for (int nb = 1; nb <= pc2k::RNS_NBMAX; ++nb) {
+        if (T > tn || !rns_slots(ctx, T, nb)) continue;
+        const RnsPlan p = rns_plan_nb(ctx, T, 2, ch, nb, w);
+        need = std::max(need, rns_encrypt_bytes(p));
+        if (T <= tp) {
+          need = std::max(need, rns_decrypt_bytes(p, ch, Ls, nl2));
+          need = std::max(need, rns_encrypt_sk_bytes(p, ch, nl2));
+        }
+      }
+  }
   return need;
 }
 
@@ -659,6 +843,140 @@ int scratch_end(pc2_ctx* ctx, void* stream, int rc) {
 }
 
 int status_of(hipError_t e) { return e == hipSuccess ? PC2_OK : PC2_E_DEVICE; }
+
+// Public-key encryption on the RNS engine from this many elements on; below,
+// the engines that give an element a wavefront or a tile of its own finish
+// sooner.
+bool use_rns(const pc2_ctx* ctx, const pc2k::RnsKey& k, size_t count) {
+  if (!k.T || ctx->modmul == PC2_MODMUL_VALU) return false;
+  return count >= 256;
+}
+
+int rns_encrypt(const pc2_pk* pk, const uint32_t* m, int m_limbs, const uint32_t* r, uint32_t* c,
+                size_t count, void* stream) {
+  pc2_ctx* ctx = pk->ctx;
+  const pc2k::RnsKey& K = pk->rn;
+  const size_t chunk = std::min(count, pc2k::DEC_CHUNK), L = pk->L;
+  const RnsPlan p = rns_plan(ctx, K.T, 1, chunk);
+  if (!ctx->scratch || rns_encrypt_bytes(p) > ctx->scratch_bytes) return PC2_E_NOMEM;
+  uint8_t* base = reinterpret_cast<uint8_t*>(ctx->scratch);
+  uint8_t* in = base + p.table_bytes;
+  uint8_t* gm = in + p.stage_bytes();
+  int rc = scratch_begin(ctx, stream);
+  for (size_t b = 0; b < count && !rc; b += chunk) {
+    const size_t n = std::min(chunk, count - b);
+    const uint32_t* mb = m + b * m_limbs;
+    const uint32_t* rb = r + b * L;
+    uint32_t* cb = c + b * 2 * L;
+    pc2k::RnsPow pw{};
+    pw.M[0] = K.M;
+    pw.ops[0] = K.ops[p.w - pc2k::SCHED_WMIN];
+    pw.in[0] = in;
+    pw.gm[0] = gm;
+    pw.table = base;
+    pw.nmod = 1;
+    pw.ngroups = (int)((n + 32 * p.nb - 1) / (32 * p.nb));
+    pw.entries = 1 << (p.w - 1);
+    hipError_t e = pc2k::launch_rns_to(K.x, K.T, p.nb, rb, (int)L, n, in, stream);
+    if (e == hipSuccess) e = pc2k::launch_rns_to(K.gm, K.T, p.nb, mb, m_limbs, n, gm, stream);
+    if (e == hipSuccess)
+      e = pc2k::launch_rns_pow(K.T, p.nb, std::min(p.grid, pw.ngroups), pw, stream);
+    if (e == hipSuccess)
+      e = pc2k::launch_rns_from(K.from, K.T, p.nb, in, n, cb, 2 * L, stream);
+    if (e == hipSuccess)
+      e = pc2k::launch_rns_enc_check(pk->c, mb, m_limbs, rb, cb, n, nullptr, 0, ctx->err, stream);
+    rc = status_of(e);
+  }
+  return scratch_end(ctx, stream, rc);
+}
+
+int rns_decrypt(const pc2_sk* sk, const uint32_t* c, uint32_t* m, size_t count, void* stream) {
+  pc2_ctx* ctx = sk->ctx;
+  const int T = sk->dec[0].T, Ls = sk->c.h[0].Ls, nl2 = sk->c.h[0].s2.nl;
+  const size_t chunk = std::min(count, pc2k::DEC_CHUNK), L = sk->pk.L;
+  const RnsPlan p = rns_plan(ctx, T, 2, chunk);
+  if (!ctx->scratch || rns_decrypt_bytes(p, chunk, Ls, nl2) > ctx->scratch_bytes)
+    return PC2_E_NOMEM;
+  uint8_t* base = reinterpret_cast<uint8_t*>(ctx->scratch);
+  uint8_t* in = base + p.table_bytes;
+  uint32_t* ys = reinterpret_cast<uint32_t*>(in + 2 * p.stage_bytes());
+  uint32_t* halves = ys + align256(chunk * 2 * (size_t)(nl2 + 1) * 4) / 4;
+  const size_t stride = nl2 + 1;
+  int rc = scratch_begin(ctx, stream);
+  for (size_t b = 0; b < count && !rc; b += chunk) {
+    const size_t n = std::min(chunk, count - b);
+    const uint32_t* cb = c + b * 2 * L;
+    pc2k::RnsPow pw{};
+    pw.table = base;
+    pw.nmod = 2;
+    pw.ngroups = (int)((n + 32 * p.nb - 1) / (32 * p.nb));
+    pw.entries = 1 << (p.w - 1);
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < 2 && e == hipSuccess; ++i) {
+      pw.M[i] = sk->dec[i].M;
+      pw.ops[i] = sk->dec[i].ops[p.w - pc2k::SCHED_WMIN];
+      pw.in[i] = in + i * p.stage_bytes();
+      e = pc2k::launch_rns_to(sk->dec[i].x, T, p.nb, cb, (int)(2 * L), n, pw.in[i], stream);
+    }
+    if (e == hipSuccess)
+      e = pc2k::launch_rns_pow(T, p.nb, std::min(p.grid, 2 * pw.ngroups), pw, stream);
+    for (int i = 0; i < 2 && e == hipSuccess; ++i)
+      e = pc2k::launch_rns_from(sk->dec[i].from, T, p.nb, pw.in[i], n, ys + i * stride,
+                                2 * stride, stream);
+    if (e == hipSuccess)
+      e = pc2k::launch_rns_dec_finish(sk->c, cb, ys, stride, n, halves, stream);
+    if (e == hipSuccess) e = pc2k::launch_garner(sk->c, halves, m + b * L, n, ctx->err, stream);
+    rc = status_of(e);
+  }
+  return scratch_end(ctx, stream, rc);
+}
+
+int rns_encrypt_sk(const pc2_sk* sk, const uint32_t* m, int m_limbs, const uint32_t* r,
+                   uint32_t* c, size_t count, void* stream) {
+  pc2_ctx* ctx = sk->ctx;
+  const int T = sk->enc[0].T, nl2 = sk->c.h[0].s2.nl;
+  const size_t chunk = std::min(count, pc2k::DEC_CHUNK), L = sk->pk.L;
+  const RnsPlan p = rns_plan(ctx, T, 2, chunk);
+  if (!ctx->scratch || rns_encrypt_sk_bytes(p, chunk, nl2) > ctx->scratch_bytes)
+    return PC2_E_NOMEM;
+  uint8_t* base = reinterpret_cast<uint8_t*>(ctx->scratch);
+  uint8_t* in = base + p.table_bytes;
+  uint32_t* stage = reinterpret_cast<uint32_t*>(in + 4 * p.stage_bytes());
+  const size_t stride = nl2 + 1;
+  int rc = scratch_begin(ctx, stream);
+  for (size_t b = 0; b < count && !rc; b += chunk) {
+    const size_t n = std::min(chunk, count - b);
+    const uint32_t* mb = m + b * m_limbs;
+    const uint32_t* rb = r + b * L;
+    pc2k::RnsPow pw{};
+    pw.table = base;
+    pw.nmod = 2;
+    pw.ngroups = (int)((n + 32 * p.nb - 1) / (32 * p.nb));
+    pw.entries = 1 << (p.w - 1);
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < 2 && e == hipSuccess; ++i) {
+      pw.M[i] = sk->enc[i].M;
+      pw.ops[i] = sk->enc[i].ops[p.w - pc2k::SCHED_WMIN];
+      pw.in[i] = in + 2 * i * p.stage_bytes();
+      pw.gm[i] = pw.in[i] + p.stage_bytes();
+      e = pc2k::launch_rns_to(sk->enc[i].x, T, p.nb, rb, (int)L, n, pw.in[i], stream);
+      if (e == hipSuccess)
+        e = pc2k::launch_rns_to(sk->enc[i].gm, T, p.nb, mb, m_limbs, n, pw.gm[i], stream);
+    }
+    if (e == hipSuccess)
+      e = pc2k::launch_rns_pow(T, p.nb, std::min(p.grid, 2 * pw.ngroups), pw, stream);
+    for (int i = 0; i < 2 && e == hipSuccess; ++i)
+      e = pc2k::launch_rns_from(sk->enc[i].from, T, p.nb, pw.in[i], n, stage + i * stride,
+                                2 * stride, stream);
+    if (e == hipSuccess)
+      e = pc2k::launch_rns_enc_check(sk->pk.c, mb, m_limbs, rb, nullptr, n, stage + nl2, stride,
+                                     nullptr, stream);
+    if (e == hipSuccess)
+      e = pc2k::launch_garner_crt(sk->c, stage, c + b * 2 * L, n, ctx->err, stream);
+    rc = status_of(e);
+  }
+  return scratch_end(ctx, stream, rc);
+}
 
 
 
@@ -814,6 +1132,7 @@ int pc2_pk_create(pc2_ctx* ctx, uint32_t nbits, const uint32_t* n_limbs, pc2_pk*
   if (nb > (int)nbits || (n[0] & 1u) == 0 || pc2h::cmp(n, Limbs{15}) < 0) return PC2_E_INVAL;
   DevBuf buf;
   PkOffsets o = add_public(buf, n, cls, L);
+  const RnsOffsets rn = add_rns_public(buf, n, cls, L);
   pc2_pk* pk = new (std::nothrow) pc2_pk();
   if (!pk) return PC2_E_NOMEM;
   int rc = upload(ctx, buf, &pk->dev);
@@ -828,6 +1147,7 @@ int pc2_pk_create(pc2_ctx* ctx, uint32_t nbits, const uint32_t* n_limbs, pc2_pk*
   pk->cls = cls;
   pk->c = pk_const((const uint32_t*)pk->dev, o, L, nb);
   if (pc2k::ALT_GEO[cls] >= 0) pk->alt = pk_const_alt((const uint32_t*)pk->dev, o, pk->c);
+  pk->rn = rns_const((const uint32_t*)pk->dev, rn, 2 * L);
   rc = pc2_ctx_reserve(ctx, nbits);  // every later data call under this key fits
   if (rc) {
     (void)hipFree(pk->dev);
@@ -863,6 +1183,7 @@ int pc2_sk_create(pc2_ctx* ctx, uint32_t nbits, const uint32_t* p_limbs, const u
   const int nl2 = (pc2h::bitlen(p2) + 31) / 32;
   DevBuf buf;
   PkOffsets po = add_public(buf, n, cls, L);
+  const RnsOffsets rn = add_rns_public(buf, n, cls, L);
   HalfOffsets hp = add_half(buf, p, q, n, cls, Ls, nl2);
   HalfOffsets hq = add_half(buf, q, p, n, cls, Ls, nl2);
   // q^-1 2^(32 Ls) mod p
@@ -876,6 +1197,21 @@ int pc2_sk_create(pc2_ctx* ctx, uint32_t nbits, const uint32_t* p_limbs, const u
   pc2h::trim(phi);
   Limbs q2inv = MP2.pow(pc2h::mod(q2, p2), pc2h::sub(phi, Limbs{1}));
   size_t q2i = buf.add(pc2h::resized(pc2h::shl_mod(q2inv, (uint64_t)32 * nl2, p2), nl2));
+  // the RNS engine modulo p^2 and q^2: decryption and key-holder encryption
+  // (both primes on one tile count, or neither)
+  RnsOffsets rd[2], re[2];
+  const int rt = rns_tiles_for(cls, p2), rtq = rns_tiles_for(cls, q2);
+  if (rt && rtq && rtq <= rt) {
+    const Limbs* sq[2] = {&p2, &q2};
+    const Limbs* pr[2] = {&p, &q};
+    for (int i = 0; i < 2; ++i) {
+      const Limbs sm1 = pc2h::sub(*pr[i], Limbs{1});
+      Limbs order = pc2h::mul(*pr[i], sm1);
+      rd[i] = add_rns(buf, *sq[i], rt, sm1, 4 * L, nullptr, 0, i ? &rd[0] : nullptr);
+      if (rd[0].T)
+        re[i] = add_rns(buf, *sq[i], rt, pc2h::mod(n, order), 2 * L, &n, 2 * L, &rd[0]);
+    }
+  }
   // the key-holder encryption needs r, m < n < 2 q^2, i.e. p < 2 q
   const bool crt_ok = pc2h::cmp(p, pc2h::add(q, q)) < 0;
   pc2_sk* sk = new (std::nothrow) pc2_sk();
@@ -901,6 +1237,11 @@ int pc2_sk_create(pc2_ctx* ctx, uint32_t nbits, const uint32_t* p_limbs, const u
   sk->c.QI = base + qi;
   sk->c.Q2I = base + q2i;
   sk->c.p2_n0 = 0u - pc2h::inv32(p2[0]);
+  sk->pk.rn = rns_const(base, rn, 2 * L);
+  for (int i = 0; i < 2; ++i) {
+    sk->dec[i] = rns_const(base, rd[i], nl2);
+    sk->enc[i] = rns_const(base, re[i], nl2);
+  }
   sk->crt_ok = crt_ok;
   Limbs pm1 = pc2h::sub(p, Limbs{1}), qm1 = pc2h::sub(q, Limbs{1});
   sk->c.ebits = std::max(pc2h::bitlen(pm1), pc2h::bitlen(qm1));
@@ -990,6 +1331,7 @@ int pc2_encrypt(const pc2_pk* pk, const uint32_t* m, uint32_t m_limbs, const uin
     return PC2_E_INVAL;
   pc2_ctx* ctx = pk->ctx;
   pc2k::Launch l{};
+  if (use_rns(ctx, pk->rn, count)) return rns_encrypt(pk, m, (int)m_limbs, r, c, count, stream);
   if (use_mfma(ctx, pk->cls)) {
     int rc = prepare(ctx, pk->cls, pc2k::OP_ENC_MFMA, count, 0, pk->L, &l, stream);
     if (!rc) rc = scratch_begin(ctx, stream);
@@ -1011,6 +1353,8 @@ int pc2_decrypt(const pc2_sk* sk, const uint32_t* c, uint32_t* m, size_t count, 
   if (!c || !m) return PC2_E_INVAL;
   if (partial_overlap(c, 8 * (size_t)sk->pk.L * count, m, 4 * (size_t)sk->pk.L * count))
     return PC2_E_INVAL;
+  if (sk->dec[1].T && sk->ctx->modmul != PC2_MODMUL_VALU)
+    return rns_decrypt(sk, c, m, count, stream);
   // the two CRT halves of up to DEC_CHUNK elements are staged between the
   // per-prime phase and the recombination
   const int Ls = sk->c.h[0].Ls;
@@ -1088,6 +1432,8 @@ int pc2_encrypt_sk(const pc2_sk* sk, const uint32_t* m, uint32_t m_limbs, const 
       return PC2_E_INVAL;
   }
   if (!sk->crt_ok) return PC2_E_UNSUPPORTED;
+  if (sk->enc[1].T && sk->ctx->modmul != PC2_MODMUL_VALU)
+    return rns_encrypt_sk(sk, m, (int)m_limbs, r, c, count, stream);
   // the two halves of up to DEC_CHUNK elements are staged before the recombination
   const int nl2 = sk->c.h[0].s2.nl, L = sk->pk.L, cls = sk->pk.cls;
   const size_t chunk = std::min(count, pc2k::DEC_CHUNK);

@@ -1,0 +1,401 @@
+// Powering kernels of the RNS engine (rns_mont.hpp) and its conversions.
+//
+//   k_rns_to    integers (32-bit limbs) -> residues of both bases, in
+//               Montgomery form (times MA) or times another constant
+//   k_rns_pow   runs a program of Montgomery products over groups of 32 NB
+//               elements, one group at a time per workgroup: the table of
+//               odd powers, sliding windows, the closing product
+//   k_rns_from  residues of base B -> the canonical integer mod N
+//
+// Both conversions are plain sums over constants on the vector ALUs (together
+// a few products' worth of a powering of thousands).
+#include <hip/hip_runtime.h>
+
+#include "bn_scalar.hpp"
+#include "paillier_ops.hpp"
+#include "rns_launch.hpp"
+#include "rns_mont.hpp"
+
+using namespace pc2r;
+using pc2k::RnsFrom;
+using pc2k::RnsPow;
+using pc2k::RnsTo;
+
+namespace {
+
+// One wavefront per SIMD pair of the program's steps; see RGeo for the split.
+template <class G>
+__global__ __launch_bounds__(G::W * 64, G::W == 8 ? 2 : 2) void k_rns_pow(RnsPow P) {
+  __shared__ __align__(16) RWork<G> ws;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr size_t GB = 2 * (size_t)G::PART * 16;  // bytes of one group's residues
+  uint8_t* slot = P.table + (size_t)blockIdx.x * P.entries * GB;
+  const int nitems = P.ngroups * P.nmod;
+  for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
+    const int mod = P.nmod == 2 ? (it & 1) : 0;
+    const int g = P.nmod == 2 ? it >> 1 : it;
+    const RConst<G> M(P.M[mod]);
+    const uint32_t* ops = P.ops[mod];
+    uint8_t* in = P.in[mod] + (size_t)g * GB;
+    uint8_t* gm = P.gm[mod] ? P.gm[mod] + (size_t)g * GB : in;
+    auto entry = [&](uint32_t e) {
+      uint8_t* p = slot + (size_t)(e - 1) * GB;
+      if (e == pc2k::RNS_GM) p = gm;
+      if (e == 0 || e >= pc2k::RNS_OUT) p = in;
+      return Buf(p, (uint32_t)GB);
+    };
+    uint32_t op = ops[0];
+    int par = 0;
+    for (int k = 1;; ++k) {
+      const uint32_t next = ops[k];
+      const uint32_t y = op & 0xFF, d = (op >> 8) & 0xFF;
+      const uint32_t nk = next >> 16, ny = next & 0xFF;
+      const bool nmul = nk == pc2k::RNS_MUL && ny != pc2k::RNS_SQ;
+      const Buf nb = entry(ny);  // the next product's multiplier
+      if (op >> 16 == pc2k::RNS_LOAD) {
+        const Buf e = entry(y);
+        PC2R_FOR_ITEMS(G, wave, {
+          for (int m = 0; m < MT; ++m)
+            for (int b = 0; b < NBN; ++b) load_unit<G>(M, ws, t0 + m, nb0 + b, e, nmul, nb, lane);
+        });
+        for (int i = threadIdx.x; i < 2 * G::NB * 32; i += G::W * 64) (&ws.beta[0][0])[i] = 0;
+        lds_barrier();
+      } else {
+        const bool mul = y != pc2k::RNS_SQ, store = d != pc2k::RNS_NODST;
+        const Buf yb = entry(y), db = entry(d);
+        PC2R_FOR_ITEMS(G, wave, (ext1<G, MT, NBN>(M, ws, par, t0, nb0, mul, yb, store, db, lane)));
+        lds_barrier();
+        if (nk == pc2k::RNS_END) break;
+        PC2R_FOR_ITEMS(G, wave,
+                       (ext2<G, MT, NBN>(M, ws, par, t0, nb0, nmul, nb, store, db, lane)));
+        par ^= 1;
+        if ((int)threadIdx.x < G::NB * 32) ws.beta[par][threadIdx.x] = 0;
+        lds_barrier();
+      }
+      op = next;
+    }
+  }
+}
+
+// Residues of one wavefront's slot (part, tile, half: eight channels) for 64
+// elements, one per lane: sum_i half_i P[i] + add.  The constants are uniform
+// (scalar loads); elements past `count` repeat the last one, so that every
+// column of a group holds valid residues.
+__global__ __launch_bounds__(256) void k_rns_to(RnsTo C, const uint32_t* __restrict__ x,
+                                                int limbs, size_t count, int T, int nb,
+                                                uint8_t* __restrict__ out) {
+  const int lane = threadIdx.x & 63;
+  const int slot = __builtin_amdgcn_readfirstlane(blockIdx.y * 4 + (threadIdx.x >> 6));
+  if (slot >= 4 * T) return;
+  const size_t pos = (size_t)blockIdx.x * 64 + lane;  // position in the padded groups
+  const size_t per = (size_t)nb * 32;
+  const size_t total = (count + per - 1) / per * per;
+  if (pos >= total) return;
+  const size_t e = pos < count ? pos : count - 1;
+  const int nhalf = 2 * limbs < C.nhalf ? 2 * limbs : C.nhalf;
+  const uint32_t* P = C.P + (size_t)slot * C.nhalf * 8;
+  const uint32_t* xe = x + e * limbs;
+  uint64_t acc[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) acc[c] = C.add[slot * 8 + c];
+  for (int i = 0; i < nhalf; i += 2) {
+    const uint32_t w = xe[i >> 1];
+    const uint32_t lo = w & 0xFFFFu, hi = w >> 16;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) acc[c] += (uint64_t)lo * P[i * 8 + c];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) acc[c] += (uint64_t)hi * P[i * 8 + 8 + c];
+  }
+  v4u o;
+  uint32_t r[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    // acc < 2^42: the quotient by the modulus is exact to +-1 in double
+    const uint32_t m = C.m[slot * 8 + c];
+    const uint64_t q = (uint64_t)((double)acc[c] * (1.0 / (double)m));
+    int v = (int)(uint32_t)(acc[c] - q * m);  // in [-m, 2 m)
+    if (v < 0) v += (int)m;
+    if (v >= (int)m) v -= (int)m;
+    if (2 * v > (int)m) v -= (int)m;
+    r[c] = (uint32_t)v;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) o[i] = pack16(r[2 * i], r[2 * i + 1]);
+  // slot = (part T + tile) 2 + half
+  const int h = slot & 1, pt = slot >> 1;
+  const size_t grp = pos / per, b = pos % per / 32, n = pos & 31;
+  uint8_t* g = out + grp * pc2k::rns_group_bytes(T, nb);
+  reinterpret_cast<v4u*>(g)[((size_t)pt * nb + b) * 64 + h * 32 + n] = o;
+}
+
+// The value of base-B residues mod N, canonical.  A block handles 64
+// elements, one per lane of every wavefront: the wavefronts form the columns
+// sum_j w_j C_j[l] + beta D[l] + O[l] of eight limbs each (constants by
+// scalar loads) and resolve the carries inside their block of limbs; the
+// first wavefront then joins the blocks, subtracts the quotient by N, and
+// all write the words.
+__global__ __launch_bounds__(512) void k_rns_from(RnsFrom C, const uint8_t* __restrict__ in,
+                                                  size_t count, int T, int nb,
+                                                  uint32_t* __restrict__ out, size_t stride) {
+  extern __shared__ __align__(16) uint32_t lds[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nblk = C.nblk;
+  uint32_t* limb = lds;                                              // [8 nblk][64]
+  int64_t* cy = reinterpret_cast<int64_t*>(lds + (size_t)nblk * 512);  // [nblk][64]
+  const size_t pos0 = (size_t)blockIdx.x * 64 + lane;
+  const size_t pos = pos0 < count ? pos0 : count - 1;
+  const size_t per = (size_t)nb * 32;
+  const size_t grp = pos / per, b = pos % per / 32, n = pos & 31;
+  const v4u* g = reinterpret_cast<const v4u*>(in + grp * pc2k::rns_group_bytes(T, nb)) + b * 64 + n;
+  // beta = round(sum_j w_j g_j / b_j)
+  int64_t s = 0;
+  for (int ts = 0; ts < 2 * T; ++ts) {
+    const v4u v = g[(size_t)(ts >> 1) * nb * 64 + (ts & 1) * 32];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      s += (int64_t)(int16_t)(v[i >> 1] >> (16 * (i & 1))) * C.F[ts * 8 + i];
+  }
+  const int32_t beta = (int32_t)((s + ((int64_t)1 << 35)) >> 36);
+  for (int k = wave; k < nblk; k += 8) {
+    int64_t col[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) col[c] = (int64_t)beta * C.D[k * 8 + c] + C.O[k * 8 + c];
+    const uint32_t* Ck = C.C + (size_t)k * 16 * T * 8;
+    for (int ts = 0; ts < 2 * T; ++ts) {
+      const v4u v = g[(size_t)(ts >> 1) * nb * 64 + (ts & 1) * 32];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int32_t w = (int16_t)(v[i >> 1] >> (16 * (i & 1)));
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+          col[c] += (int64_t)w * (int32_t)Ck[(ts * 8 + i) * 8 + c];
+      }
+    }
+    int64_t carry = 0;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int64_t v = col[c] + carry;
+      limb[(k * 8 + c) * 64 + lane] = (uint32_t)v & 0xFFFFFFFu;
+      carry = v >> 28;
+    }
+    cy[k * 64 + lane] = carry;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    // join the blocks: y in [0, 2^27 N)
+    const int S = C.S;
+    int64_t carry = 0;
+    for (int k = 0; k < nblk; ++k) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const int64_t v = (int64_t)limb[(k * 8 + c) * 64 + lane] + carry;
+        limb[(k * 8 + c) * 64 + lane] = (uint32_t)v & 0xFFFFFFFu;
+        carry = v >> 28;
+      }
+      carry += cy[k * 64 + lane];
+    }
+    // quotient from the top limbs, exact or one too small
+    double top = 0.0;
+    for (int i = S - 1; i >= S - 4 && i >= 0; --i)
+      top = top * 268435456.0 + (double)limb[i * 64 + lane];
+    double qd = top * C.ntop_inv - 0.001;
+    const int64_t q = qd > 0.0 ? (int64_t)qd : 0;
+    carry = 0;
+    for (int i = 0; i < S; ++i) {
+      const int64_t v = (int64_t)limb[i * 64 + lane] - q * (int64_t)C.N28[i] + carry;
+      limb[i * 64 + lane] = (uint32_t)v & 0xFFFFFFFu;
+      carry = v >> 28;
+    }
+    int c = 0;  // y >= N ?
+    for (int i = S - 1; i >= 0 && c == 0; --i) {
+      const uint32_t v = limb[i * 64 + lane];
+      if (v != C.N28[i]) c = v > C.N28[i] ? 1 : -1;
+    }
+    if (c >= 0) {
+      carry = 0;
+      for (int i = 0; i < S; ++i) {
+        const int64_t v = (int64_t)limb[i * 64 + lane] - (int64_t)C.N28[i] + carry;
+        limb[i * 64 + lane] = (uint32_t)v & 0xFFFFFFFu;
+        carry = v >> 28;
+      }
+    }
+  }
+  __syncthreads();
+  // 32-bit words, coalesced over the words of an element
+  for (int e = wave; e < 64; e += 8) {
+    const size_t p = (size_t)blockIdx.x * 64 + e;
+    if (p >= count) break;
+    for (int j = lane; j < C.nw; j += 64) {
+      const int bit = 32 * j, i = bit / 28, sh = bit % 28;
+      uint64_t v = limb[i * 64 + e];
+      if (i + 1 < 8 * nblk) v |= (uint64_t)limb[(i + 1) * 64 + e] << 28;
+      if (i + 2 < 8 * nblk) v |= (uint64_t)limb[(i + 2) * 64 + e] << 56;
+      out[p * stride + j] = (uint32_t)(v >> sh);
+    }
+  }
+}
+
+// Input checks of an encryption, one lane per element: with c the element's
+// ciphertext is zeroed if m >= n, r = 0 or r >= n, and ERR_RANGE latched;
+// with okw the result of the check goes there instead (both halves' words).
+__global__ __launch_bounds__(64) void k_rns_enc_check(pc2k::PkConst pk,
+                                                      const uint32_t* __restrict__ m, int m_limbs,
+                                                      const uint32_t* __restrict__ r,
+                                                      uint32_t* __restrict__ c, size_t count,
+                                                      uint32_t* __restrict__ okw, size_t stride,
+                                                      int* err) {
+  const size_t e = (size_t)blockIdx.x * 64 + threadIdx.x;
+  if (e >= count) return;
+  const int L = pk.L;
+  const uint32_t* re = r + e * L;
+  bool ok = pc2d::sc_cmp(m + e * m_limbs, m_limbs, pk.n, L) < 0 && pc2d::sc_cmp(re, L, pk.n, L) < 0;
+  int i = L - 1;
+  while (i >= 0 && re[i] == 0) --i;
+  ok = ok && i >= 0;
+  if (okw) {
+    okw[2 * e * stride] = ok;
+    okw[(2 * e + 1) * stride] = ok;
+  } else if (!ok) {
+    for (int j = 0; j < 2 * L; ++j) c[e * 2 * L + j] = 0u;
+    atomicOr(err, pc2k::ERR_RANGE);
+  }
+}
+
+// The scalar end of a decryption half, one lane per (element, prime): y =
+// c^(s-1) mod s^2 (canonical, nl words at y + (2 e + half) stride) -> m_s =
+// L_s(y) h_s mod s and its validity word at halves + (2 e + half)(Ls + 1).
+__global__ __launch_bounds__(64) void k_rns_dec_finish(pc2k::SkConst sk,
+                                                       const uint32_t* __restrict__ c,
+                                                       const uint32_t* __restrict__ ys,
+                                                       size_t stride, size_t count,
+                                                       uint32_t* __restrict__ halves) {
+  const size_t i = (size_t)blockIdx.x * 64 + threadIdx.x;
+  const int half = blockIdx.y;
+  if (i >= count) return;
+  const pc2k::HalfConst& H = sk.h[half];
+  const int Ls = H.Ls, nl = H.s2.nl, L2 = 2 * sk.pk.L;
+  const bool cv = pc2d::sc_cmp(c + i * L2, L2, sk.pk.n2.Nl, L2) < 0;
+  uint32_t y[2 * pc2k::LS_MAX + 1], u[pc2k::LS_MAX], us[2 * pc2k::LS_MAX],
+      tmp[pc2k::LS_MAX + 2];
+  const uint32_t* src = ys + (2 * i + half) * stride;
+  for (int j = 0; j < nl; ++j) y[j] = src[j];
+  const uint32_t one = 1u;
+  const uint32_t bor = pc2d::sc_sub(y, nl, &one, 1);
+  pc2d::sc_mullo(u, y, H.sinv, Ls);
+  pc2d::sc_mul(us, u, Ls, H.s, Ls);
+  const bool good = bor == 0 && pc2d::sc_cmp(us, 2 * Ls, y, nl) == 0 && cv;
+  uint32_t* dst = halves + (2 * i + half) * (size_t)(Ls + 1);
+  pc2d::sc_montmul(u, u, H.H, H.s, H.s_n0, Ls, tmp);
+  for (int j = 0; j < Ls; ++j) dst[j] = u[j];
+  dst[Ls] = good ? 1u : 0u;
+}
+
+}  // namespace
+
+namespace pc2k {
+
+namespace {
+// (T, NB) -> geometry: see RGeo.  P pairs, Q singles, unit offset.
+template <int T, int NB>
+struct Pick;
+#define PC2_RNS_GEO(T, NB, W, P, Q, UO) \
+  template <>                           \
+  struct Pick<T, NB> {                  \
+    using G = RGeo<T, NB, W, P, Q, UO>; \
+  };
+PC2_RNS_GEO(5, 1, 4, 0, 4, 0)
+PC2_RNS_GEO(5, 2, 4, 0, 4, 0)
+PC2_RNS_GEO(5, 4, 4, 0, 4, 0)
+PC2_RNS_GEO(9, 1, 8, 0, 8, 0)
+PC2_RNS_GEO(9, 2, 4, 4, 0, 0)
+PC2_RNS_GEO(9, 4, 4, 4, 0, 0)
+PC2_RNS_GEO(13, 1, 8, 4, 4, 4)
+PC2_RNS_GEO(13, 2, 8, 4, 4, 4)
+PC2_RNS_GEO(13, 4, 8, 4, 4, 4)
+PC2_RNS_GEO(17, 1, 8, 8, 0, 0)
+PC2_RNS_GEO(17, 2, 8, 8, 0, 0)
+PC2_RNS_GEO(17, 4, 8, 8, 0, 0)
+PC2_RNS_GEO(26, 1, 8, 12, 0, 4)
+PC2_RNS_GEO(26, 2, 8, 12, 0, 4)
+PC2_RNS_GEO(26, 3, 8, 12, 0, 4)
+PC2_RNS_GEO(34, 1, 8, 16, 0, 0)
+PC2_RNS_GEO(34, 2, 8, 16, 0, 0)
+#undef PC2_RNS_GEO
+}  // namespace
+
+#define PC2_RNS_CASE(T, NB, EXPR) \
+  if (t == T && nb == NB) {       \
+    using G = Pick<T, NB>::G;     \
+    EXPR;                         \
+  }
+#define PC2_RNS_DISPATCH(EXPR) \
+  PC2_RNS_CASE(5, 1, EXPR)     \
+  PC2_RNS_CASE(5, 2, EXPR)     \
+  PC2_RNS_CASE(5, 4, EXPR)     \
+  PC2_RNS_CASE(9, 1, EXPR)     \
+  PC2_RNS_CASE(9, 2, EXPR)     \
+  PC2_RNS_CASE(9, 4, EXPR)     \
+  PC2_RNS_CASE(13, 1, EXPR)    \
+  PC2_RNS_CASE(13, 2, EXPR)    \
+  PC2_RNS_CASE(13, 4, EXPR)    \
+  PC2_RNS_CASE(17, 1, EXPR)    \
+  PC2_RNS_CASE(17, 2, EXPR)    \
+  PC2_RNS_CASE(17, 4, EXPR)    \
+  PC2_RNS_CASE(26, 1, EXPR)    \
+  PC2_RNS_CASE(26, 2, EXPR)    \
+  PC2_RNS_CASE(26, 3, EXPR)    \
+  PC2_RNS_CASE(34, 1, EXPR)    \
+  PC2_RNS_CASE(34, 2, EXPR)
+
+const void* rns_pow_kernel(int t, int nb) {
+  PC2_RNS_DISPATCH(return (const void*)&k_rns_pow<G>)
+  return nullptr;
+}
+
+int rns_pow_threads(int t, int nb) {
+  PC2_RNS_DISPATCH(return G::W * 64)
+  return 0;
+}
+
+hipError_t launch_rns_to(const RnsTo& c, int T, int nb, const uint32_t* x, int limbs,
+                         size_t count, uint8_t* out, void* stream) {
+  const size_t per = (size_t)nb * 32;
+  const size_t total = (count + per - 1) / per * per;
+  hipLaunchKernelGGL(k_rns_to, dim3((unsigned)((total + 63) / 64), (unsigned)T), dim3(256), 0,
+                     (hipStream_t)stream, c, x, limbs, count, T, nb, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_rns_pow(int t, int nb, int grid, const RnsPow& p, void* stream) {
+  const void* k = rns_pow_kernel(t, nb);
+  if (!k) return hipErrorInvalidValue;
+  void* args[] = {(void*)&p};
+  return hipLaunchKernel(k, dim3(grid), dim3(rns_pow_threads(t, nb)), args, 0,
+                         (hipStream_t)stream);
+}
+
+hipError_t launch_rns_enc_check(const PkConst& pk, const uint32_t* m, int m_limbs,
+                                const uint32_t* r, uint32_t* c, size_t count, uint32_t* okw,
+                                size_t stride, int* err, void* stream) {
+  hipLaunchKernelGGL(k_rns_enc_check, dim3((unsigned)((count + 63) / 64)), dim3(64), 0,
+                     (hipStream_t)stream, pk, m, m_limbs, r, c, count, okw, stride, err);
+  return hipGetLastError();
+}
+
+hipError_t launch_rns_dec_finish(const SkConst& sk, const uint32_t* c, const uint32_t* ys,
+                                 size_t stride, size_t count, uint32_t* halves, void* stream) {
+  hipLaunchKernelGGL(k_rns_dec_finish, dim3((unsigned)((count + 63) / 64), 2), dim3(64), 0,
+                     (hipStream_t)stream, sk, c, ys, stride, count, halves);
+  return hipGetLastError();
+}
+
+hipError_t launch_rns_from(const RnsFrom& c, int T, int nb, const uint8_t* in, size_t count,
+                           uint32_t* out, size_t stride, void* stream) {
+  const size_t lds = (size_t)c.nblk * (512 * 4 + 64 * 8);
+  hipLaunchKernelGGL(k_rns_from, dim3((unsigned)((count + 63) / 64)), dim3(512), lds,
+                     (hipStream_t)stream, c, in, count, T, nb, out, stride);
+  return hipGetLastError();
+}
+
+}  // namespace pc2k

@@ -1,0 +1,486 @@
+// Host-side constants of the RNS engine (rns_mont.hpp): the channel moduli and
+// everything that depends on them alone, once per tile count, and a modulus'
+// own matrices and conversion tables, once per key.
+#pragma once
+#include <cmath>
+#include <cstdint>
+#include <mutex>
+#include <vector>
+
+#include "host_bn.hpp"
+#include "rns_types.hpp"
+
+namespace pc2h {
+
+// x mod m by word-wise long division (Knuth's algorithm D)
+inline Limbs mod_words(const Limbs& x0, const Limbs& m0) {
+  Limbs x = x0, m = m0;
+  trim(x);
+  trim(m);
+  if (cmp(x, m) < 0) return resized(x, m.size());
+  const size_t n = m.size();
+  const int sh = __builtin_clz(m[n - 1]);
+  if (n == 1) {
+    uint64_t r = 0;
+    for (size_t i = x.size(); i-- > 0;) r = ((r << 32) | x[i]) % m[0];
+    return Limbs{(uint32_t)r};
+  }
+  auto shl = [&](const Limbs& a, size_t len) {
+    Limbs r(len, 0);
+    for (size_t i = 0; i < len; ++i) {
+      const uint64_t lo = i > 0 && i - 1 < a.size() ? a[i - 1] : 0, hi = i < a.size() ? a[i] : 0;
+      r[i] = (uint32_t)((((hi << 32) | lo) << sh) >> 32);
+    }
+    return r;
+  };
+  const Limbs d = shl(m, n);
+  Limbs u = shl(x, x.size() + 1);
+  for (size_t j = u.size() - n; j-- > 0;) {
+    const uint64_t num = ((uint64_t)u[j + n] << 32) | u[j + n - 1];
+    uint64_t q = u[j + n] >= d[n - 1] ? 0xFFFFFFFFull : num / d[n - 1];
+    uint64_t r = num - q * d[n - 1];
+    while (r >> 32 == 0 && q * d[n - 2] > ((r << 32) | u[j + n - 2])) {
+      --q;
+      r += d[n - 1];
+    }
+    int64_t borrow = 0;
+    uint64_t c = 0;
+    for (size_t i = 0; i < n; ++i) {
+      c += q * d[i];
+      const int64_t t = (int64_t)u[i + j] - (int64_t)(uint32_t)c + borrow;
+      u[i + j] = (uint32_t)t;
+      borrow = t >> 32;
+      c >>= 32;
+    }
+    const int64_t t = (int64_t)u[j + n] - (int64_t)c + borrow;
+    u[j + n] = (uint32_t)t;
+    if (t < 0) {
+      uint64_t k = 0;
+      for (size_t i = 0; i < n; ++i) {
+        k += (uint64_t)u[i + j] + d[i];
+        u[i + j] = (uint32_t)k;
+        k >>= 32;
+      }
+      u[j + n] += (uint32_t)k;
+    }
+  }
+  Limbs out(n, 0);
+  for (size_t i = 0; i < n; ++i) {
+    const uint64_t lo = u[i], hi = i + 1 < n ? u[i + 1] : 0;
+    out[i] = (uint32_t)(((hi << 32) | lo) >> sh);
+  }
+  return out;
+}
+
+inline uint32_t mod_small(const Limbs& x, uint32_t m) {
+  uint64_t r = 0;
+  for (size_t i = x.size(); i-- > 0;) r = ((r << 32) | x[i]) % m;
+  return (uint32_t)r;
+}
+inline Limbs div_small(const Limbs& x, uint32_t m) {  // exact or floor
+  Limbs q(x.size(), 0);
+  uint64_t r = 0;
+  for (size_t i = x.size(); i-- > 0;) {
+    r = (r << 32) | x[i];
+    q[i] = (uint32_t)(r / m);
+    r %= m;
+  }
+  trim(q);
+  return q;
+}
+inline Limbs mul_small(const Limbs& x, uint32_t m) {
+  Limbs r(x.size() + 1, 0);
+  uint64_t c = 0;
+  for (size_t i = 0; i < x.size(); ++i) {
+    c += (uint64_t)x[i] * m;
+    r[i] = (uint32_t)c;
+    c >>= 32;
+  }
+  r[x.size()] = (uint32_t)c;
+  return r;
+}
+inline uint32_t inv_small(uint32_t a, uint32_t m) {  // a^-1 mod m, 0 if not invertible
+  int64_t r0 = m, r1 = a % m, t0 = 0, t1 = 1;
+  while (r1) {
+    const int64_t q = r0 / r1;
+    int64_t t = r0 - q * r1;
+    r0 = r1;
+    r1 = t;
+    t = t0 - q * t1;
+    t0 = t1;
+    t1 = t;
+  }
+  if (r0 != 1) return 0;
+  return (uint32_t)(t0 < 0 ? t0 + m : t0);
+}
+
+// v mod m in (-m/2, m/2]
+inline int32_t centred(int64_t v, uint32_t m) {
+  int64_t r = v % (int64_t)m;
+  if (r < 0) r += m;
+  return (int32_t)(2 * r > (int64_t)m ? r - m : r);
+}
+
+// largest prime allowed per tile count: small enough for the bounds on the
+// 32-bit sums, large enough that 16 T of them hold the modulus and 2^30
+inline uint32_t rns_top(int T) {
+  return T >= 34 ? 49000 : T >= 26 ? 38500 : T >= 17 ? 46341 : T >= 13 ? 36000 : 32768;
+}
+
+// What depends on the tile count alone.
+struct RnsBase {
+  int T = 0, n = 0;
+  std::vector<uint32_t> a, b;      // channel moduli
+  Limbs MA, MB;
+  std::vector<uint32_t> s;         // MA^-1 mod b_j
+  std::vector<uint32_t> iMAi;      // (MA / a_i)^-1 mod a_i
+  std::vector<uint32_t> ia;        // [j][i] a_i^-1 mod b_j
+  std::vector<int32_t> g;          // MA (MB / b_j)^-1 mod b_j, centred
+  std::vector<Limbs> gMB;          // |g_j| MB / b_j
+  std::vector<uint32_t> E2;        // fragments (T T 256 words)
+  std::vector<uint32_t> c2, kb, ka;
+  bool ok = false;
+};
+
+// E[row channel][column channel] (centred mod m_row) -> fragments, initial
+// accumulators and the check of the bounds: |sum| + extra_row < 2^31 for all
+// inputs with |r_col| < 0.52 m_col.
+inline bool rns_pack(const std::vector<int32_t>& E, const std::vector<uint32_t>& mrow,
+                     const std::vector<uint32_t>& mcol, bool square, std::vector<uint32_t>* frag,
+                     std::vector<uint32_t>* cst) {
+  const int n = (int)mrow.size(), T = n / 16;
+  frag->assign((size_t)T * T * 256, 0);
+  cst->assign((size_t)T * 32, 0);
+  uint8_t* out = reinterpret_cast<uint8_t*>(frag->data());
+  bool ok = true;
+  for (int j = 0; j < n; ++j) {
+    const int t = j / 16, H = (j >> 3) & 1, u = j & 7;
+    int64_t sum = 0, bound = 0;
+    for (int i = 0; i < n; ++i) {
+      const int32_t e = E[(size_t)j * n + i];
+      const int32_t f = centred((int64_t)e * 256, mrow[j]);
+      sum += e;
+      const int64_t hmax = (int64_t)(0.52 * mcol[i] / 256) + 1;
+      bound += 128 * (int64_t)std::abs(e) + hmax * std::abs(f);
+      const int c = i / 16, Hk = (i >> 3) & 1, s0 = 2 * (i & 7);
+      for (int k = 0; k < 2; ++k) {
+        const int32_t v = k ? f : e;
+        const int32_t lo = (int32_t)(int8_t)(v & 255), hi = (v - lo) >> 8;
+        if (hi < -128 || hi > 127) ok = false;
+        for (int part = 0; part < 2; ++part) {
+          const int r = 2 * u + part, rho = 8 * (r >> 2) + 4 * H + (r & 3);
+          out[(((size_t)t * T + c) * 64 + 32 * Hk + rho) * 16 + s0 + k] =
+              (uint8_t)(part ? hi : lo);
+        }
+      }
+    }
+    const int32_t c0 = centred(128 * sum, mrow[j]);
+    (*cst)[(size_t)(t * 2 + H) * 16 + 2 * u] = (uint32_t)c0;
+    const double sq = 0.52 * mrow[j];
+    const double extra = square ? sq * sq : (double)(1 << 27);
+    if ((double)bound + std::abs(c0) + extra + (1 << 24) >= 2147483648.0) ok = false;
+  }
+  return ok;
+}
+
+inline uint32_t float_bits(float f) {
+  uint32_t u;
+  static_assert(sizeof(u) == sizeof(f), "");
+  __builtin_memcpy(&u, &f, 4);
+  return u;
+}
+inline uint32_t pair16(int32_t lo, int32_t hi) {
+  return ((uint32_t)lo & 0xFFFFu) | ((uint32_t)hi << 16);
+}
+
+inline RnsBase make_rns_base(int T) {
+  RnsBase R;
+  R.T = T;
+  const int n = R.n = 16 * T;
+  std::vector<uint32_t> ps;
+  for (uint32_t x = rns_top(T) | 1; (int)ps.size() < 2 * n; x -= 2) {
+    if (x >= rns_top(T)) continue;
+    bool prime = true;
+    for (uint32_t d = 3; d * d <= x && prime; d += 2) prime = x % d != 0;
+    if (prime) ps.push_back(x);
+  }
+  R.a.assign(ps.begin(), ps.begin() + n);
+  R.b.assign(ps.begin() + n, ps.end());
+  R.MA = R.MB = Limbs{1};
+  for (int i = 0; i < n; ++i) {
+    R.MA = mul_small(R.MA, R.a[i]);
+    R.MB = mul_small(R.MB, R.b[i]);
+  }
+  trim(R.MA);
+  trim(R.MB);
+  // products of a base's other moduli, and of the other base, per channel
+  auto prod_mod = [](const std::vector<uint32_t>& v, uint32_t m, int skip) {
+    uint64_t r = 1;
+    for (int i = 0; i < (int)v.size(); ++i)
+      if (i != skip) r = r * v[i] % m;
+    return (uint32_t)r;
+  };
+  R.s.resize(n);
+  R.iMAi.resize(n);
+  R.g.resize(n);
+  R.ia.resize((size_t)n * n);
+  std::vector<uint32_t> pre(n + 1);
+  for (int i = 0; i < n; ++i) R.iMAi[i] = inv_small(prod_mod(R.a, R.a[i], i), R.a[i]);
+  for (int j = 0; j < n; ++j) {
+    const uint32_t m = R.b[j];
+    pre[0] = 1;
+    for (int i = 0; i < n; ++i) pre[i + 1] = (uint32_t)((uint64_t)pre[i] * (R.a[i] % m) % m);
+    R.s[j] = inv_small(pre[n], m);
+    uint64_t run = R.s[j];
+    for (int i = n; i-- > 0;) {  // inverse of every a_i from one inverse of their product
+      R.ia[(size_t)j * n + i] = (uint32_t)(run * pre[i] % m);
+      run = run * (R.a[i] % m) % m;
+    }
+    R.g[j] = centred((int64_t)((uint64_t)pre[n] * inv_small(prod_mod(R.b, m, j), m) % m), m);
+  }
+  std::vector<int32_t> E2((size_t)n * n);
+  for (int i = 0; i < n; ++i) {
+    const uint32_t m = R.a[i];
+    std::vector<uint32_t> suf(n + 1);
+    suf[n] = 1;
+    for (int j = n; j-- > 0;) suf[j] = (uint32_t)((uint64_t)suf[j + 1] * R.b[j] % m);
+    uint64_t p = 1;
+    for (int j = 0; j < n; ++j) {
+      const uint64_t mbj = p * suf[j + 1] % m;
+      E2[(size_t)i * n + j] = centred((int64_t)mbj * R.g[j], m);
+      p = p * R.b[j] % m;
+    }
+  }
+  R.ok = rns_pack(E2, R.a, R.b, false, &R.E2, &R.c2);
+  for (int j = 0; j < n; ++j) {
+    const uint32_t ag = (uint32_t)std::abs(R.g[j]);
+    R.gMB.push_back(mul_small(div_small(R.MB, R.b[j]), ag));
+  }
+  R.kb.assign((size_t)T * 48, 0);
+  R.ka.assign((size_t)T * 48, 0);
+  for (int c = 0; c < n; ++c) {
+    const size_t at = (size_t)(c / 8) * 24;
+    const int u = c & 7;
+    R.kb[at + u] = float_bits(1.0f / (float)R.b[c]);
+    R.kb[at + 8 + u] = 0u - R.b[c];
+    R.ka[at + u] = float_bits(1.0f / (float)R.a[c]);
+    R.ka[at + 8 + u] = 0u - R.a[c];
+    // beta = lo + 4096 hi: -MB and -4096 MB mod a_i
+    const uint32_t mb = mod_small(R.MB, R.a[c]);
+    R.ka[at + 16 + u] = pair16(centred(-(int64_t)mb, R.a[c]), centred(-4096ll * mb, R.a[c]));
+    if (R.a[c] >= 60000 || R.b[c] >= 60000) R.ok = false;
+  }
+  for (int c = 0; c < n; c += 2) {  // g_j / b_j = F1 2^-12 + F2 2^-25
+    int32_t f1[2], f2[2];
+    for (int k = 0; k < 2; ++k) {
+      const double x = (double)R.g[c + k] / (double)R.b[c + k];
+      f1[k] = (int32_t)std::nearbyint(x * 4096.0);
+      f2[k] = (int32_t)std::nearbyint((x - f1[k] / 4096.0) * 33554432.0);
+    }
+    const size_t at = (size_t)(c / 8) * 24;
+    const int u = (c & 7) / 2;
+    R.kb[at + 16 + u] = pair16(f1[0], f1[1]);
+    R.kb[at + 20 + u] = pair16(f2[0], f2[1]);
+  }
+  return R;
+}
+
+// The tables of a tile count, made once per process.
+inline const RnsBase& rns_base(int T) {
+  static std::once_flag once[64];
+  static RnsBase* made[64];
+  std::call_once(once[T], [T] { made[T] = new RnsBase(make_rns_base(T)); });
+  return *made[T];
+}
+
+// Smallest compiled tile count whose bases hold a modulus of `bits` bits with
+// 2^30 to spare, or 0.
+inline int rns_tiles(int bits) {
+  for (int T : pc2k::RNS_T) {
+    if (256 * T < bits) continue;  // 16 T channels of less than 16 bits
+    const RnsBase& R = rns_base(T);
+    if (R.ok && bitlen(R.MA) > bits + 31 && bitlen(R.MB) > bits + 31) return T;
+  }
+  return 0;
+}
+
+// The first extension's matrix of modulus N; false if N shares a factor with
+// a channel modulus or a bound does not hold.
+inline bool rns_e1(const RnsBase& R, const Limbs& N, std::vector<uint32_t>* frag,
+                   std::vector<uint32_t>* cst) {
+  const int n = R.n;
+  std::vector<int32_t> E((size_t)n * n);
+  std::vector<uint32_t> k(n);
+  for (int i = 0; i < n; ++i) {
+    const uint32_t a = R.a[i], inv = inv_small(mod_small(N, a), a);
+    if (!inv) return false;
+    k[i] = (uint32_t)((uint64_t)(a - inv) * R.iMAi[i] % a);
+  }
+  for (int j = 0; j < n; ++j) {
+    const uint32_t m = R.b[j];
+    const uint64_t Nj = mod_small(N, m);
+    if (!Nj) return false;
+    const uint64_t f = Nj * R.s[j] % m;
+    for (int i = 0; i < n; ++i) {
+      const int64_t ki = centred(k[i], R.a[i]);  // centred, as q's bound wants
+      const int64_t t = (int64_t)(f * R.ia[(size_t)j * n + i] % m);
+      E[(size_t)j * n + i] = centred(ki * t, m);
+    }
+  }
+  return rns_pack(E, R.b, R.a, true, frag, cst);
+}
+
+// Input conversion by the constant f: rows 2^(16 i) f mod N (add: plus 1).
+struct RnsToHost {
+  std::vector<uint32_t> P, add, m;
+  int nhalf = 0;
+};
+inline RnsToHost rns_to(const RnsBase& R, const Limbs& N0, const Limbs& f, int nhalf,
+                        bool add_one) {
+  RnsToHost o;
+  Limbs N = N0;
+  trim(N);
+  const int n = R.n, T = R.T;
+  o.nhalf = nhalf;
+  o.P.assign((size_t)4 * T * nhalf * 8, 0);
+  o.add.assign((size_t)4 * T * 8, 0);
+  o.m.assign((size_t)4 * T * 8, 0);
+  std::vector<uint32_t> m(2 * n), r(2 * n), Nm(2 * n);
+  for (int c = 0; c < 2 * n; ++c) m[c] = c < n ? R.b[c] : R.a[c - n];  // part 0: base B
+  Limbs v = mod_words(f, N);
+  v = resized(v, N.size());
+  for (int c = 0; c < 2 * n; ++c) {
+    r[c] = mod_small(v, m[c]);
+    Nm[c] = mod_small(N, m[c]);
+  }
+  const size_t nl = N.size();
+  const double Ntop = (double)N[nl - 1] * 4294967296.0 + (nl > 1 ? N[nl - 2] : 0);
+  for (int i = 0; i < nhalf; ++i) {
+    for (int c = 0; c < 2 * n; ++c) {
+      const uint64_t sc = c < n ? R.s[c] : 1;
+      o.P[((size_t)(c / 8) * nhalf + i) * 8 + (c & 7)] = (uint32_t)(r[c] * sc % m[c]);
+    }
+    if (i + 1 == nhalf) break;
+    // v <- 2^16 v mod N, on the limbs and on the residues
+    Limbs w(nl + 1, 0);
+    for (size_t l = 0; l < nl; ++l) {
+      w[l] |= v[l] << 16;
+      w[l + 1] |= v[l] >> 16;
+    }
+    const double wtop = ((double)w[nl] * 4294967296.0 + w[nl - 1]) * 4294967296.0 +
+                        (nl > 1 ? w[nl - 2] : 0);
+    int64_t q = (int64_t)(wtop / Ntop);
+    Limbs qn = resized(mul_small(N, (uint32_t)q), nl + 1);
+    if (cmp(qn, w) > 0) {
+      --q;
+      qn = resized(mul_small(N, (uint32_t)q), nl + 1);
+    }
+    w = sub(w, qn);
+    if (cmp(w, N) >= 0) {
+      ++q;
+      w = sub(w, N);
+    }
+    v = resized(w, nl);
+    for (int c = 0; c < 2 * n; ++c) {
+      int64_t t = ((int64_t)r[c] * 65536 - q * (int64_t)Nm[c]) % (int64_t)m[c];
+      r[c] = (uint32_t)(t < 0 ? t + m[c] : t);
+    }
+  }
+  for (int c = 0; c < 2 * n; ++c) {
+    o.m[c] = m[c];
+    if (add_one) o.add[c] = c < n ? R.s[c] : 1u;
+  }
+  return o;
+}
+
+// Output conversion; mont: of values in Montgomery form (divides by MA).
+struct RnsFromHost {
+  std::vector<uint32_t> C, D, O, N28;
+  std::vector<int64_t> F;
+  int S = 0, nblk = 0;
+  double ntop_inv = 0;
+};
+inline std::vector<uint32_t> limbs28(const Limbs& v, int S) {
+  std::vector<uint32_t> out(S, 0);
+  for (int i = 0; i < S; ++i) {
+    const long bit = 28l * i;
+    const size_t w = bit / 32;
+    const uint64_t lo = w < v.size() ? v[w] : 0, hi = w + 1 < v.size() ? v[w + 1] : 0;
+    out[i] = (uint32_t)(((hi << 32) | lo) >> (bit % 32)) & ((1u << 28) - 1u);
+  }
+  return out;
+}
+inline RnsFromHost rns_from(const RnsBase& R, const Limbs& N0, bool mont) {
+  RnsFromHost o;
+  Limbs N = N0;
+  trim(N);
+  const int n = R.n;
+  o.S = (bitlen(N) + 27 + 27) / 28;
+  o.nblk = (o.S + 7) / 8;
+  const int SB = 8 * o.nblk;
+  const Mont32 M(N);
+  Limbs iMA;  // MA^-1 mod N
+  if (mont) {
+    // the product of the a_i^-1 mod N, each (1 + N t) / a_i with
+    // t = -N^-1 mod a_i
+    iMA = M.to(Limbs{1});
+    for (int i = 0; i < n; ++i) {
+      const uint32_t a = R.a[i];
+      const uint32_t t = (a - inv_small(mod_small(N, a), a)) % a;
+      Limbs x = mul_small(N, t);
+      x = add(x, Limbs{1});
+      iMA = M.mm(iMA, M.to(div_small(x, a)));
+    }
+    iMA = M.from(iMA);
+  }
+  const Limbs f = mont ? M.to(iMA) : Limbs{};
+  auto scaled = [&](const Limbs& x) {
+    Limbs r = resized(mod_words(x, N), N.size());
+    return mont ? M.mm(r, f) : r;
+  };
+  o.C.assign((size_t)o.nblk * n * 8, 0);
+  for (int j = 0; j < n; ++j) {
+    Limbs c = scaled(R.gMB[j]);
+    if (R.g[j] < 0 && !is_zero(c)) c = sub(resized(N, N.size()), c);
+    const std::vector<uint32_t> l = limbs28(c, SB);
+    for (int i = 0; i < SB; ++i) o.C[((size_t)(i / 8) * n + j) * 8 + i % 8] = l[i];
+    o.F.push_back((int64_t)std::nearbyintl((long double)R.g[j] / (long double)R.b[j] *
+                                           68719476736.0L));
+  }
+  Limbs d = scaled(R.MB);
+  if (!is_zero(d)) d = sub(resized(N, N.size()), d);
+  o.D = limbs28(d, SB);
+  Limbs off(N.size() + 1, 0);
+  off = resized(mul_small(N, 1u << 26), N.size() + 1);
+  o.O = limbs28(off, SB);
+  o.N28 = limbs28(N, SB);
+  double top = 0;
+  for (int i = o.S - 1; i >= o.S - 4 && i >= 0; --i) top = top * 268435456.0 + o.N28[i];
+  o.ntop_inv = 1.0 / top;
+  return o;
+}
+
+// The program of x^e (sliding-window schedule `sched` of width w), closed by
+// the product with the second input if gm.
+inline std::vector<uint32_t> rns_program(const std::vector<uint32_t>& sched, int w, bool gm) {
+  using namespace pc2k;
+  std::vector<uint32_t> p;
+  const uint32_t half = 1u << (w - 1);  // entry j < half: x^(2 j + 1); entry half: x^2
+  p.push_back(rns_op(RNS_LOAD, 0, RNS_NODST));
+  p.push_back(rns_op(RNS_MUL, RNS_SQ, half));
+  p.push_back(rns_op(RNS_MUL, 0, 1));
+  for (uint32_t j = 2; j < half; ++j) p.push_back(rns_op(RNS_MUL, half, j));
+  p.push_back(rns_op(RNS_LOAD, (sched[0] & 0xFFFFu) >> 1, RNS_NODST));
+  for (size_t i = 1; i < sched.size(); ++i) {
+    for (uint32_t k = sched[i] >> 16; k; --k) p.push_back(rns_op(RNS_MUL, RNS_SQ, RNS_NODST));
+    const uint32_t d = sched[i] & 0xFFFFu;
+    if (d) p.push_back(rns_op(RNS_MUL, d >> 1, RNS_NODST));
+  }
+  if (gm) p.push_back(rns_op(RNS_MUL, RNS_GM, RNS_NODST));
+  if (p.back() >> 16 != RNS_MUL) return {};  // the power is a table entry: not a key's exponent
+  p.back() = rns_op(RNS_MUL, p.back() & 0xFFu, RNS_OUT);
+  p.push_back(rns_op(RNS_END, 0, RNS_NODST));
+  return p;
+}
+
+}  // namespace pc2h

@@ -1,0 +1,80 @@
+// Device-visible constants of the residue-number-system (RNS) powering engine
+// (rns_mont.hpp) and its launch plumbing.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stddef.h>
+#include <stdint.h>
+
+namespace pc2k {
+
+// One odd modulus N in the RNS of T tiles: two bases of 16 T channels each, A
+// (moduli a_i, product MA, the Montgomery R) and B (moduli b_j, product MB).
+// "Half" h of tile t holds channels 16 t + 8 h .. + 7.
+struct RnsMod {
+  const uint8_t* E1;    // base extension A -> B: T x T fragments of 1 KB
+  const uint8_t* E2;    // base extension B -> A
+  const int32_t* c1;    // [T][2 halves][16] initial accumulators of E1
+  const int32_t* c2;    // ... of E2
+  const uint32_t* kb;   // [T][2][24]: 1/b_j (8 floats), -b_j (8), F1 pairs (4), F2 pairs (4)
+  const uint32_t* ka;   // [T][2][24]: 1/a_i (8 floats), -a_i (8), -MB pairs (8)
+};
+
+// Input conversion: sum_i half_i P[i] over the 16-bit halves of the input,
+// P[i] one residue per channel, plus a constant `add` per channel.
+struct RnsTo {
+  const uint32_t* P;    // [2 parts][T][2 halves][nhalf][8]
+  const uint32_t* add;  // [2 parts][T][2 halves][8]
+  const uint32_t* m;    // [2 parts][T][2 halves][8] channel moduli
+  int nhalf;            // halves of the longest input
+};
+
+// Output conversion: the value mod N (canonical) from the residues mod b_j.
+struct RnsFrom {
+  const uint32_t* C;    // [limb blocks of 8][16 T][8]: 28-bit limbs of C_j
+  const uint32_t* D;    // 28-bit limbs of -MB (or -MB / MA) mod N, 8 blocks limbs
+  const uint32_t* O;    // 28-bit limbs of 2^26 N
+  const uint32_t* N28;  // 28-bit limbs of N
+  const int64_t* F;     // [16 T]: round(2^36 g_j / b_j)
+  int S;                // 28-bit limbs of 2^27 N
+  int nblk;             // limb blocks: S <= 8 nblk
+  int nw;               // 32-bit words of a result
+  double ntop_inv;      // 1 / (N's limbs S - 4 .. S - 1 as a number)
+};
+
+// Powering programs (rns_mont.hpp): one word per operation.
+constexpr uint32_t RNS_SQ = 0xFF;                          // multiplier: the running value
+constexpr uint32_t RNS_GM = 0xFD;                          // multiplier: the second input
+constexpr uint32_t RNS_NODST = 0xFF, RNS_OUT = 0xFE;       // destinations
+constexpr uint32_t RNS_MUL = 0, RNS_LOAD = 1, RNS_END = 2; // kinds
+constexpr uint32_t rns_op(uint32_t kind, uint32_t y, uint32_t dst) {
+  return kind << 16 | dst << 8 | y;
+}
+
+// A launch of k_rns_pow: nmod moduli (1, or the two primes' squares), each
+// with its program and its groups' inputs; item i is group i / nmod of
+// modulus i % nmod.
+struct RnsPow {
+  RnsMod M[2];
+  const uint32_t* ops[2];
+  uint8_t* in[2];        // first input (Montgomery form) and the result, per group
+  uint8_t* gm[2];        // second input, or null
+  uint8_t* table;        // per workgroup: entries x one group's residues
+  int nmod, ngroups, entries;
+};
+
+constexpr int RNS_NT = 6, RNS_NBMAX = 4;
+constexpr int RNS_T[RNS_NT] = {5, 9, 13, 17, 26, 34};  // compiled tile counts
+
+// A modulus and its programs for window widths 2..6.
+struct RnsKey {
+  int T;                    // 0: the engine does not take this modulus
+  RnsMod M;
+  RnsTo x, gm;              // the power's base (times MA); 1 + m n
+  RnsFrom from;
+  const uint32_t* ops[5];
+};
+
+// bytes of the residues of one group of nb column blocks, both bases
+constexpr size_t rns_group_bytes(int T, int nb) { return (size_t)T * nb * 2048; }
+
+}  // namespace pc2k
