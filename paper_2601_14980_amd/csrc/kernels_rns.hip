@@ -23,14 +23,23 @@ using pc2k::RnsTo;
 
 namespace {
 
-// One wavefront per SIMD pair of the program's steps; see RGeo for the split.
-template <class G>
-__global__ __launch_bounds__(G::W * 64, G::W == 8 ? 2 : 2) void k_rns_pow(RnsPow P) {
-  __shared__ __align__(16) RWork<G> ws;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+// One wavefront's run over its workgroup's groups; SIDE 0: X (or the only
+// group of wavefronts), 1: Y.  Both sides meet at the same barriers; see RGeo.
+template <class G, int SIDE>
+__device__ __forceinline__ void pow_run(const RnsPow& P, RWork<G>& ws, int wave, int lane) {
+  constexpr bool X = SIDE == 0;
+  constexpr bool U = (X ? G::RX : G::RY) > 0;
   constexpr size_t GB = 2 * (size_t)G::PART * 16;  // bytes of one group's residues
+  const int w = X ? wave : wave - G::W / 2;
+  const int t0 = (X ? 0 : G::NX) + w * G::MT;
+  const bool unit = w < (X ? G::RX : G::RY) * G::NB;
+  const int u = unit ? w : 0;
+  const int tu = (X ? 0 : G::NX) + (G::XY ? G::W / 2 : G::W) * G::MT + (U ? u / G::NB : 0);
+  const int bu = U ? u % G::NB : 0;
+  const bool first = (int)threadIdx.x < G::NB * 32;  // (X wavefronts) clears beta
   uint8_t* slot = P.table + (size_t)blockIdx.x * P.entries * GB;
   const int nitems = P.ngroups * P.nmod;
+  Share<G, U> h;
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
     const int mod = P.nmod == 2 ? (it & 1) : 0;
     const int g = P.nmod == 2 ? it >> 1 : it;
@@ -44,36 +53,116 @@ __global__ __launch_bounds__(G::W * 64, G::W == 8 ? 2 : 2) void k_rns_pow(RnsPow
       if (e == 0 || e >= pc2k::RNS_OUT) p = in;
       return Buf(p, (uint32_t)GB);
     };
-    uint32_t op = ops[0];
+    auto is_mul = [](uint32_t op) { return op >> 16 == pc2k::RNS_MUL && (op & 0xFF) != pc2k::RNS_SQ; };
+    auto stores = [](uint32_t op) { return ((op >> 8) & 0xFF) != pc2k::RNS_NODST; };
+    // operands of the reductions of product `op` in base B, and in base A,
+    // where the multiplier is the next product's
+    auto ops_b = [&](uint32_t op) {
+      return Operands{is_mul(op), stores(op), entry(op & 0xFF), entry((op >> 8) & 0xFF)};
+    };
+    auto ops_a = [&](uint32_t op, uint32_t next) {
+      return Operands{is_mul(next), stores(op), entry(next & 0xFF), entry((op >> 8) & 0xFF)};
+    };
     int par = 0;
-    for (int k = 1;; ++k) {
-      const uint32_t next = ops[k];
-      const uint32_t y = op & 0xFF, d = (op >> 8) & 0xFF;
-      const uint32_t nk = next >> 16, ny = next & 0xFF;
-      const bool nmul = nk == pc2k::RNS_MUL && ny != pc2k::RNS_SQ;
-      const Buf nb = entry(ny);  // the next product's multiplier
-      if (op >> 16 == pc2k::RNS_LOAD) {
-        const Buf e = entry(y);
-        PC2R_FOR_ITEMS(G, wave, {
-          for (int m = 0; m < MT; ++m)
-            for (int b = 0; b < NBN; ++b) load_unit<G>(M, ws, t0 + m, nb0 + b, e, nmul, nb, lane);
-        });
+    int k = 0;
+    uint32_t op = ops[0], prev = 0;
+    for (;;) {
+      // op is a load: every wavefront its own tiles
+      {
+        const uint32_t next = ops[k + 1];
+        const Buf e = entry(op & 0xFF), y = entry(next & 0xFF);
+        for (int m = 0; m < G::MT; ++m)
+          for (int b = 0; b < G::NB; ++b)
+            load_unit<G>(M, ws, t0 + m, b, e, is_mul(next), y, lane);
+        if (U && unit) load_unit<G>(M, ws, tu, bu, e, is_mul(next), y, lane);
         for (int i = threadIdx.x; i < 2 * G::NB * 32; i += G::W * 64) (&ws.beta[0][0])[i] = 0;
-        lds_barrier();
-      } else {
-        const bool mul = y != pc2k::RNS_SQ, store = d != pc2k::RNS_NODST;
-        const Buf yb = entry(y), db = entry(d);
-        PC2R_FOR_ITEMS(G, wave, (ext1<G, MT, NBN>(M, ws, par, t0, nb0, mul, yb, store, db, lane)));
-        lds_barrier();
-        if (nk == pc2k::RNS_END) break;
-        PC2R_FOR_ITEMS(G, wave,
-                       (ext2<G, MT, NBN>(M, ws, par, t0, nb0, nmul, nb, store, db, lane)));
-        par ^= 1;
-        if ((int)threadIdx.x < G::NB * 32) ws.beta[par][threadIdx.x] = 0;
+        op = next;
+        ++k;
+        if (X) h.prime(M.E1, M.c1, t0, tu, lane);
         lds_barrier();
       }
-      op = next;
+      bool pending = false;  // Y: the last product's reductions in base A
+      for (;;) {
+        // products: A -> B
+        const uint32_t next = ops[++k];
+        if constexpr (!G::XY) {
+          h.template part<0, G::T>(M.E1, M.kb, ws.xi, t0, tu, bu, lane);
+          finish_b(h, M, ws, par, t0, unit, tu, bu, ops_b(op), lane);
+          h.prime(M.E2, M.c2, t0, tu, lane);
+          lds_barrier();
+          if (next >> 16 == pc2k::RNS_END) break;
+          h.template part<0, G::T>(M.E2, M.ka, ws.om, t0, tu, bu, lane);
+          finish_a(h, M, ws, par, t0, unit, tu, bu, ops_a(op, next), lane);
+          par ^= 1;
+          if (first) ws.beta[par][threadIdx.x] = 0;
+          h.prime(M.E1, M.c1, t0, tu, lane);
+          lds_barrier();
+        } else if constexpr (X) {
+          __builtin_amdgcn_s_setprio(1);
+          h.template part<0, G::NX>(M.E1, M.kb, ws.xi, t0, tu, bu, lane);
+          lds_barrier();
+          __builtin_amdgcn_s_setprio(2);
+          h.template part<G::NX, G::T>(M.E1, M.kb, ws.xi, t0, tu, bu, lane);
+          __builtin_amdgcn_s_setprio(0);
+          finish_b(h, M, ws, par, t0, unit, tu, bu, ops_b(op), lane);
+          h.prime(M.E2, M.c2, t0, tu, lane);
+          lds_barrier();
+          if (next >> 16 == pc2k::RNS_END) break;
+          __builtin_amdgcn_s_setprio(1);
+          h.template part<0, G::NX>(M.E2, M.ka, ws.om, t0, tu, bu, lane);
+          lds_barrier();
+          __builtin_amdgcn_s_setprio(2);
+          h.template part<G::NX, G::T>(M.E2, M.ka, ws.om, t0, tu, bu, lane);
+          __builtin_amdgcn_s_setprio(0);
+          finish_a(h, M, ws, par, t0, unit, tu, bu, ops_a(op, next), lane);
+          par ^= 1;
+          if (first) ws.beta[par][threadIdx.x] = 0;
+          h.prime(M.E1, M.c1, t0, tu, lane);
+          lds_barrier();
+        } else {
+          if (pending) finish_a(h, M, ws, par ^ 1, t0, unit, tu, bu, ops_a(prev, op), lane);
+          h.prime(M.E1, M.c1, t0, tu, lane);
+          lds_barrier();
+          __builtin_amdgcn_s_setprio(1);
+          h.template part<0, G::T>(M.E1, M.kb, ws.xi, t0, tu, bu, lane);
+          __builtin_amdgcn_s_setprio(0);
+          lds_barrier();
+          finish_b(h, M, ws, par, t0, unit, tu, bu, ops_b(op), lane);
+          if (next >> 16 == pc2k::RNS_END) break;
+          h.prime(M.E2, M.c2, t0, tu, lane);
+          lds_barrier();
+          __builtin_amdgcn_s_setprio(1);
+          h.template part<0, G::T>(M.E2, M.ka, ws.om, t0, tu, bu, lane);
+          __builtin_amdgcn_s_setprio(0);
+          par ^= 1;
+          pending = true;
+          lds_barrier();
+        }
+        prev = op;
+        op = next;
+        if (op >> 16 != pc2k::RNS_MUL) break;
+      }
+      if (ops[k] >> 16 == pc2k::RNS_END) break;
+      if constexpr (G::XY) {
+        if (!X) finish_a(h, M, ws, par ^ 1, t0, unit, tu, bu, ops_a(prev, op), lane);
+        lds_barrier();  // beta is read before the load clears it
+      }
     }
+    lds_barrier();  // the next group's load overwrites the residues
+  }
+}
+
+template <class G>
+__global__ __launch_bounds__(G::W * 64, 2) void k_rns_pow(RnsPow P) {
+  __shared__ __align__(16) RWork<G> ws;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if constexpr (G::XY) {
+    if (wave < G::W / 2)
+      pow_run<G, 0>(P, ws, wave, lane);
+    else
+      pow_run<G, 1>(P, ws, wave, lane);
+  } else {
+    pow_run<G, 0>(P, ws, wave, lane);
   }
 }
 
@@ -296,65 +385,42 @@ __global__ __launch_bounds__(64) void k_rns_dec_finish(pc2k::SkConst sk,
 namespace pc2k {
 
 namespace {
-// (T, NB) -> geometry: see RGeo.  P pairs, Q singles, unit offset.
+// (T, NB) -> geometry: wavefronts, and whether they run as two sides.
 template <int T, int NB>
 struct Pick;
-#define PC2_RNS_GEO(T, NB, W, P, Q, UO) \
-  template <>                           \
-  struct Pick<T, NB> {                  \
-    using G = RGeo<T, NB, W, P, Q, UO>; \
+#define PC2_RNS_GEOS(D)                                                       \
+  D(5, 1, 4, false) D(5, 2, 4, false) D(5, 4, 4, false)                       \
+  D(9, 1, 8, false) D(9, 2, 4, false) D(9, 4, 4, false)                       \
+  D(13, 1, 8, false) D(13, 2, 4, false) D(13, 3, 4, false)                    \
+  D(17, 1, 8, true) D(17, 2, 8, true) D(17, 4, 8, true)                       \
+  D(26, 1, 8, true) D(26, 2, 8, true) D(26, 3, 8, true)                       \
+  D(34, 1, 8, true) D(34, 2, 8, true)
+#define PC2_RNS_PICK(T, NB, W, XY) \
+  template <>                      \
+  struct Pick<T, NB> {             \
+    using G = RGeo<T, NB, W, XY>;  \
   };
-PC2_RNS_GEO(5, 1, 4, 0, 4, 0)
-PC2_RNS_GEO(5, 2, 4, 0, 4, 0)
-PC2_RNS_GEO(5, 4, 4, 0, 4, 0)
-PC2_RNS_GEO(9, 1, 8, 0, 8, 0)
-PC2_RNS_GEO(9, 2, 4, 4, 0, 0)
-PC2_RNS_GEO(9, 4, 4, 4, 0, 0)
-PC2_RNS_GEO(13, 1, 8, 4, 4, 4)
-PC2_RNS_GEO(13, 2, 8, 4, 4, 4)
-PC2_RNS_GEO(13, 4, 8, 4, 4, 4)
-PC2_RNS_GEO(17, 1, 8, 8, 0, 0)
-PC2_RNS_GEO(17, 2, 8, 8, 0, 0)
-PC2_RNS_GEO(17, 4, 8, 8, 0, 0)
-PC2_RNS_GEO(26, 1, 8, 12, 0, 4)
-PC2_RNS_GEO(26, 2, 8, 12, 0, 4)
-PC2_RNS_GEO(26, 3, 8, 12, 0, 4)
-PC2_RNS_GEO(34, 1, 8, 16, 0, 0)
-PC2_RNS_GEO(34, 2, 8, 16, 0, 0)
-#undef PC2_RNS_GEO
+PC2_RNS_GEOS(PC2_RNS_PICK)
+#undef PC2_RNS_PICK
 }  // namespace
 
-#define PC2_RNS_CASE(T, NB, EXPR) \
-  if (t == T && nb == NB) {       \
-    using G = Pick<T, NB>::G;     \
-    EXPR;                         \
+#define PC2_RNS_CASE(T, NB, W, XY) \
+  if (t == T && nb == NB) {        \
+    using G = Pick<T, NB>::G;      \
+    PC2_RNS_DO;                    \
   }
-#define PC2_RNS_DISPATCH(EXPR) \
-  PC2_RNS_CASE(5, 1, EXPR)     \
-  PC2_RNS_CASE(5, 2, EXPR)     \
-  PC2_RNS_CASE(5, 4, EXPR)     \
-  PC2_RNS_CASE(9, 1, EXPR)     \
-  PC2_RNS_CASE(9, 2, EXPR)     \
-  PC2_RNS_CASE(9, 4, EXPR)     \
-  PC2_RNS_CASE(13, 1, EXPR)    \
-  PC2_RNS_CASE(13, 2, EXPR)    \
-  PC2_RNS_CASE(13, 4, EXPR)    \
-  PC2_RNS_CASE(17, 1, EXPR)    \
-  PC2_RNS_CASE(17, 2, EXPR)    \
-  PC2_RNS_CASE(17, 4, EXPR)    \
-  PC2_RNS_CASE(26, 1, EXPR)    \
-  PC2_RNS_CASE(26, 2, EXPR)    \
-  PC2_RNS_CASE(26, 3, EXPR)    \
-  PC2_RNS_CASE(34, 1, EXPR)    \
-  PC2_RNS_CASE(34, 2, EXPR)
 
 const void* rns_pow_kernel(int t, int nb) {
-  PC2_RNS_DISPATCH(return (const void*)&k_rns_pow<G>)
+#define PC2_RNS_DO return (const void*)&k_rns_pow<G>
+  PC2_RNS_GEOS(PC2_RNS_CASE)
+#undef PC2_RNS_DO
   return nullptr;
 }
 
 int rns_pow_threads(int t, int nb) {
-  PC2_RNS_DISPATCH(return G::W * 64)
+#define PC2_RNS_DO return G::W * 64
+  PC2_RNS_GEOS(PC2_RNS_CASE)
+#undef PC2_RNS_DO
   return 0;
 }
 

@@ -56,20 +56,28 @@ namespace pc2r {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-typedef short v2s __attribute__((ext_vector_type(2)));
 
-// T tiles, NB column blocks, W wavefronts.  Of the T x NB (tile, column
-// block) units, P pairs of tiles and Q single tiles are taken over all column
-// blocks at once (wavefront p % W), the units of the remaining tiles one by
-// one (wavefront (u + UO) % W; the single tile q goes to wavefront (P + q) %
-// W): chosen so that the four SIMDs get the same
-// number of units.
-template <int T_, int NB_, int W_, int P_, int Q_, int UO_>
+// T tiles, NB column blocks, W wavefronts.  A wavefront owns MT tiles over all
+// column blocks; each of the R = T - W MT tiles left is split into its NB
+// column blocks ("units"), one per wavefront.
+//
+// XY: the wavefronts 0..3 (X) and 4..7 (Y; one of each per SIMD) run half a
+// phase apart, so that one's reductions (vector ALUs) run beside the other's
+// matrix instructions.  X owns tiles 0 .. NX - 1 and starts a phase with the
+// chunks of its own tiles while Y still reduces the previous phase; Y joins
+// for the whole matrix product, and reduces while X has gone on.
+template <int T_, int NB_, int W_, bool XY_>
 struct RGeo {
-  static constexpr int T = T_, NB = NB_, W = W_, P = P_, Q = Q_, UO = UO_;
-  static constexpr int NU = (T_ - 2 * P_ - Q_) * NB_;  // single units
+  static constexpr int T = T_, NB = NB_, W = W_;
+  static constexpr bool XY = XY_;
+  static constexpr int MT = T_ / W_;
+  static constexpr int R = T_ - W_ * MT;               // tiles split into units
+  static constexpr int RX = XY_ ? (R + 1) / 2 : R;     // ... of X
+  static constexpr int RY = R - RX;
+  static constexpr int NX = XY_ ? W_ / 2 * MT + RX : T_;  // tiles of X
   static constexpr int PART = T_ * NB_ * 64;           // 16-byte slots of one base
-  static_assert(2 * P_ + Q_ <= T_, "tiles");
+  static_assert(MT >= 1 && (!XY_ || W_ == 8), "wavefronts");
+  static_assert(RX * NB_ <= (XY_ ? W_ / 2 : W_) && RY * NB_ <= W_ / 2, "one unit a wavefront");
 };
 
 template <class G>
@@ -83,9 +91,6 @@ constexpr uint32_t FLIP = 0x00800080u;
 
 __device__ __forceinline__ uint32_t pack16(uint32_t lo, uint32_t hi) {
   return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-}
-__device__ __forceinline__ int dot2(uint32_t a, uint32_t b, int c) {
-  return __builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, a), __builtin_bit_cast(v2s, b), c, false);
 }
 // signed 16-bit halves of packed words
 template <int H>
@@ -124,8 +129,11 @@ struct Buf {
   __device__ __forceinline__ v4u load(uint32_t lane_off, uint32_t off) const {
     return __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)off, 0);
   }
+  // (no scalar offset here: with one the compiler takes a wide store's data
+  // as safe to overwrite in the next vector instruction, which on this chip
+  // it is not -- the last lanes stored the new value)
   __device__ __forceinline__ void store(v4u v, uint32_t lane_off, uint32_t off) const {
-    __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)lane_off, (int)off, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)(lane_off + off), 0, 0);
   }
 };
 
@@ -138,54 +146,10 @@ struct RConst {
         c2(M.c2, G::T * 128), kb(M.kb, G::T * 192), ka(M.ka, G::T * 192) {}
 };
 
-// acc[m][b] = tile t0 + m of the matrix E times column block nb0 + b of src
-template <class G, int MT, int NBN>
-__device__ __forceinline__ void gemm(v16i (&acc)[MT][NBN], const Buf& E, const Buf& cst,
-                                     const v4u* src, int t0, int nb0, int lane) {
-  constexpr int T = G::T, PD = 3;
-  const v4i* s = reinterpret_cast<const v4i*>(src) + nb0 * 64 + lane;
-  const uint32_t lo = lane * 16;
-  v4i a[PD][MT];
-#pragma unroll
-  for (int c = 0; c < PD; ++c)
-#pragma unroll
-    for (int m = 0; m < MT; ++m)
-      a[c][m] = __builtin_bit_cast(v4i, E.load(lo, ((t0 + m) * T + c) * 1024));
-#pragma unroll
-  for (int m = 0; m < MT; ++m) {
-    v16i c0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const v4u v = cst.load((lane >> 5) * 64, (t0 + m) * 128 + 16 * i);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) c0[4 * i + j] = (int)v[j];
-    }
-#pragma unroll
-    for (int b = 0; b < NBN; ++b) acc[m][b] = c0;
-  }
-#pragma unroll
-  for (int c = 0; c < T; ++c) {
-    v4i y[NBN];
-#pragma unroll
-    for (int b = 0; b < NBN; ++b) y[b] = s[(c * G::NB + b) * 64];
-#pragma unroll
-    for (int m = 0; m < MT; ++m)
-#pragma unroll
-      for (int b = 0; b < NBN; ++b)
-        acc[m][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[c % PD][m], y[b], acc[m][b], 0, 0, 0);
-    if (c + PD < T) {
-#pragma unroll
-      for (int m = 0; m < MT; ++m)
-        a[c % PD][m] = __builtin_bit_cast(v4i, E.load(lo, ((t0 + m) * T + c + PD) * 1024));
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
 // Channel constants of one tile half: three groups of eight words.
 struct ChanConst {
   uint32_t w[24];
-  __device__ __forceinline__ ChanConst(const Buf& k, int t, int lane) {
+  __device__ __forceinline__ void load(const Buf& k, int t, int lane) {
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
       const v4u v = k.load((lane >> 5) * 96, t * 192 + 16 * i);
@@ -195,108 +159,232 @@ struct ChanConst {
   }
 };
 
-// A -> B: tiles t0 .. t0 + MT - 1 of w <- w y + E1 xi, for NBN column blocks.
-// y: the multiplier (mul; else w itself); dst: where a copy of the result
-// goes (store); the tiles' share of beta is added to ws.beta[par].
-template <class G, int MT, int NBN>
-__device__ __forceinline__ void ext1(const RConst<G>& M, RWork<G>& ws, int par, int t0, int nb0,
-                                     bool mul, const Buf& y, bool store, const Buf& dst,
-                                     int lane) {
-  v16i acc[MT][NBN];
-  gemm<G, MT, NBN>(acc, M.E1, M.c1, ws.xi, t0, nb0, lane);
-  int s1[NBN], s2[NBN];
+// A wavefront's share of a phase: the tiles t0 .. t0 + MT - 1 over all column
+// blocks and (U) the unit (tu, bu), with its accumulators and the fragments of
+// the constant matrix in flight (PD chunks ahead).
+template <class G, bool U>
+struct Share {
+  static constexpr int T = G::T, MT = G::MT, NB = G::NB, PD = 3, MA = MT + (U ? 1 : 0);
+  v16i acc[MT][NB];
+  v16i accu;
+  v4i a[PD][MA];
+  ChanConst k;  // of tile t0, loaded ahead of the reductions
+
+  // fragment row of accumulator m (opaque, so that the scalar offsets of a
+  // product's fragments are formed where they are used and not kept)
+  __device__ __forceinline__ static uint32_t row(int t0, int tu, int m) {
+    uint32_t r = (uint32_t)(m < MT ? t0 + m : tu) * (T * 1024);
+    asm volatile("" : "+s"(r));
+    return r;
+  }
+  // issue the first loads of a product with E
+  __device__ __forceinline__ void prime(const Buf& E, const Buf& cst, int t0, int tu, int lane) {
 #pragma unroll
-  for (int b = 0; b < NBN; ++b) s1[b] = s2[b] = 0;
+    for (int c = 0; c < PD; ++c)
 #pragma unroll
-  for (int m = 0; m < MT; ++m) {
-    const ChanConst k(M.kb, t0 + m, lane);
-    const int at = ((t0 + m) * G::NB + nb0) * 64;
-    v4u x[NBN], f[NBN];
+      for (int m = 0; m < MA; ++m)
+        a[c][m] = __builtin_bit_cast(v4i, E.load(lane * 16, row(t0, tu, m) + c * 1024));
 #pragma unroll
-    for (int b = 0; b < NBN; ++b) x[b] = f[b] = ws.om[at + b * 64 + lane] ^ FLIP;
-    if (mul) {
-#pragma unroll
-      for (int b = 0; b < NBN; ++b) f[b] = y.load(lane * 16, (at + b * 64) * 16);
-    }
-#pragma unroll
-    for (int b = 0; b < NBN; ++b) {
-      v4u o;
+    for (int m = 0; m < MA; ++m) {
+      v16i c0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        uint32_t r[2];
-        r[0] = reduce(mad16<0>(x[b][i], f[b][i], (acc[m][b][4 * i + 1] << 8) + acc[m][b][4 * i]),
-                      k.w[2 * i], k.w[8 + 2 * i]);
-        r[1] = reduce(
-            mad16<1>(x[b][i], f[b][i], (acc[m][b][4 * i + 3] << 8) + acc[m][b][4 * i + 2]),
-            k.w[2 * i + 1], k.w[8 + 2 * i + 1]);
-        o[i] = pack16(r[0], r[1]);
-        s1[b] = dot2(o[i], k.w[16 + i], s1[b]);
-        s2[b] = dot2(o[i], k.w[20 + i], s2[b]);
+        const v4u v = cst.load((lane >> 5) * 64, (m < MT ? t0 + m : tu) * 128 + 16 * i);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) c0[4 * i + j] = (int)v[j];
       }
-      if (store) dst.store(o, lane * 16, (at + b * 64) * 16);
-      ws.om[at + b * 64 + lane] = o ^ FLIP;
+      if (m < MT)
+        acc[m][0] = c0;
+      else
+        accu = c0;
     }
+  }
+  // chunks C0 .. C1 - 1 of the product; src: the residues in LDS; kc: the
+  // channel constants that the reductions after the last chunk need
+  template <int C0, int C1>
+  __device__ __forceinline__ void part(const Buf& E, const Buf& kc, const v4u* src, int t0,
+                                       int tu, int bu, int lane) {
+    const v4i* s = reinterpret_cast<const v4i*>(src) + lane;
+    const v4i* su = s + bu * 64;
+    uint32_t at[MA];
+#pragma unroll
+    for (int m = 0; m < MA; ++m) at[m] = row(t0, tu, m);
+    v4i y[2][NB], yu[2];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) y[C0 & 1][b] = s[(C0 * NB + b) * 64];
+    if constexpr (U) yu[C0 & 1] = su[C0 * NB * 64];
+#pragma unroll
+    for (int c = C0; c < C1; ++c) {
+      if (c + 1 < C1) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) y[(c + 1) & 1][b] = s[((c + 1) * NB + b) * 64];
+        if constexpr (U) yu[(c + 1) & 1] = su[(c + 1) * NB * 64];
+      }
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int b = NB - 1; b >= 0; --b)
+          acc[m][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
+              a[c % PD][m], y[c & 1][b], c == 0 ? acc[m][0] : acc[m][b], 0, 0, 0);
+      if constexpr (U)
+        accu = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[c % PD][MT], yu[c & 1], accu, 0, 0, 0);
+      if (c + PD < T) {
+#pragma unroll
+        for (int m = 0; m < MA; ++m)
+          a[c % PD][m] = __builtin_bit_cast(v4i, E.load(lane * 16, at[m] + (c + PD) * 1024));
+      }
+      if (c == T - 2) k.load(kc, t0, lane);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+};
+
+// The multiplier of a product (mul; else the running value itself) and the
+// destination of a copy of its result (store).
+struct Operands {
+  bool mul, store;
+  Buf y, dst;
+};
+
+// The reductions after A -> B, tile t over column blocks nb0 ..: w <- w y +
+// acc, and the tile's share of beta into s1, s2.
+template <class G, int NBN>
+__device__ __forceinline__ void reduce_b(const v16i (&acc)[NBN], const ChanConst& k, RWork<G>& ws,
+                                         int t, int nb0, const Operands& o, int (&s1)[NBN],
+                                         int (&s2)[NBN], int lane) {
+  const int at = (t * G::NB + nb0) * 64;
+  v4u x[NBN], f[NBN];
+#pragma unroll
+  for (int b = 0; b < NBN; ++b) x[b] = f[b] = ws.om[at + b * 64 + lane] ^ FLIP;
+  if (o.mul) {
+#pragma unroll
+    for (int b = 0; b < NBN; ++b) f[b] = o.y.load(lane * 16, (at + b * 64) * 16);
   }
 #pragma unroll
   for (int b = 0; b < NBN; ++b) {
-    const long long s = (long long)s1[b] * 8192 + s2[b];
-    __hip_atomic_fetch_add(&ws.beta[par][(nb0 + b) * 32 + (lane & 31)], (unsigned long long)s,
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    v4u z;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t r0 =
+          reduce(mad16<0>(x[b][i], f[b][i], (acc[b][4 * i + 1] << 8) + acc[b][4 * i]),
+                 k.w[2 * i], k.w[8 + 2 * i]);
+      const uint32_t r1 =
+          reduce(mad16<1>(x[b][i], f[b][i], (acc[b][4 * i + 3] << 8) + acc[b][4 * i + 2]),
+                 k.w[2 * i + 1], k.w[9 + 2 * i]);
+      z[i] = pack16(r0, r1);
+      s1[b] = mad16<1>(z[i], k.w[16 + i], mad16<0>(z[i], k.w[16 + i], s1[b]));
+      s2[b] = mad16<1>(z[i], k.w[20 + i], mad16<0>(z[i], k.w[20 + i], s2[b]));
+    }
+    if (o.store) o.dst.store(z, lane * 16, (at + b * 64) * 16);
+    ws.om[at + b * 64 + lane] = z ^ FLIP;
+  }
+}
+template <class G>
+__device__ __forceinline__ void add_beta(RWork<G>& ws, int par, int b, int s1, int s2, int lane) {
+  const long long s = (long long)s1 * 8192 + s2;
+  __hip_atomic_fetch_add(&ws.beta[par][b * 32 + (lane & 31)], (unsigned long long)s,
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <class G, bool U>
+__device__ __forceinline__ void finish_b(Share<G, U>& h, const RConst<G>& M, RWork<G>& ws,
+                                         int par, int t0, bool unit, int tu, int bu,
+                                         const Operands& o, int lane) {
+  int s1[G::NB] = {}, s2[G::NB] = {};
+  ChanConst k[2];
+  k[0] = h.k;
+#pragma unroll
+  for (int m = 0; m < G::MT; ++m) {
+    if (m + 1 < G::MT)
+      k[(m + 1) & 1].load(M.kb, t0 + m + 1, lane);
+    else if (U)
+      k[(m + 1) & 1].load(M.kb, tu, lane);
+    reduce_b<G, G::NB>(h.acc[m], k[m & 1], ws, t0 + m, 0, o, s1, s2, lane);
+  }
+#pragma unroll
+  for (int b = 0; b < G::NB; ++b) add_beta<G>(ws, par, b, s1[b], s2[b], lane);
+  if constexpr (U) {
+    if (unit) {
+      int u1[1] = {}, u2[1] = {};
+      const v16i au[1] = {h.accu};
+      reduce_b<G, 1>(au, k[G::MT & 1], ws, tu, bu, o, u1, u2, lane);
+      add_beta<G>(ws, par, bu, u1[0], u2[0], lane);
+    }
   }
 }
 
-// B -> A: tiles of x <- E2 w - beta MB, then xi <- x y for the next product
-// (y: its multiplier if mul, else x itself); a copy of x goes to dst (store).
-template <class G, int MT, int NBN>
-__device__ __forceinline__ void ext2(const RConst<G>& M, RWork<G>& ws, int par, int t0, int nb0,
-                                     bool mul, const Buf& y, bool store, const Buf& dst,
-                                     int lane) {
-  v16i acc[MT][NBN];
-  gemm<G, MT, NBN>(acc, M.E2, M.c2, ws.om, t0, nb0, lane);
-  uint32_t bp[NBN];
+// beta of column block b, as the pair (low 12 bits, rest)
+template <class G>
+__device__ __forceinline__ uint32_t read_beta(const RWork<G>& ws, int par, int b, int lane) {
+  const long long s = (long long)ws.beta[par][b * 32 + (lane & 31)];
+  const int beta = (int)((s + (1 << 24)) >> 25);
+  const int lo = (int)((uint32_t)beta << 20) >> 20;
+  return pack16((uint32_t)lo, (uint32_t)((beta - lo) >> 12));
+}
+
+// The reductions after B -> A: x <- acc - beta MB, then xi <- x y for the next
+// product, whose multiplier o names (o.dst: where this product's x goes).
+template <class G, int NBN>
+__device__ __forceinline__ void reduce_a(const v16i (&acc)[NBN], const uint32_t (&bp)[NBN],
+                                         const ChanConst& k, RWork<G>& ws, int t, int nb0,
+                                         const Operands& o, int lane) {
+  const int at = (t * G::NB + nb0) * 64;
+  v4u x[NBN], f[NBN];
 #pragma unroll
   for (int b = 0; b < NBN; ++b) {
-    const long long s = (long long)ws.beta[par][(nb0 + b) * 32 + (lane & 31)];
-    const int beta = (int)((s + (1 << 24)) >> 25);
-    const int lo = (int)((uint32_t)beta << 20) >> 20;
-    bp[b] = pack16((uint32_t)lo, (uint32_t)((beta - lo) >> 12));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t r[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        r[j] = reduce(mad16<1>(bp[b], k.w[16 + 2 * i + j],
+                               mad16<0>(bp[b], k.w[16 + 2 * i + j],
+                                        (acc[b][4 * i + 2 * j + 1] << 8) +
+                                            acc[b][4 * i + 2 * j])),
+                      k.w[2 * i + j], k.w[8 + 2 * i + j]);
+      x[b][i] = pack16(r[0], r[1]);
+    }
+    f[b] = x[b];
+  }
+  if (o.store) {
+#pragma unroll
+    for (int b = 0; b < NBN; ++b) o.dst.store(x[b], lane * 16, (G::PART + at + b * 64) * 16);
+  }
+  if (o.mul) {
+#pragma unroll
+    for (int b = 0; b < NBN; ++b) f[b] = o.y.load(lane * 16, (G::PART + at + b * 64) * 16);
   }
 #pragma unroll
-  for (int m = 0; m < MT; ++m) {
-    const ChanConst k(M.ka, t0 + m, lane);
-    const int at = ((t0 + m) * G::NB + nb0) * 64;
-    v4u x[NBN], f[NBN];
+  for (int b = 0; b < NBN; ++b) {
+    v4u z;
 #pragma unroll
-    for (int b = 0; b < NBN; ++b) {
+    for (int i = 0; i < 4; ++i)
+      z[i] = pack16(reduce(mad16<0>(x[b][i], f[b][i], 0), k.w[2 * i], k.w[8 + 2 * i]),
+                    reduce(mad16<1>(x[b][i], f[b][i], 0), k.w[2 * i + 1], k.w[9 + 2 * i]));
+    ws.xi[at + b * 64 + lane] = z ^ FLIP;
+  }
+}
+template <class G, bool U>
+__device__ __forceinline__ void finish_a(Share<G, U>& h, const RConst<G>& M, RWork<G>& ws,
+                                         int par, int t0, bool unit, int tu, int bu,
+                                         const Operands& o, int lane) {
+  uint32_t bp[G::NB];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        uint32_t r[2];
+  for (int b = 0; b < G::NB; ++b) bp[b] = read_beta<G>(ws, par, b, lane);
+  ChanConst k[2];
+  k[0] = h.k;
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-          r[j] = reduce(dot2(bp[b], k.w[16 + 2 * i + j],
-                             (acc[m][b][4 * i + 2 * j + 1] << 8) + acc[m][b][4 * i + 2 * j]),
-                        k.w[2 * i + j], k.w[8 + 2 * i + j]);
-        x[b][i] = pack16(r[0], r[1]);
-      }
-      f[b] = x[b];
-    }
-    if (store) {
-#pragma unroll
-      for (int b = 0; b < NBN; ++b) dst.store(x[b], lane * 16, (G::PART + at + b * 64) * 16);
-    }
-    if (mul) {
-#pragma unroll
-      for (int b = 0; b < NBN; ++b) f[b] = y.load(lane * 16, (G::PART + at + b * 64) * 16);
-    }
-#pragma unroll
-    for (int b = 0; b < NBN; ++b) {
-      v4u o;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        o[i] = pack16(
-            reduce(mad16<0>(x[b][i], f[b][i], 0), k.w[2 * i], k.w[8 + 2 * i]),
-            reduce(mad16<1>(x[b][i], f[b][i], 0), k.w[2 * i + 1], k.w[9 + 2 * i]));
-      ws.xi[at + b * 64 + lane] = o ^ FLIP;
+  for (int m = 0; m < G::MT; ++m) {
+    if (m + 1 < G::MT)
+      k[(m + 1) & 1].load(M.ka, t0 + m + 1, lane);
+    else if (U)
+      k[(m + 1) & 1].load(M.ka, tu, lane);
+    reduce_a<G, G::NB>(h.acc[m], bp, k[m & 1], ws, t0 + m, 0, o, lane);
+  }
+  if constexpr (U) {
+    if (unit) {
+      const uint32_t bpu[1] = {read_beta<G>(ws, par, bu, lane)};
+      const v16i au[1] = {h.accu};
+      reduce_a<G, 1>(au, bpu, k[G::MT & 1], ws, tu, bu, o, lane);
     }
   }
 }
@@ -310,7 +398,8 @@ __device__ __forceinline__ void load_unit(const RConst<G>& M, RWork<G>& ws, int 
   const v4u x = e.load(lane * 16, (G::PART + at) * 16);
   v4u y = x;
   if (mul) y = yb.load(lane * 16, (G::PART + at) * 16);
-  const ChanConst k(M.ka, t, lane);
+  ChanConst k;
+  k.load(M.ka, t, lane);
   v4u o;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -318,25 +407,5 @@ __device__ __forceinline__ void load_unit(const RConst<G>& M, RWork<G>& ws, int 
                   reduce(mad16<1>(x[i], y[i], 0), k.w[2 * i + 1], k.w[9 + 2 * i]));
   ws.xi[at + lane] = o ^ FLIP;
 }
-
-// run F<MT, NBN>(t0, nb0) over the wavefront's share of the units
-#define PC2R_FOR_ITEMS(G, wave, CALL)                                        \
-  do {                                                                       \
-    for (int u_ = (wave); u_ < G::P; u_ += G::W) {                           \
-      constexpr int MT = 2, NBN = G::NB;                                     \
-      const int t0 = 2 * u_, nb0 = 0;                                        \
-      CALL;                                                                  \
-    }                                                                        \
-    for (int u_ = ((wave) + G::W - G::P % G::W) % G::W; u_ < G::Q; u_ += G::W) { \
-      constexpr int MT = 1, NBN = G::NB;                                     \
-      const int t0 = 2 * G::P + u_, nb0 = 0;                                 \
-      CALL;                                                                  \
-    }                                                                        \
-    for (int u_ = ((wave) + G::W - G::UO % G::W) % G::W; u_ < G::NU; u_ += G::W) { \
-      constexpr int MT = 1, NBN = 1;                                         \
-      const int t0 = 2 * G::P + G::Q + u_ / G::NB, nb0 = u_ % G::NB;         \
-      CALL;                                                                  \
-    }                                                                        \
-  } while (0)
 
 }  // namespace pc2r
