@@ -396,7 +396,7 @@ pc2k::PkConst pk_const_alt(const uint32_t* base, const PkOffsets& o, const pc2k:
 // ---------------------------------------------------------- RNS engine keys
 struct RnsOffsets {
   int T = 0;
-  size_t E1, E2, c1, c2, kb, ka;
+  size_t E1, E2, c2, kb, ka;
   struct To { size_t P, add, m; int nhalf; } x, gm;
   struct From { size_t C, D, O, N28, F; int S, nblk; double ntop_inv; } from;
   size_t ops[5];
@@ -426,7 +426,6 @@ RnsOffsets add_rns(DevBuf& buf, const Limbs& N, int T, const Limbs& e, int nhalf
     if (prog[w - pc2k::SCHED_WMIN].empty()) return o;
   }
   o.E1 = add_aligned(buf, E1);
-  o.c1 = add_aligned(buf, c1);
   if (same && same->T == T) {
     o.E2 = same->E2;
     o.c2 = same->c2;
@@ -460,7 +459,7 @@ pc2k::RnsKey rns_const(const uint32_t* base, const RnsOffsets& o, int nw) {
   if (o.T == 0) return k;
   k.T = o.T;
   k.M = {(const uint8_t*)(base + o.E1), (const uint8_t*)(base + o.E2),
-         (const int32_t*)(base + o.c1), (const int32_t*)(base + o.c2), base + o.kb, base + o.ka};
+         (const int32_t*)(base + o.c2), base + o.kb, base + o.ka};
   k.x = rns_to_const(base, o.x);
   if (o.gm.nhalf) k.gm = rns_to_const(base, o.gm);
   k.from = {base + o.from.C, base + o.from.D, base + o.from.O, base + o.from.N28,

@@ -78,7 +78,7 @@ __device__ __forceinline__ void pow_run(const RnsPow& P, RWork<G>& ws, int wave,
         for (int i = threadIdx.x; i < 2 * G::NB * 32; i += G::W * 64) (&ws.beta[0][0])[i] = 0;
         op = next;
         ++k;
-        if (X) h.prime(M.E1, M.c1, t0, tu, lane);
+        if (X) h.prime(M.E1, t0, tu, lane);
         lds_barrier();
       }
       bool pending = false;  // Y: the last product's reductions in base A
@@ -86,53 +86,59 @@ __device__ __forceinline__ void pow_run(const RnsPow& P, RWork<G>& ws, int wave,
         // products: A -> B
         const uint32_t next = ops[++k];
         if constexpr (!G::XY) {
-          h.template part<0, G::T>(M.E1, M.kb, ws.xi, t0, tu, bu, lane);
+          h.template init<false>(ws.c2, M.c2, t0, tu, lane);
+          h.template part<0, G::T>(M.E1, ws.kb, M.kb, ws.xi, t0, tu, bu, lane);
           finish_b(h, M, ws, par, t0, unit, tu, bu, ops_b(op), lane);
-          h.prime(M.E2, M.c2, t0, tu, lane);
+          h.prime(M.E2, t0, tu, lane);
           lds_barrier();
           if (next >> 16 == pc2k::RNS_END) break;
-          h.template part<0, G::T>(M.E2, M.ka, ws.om, t0, tu, bu, lane);
+          h.template init<true>(ws.c2, M.c2, t0, tu, lane);
+          h.template part<0, G::T>(M.E2, ws.ka, M.ka, ws.om, t0, tu, bu, lane);
           finish_a(h, M, ws, par, t0, unit, tu, bu, ops_a(op, next), lane);
           par ^= 1;
           if (first) ws.beta[par][threadIdx.x] = 0;
-          h.prime(M.E1, M.c1, t0, tu, lane);
+          h.prime(M.E1, t0, tu, lane);
           lds_barrier();
         } else if constexpr (X) {
           __builtin_amdgcn_s_setprio(1);
-          h.template part<0, G::NX>(M.E1, M.kb, ws.xi, t0, tu, bu, lane);
+          h.template init<false>(ws.c2, M.c2, t0, tu, lane);
+          h.template part<0, G::NX>(M.E1, ws.kb, M.kb, ws.xi, t0, tu, bu, lane);
           lds_barrier();
           __builtin_amdgcn_s_setprio(2);
-          h.template part<G::NX, G::T>(M.E1, M.kb, ws.xi, t0, tu, bu, lane);
+          h.template part<G::NX, G::T>(M.E1, ws.kb, M.kb, ws.xi, t0, tu, bu, lane);
           __builtin_amdgcn_s_setprio(0);
           finish_b(h, M, ws, par, t0, unit, tu, bu, ops_b(op), lane);
-          h.prime(M.E2, M.c2, t0, tu, lane);
+          h.prime(M.E2, t0, tu, lane);
           lds_barrier();
           if (next >> 16 == pc2k::RNS_END) break;
           __builtin_amdgcn_s_setprio(1);
-          h.template part<0, G::NX>(M.E2, M.ka, ws.om, t0, tu, bu, lane);
+          h.template init<true>(ws.c2, M.c2, t0, tu, lane);
+          h.template part<0, G::NX>(M.E2, ws.ka, M.ka, ws.om, t0, tu, bu, lane);
           lds_barrier();
           __builtin_amdgcn_s_setprio(2);
-          h.template part<G::NX, G::T>(M.E2, M.ka, ws.om, t0, tu, bu, lane);
+          h.template part<G::NX, G::T>(M.E2, ws.ka, M.ka, ws.om, t0, tu, bu, lane);
           __builtin_amdgcn_s_setprio(0);
           finish_a(h, M, ws, par, t0, unit, tu, bu, ops_a(op, next), lane);
           par ^= 1;
           if (first) ws.beta[par][threadIdx.x] = 0;
-          h.prime(M.E1, M.c1, t0, tu, lane);
+          h.prime(M.E1, t0, tu, lane);
           lds_barrier();
         } else {
           if (pending) finish_a(h, M, ws, par ^ 1, t0, unit, tu, bu, ops_a(prev, op), lane);
-          h.prime(M.E1, M.c1, t0, tu, lane);
+          h.prime(M.E1, t0, tu, lane);
           lds_barrier();
           __builtin_amdgcn_s_setprio(1);
-          h.template part<0, G::T>(M.E1, M.kb, ws.xi, t0, tu, bu, lane);
+          h.template init<false>(ws.c2, M.c2, t0, tu, lane);
+          h.template part<0, G::T>(M.E1, ws.kb, M.kb, ws.xi, t0, tu, bu, lane);
           __builtin_amdgcn_s_setprio(0);
           lds_barrier();
           finish_b(h, M, ws, par, t0, unit, tu, bu, ops_b(op), lane);
           if (next >> 16 == pc2k::RNS_END) break;
-          h.prime(M.E2, M.c2, t0, tu, lane);
+          h.prime(M.E2, t0, tu, lane);
           lds_barrier();
           __builtin_amdgcn_s_setprio(1);
-          h.template part<0, G::T>(M.E2, M.ka, ws.om, t0, tu, bu, lane);
+          h.template init<true>(ws.c2, M.c2, t0, tu, lane);
+          h.template part<0, G::T>(M.E2, ws.ka, M.ka, ws.om, t0, tu, bu, lane);
           __builtin_amdgcn_s_setprio(0);
           par ^= 1;
           pending = true;
@@ -156,6 +162,8 @@ template <class G>
 __global__ __launch_bounds__(G::W * 64, 2) void k_rns_pow(RnsPow P) {
   __shared__ __align__(16) RWork<G> ws;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  load_constants<G>(P.M[0], ws);
+  lds_barrier();
   if constexpr (G::XY) {
     if (wave < G::W / 2)
       pow_run<G, 0>(P, ws, wave, lane);

@@ -142,15 +142,15 @@ struct RnsBase {
   bool ok = false;
 };
 
-// E[row channel][column channel] (centred mod m_row) -> fragments, initial
-// accumulators and the check of the bounds: |sum| + extra_row < 2^31 for all
-// inputs with |r_col| < 0.52 m_col.
+// E[row channel][column channel] (centred mod m_row) -> fragments, initial sums
+// (128 sum_i E) and the check of the bounds: |sum| + extra_row < 2^31 for all
+// inputs with |r_col| < 0.52 m_col + 128.
 inline bool rns_pack(const std::vector<int32_t>& E, const std::vector<uint32_t>& mrow,
                      const std::vector<uint32_t>& mcol, bool square, std::vector<uint32_t>* frag,
                      std::vector<uint32_t>* cst) {
   const int n = (int)mrow.size(), T = n / 16;
   frag->assign((size_t)T * T * 256, 0);
-  cst->assign((size_t)T * 32, 0);
+  cst->assign((size_t)T * 16, 0);
   uint8_t* out = reinterpret_cast<uint8_t*>(frag->data());
   bool ok = true;
   for (int j = 0; j < n; ++j) {
@@ -160,7 +160,7 @@ inline bool rns_pack(const std::vector<int32_t>& E, const std::vector<uint32_t>&
       const int32_t e = E[(size_t)j * n + i];
       const int32_t f = centred((int64_t)e * 256, mrow[j]);
       sum += e;
-      const int64_t hmax = (int64_t)(0.52 * mcol[i] / 256) + 1;
+      const int64_t hmax = (int64_t)((0.52 * mcol[i] + 128) / 256) + 1;
       bound += 128 * (int64_t)std::abs(e) + hmax * std::abs(f);
       const int c = i / 16, Hk = (i >> 3) & 1, s0 = 2 * (i & 7);
       for (int k = 0; k < 2; ++k) {
@@ -175,7 +175,7 @@ inline bool rns_pack(const std::vector<int32_t>& E, const std::vector<uint32_t>&
       }
     }
     const int32_t c0 = centred(128 * sum, mrow[j]);
-    (*cst)[(size_t)(t * 2 + H) * 16 + 2 * u] = (uint32_t)c0;
+    (*cst)[(size_t)(t * 2 + H) * 8 + u] = (uint32_t)c0;
     const double sq = 0.52 * mrow[j];
     const double extra = square ? sq * sq : (double)(1 << 27);
     if ((double)bound + std::abs(c0) + extra + (1 << 24) >= 2147483648.0) ok = false;

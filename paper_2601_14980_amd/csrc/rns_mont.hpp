@@ -22,8 +22,10 @@
 // carry and no lane exchange.
 //
 // Matrix layout (v_mfma_i32_32x32x32_i8).  A residue r is two signed bytes,
-// the low one with its top bit flipped (r = 256 h + l + 128; the 128 sum_i
-// E[j][i] this adds sits in the initial accumulators).  Both bytes of a
+// the low one with its top bit flipped (r = 256 h + l + 128).  For xi the 128
+// is added to x y before its reduction, so that 256 h + l is the residue; for
+// w, which is also read back as a factor, the 128 sum_j E2[i][j] sits in the
+// initial accumulators of the second extension.  Both bytes of a
 // channel are rows of the right operand: the low byte meets E, the high byte
 // 256 E mod m.  The left operand's rows are the low and the high byte of a
 // channel's constants, in adjacent accumulators of one lane, so that
@@ -76,6 +78,11 @@ struct RGeo {
   static constexpr int RY = R - RX;
   static constexpr int NX = XY_ ? W_ / 2 * MT + RX : T_;  // tiles of X
   static constexpr int PART = T_ * NB_ * 64;           // 16-byte slots of one base
+  // the channel constants (448 bytes a tile) in LDS beside the residues where
+  // they fit without costing a resident workgroup
+  static constexpr int LDS = 2 * PART * 16 + NB_ * 512;
+  static constexpr int WG = W_ == 8 ? 1 : 2;           // workgroups a CU is planned for
+  static constexpr bool KL = (LDS + T_ * 448) * WG <= 160 * 1024;
   static_assert(MT >= 1 && (!XY_ || W_ == 8), "wavefronts");
   static_assert(RX * NB_ <= (XY_ ? W_ / 2 : W_) && RY * NB_ <= W_ / 2, "one unit a wavefront");
 };
@@ -85,9 +92,12 @@ struct RWork {
   v4u xi[G::PART];                          // xi (base A), low bytes flipped
   v4u om[G::PART];                          // w (base B), low bytes flipped
   unsigned long long beta[2][G::NB * 32];   // sum_j w_j g_j / b_j in 2^-25
+  v4u kb[G::KL ? G::T * 12 : 1], ka[G::KL ? G::T * 12 : 1];  // channel constants
+  v4u c2[G::KL ? G::T * 4 : 1];             // initial sums of the second extension
 };
 
 constexpr uint32_t FLIP = 0x00800080u;
+constexpr int BIAS = 128;  // FLIP's value in a residue
 
 __device__ __forceinline__ uint32_t pack16(uint32_t lo, uint32_t hi) {
   return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
@@ -100,6 +110,16 @@ __device__ __forceinline__ int mad16(uint32_t a, uint32_t b, int c) {
     asm("v_mad_i32_i16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   else
     asm("v_mad_i32_i16 %0, %1, %2, %3 op_sel:[1,1,0,0]" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+// a b + bias (a scalar register)
+template <int H>
+__device__ __forceinline__ int mul16_biased(uint32_t a, uint32_t b, int bias) {
+  int r;
+  if constexpr (H == 0)
+    asm("v_mad_i32_i16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(bias));
+  else
+    asm("v_mad_i32_i16 %0, %1, %2, %3 op_sel:[1,1,0,0]" : "=v"(r) : "v"(a), "v"(b), "s"(bias));
   return r;
 }
 // W mod m, centred, in the low 16 bits (the high bits are not meaningful):
@@ -140,19 +160,39 @@ struct Buf {
 // The constants of a modulus.
 template <class G>
 struct RConst {
-  Buf E1, E2, c1, c2, kb, ka;
+  Buf E1, E2, c2, kb, ka;
   __device__ __forceinline__ explicit RConst(const pc2k::RnsMod& M)
-      : E1(M.E1, G::T * G::T * 1024), E2(M.E2, G::T * G::T * 1024), c1(M.c1, G::T * 128),
-        c2(M.c2, G::T * 128), kb(M.kb, G::T * 192), ka(M.ka, G::T * 192) {}
+      : E1(M.E1, G::T * G::T * 1024), E2(M.E2, G::T * G::T * 1024), c2(M.c2, G::T * 64),
+        kb(M.kb, G::T * 192), ka(M.ka, G::T * 192) {}
 };
 
-// Channel constants of one tile half: three groups of eight words.
+// the channel constants to LDS (they depend on T alone, not on the modulus)
+template <class G>
+__device__ __forceinline__ void load_constants(const pc2k::RnsMod& M, RWork<G>& ws) {
+  if constexpr (G::KL) {
+    const v4u *kb = reinterpret_cast<const v4u*>(M.kb), *ka = reinterpret_cast<const v4u*>(M.ka),
+              *c2 = reinterpret_cast<const v4u*>(M.c2);
+    for (int i = threadIdx.x; i < G::T * 12; i += G::W * 64) {
+      ws.kb[i] = kb[i];
+      ws.ka[i] = ka[i];
+      if (i < G::T * 4) ws.c2[i] = c2[i];
+    }
+  }
+}
+
+// Channel constants of one tile half: three groups of eight words, from LDS
+// (loc) or global memory.
+template <class G>
 struct ChanConst {
   uint32_t w[24];
-  __device__ __forceinline__ void load(const Buf& k, int t, int lane) {
+  __device__ __forceinline__ void load(const v4u* loc, const Buf& k, int t, int lane) {
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
-      const v4u v = k.load((lane >> 5) * 96, t * 192 + 16 * i);
+      v4u v;
+      if constexpr (G::KL)
+        v = loc[(t * 2 + (lane >> 5)) * 6 + i];
+      else
+        v = k.load((lane >> 5) * 96, t * 192 + 16 * i);
 #pragma unroll
       for (int j = 0; j < 4; ++j) w[4 * i + j] = v[j];
     }
@@ -168,7 +208,7 @@ struct Share {
   v16i acc[MT][NB];
   v16i accu;
   v4i a[PD][MA];
-  ChanConst k;  // of tile t0, loaded ahead of the reductions
+  ChanConst<G> k;  // of tile t0, loaded ahead of the reductions
 
   // fragment row of accumulator m (opaque, so that the scalar offsets of a
   // product's fragments are formed where they are used and not kept)
@@ -178,20 +218,34 @@ struct Share {
     return r;
   }
   // issue the first loads of a product with E
-  __device__ __forceinline__ void prime(const Buf& E, const Buf& cst, int t0, int tu, int lane) {
+  __device__ __forceinline__ void prime(const Buf& E, int t0, int tu, int lane) {
+    uint32_t at[MA];
+#pragma unroll
+    for (int m = 0; m < MA; ++m) at[m] = row(t0, tu, m);
 #pragma unroll
     for (int c = 0; c < PD; ++c)
 #pragma unroll
       for (int m = 0; m < MA; ++m)
-        a[c][m] = __builtin_bit_cast(v4i, E.load(lane * 16, row(t0, tu, m) + c * 1024));
+        a[c][m] = __builtin_bit_cast(v4i, E.load(lane * 16, at[m] + c * 1024));
+  }
+  // initial sums: zero, or (CST) the second extension's constants
+  template <bool CST>
+  __device__ __forceinline__ void init(const v4u* loc, const Buf& cst, int t0, int tu, int lane) {
 #pragma unroll
     for (int m = 0; m < MA; ++m) {
-      v16i c0;
+      v16i c0{};
+      if constexpr (CST) {
+        const int t = m < MT ? t0 + m : tu;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const v4u v = cst.load((lane >> 5) * 64, (m < MT ? t0 + m : tu) * 128 + 16 * i);
+        for (int i = 0; i < 2; ++i) {
+          v4u v;
+          if constexpr (G::KL)
+            v = loc[(t * 2 + (lane >> 5)) * 2 + i];
+          else
+            v = cst.load((lane >> 5) * 32, t * 64 + 16 * i);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) c0[4 * i + j] = (int)v[j];
+          for (int j = 0; j < 4; ++j) c0[8 * i + 2 * j] = (int)v[j];
+        }
       }
       if (m < MT)
         acc[m][0] = c0;
@@ -202,8 +256,8 @@ struct Share {
   // chunks C0 .. C1 - 1 of the product; src: the residues in LDS; kc: the
   // channel constants that the reductions after the last chunk need
   template <int C0, int C1>
-  __device__ __forceinline__ void part(const Buf& E, const Buf& kc, const v4u* src, int t0,
-                                       int tu, int bu, int lane) {
+  __device__ __forceinline__ void part(const Buf& E, const v4u* kloc, const Buf& kc,
+                                       const v4u* src, int t0, int tu, int bu, int lane) {
     const v4i* s = reinterpret_cast<const v4i*>(src) + lane;
     const v4i* su = s + bu * 64;
     uint32_t at[MA];
@@ -233,7 +287,7 @@ struct Share {
         for (int m = 0; m < MA; ++m)
           a[c % PD][m] = __builtin_bit_cast(v4i, E.load(lane * 16, at[m] + (c + PD) * 1024));
       }
-      if (c == T - 2) k.load(kc, t0, lane);
+      if (c == T - 2) k.load(kloc, kc, t0, lane);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -249,7 +303,7 @@ struct Operands {
 // The reductions after A -> B, tile t over column blocks nb0 ..: w <- w y +
 // acc, and the tile's share of beta into s1, s2.
 template <class G, int NBN>
-__device__ __forceinline__ void reduce_b(const v16i (&acc)[NBN], const ChanConst& k, RWork<G>& ws,
+__device__ __forceinline__ void reduce_b(const v16i (&acc)[NBN], const ChanConst<G>& k, RWork<G>& ws,
                                          int t, int nb0, const Operands& o, int (&s1)[NBN],
                                          int (&s2)[NBN], int lane) {
   const int at = (t * G::NB + nb0) * 64;
@@ -290,14 +344,14 @@ __device__ __forceinline__ void finish_b(Share<G, U>& h, const RConst<G>& M, RWo
                                          int par, int t0, bool unit, int tu, int bu,
                                          const Operands& o, int lane) {
   int s1[G::NB] = {}, s2[G::NB] = {};
-  ChanConst k[2];
+  ChanConst<G> k[2];
   k[0] = h.k;
 #pragma unroll
   for (int m = 0; m < G::MT; ++m) {
     if (m + 1 < G::MT)
-      k[(m + 1) & 1].load(M.kb, t0 + m + 1, lane);
+      k[(m + 1) & 1].load(ws.kb, M.kb, t0 + m + 1, lane);
     else if (U)
-      k[(m + 1) & 1].load(M.kb, tu, lane);
+      k[(m + 1) & 1].load(ws.kb, M.kb, tu, lane);
     reduce_b<G, G::NB>(h.acc[m], k[m & 1], ws, t0 + m, 0, o, s1, s2, lane);
   }
 #pragma unroll
@@ -325,7 +379,7 @@ __device__ __forceinline__ uint32_t read_beta(const RWork<G>& ws, int par, int b
 // product, whose multiplier o names (o.dst: where this product's x goes).
 template <class G, int NBN>
 __device__ __forceinline__ void reduce_a(const v16i (&acc)[NBN], const uint32_t (&bp)[NBN],
-                                         const ChanConst& k, RWork<G>& ws, int t, int nb0,
+                                         const ChanConst<G>& k, RWork<G>& ws, int t, int nb0,
                                          const Operands& o, int lane) {
   const int at = (t * G::NB + nb0) * 64;
   v4u x[NBN], f[NBN];
@@ -358,8 +412,8 @@ __device__ __forceinline__ void reduce_a(const v16i (&acc)[NBN], const uint32_t 
     v4u z;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      z[i] = pack16(reduce(mad16<0>(x[b][i], f[b][i], 0), k.w[2 * i], k.w[8 + 2 * i]),
-                    reduce(mad16<1>(x[b][i], f[b][i], 0), k.w[2 * i + 1], k.w[9 + 2 * i]));
+      z[i] = pack16(reduce(mul16_biased<0>(x[b][i], f[b][i], BIAS), k.w[2 * i], k.w[8 + 2 * i]),
+                    reduce(mul16_biased<1>(x[b][i], f[b][i], BIAS), k.w[2 * i + 1], k.w[9 + 2 * i]));
     ws.xi[at + b * 64 + lane] = z ^ FLIP;
   }
 }
@@ -370,14 +424,14 @@ __device__ __forceinline__ void finish_a(Share<G, U>& h, const RConst<G>& M, RWo
   uint32_t bp[G::NB];
 #pragma unroll
   for (int b = 0; b < G::NB; ++b) bp[b] = read_beta<G>(ws, par, b, lane);
-  ChanConst k[2];
+  ChanConst<G> k[2];
   k[0] = h.k;
 #pragma unroll
   for (int m = 0; m < G::MT; ++m) {
     if (m + 1 < G::MT)
-      k[(m + 1) & 1].load(M.ka, t0 + m + 1, lane);
+      k[(m + 1) & 1].load(ws.ka, M.ka, t0 + m + 1, lane);
     else if (U)
-      k[(m + 1) & 1].load(M.ka, tu, lane);
+      k[(m + 1) & 1].load(ws.ka, M.ka, tu, lane);
     reduce_a<G, G::NB>(h.acc[m], bp, k[m & 1], ws, t0 + m, 0, o, lane);
   }
   if constexpr (U) {
@@ -398,13 +452,13 @@ __device__ __forceinline__ void load_unit(const RConst<G>& M, RWork<G>& ws, int 
   const v4u x = e.load(lane * 16, (G::PART + at) * 16);
   v4u y = x;
   if (mul) y = yb.load(lane * 16, (G::PART + at) * 16);
-  ChanConst k;
-  k.load(M.ka, t, lane);
+  ChanConst<G> k;
+  k.load(ws.ka, M.ka, t, lane);
   v4u o;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
-    o[i] = pack16(reduce(mad16<0>(x[i], y[i], 0), k.w[2 * i], k.w[8 + 2 * i]),
-                  reduce(mad16<1>(x[i], y[i], 0), k.w[2 * i + 1], k.w[9 + 2 * i]));
+    o[i] = pack16(reduce(mul16_biased<0>(x[i], y[i], BIAS), k.w[2 * i], k.w[8 + 2 * i]),
+                  reduce(mul16_biased<1>(x[i], y[i], BIAS), k.w[2 * i + 1], k.w[9 + 2 * i]));
   ws.xi[at + lane] = o ^ FLIP;
 }
 

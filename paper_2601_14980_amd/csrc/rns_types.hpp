@@ -13,8 +13,7 @@ namespace pc2k {
 struct RnsMod {
   const uint8_t* E1;    // base extension A -> B: T x T fragments of 1 KB
   const uint8_t* E2;    // base extension B -> A
-  const int32_t* c1;    // [T][2 halves][16] initial accumulators of E1
-  const int32_t* c2;    // ... of E2
+  const int32_t* c2;    // [T][2 halves][8] initial sums of E2
   const uint32_t* kb;   // [T][2][24]: 1/b_j (8 floats), -b_j (8), F1 pairs (4), F2 pairs (4)
   const uint32_t* ka;   // [T][2][24]: 1/a_i (8 floats), -a_i (8), -MB pairs (8)
 };
