@@ -722,9 +722,14 @@ RnsPlan rns_plan(pc2_ctx* ctx, int T, int nmod, size_t count) {
     const int slots = rns_slots(ctx, T, nb);
     if (!slots) continue;
     RnsPlan p = rns_plan_nb(ctx, T, nmod, count, nb, w);
-    const size_t rounds = (p.ngroups * nmod + slots - 1) / slots;
-    const double per_cu = (double)slots / ctx->cus;  // workgroups that share a CU
-    const double cost = (double)rounds * (1.0 + per_cu * nb);
+    // a round of w workgroups per CU measured 1.45 + w nb, in units of what a
+    // column block adds (2048-bit decryption halves, nb 1 / 2 / 4: 4.1 / 5.9 /
+    // 8.8 ms one per CU, nb 2 / 4: 9.4 / 15.6 ms two per CU; 2048-bit n^2, one
+    // per CU: 16.9 / 24.7 / 41.3 ms)
+    const size_t items = p.ngroups * nmod, occ = (size_t)slots / ctx->cus;
+    const size_t full = items / slots, rest = (items % slots + ctx->cus - 1) / ctx->cus;
+    const double cost = (double)full * (1.45 + (double)(occ * nb)) +
+                        (rest ? 1.45 + (double)(rest * nb) : 0.0);
     if (!best.T || cost < best_cost) {
       best = p;
       best_cost = cost;
@@ -781,8 +786,9 @@ size_t class_scratch_need(pc2_ctx* ctx, int cls, int L, int Ls, int nl2) {
       for (int nb = 1; nb <= pc2k::RNS_NBMAX; ++nb) {
         if (T > tn || !rns_slots(ctx, T, nb)) continue;
         const RnsPlan p = rns_plan_nb(ctx, T, 2, ch, nb, w);
-        need = std::max(need, rns_encrypt_bytes(p));
+        need = std::max(need, rns_encrypt_bytes(p) + 2 * align256(ch * 8 * (size_t)L));
         if (T <= tp) {
+          need = std::max(need, rns_decrypt_bytes(p, ch, Ls, nl2) + align256(ch * 8 * (size_t)L));
           need = std::max(need, rns_decrypt_bytes(p, ch, Ls, nl2));
           need = std::max(need, rns_encrypt_sk_bytes(p, ch, nl2));
         }
@@ -843,140 +849,189 @@ int scratch_end(pc2_ctx* ctx, void* stream, int rc) {
 
 int status_of(hipError_t e) { return e == hipSuccess ? PC2_OK : PC2_E_DEVICE; }
 
-// Public-key encryption on the RNS engine from this many elements on; below,
-// the engines that give an element a wavefront or a tile of its own finish
-// sooner.
-bool use_rns(const pc2_ctx* ctx, const pc2k::RnsKey& k, size_t count) {
-  if (!k.T || ctx->modmul == PC2_MODMUL_VALU) return false;
-  return count >= 256;
+// The Montgomery engine of a public-key encryption of `count` elements.  The
+// RNS engine needs a device-filling number of elements; below that an element
+// with a wavefront of its own finishes sooner (one launch, ms, per-element /
+// RNS: 1024 bits, 2048 elements 1.9 / 3.2, 4096: 3.6 / 3.4; 2048 bits, 2048:
+// 6.7 / 13.1, 4096: 13.7 / 13.3; 3072 bits, 4096: 27.6 / 43.6, 8192: 55.6 /
+// 49.6; 4096 bits, 8192: 115 / 106).  Keys below 1024 bits stay on the VALU
+// engine once it fills the device (VALU / per-element: 256 bits, 4096: 0.62 /
+// 0.40, 16384: 0.68 / 1.46; 512 bits, 4096: 2.67 / 1.14, 16384: 2.71 / 4.05);
+// so does a 1024-bit key that the RNS engine does not take (16384: 9.6 / 11.6).
+enum Engine { ENG_VALU, ENG_ELEM, ENG_RNS };
+constexpr size_t RNS_MIN_COUNT[pc2k::NUM_CLASSES] = {0, 0, 0, 0, 0, 3584, 3840, 6656, 7424};
+constexpr size_t ELEM_MAX_COUNT[pc2k::NUM_CLASSES] = {0, 0, 0, 4096, 8192, 12288};
+Engine enc_engine(const pc2_ctx* ctx, const pc2_pk* pk, size_t count) {
+  if (ctx->modmul == PC2_MODMUL_VALU) return ENG_VALU;
+  if (pk->rn.T && count >= RNS_MIN_COUNT[pk->cls]) return ENG_RNS;
+  if (use_mfma(ctx, pk->cls)) return ENG_ELEM;
+  // (a tile asked for by option is a tile of the VALU engine)
+  return !ctx->tile && count <= ELEM_MAX_COUNT[pk->cls] ? ENG_ELEM : ENG_VALU;
+}
+bool dec_rns(const pc2_ctx* ctx, const pc2_sk* sk) {
+  return sk->dec[1].T && ctx->modmul != PC2_MODMUL_VALU;
 }
 
+pc2k::RnsJobs one_job(const uint32_t* x, const uint32_t* m, int m_limbs, uint32_t* out,
+                      size_t count) {
+  pc2k::RnsJobs J{};
+  J.one = {x, m, out, 0, (uint32_t)count, 0, m_limbs};
+  J.n = 1;
+  J.npos = (uint32_t)count;
+  return J;
+}
+
+// The launches of one key's jobs; base: scratch of rns_encrypt_bytes (...)
+int rns_encrypt_run(pc2_ctx* ctx, const pc2_pk* pk, const pc2k::RnsJobs& J, const RnsPlan& p,
+                    uint8_t* base, void* stream) {
+  const pc2k::RnsKey& K = pk->rn;
+  pc2k::RnsPow pw{};
+  pw.M[0] = K.M;
+  pw.ops[0] = K.ops[p.w - pc2k::SCHED_WMIN];
+  pw.in[0] = base + p.table_bytes;
+  pw.gm[0] = pw.in[0] + p.stage_bytes();
+  pw.table = base;
+  pw.nmod = 1;
+  pw.ngroups = (int)((J.npos + 32 * p.nb - 1) / (32 * p.nb));
+  pw.entries = 1 << (p.w - 1);
+  hipError_t e = pc2k::launch_rns_to(K.x, K.T, p.nb, J, false, pk->L, pw.in[0], stream);
+  if (e == hipSuccess) e = pc2k::launch_rns_to(K.gm, K.T, p.nb, J, true, 0, pw.gm[0], stream);
+  if (e == hipSuccess)
+    e = pc2k::launch_rns_pow(K.T, p.nb, std::min(p.grid, pw.ngroups), pw, stream);
+  if (e == hipSuccess)
+    e = pc2k::launch_rns_from(K.from, K.T, p.nb, pw.in[0], J, nullptr, 0, stream);
+  if (e == hipSuccess)
+    e = pc2k::launch_rns_enc_check(pk->c, J, nullptr, 0, ctx->err, stream);
+  return status_of(e);
+}
+
+int rns_decrypt_run(pc2_ctx* ctx, const pc2_sk* sk, const pc2k::RnsJobs& J, const RnsPlan& p,
+                    uint8_t* base, void* stream) {
+  const int T = p.T, nl2 = sk->c.h[0].s2.nl;
+  uint8_t* in = base + p.table_bytes;
+  uint32_t* ys = reinterpret_cast<uint32_t*>(in + 2 * p.stage_bytes());
+  const size_t stride = nl2 + 1;
+  uint32_t* halves = ys + align256(J.npos * 2 * stride * 4) / 4;
+  pc2k::RnsPow pw{};
+  pw.table = base;
+  pw.nmod = 2;
+  pw.ngroups = (int)((J.npos + 32 * p.nb - 1) / (32 * p.nb));
+  pw.entries = 1 << (p.w - 1);
+  hipError_t e = hipSuccess;
+  for (int i = 0; i < 2 && e == hipSuccess; ++i) {
+    pw.M[i] = sk->dec[i].M;
+    pw.ops[i] = sk->dec[i].ops[p.w - pc2k::SCHED_WMIN];
+    pw.in[i] = in + i * p.stage_bytes();
+    e = pc2k::launch_rns_to(sk->dec[i].x, T, p.nb, J, false, 2 * sk->pk.L, pw.in[i], stream);
+  }
+  if (e == hipSuccess)
+    e = pc2k::launch_rns_pow(T, p.nb, std::min(p.grid, 2 * pw.ngroups), pw, stream);
+  for (int i = 0; i < 2 && e == hipSuccess; ++i)
+    e = pc2k::launch_rns_from(sk->dec[i].from, T, p.nb, pw.in[i], J, ys + i * stride, 2 * stride,
+                              stream);
+  if (e == hipSuccess)
+    e = pc2k::launch_rns_dec_finish(sk->c, J, ys, stride, halves, ctx->err, stream);
+  return status_of(e);
+}
+
+int rns_encrypt_sk_run(pc2_ctx* ctx, const pc2_sk* sk, const pc2k::RnsJobs& J, const RnsPlan& p,
+                       uint8_t* base, void* stream) {
+  const int T = p.T, nl2 = sk->c.h[0].s2.nl;
+  uint8_t* in = base + p.table_bytes;
+  uint32_t* stage = reinterpret_cast<uint32_t*>(in + 4 * p.stage_bytes());
+  const size_t stride = nl2 + 1;
+  pc2k::RnsPow pw{};
+  pw.table = base;
+  pw.nmod = 2;
+  pw.ngroups = (int)((J.npos + 32 * p.nb - 1) / (32 * p.nb));
+  pw.entries = 1 << (p.w - 1);
+  hipError_t e = hipSuccess;
+  for (int i = 0; i < 2 && e == hipSuccess; ++i) {
+    pw.M[i] = sk->enc[i].M;
+    pw.ops[i] = sk->enc[i].ops[p.w - pc2k::SCHED_WMIN];
+    pw.in[i] = in + 2 * i * p.stage_bytes();
+    pw.gm[i] = pw.in[i] + p.stage_bytes();
+    e = pc2k::launch_rns_to(sk->enc[i].x, T, p.nb, J, false, sk->pk.L, pw.in[i], stream);
+    if (e == hipSuccess)
+      e = pc2k::launch_rns_to(sk->enc[i].gm, T, p.nb, J, true, 0, pw.gm[i], stream);
+  }
+  if (e == hipSuccess)
+    e = pc2k::launch_rns_pow(T, p.nb, std::min(p.grid, 2 * pw.ngroups), pw, stream);
+  for (int i = 0; i < 2 && e == hipSuccess; ++i)
+    e = pc2k::launch_rns_from(sk->enc[i].from, T, p.nb, pw.in[i], J, stage + i * stride,
+                              2 * stride, stream);
+  if (e == hipSuccess)
+    e = pc2k::launch_rns_enc_check(sk->pk.c, J, stage + nl2, stride, nullptr, stream);
+  if (e == hipSuccess) e = pc2k::launch_rns_garner_crt(sk->c, J, stage, ctx->err, stream);
+  return status_of(e);
+}
+
+// One-call forms in the context's scratch, in chunks of DEC_CHUNK elements.
 int rns_encrypt(const pc2_pk* pk, const uint32_t* m, int m_limbs, const uint32_t* r, uint32_t* c,
                 size_t count, void* stream) {
   pc2_ctx* ctx = pk->ctx;
-  const pc2k::RnsKey& K = pk->rn;
   const size_t chunk = std::min(count, pc2k::DEC_CHUNK), L = pk->L;
-  const RnsPlan p = rns_plan(ctx, K.T, 1, chunk);
+  const RnsPlan p = rns_plan(ctx, pk->rn.T, 1, chunk);
   if (!ctx->scratch || rns_encrypt_bytes(p) > ctx->scratch_bytes) return PC2_E_NOMEM;
-  uint8_t* base = reinterpret_cast<uint8_t*>(ctx->scratch);
-  uint8_t* in = base + p.table_bytes;
-  uint8_t* gm = in + p.stage_bytes();
   int rc = scratch_begin(ctx, stream);
-  for (size_t b = 0; b < count && !rc; b += chunk) {
-    const size_t n = std::min(chunk, count - b);
-    const uint32_t* mb = m + b * m_limbs;
-    const uint32_t* rb = r + b * L;
-    uint32_t* cb = c + b * 2 * L;
-    pc2k::RnsPow pw{};
-    pw.M[0] = K.M;
-    pw.ops[0] = K.ops[p.w - pc2k::SCHED_WMIN];
-    pw.in[0] = in;
-    pw.gm[0] = gm;
-    pw.table = base;
-    pw.nmod = 1;
-    pw.ngroups = (int)((n + 32 * p.nb - 1) / (32 * p.nb));
-    pw.entries = 1 << (p.w - 1);
-    hipError_t e = pc2k::launch_rns_to(K.x, K.T, p.nb, rb, (int)L, n, in, stream);
-    if (e == hipSuccess) e = pc2k::launch_rns_to(K.gm, K.T, p.nb, mb, m_limbs, n, gm, stream);
-    if (e == hipSuccess)
-      e = pc2k::launch_rns_pow(K.T, p.nb, std::min(p.grid, pw.ngroups), pw, stream);
-    if (e == hipSuccess)
-      e = pc2k::launch_rns_from(K.from, K.T, p.nb, in, n, cb, 2 * L, stream);
-    if (e == hipSuccess)
-      e = pc2k::launch_rns_enc_check(pk->c, mb, m_limbs, rb, cb, n, nullptr, 0, ctx->err, stream);
-    rc = status_of(e);
-  }
+  for (size_t b = 0; b < count && !rc; b += chunk)
+    rc = rns_encrypt_run(ctx, pk,
+                         one_job(r + b * L, m + b * m_limbs, m_limbs, c + b * 2 * L,
+                                 std::min(chunk, count - b)),
+                         p, reinterpret_cast<uint8_t*>(ctx->scratch), stream);
   return scratch_end(ctx, stream, rc);
 }
 
 int rns_decrypt(const pc2_sk* sk, const uint32_t* c, uint32_t* m, size_t count, void* stream) {
   pc2_ctx* ctx = sk->ctx;
-  const int T = sk->dec[0].T, Ls = sk->c.h[0].Ls, nl2 = sk->c.h[0].s2.nl;
   const size_t chunk = std::min(count, pc2k::DEC_CHUNK), L = sk->pk.L;
-  const RnsPlan p = rns_plan(ctx, T, 2, chunk);
-  if (!ctx->scratch || rns_decrypt_bytes(p, chunk, Ls, nl2) > ctx->scratch_bytes)
+  const RnsPlan p = rns_plan(ctx, sk->dec[0].T, 2, chunk);
+  if (!ctx->scratch ||
+      rns_decrypt_bytes(p, chunk, sk->c.h[0].Ls, sk->c.h[0].s2.nl) > ctx->scratch_bytes)
     return PC2_E_NOMEM;
-  uint8_t* base = reinterpret_cast<uint8_t*>(ctx->scratch);
-  uint8_t* in = base + p.table_bytes;
-  uint32_t* ys = reinterpret_cast<uint32_t*>(in + 2 * p.stage_bytes());
-  uint32_t* halves = ys + align256(chunk * 2 * (size_t)(nl2 + 1) * 4) / 4;
-  const size_t stride = nl2 + 1;
   int rc = scratch_begin(ctx, stream);
-  for (size_t b = 0; b < count && !rc; b += chunk) {
-    const size_t n = std::min(chunk, count - b);
-    const uint32_t* cb = c + b * 2 * L;
-    pc2k::RnsPow pw{};
-    pw.table = base;
-    pw.nmod = 2;
-    pw.ngroups = (int)((n + 32 * p.nb - 1) / (32 * p.nb));
-    pw.entries = 1 << (p.w - 1);
-    hipError_t e = hipSuccess;
-    for (int i = 0; i < 2 && e == hipSuccess; ++i) {
-      pw.M[i] = sk->dec[i].M;
-      pw.ops[i] = sk->dec[i].ops[p.w - pc2k::SCHED_WMIN];
-      pw.in[i] = in + i * p.stage_bytes();
-      e = pc2k::launch_rns_to(sk->dec[i].x, T, p.nb, cb, (int)(2 * L), n, pw.in[i], stream);
-    }
-    if (e == hipSuccess)
-      e = pc2k::launch_rns_pow(T, p.nb, std::min(p.grid, 2 * pw.ngroups), pw, stream);
-    for (int i = 0; i < 2 && e == hipSuccess; ++i)
-      e = pc2k::launch_rns_from(sk->dec[i].from, T, p.nb, pw.in[i], n, ys + i * stride,
-                                2 * stride, stream);
-    if (e == hipSuccess)
-      e = pc2k::launch_rns_dec_finish(sk->c, cb, ys, stride, n, halves, stream);
-    if (e == hipSuccess) e = pc2k::launch_garner(sk->c, halves, m + b * L, n, ctx->err, stream);
-    rc = status_of(e);
-  }
+  for (size_t b = 0; b < count && !rc; b += chunk)
+    rc = rns_decrypt_run(
+        ctx, sk, one_job(c + b * 2 * L, nullptr, 0, m + b * L, std::min(chunk, count - b)), p,
+        reinterpret_cast<uint8_t*>(ctx->scratch), stream);
   return scratch_end(ctx, stream, rc);
 }
 
 int rns_encrypt_sk(const pc2_sk* sk, const uint32_t* m, int m_limbs, const uint32_t* r,
                    uint32_t* c, size_t count, void* stream) {
   pc2_ctx* ctx = sk->ctx;
-  const int T = sk->enc[0].T, nl2 = sk->c.h[0].s2.nl;
   const size_t chunk = std::min(count, pc2k::DEC_CHUNK), L = sk->pk.L;
-  const RnsPlan p = rns_plan(ctx, T, 2, chunk);
-  if (!ctx->scratch || rns_encrypt_sk_bytes(p, chunk, nl2) > ctx->scratch_bytes)
+  const RnsPlan p = rns_plan(ctx, sk->enc[0].T, 2, chunk);
+  if (!ctx->scratch || rns_encrypt_sk_bytes(p, chunk, sk->c.h[0].s2.nl) > ctx->scratch_bytes)
     return PC2_E_NOMEM;
-  uint8_t* base = reinterpret_cast<uint8_t*>(ctx->scratch);
-  uint8_t* in = base + p.table_bytes;
-  uint32_t* stage = reinterpret_cast<uint32_t*>(in + 4 * p.stage_bytes());
-  const size_t stride = nl2 + 1;
   int rc = scratch_begin(ctx, stream);
-  for (size_t b = 0; b < count && !rc; b += chunk) {
-    const size_t n = std::min(chunk, count - b);
-    const uint32_t* mb = m + b * m_limbs;
-    const uint32_t* rb = r + b * L;
-    pc2k::RnsPow pw{};
-    pw.table = base;
-    pw.nmod = 2;
-    pw.ngroups = (int)((n + 32 * p.nb - 1) / (32 * p.nb));
-    pw.entries = 1 << (p.w - 1);
-    hipError_t e = hipSuccess;
-    for (int i = 0; i < 2 && e == hipSuccess; ++i) {
-      pw.M[i] = sk->enc[i].M;
-      pw.ops[i] = sk->enc[i].ops[p.w - pc2k::SCHED_WMIN];
-      pw.in[i] = in + 2 * i * p.stage_bytes();
-      pw.gm[i] = pw.in[i] + p.stage_bytes();
-      e = pc2k::launch_rns_to(sk->enc[i].x, T, p.nb, rb, (int)L, n, pw.in[i], stream);
-      if (e == hipSuccess)
-        e = pc2k::launch_rns_to(sk->enc[i].gm, T, p.nb, mb, m_limbs, n, pw.gm[i], stream);
-    }
-    if (e == hipSuccess)
-      e = pc2k::launch_rns_pow(T, p.nb, std::min(p.grid, 2 * pw.ngroups), pw, stream);
-    for (int i = 0; i < 2 && e == hipSuccess; ++i)
-      e = pc2k::launch_rns_from(sk->enc[i].from, T, p.nb, pw.in[i], n, stage + i * stride,
-                                2 * stride, stream);
-    if (e == hipSuccess)
-      e = pc2k::launch_rns_enc_check(sk->pk.c, mb, m_limbs, rb, nullptr, n, stage + nl2, stride,
-                                     nullptr, stream);
-    if (e == hipSuccess)
-      e = pc2k::launch_garner_crt(sk->c, stage, c + b * 2 * L, n, ctx->err, stream);
-    rc = status_of(e);
-  }
+  for (size_t b = 0; b < count && !rc; b += chunk)
+    rc = rns_encrypt_sk_run(ctx, sk,
+                            one_job(r + b * L, m + b * m_limbs, m_limbs, c + b * 2 * L,
+                                    std::min(chunk, count - b)),
+                            p, reinterpret_cast<uint8_t*>(ctx->scratch), stream);
   return scratch_end(ctx, stream, rc);
 }
 
+// The fused path's first phase: prod = prod_k Enc(m_k, r_k), one encryption and
+// one aggregation per addend (a bad input's ciphertext is zero, and so is its
+// product, which does not decrypt).  stage: prod and one addend's ciphertexts.
+int rns_enc_prod(const pc2_sk* sk, const pc2k::PtrList& ms, const pc2k::PtrList& rs, int K,
+                 int m_limbs, uint32_t* prod, uint32_t* tmp, size_t n, const RnsPlan& p,
+                 uint8_t* base, void* stream) {
+  pc2_ctx* ctx = sk->ctx;
+  int rc = PC2_OK;
+  for (int k = 0; k < K && !rc; ++k) {
+    uint32_t* dst = k ? tmp : prod;
+    rc = rns_encrypt_run(ctx, &sk->pk, one_job(rs.p[k], ms.p[k], m_limbs, dst, n), p, base,
+                         stream);
+    if (!rc && k) {
+      const uint32_t* two[2] = {prod, tmp};
+      rc = pc2_hom_sum(&sk->pk, two, 2, prod, n, stream);
+    }
+  }
+  return rc;
+}
 
 
 // Two device arrays [a, a + na) and [b, b + nb) overlap without being the
@@ -1330,8 +1385,9 @@ int pc2_encrypt(const pc2_pk* pk, const uint32_t* m, uint32_t m_limbs, const uin
     return PC2_E_INVAL;
   pc2_ctx* ctx = pk->ctx;
   pc2k::Launch l{};
-  if (use_rns(ctx, pk->rn, count)) return rns_encrypt(pk, m, (int)m_limbs, r, c, count, stream);
-  if (use_mfma(ctx, pk->cls)) {
+  const Engine eng = enc_engine(ctx, pk, count);
+  if (eng == ENG_RNS) return rns_encrypt(pk, m, (int)m_limbs, r, c, count, stream);
+  if (eng == ENG_ELEM) {
     int rc = prepare(ctx, pk->cls, pc2k::OP_ENC_MFMA, count, 0, pk->L, &l, stream);
     if (!rc) rc = scratch_begin(ctx, stream);
     if (rc) return rc;
@@ -1352,8 +1408,7 @@ int pc2_decrypt(const pc2_sk* sk, const uint32_t* c, uint32_t* m, size_t count, 
   if (!c || !m) return PC2_E_INVAL;
   if (partial_overlap(c, 8 * (size_t)sk->pk.L * count, m, 4 * (size_t)sk->pk.L * count))
     return PC2_E_INVAL;
-  if (sk->dec[1].T && sk->ctx->modmul != PC2_MODMUL_VALU)
-    return rns_decrypt(sk, c, m, count, stream);
+  if (dec_rns(sk->ctx, sk)) return rns_decrypt(sk, c, m, count, stream);
   // the two CRT halves of up to DEC_CHUNK elements are staged between the
   // per-prime phase and the recombination
   const int Ls = sk->c.h[0].Ls;
@@ -1516,12 +1571,38 @@ int pc2_enc_sum_dec(const pc2_sk* sk, const uint32_t* const* m_k, const uint32_t
     ms.p[k] = m_k[k];
     rs.p[k] = r_k[k];
   }
-  // per chunk: the products (2L limbs per element), the CRT halves, the
-  // running products (chunked, 16-byte aligned) and the input checks
   pc2_ctx* ctx = sk->ctx;
   const int Ls = sk->c.h[0].Ls, L = sk->pk.L, cls = sk->pk.cls;
-  const bool mf = use_mfma(ctx, cls);
   const size_t chunk = std::min(count, pc2k::DEC_CHUNK);
+  const Engine eng = enc_engine(ctx, &sk->pk, chunk);
+  if (eng == ENG_RNS && dec_rns(ctx, sk)) {
+    const size_t cb = align256(chunk * 8 * (size_t)L);
+    const RnsPlan pe = rns_plan(ctx, sk->pk.rn.T, 1, chunk);
+    const RnsPlan pd = rns_plan(ctx, sk->dec[0].T, 2, chunk);
+    if (!ctx->scratch || 2 * cb + rns_encrypt_bytes(pe) > ctx->scratch_bytes ||
+        cb + rns_decrypt_bytes(pd, chunk, Ls, sk->c.h[0].s2.nl) > ctx->scratch_bytes)
+      return PC2_E_NOMEM;
+    uint32_t* prod = ctx->scratch;
+    uint8_t* rest = reinterpret_cast<uint8_t*>(ctx->scratch) + cb;
+    int rc = scratch_begin(ctx, stream);
+    for (size_t b = 0; b < count && !rc; b += chunk) {
+      const size_t n = std::min(chunk, count - b);
+      pc2k::PtrList mb{}, rb{};
+      for (uint32_t k = 0; k < K; ++k) {
+        mb.p[k] = ms.p[k] + b * m_limbs;
+        rb.p[k] = rs.p[k] + b * (size_t)L;
+      }
+      rc = rns_enc_prod(sk, mb, rb, (int)K, (int)m_limbs, prod,
+                        reinterpret_cast<uint32_t*>(rest), n, pe, rest + cb, stream);
+      if (!rc)
+        rc = rns_decrypt_run(ctx, sk, one_job(prod, nullptr, 0, m_out + b * L, n), pd, rest,
+                             stream);
+    }
+    return scratch_end(ctx, stream, rc);
+  }
+  // per chunk: the products (2L limbs per element), the CRT halves, the
+  // running products (chunked, 16-byte aligned) and the input checks
+  const bool mf = eng == ENG_ELEM || (eng == ENG_RNS && use_mfma(ctx, cls));
   const size_t prod_words = (chunk * 2 * (size_t)L + 63) & ~(size_t)63;
   const size_t half_words = (chunk * 2 * (size_t)(Ls + 1) + 63) & ~(size_t)63;
   const size_t acc_words =

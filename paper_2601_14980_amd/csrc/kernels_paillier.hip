@@ -342,21 +342,6 @@ hipError_t launch_encrypt(int geo, const Launch& l, const PkConst& pk, const uin
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_garner(const SkConst& sk, const uint32_t* halves, uint32_t* m, size_t count,
-                         int* err, void* stream) {
-  if (sk.h[0].Ls > LS_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_garner, dim3((unsigned)((count + 63) / 64)), dim3(64), 0,
-                     (hipStream_t)stream, sk, halves, m, count, err);
-  return hipGetLastError();
-}
-hipError_t launch_garner_crt(const SkConst& sk, const uint32_t* stage, uint32_t* c, size_t count,
-                             int* err, void* stream) {
-  if (sk.h[0].s2.nl > NL2_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_garner_crt, dim3((unsigned)((count + 63) / 64)), dim3(64), 0,
-                     (hipStream_t)stream, sk, stage, c, count, err);
-  return hipGetLastError();
-}
-
 template <int C>
 static hipError_t dec_t(const Launch& l, const SkConst& sk, const uint32_t* c, uint32_t* m,
                         size_t count, uint32_t* halves) {
@@ -366,7 +351,9 @@ static hipError_t dec_t(const Launch& l, const SkConst& sk, const uint32_t* c, u
                      halves);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_garner(sk, halves, m, count, l.err, l.stream);
+  hipLaunchKernelGGL(k_garner, dim3((unsigned)((count + 63) / 64)), dim3(64), 0,
+                     (hipStream_t)l.stream, sk, halves, m, count, l.err);
+  return hipGetLastError();
 }
 hipError_t launch_decrypt(int cls, const Launch& l, const SkConst& sk, const uint32_t* c,
                           uint32_t* m, size_t count, uint32_t* halves) {
@@ -410,7 +397,9 @@ static hipError_t enc_crt_t(const Launch& l, const SkConst& sk, const uint32_t* 
                      l.window, stage);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_garner_crt(sk, stage, c, count, l.err, l.stream);
+  hipLaunchKernelGGL(k_garner_crt, dim3((unsigned)((count + 63) / 64)), dim3(64), 0,
+                     (hipStream_t)l.stream, sk, stage, c, count, l.err);
+  return hipGetLastError();
 }
 hipError_t launch_encrypt_crt(int cls, const Launch& l, const SkConst& sk, const uint32_t* m,
                               int m_limbs, const uint32_t* r, uint32_t* c, size_t count,

@@ -174,29 +174,52 @@ __global__ __launch_bounds__(G::W * 64, 2) void k_rns_pow(RnsPow P) {
   }
 }
 
+// the job and element at a position; false if there is none
+__device__ __forceinline__ bool find_job(const pc2k::RnsJobs& J, uint32_t pos, pc2k::RnsJob& j,
+                                         size_t& e) {
+  if (J.many == nullptr) {
+    j = J.one;
+  } else {
+    int lo = 0, hi = J.n - 1;  // the last job with pos0 <= pos (job 0 starts at 0)
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (J.many[mid].pos0 <= pos)
+        lo = mid;
+      else
+        hi = mid - 1;
+    }
+    j = J.many[lo];
+  }
+  e = j.first + (pos - j.pos0);
+  return pos - j.pos0 < j.count;
+}
+
 // Residues of one wavefront's slot (part, tile, half: eight channels) for 64
-// elements, one per lane: sum_i half_i P[i] + add.  The constants are uniform
-// (scalar loads); elements past `count` repeat the last one, so that every
-// column of a group holds valid residues.
-__global__ __launch_bounds__(256) void k_rns_to(RnsTo C, const uint32_t* __restrict__ x,
-                                                int limbs, size_t count, int T, int nb,
-                                                uint8_t* __restrict__ out) {
+// positions, one per lane: sum_i half_i P[i] + add.  The constants are uniform
+// (scalar loads).
+__global__ __launch_bounds__(256) void k_rns_to(RnsTo C, pc2k::RnsJobs J, bool plain, int limbs,
+                                                int T, int nb, uint8_t* __restrict__ out) {
   const int lane = threadIdx.x & 63;
   const int slot = __builtin_amdgcn_readfirstlane(blockIdx.y * 4 + (threadIdx.x >> 6));
   if (slot >= 4 * T) return;
-  const size_t pos = (size_t)blockIdx.x * 64 + lane;  // position in the padded groups
-  const size_t per = (size_t)nb * 32;
-  const size_t total = (count + per - 1) / per * per;
-  if (pos >= total) return;
-  const size_t e = pos < count ? pos : count - 1;
-  const int nhalf = 2 * limbs < C.nhalf ? 2 * limbs : C.nhalf;
+  const uint32_t pos = blockIdx.x * 64 + lane;
+  const uint32_t per = nb * 32;
+  if (pos >= (J.npos + per - 1) / per * per) return;
+  pc2k::RnsJob j;
+  size_t e;
+  const bool live = find_job(J, pos, j, e);
+  if (plain) limbs = j.m_limbs;
+  const int nhalf = !live ? 0 : 2 * limbs < C.nhalf ? 2 * limbs : C.nhalf;
   const uint32_t* P = C.P + (size_t)slot * C.nhalf * 8;
-  const uint32_t* xe = x + e * limbs;
+  const uint32_t* xe = (plain ? j.m : j.x) + e * limbs;
   uint64_t acc[8];
 #pragma unroll
   for (int c = 0; c < 8; ++c) acc[c] = C.add[slot * 8 + c];
-  for (int i = 0; i < nhalf; i += 2) {
-    const uint32_t w = xe[i >> 1];
+  // (uniform bound: lanes of shorter or no inputs add zeros)
+  const int top = plain ? C.nhalf : 2 * limbs < C.nhalf ? 2 * limbs : C.nhalf;
+  for (int i = 0; i < top; i += 2) {
+    if (plain && __ballot(i < nhalf) == 0) break;
+    const uint32_t w = i < nhalf ? xe[i >> 1] : 0u;
     const uint32_t lo = w & 0xFFFFu, hi = w >> 16;
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[c] += (uint64_t)lo * P[i * 8 + c];
@@ -220,7 +243,7 @@ __global__ __launch_bounds__(256) void k_rns_to(RnsTo C, const uint32_t* __restr
   for (int i = 0; i < 4; ++i) o[i] = pack16(r[2 * i], r[2 * i + 1]);
   // slot = (part T + tile) 2 + half
   const int h = slot & 1, pt = slot >> 1;
-  const size_t grp = pos / per, b = pos % per / 32, n = pos & 31;
+  const uint32_t grp = pos / per, b = pos % per / 32, n = pos & 31;
   uint8_t* g = out + grp * pc2k::rns_group_bytes(T, nb);
   reinterpret_cast<v4u*>(g)[((size_t)pt * nb + b) * 64 + h * 32 + n] = o;
 }
@@ -232,18 +255,18 @@ __global__ __launch_bounds__(256) void k_rns_to(RnsTo C, const uint32_t* __restr
 // first wavefront then joins the blocks, subtracts the quotient by N, and
 // all write the words.
 __global__ __launch_bounds__(512) void k_rns_from(RnsFrom C, const uint8_t* __restrict__ in,
-                                                  size_t count, int T, int nb,
-                                                  uint32_t* __restrict__ out, size_t stride) {
+                                                  pc2k::RnsJobs J, int T, int nb,
+                                                  uint32_t* __restrict__ stage, size_t stride) {
   extern __shared__ __align__(16) uint32_t lds[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nblk = C.nblk;
   uint32_t* limb = lds;                                              // [8 nblk][64]
   int64_t* cy = reinterpret_cast<int64_t*>(lds + (size_t)nblk * 512);  // [nblk][64]
-  const size_t pos0 = (size_t)blockIdx.x * 64 + lane;
-  const size_t pos = pos0 < count ? pos0 : count - 1;
-  const size_t per = (size_t)nb * 32;
-  const size_t grp = pos / per, b = pos % per / 32, n = pos & 31;
+  const uint32_t pos0 = blockIdx.x * 64 + lane;
+  const uint32_t pos = pos0 < J.npos ? pos0 : J.npos - 1;
+  const uint32_t per = nb * 32;
+  const uint32_t grp = pos / per, b = pos % per / 32, n = pos & 31;
   const v4u* g = reinterpret_cast<const v4u*>(in + grp * pc2k::rns_group_bytes(T, nb)) + b * 64 + n;
   // beta = round(sum_j w_j g_j / b_j)
   int64_t s = 0;
@@ -321,71 +344,105 @@ __global__ __launch_bounds__(512) void k_rns_from(RnsFrom C, const uint8_t* __re
   __syncthreads();
   // 32-bit words, coalesced over the words of an element
   for (int e = wave; e < 64; e += 8) {
-    const size_t p = (size_t)blockIdx.x * 64 + e;
-    if (p >= count) break;
+    const uint32_t p = blockIdx.x * 64 + e;
+    if (p >= J.npos) break;
+    pc2k::RnsJob job;
+    size_t el;
+    if (!find_job(J, p, job, el)) continue;
+    uint32_t* out = stage ? stage + p * stride : job.out + el * C.nw;
     for (int j = lane; j < C.nw; j += 64) {
       const int bit = 32 * j, i = bit / 28, sh = bit % 28;
       uint64_t v = limb[i * 64 + e];
       if (i + 1 < 8 * nblk) v |= (uint64_t)limb[(i + 1) * 64 + e] << 28;
       if (i + 2 < 8 * nblk) v |= (uint64_t)limb[(i + 2) * 64 + e] << 56;
-      out[p * stride + j] = (uint32_t)(v >> sh);
+      out[j] = (uint32_t)(v >> sh);
     }
   }
 }
 
-// Input checks of an encryption, one lane per element: with c the element's
+// Input checks of an encryption, one lane per position: the element's
 // ciphertext is zeroed if m >= n, r = 0 or r >= n, and ERR_RANGE latched;
 // with okw the result of the check goes there instead (both halves' words).
-__global__ __launch_bounds__(64) void k_rns_enc_check(pc2k::PkConst pk,
-                                                      const uint32_t* __restrict__ m, int m_limbs,
-                                                      const uint32_t* __restrict__ r,
-                                                      uint32_t* __restrict__ c, size_t count,
+__global__ __launch_bounds__(64) void k_rns_enc_check(pc2k::PkConst pk, pc2k::RnsJobs J,
                                                       uint32_t* __restrict__ okw, size_t stride,
                                                       int* err) {
-  const size_t e = (size_t)blockIdx.x * 64 + threadIdx.x;
-  if (e >= count) return;
+  const uint32_t pos = blockIdx.x * 64 + threadIdx.x;
+  pc2k::RnsJob j;
+  size_t e;
+  if (pos >= J.npos || !find_job(J, pos, j, e)) return;
   const int L = pk.L;
-  const uint32_t* re = r + e * L;
-  bool ok = pc2d::sc_cmp(m + e * m_limbs, m_limbs, pk.n, L) < 0 && pc2d::sc_cmp(re, L, pk.n, L) < 0;
+  const uint32_t* re = j.x + e * L;
+  bool ok = pc2d::sc_cmp(j.m + e * j.m_limbs, j.m_limbs, pk.n, L) < 0 &&
+            pc2d::sc_cmp(re, L, pk.n, L) < 0;
   int i = L - 1;
   while (i >= 0 && re[i] == 0) --i;
   ok = ok && i >= 0;
   if (okw) {
-    okw[2 * e * stride] = ok;
-    okw[(2 * e + 1) * stride] = ok;
+    okw[2 * (size_t)pos * stride] = ok;
+    okw[(2 * (size_t)pos + 1) * stride] = ok;
   } else if (!ok) {
-    for (int j = 0; j < 2 * L; ++j) c[e * 2 * L + j] = 0u;
+    for (int k = 0; k < 2 * L; ++k) j.out[e * 2 * L + k] = 0u;
     atomicOr(err, pc2k::ERR_RANGE);
   }
 }
 
-// The scalar end of a decryption half, one lane per (element, prime): y =
-// c^(s-1) mod s^2 (canonical, nl words at y + (2 e + half) stride) -> m_s =
-// L_s(y) h_s mod s and its validity word at halves + (2 e + half)(Ls + 1).
-__global__ __launch_bounds__(64) void k_rns_dec_finish(pc2k::SkConst sk,
-                                                       const uint32_t* __restrict__ c,
+// The scalar end of a decryption half, one lane per (position, prime): y =
+// c^(s-1) mod s^2 (canonical, nl words at y + (2 pos + half) stride) -> m_s =
+// L_s(y) h_s mod s and its validity word at halves + (2 pos + half)(Ls + 1).
+__global__ __launch_bounds__(64) void k_rns_dec_finish(pc2k::SkConst sk, pc2k::RnsJobs J,
                                                        const uint32_t* __restrict__ ys,
-                                                       size_t stride, size_t count,
+                                                       size_t stride,
                                                        uint32_t* __restrict__ halves) {
-  const size_t i = (size_t)blockIdx.x * 64 + threadIdx.x;
+  const uint32_t pos = blockIdx.x * 64 + threadIdx.x;
   const int half = blockIdx.y;
-  if (i >= count) return;
+  pc2k::RnsJob j;
+  size_t e;
+  if (pos >= J.npos || !find_job(J, pos, j, e)) return;
   const pc2k::HalfConst& H = sk.h[half];
   const int Ls = H.Ls, nl = H.s2.nl, L2 = 2 * sk.pk.L;
-  const bool cv = pc2d::sc_cmp(c + i * L2, L2, sk.pk.n2.Nl, L2) < 0;
+  const bool cv = pc2d::sc_cmp(j.x + e * L2, L2, sk.pk.n2.Nl, L2) < 0;
   uint32_t y[2 * pc2k::LS_MAX + 1], u[pc2k::LS_MAX], us[2 * pc2k::LS_MAX],
       tmp[pc2k::LS_MAX + 2];
-  const uint32_t* src = ys + (2 * i + half) * stride;
-  for (int j = 0; j < nl; ++j) y[j] = src[j];
+  const size_t at = 2 * (size_t)pos + half;
+  const uint32_t* src = ys + at * stride;
+  for (int k = 0; k < nl; ++k) y[k] = src[k];
   const uint32_t one = 1u;
   const uint32_t bor = pc2d::sc_sub(y, nl, &one, 1);
   pc2d::sc_mullo(u, y, H.sinv, Ls);
   pc2d::sc_mul(us, u, Ls, H.s, Ls);
   const bool good = bor == 0 && pc2d::sc_cmp(us, 2 * Ls, y, nl) == 0 && cv;
-  uint32_t* dst = halves + (2 * i + half) * (size_t)(Ls + 1);
+  uint32_t* dst = halves + at * (size_t)(Ls + 1);
   pc2d::sc_montmul(u, u, H.H, H.s, H.s_n0, Ls, tmp);
-  for (int j = 0; j < Ls; ++j) dst[j] = u[j];
+  for (int k = 0; k < Ls; ++k) dst[k] = u[k];
   dst[Ls] = good ? 1u : 0u;
+}
+
+// CRT recombination of decryption halves, one lane per position.
+__global__ __launch_bounds__(64) void k_rns_garner(pc2k::SkConst sk, pc2k::RnsJobs J,
+                                                   const uint32_t* __restrict__ halves,
+                                                   int* err) {
+  const uint32_t pos = blockIdx.x * 64 + threadIdx.x;
+  pc2k::RnsJob j;
+  size_t e;
+  if (pos >= J.npos || !find_job(J, pos, j, e)) return;
+  const int Ls = sk.h[0].Ls;
+  uint32_t work[5 * pc2k::LS_MAX + 2];
+  const uint32_t* hp = halves + pos * 2 * (size_t)(Ls + 1);
+  pc2ops::garner_elem(sk, hp, hp + Ls + 1, j.out + e * sk.pk.L, err, work);
+}
+
+// Recombination of key-holder encryption halves modulo n^2, one lane per position.
+__global__ __launch_bounds__(64) void k_rns_garner_crt(pc2k::SkConst sk, pc2k::RnsJobs J,
+                                                       const uint32_t* __restrict__ stage,
+                                                       int* err) {
+  const uint32_t pos = blockIdx.x * 64 + threadIdx.x;
+  pc2k::RnsJob j;
+  size_t e;
+  if (pos >= J.npos || !find_job(J, pos, j, e)) return;
+  const int n2 = sk.h[0].s2.nl;
+  uint32_t work[10 * pc2k::LS_MAX + 2];
+  const uint32_t* cp = stage + pos * 2 * (size_t)(n2 + 1);
+  pc2ops::garner_crt_elem(sk, cp, cp + n2 + 1, j.out + e * 2 * (size_t)sk.pk.L, err, work);
 }
 
 }  // namespace
@@ -399,9 +456,9 @@ struct Pick;
 #define PC2_RNS_GEOS(D)                                                       \
   D(5, 1, 4, false) D(5, 2, 4, false) D(5, 4, 4, false)                       \
   D(9, 1, 8, false) D(9, 2, 4, false) D(9, 4, 4, false)                       \
-  D(13, 1, 8, false) D(13, 2, 4, false) D(13, 3, 4, false)                    \
+  D(13, 1, 8, false) D(13, 2, 4, false)                                       \
   D(17, 1, 8, true) D(17, 2, 8, true) D(17, 4, 8, true)                       \
-  D(26, 1, 8, true) D(26, 2, 8, true) D(26, 3, 8, true)                       \
+  D(26, 1, 8, true) D(26, 2, 8, true)                                         \
   D(34, 1, 8, true) D(34, 2, 8, true)
 #define PC2_RNS_PICK(T, NB, W, XY) \
   template <>                      \
@@ -432,12 +489,12 @@ int rns_pow_threads(int t, int nb) {
   return 0;
 }
 
-hipError_t launch_rns_to(const RnsTo& c, int T, int nb, const uint32_t* x, int limbs,
-                         size_t count, uint8_t* out, void* stream) {
-  const size_t per = (size_t)nb * 32;
-  const size_t total = (count + per - 1) / per * per;
-  hipLaunchKernelGGL(k_rns_to, dim3((unsigned)((total + 63) / 64), (unsigned)T), dim3(256), 0,
-                     (hipStream_t)stream, c, x, limbs, count, T, nb, out);
+hipError_t launch_rns_to(const RnsTo& c, int T, int nb, const RnsJobs& jobs, bool plain,
+                         int limbs, uint8_t* out, void* stream) {
+  const uint32_t per = nb * 32;
+  const uint32_t total = (jobs.npos + per - 1) / per * per;
+  hipLaunchKernelGGL(k_rns_to, dim3((total + 63) / 64, (unsigned)T), dim3(256), 0,
+                     (hipStream_t)stream, c, jobs, plain, limbs, T, nb, out);
   return hipGetLastError();
 }
 
@@ -449,26 +506,39 @@ hipError_t launch_rns_pow(int t, int nb, int grid, const RnsPow& p, void* stream
                          (hipStream_t)stream);
 }
 
-hipError_t launch_rns_enc_check(const PkConst& pk, const uint32_t* m, int m_limbs,
-                                const uint32_t* r, uint32_t* c, size_t count, uint32_t* okw,
-                                size_t stride, int* err, void* stream) {
-  hipLaunchKernelGGL(k_rns_enc_check, dim3((unsigned)((count + 63) / 64)), dim3(64), 0,
-                     (hipStream_t)stream, pk, m, m_limbs, r, c, count, okw, stride, err);
-  return hipGetLastError();
-}
-
-hipError_t launch_rns_dec_finish(const SkConst& sk, const uint32_t* c, const uint32_t* ys,
-                                 size_t stride, size_t count, uint32_t* halves, void* stream) {
-  hipLaunchKernelGGL(k_rns_dec_finish, dim3((unsigned)((count + 63) / 64), 2), dim3(64), 0,
-                     (hipStream_t)stream, sk, c, ys, stride, count, halves);
-  return hipGetLastError();
-}
-
-hipError_t launch_rns_from(const RnsFrom& c, int T, int nb, const uint8_t* in, size_t count,
-                           uint32_t* out, size_t stride, void* stream) {
+hipError_t launch_rns_from(const RnsFrom& c, int T, int nb, const uint8_t* in,
+                           const RnsJobs& jobs, uint32_t* stage, size_t stride, void* stream) {
   const size_t lds = (size_t)c.nblk * (512 * 4 + 64 * 8);
-  hipLaunchKernelGGL(k_rns_from, dim3((unsigned)((count + 63) / 64)), dim3(512), lds,
-                     (hipStream_t)stream, c, in, count, T, nb, out, stride);
+  hipLaunchKernelGGL(k_rns_from, dim3((jobs.npos + 63) / 64), dim3(512), lds,
+                     (hipStream_t)stream, c, in, jobs, T, nb, stage, stride);
+  return hipGetLastError();
+}
+
+hipError_t launch_rns_enc_check(const PkConst& pk, const RnsJobs& jobs, uint32_t* okw,
+                                size_t stride, int* err, void* stream) {
+  hipLaunchKernelGGL(k_rns_enc_check, dim3((jobs.npos + 63) / 64), dim3(64), 0,
+                     (hipStream_t)stream, pk, jobs, okw, stride, err);
+  return hipGetLastError();
+}
+
+hipError_t launch_rns_dec_finish(const SkConst& sk, const RnsJobs& jobs, const uint32_t* ys,
+                                 size_t stride, uint32_t* halves, int* err, void* stream) {
+  if (sk.h[0].Ls > LS_MAX || sk.h[0].s2.nl > 2 * LS_MAX) return hipErrorInvalidValue;
+  const unsigned blocks = (jobs.npos + 63) / 64;
+  hipLaunchKernelGGL(k_rns_dec_finish, dim3(blocks, 2), dim3(64), 0, (hipStream_t)stream, sk,
+                     jobs, ys, stride, halves);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_rns_garner, dim3(blocks), dim3(64), 0, (hipStream_t)stream, sk, jobs,
+                     halves, err);
+  return hipGetLastError();
+}
+
+hipError_t launch_rns_garner_crt(const SkConst& sk, const RnsJobs& jobs, const uint32_t* stage,
+                                 int* err, void* stream) {
+  if (sk.h[0].s2.nl > 2 * LS_MAX) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_rns_garner_crt, dim3((jobs.npos + 63) / 64), dim3(64), 0,
+                     (hipStream_t)stream, sk, jobs, stage, err);
   return hipGetLastError();
 }
 

@@ -28,11 +28,6 @@ hipError_t launch_encrypt(int geo, const Launch& l, const PkConst& pk, const uin
 constexpr size_t DEC_CHUNK = (size_t)1 << 18;
 hipError_t launch_decrypt(int cls, const Launch& l, const SkConst& sk, const uint32_t* c,
                           uint32_t* m, size_t count, uint32_t* halves);
-// the recombinations that close launch_decrypt and launch_encrypt_crt
-hipError_t launch_garner(const SkConst& sk, const uint32_t* halves, uint32_t* m, size_t count,
-                         int* err, void* stream);
-hipError_t launch_garner_crt(const SkConst& sk, const uint32_t* stage, uint32_t* c, size_t count,
-                             int* err, void* stream);
 hipError_t launch_hom_sum(int cls, const Launch& l, const PkConst& pk, const PtrList& cs, int K,
                           uint32_t* out, size_t count);
 hipError_t launch_scalar_mul(int cls, const Launch& l, const PkConst& pk, const uint32_t* c,

@@ -8,20 +8,22 @@ namespace pc2k {
 const void* rns_pow_kernel(int T, int nb);   // null if (T, nb) is not compiled
 int rns_pow_threads(int T, int nb);
 
-// x: [count][limbs] -> residues of both bases in groups of 32 nb elements
-hipError_t launch_rns_to(const RnsTo& c, int T, int nb, const uint32_t* x, int limbs,
-                         size_t count, uint8_t* out, void* stream);
+// the jobs' x (or m) as residues of both bases; limbs: words of an x
+hipError_t launch_rns_to(const RnsTo& c, int T, int nb, const RnsJobs& jobs, bool plain,
+                         int limbs, uint8_t* out, void* stream);
 hipError_t launch_rns_pow(int T, int nb, int grid, const RnsPow& p, void* stream);
-// residues of base B in groups of 32 nb elements -> canonical words, element e
-// at out + e stride
-hipError_t launch_rns_from(const RnsFrom& c, int T, int nb, const uint8_t* in, size_t count,
-                           uint32_t* out, size_t stride, void* stream);
+// residues of base B -> canonical words: at the jobs' outputs (stage null), or
+// at stage + position stride
+hipError_t launch_rns_from(const RnsFrom& c, int T, int nb, const uint8_t* in,
+                           const RnsJobs& jobs, uint32_t* stage, size_t stride, void* stream);
 // zero the ciphertexts of bad inputs and latch the error, or (okw) write the
-// checks to both halves' words okw[(2 e + half) stride]
-hipError_t launch_rns_enc_check(const PkConst& pk, const uint32_t* m, int m_limbs,
-                                const uint32_t* r, uint32_t* c, size_t count, uint32_t* okw,
+// checks to both halves' words okw[(2 position + half) stride]
+hipError_t launch_rns_enc_check(const PkConst& pk, const RnsJobs& jobs, uint32_t* okw,
                                 size_t stride, int* err, void* stream);
-hipError_t launch_rns_dec_finish(const SkConst& sk, const uint32_t* c, const uint32_t* ys,
-                                 size_t stride, size_t count, uint32_t* halves, void* stream);
+// the scalar end of both decryption halves, then the recombinations
+hipError_t launch_rns_dec_finish(const SkConst& sk, const RnsJobs& jobs, const uint32_t* ys,
+                                 size_t stride, uint32_t* halves, int* err, void* stream);
+hipError_t launch_rns_garner_crt(const SkConst& sk, const RnsJobs& jobs, const uint32_t* stage,
+                                 int* err, void* stream);
 
 }  // namespace pc2k

@@ -49,6 +49,26 @@ constexpr uint32_t rns_op(uint32_t kind, uint32_t y, uint32_t dst) {
   return kind << 16 | dst << 8 | y;
 }
 
+// The elements of a launch: positions 0 .. npos - 1, cut into groups of 32 nb
+// of them.  A job's elements first .. first + count - 1 stand at positions
+// pos0 .. (pos0 a multiple of 32); positions of no job hold zeros and produce
+// nothing.  One job travels by value, several in device memory, by ascending
+// pos0.
+struct RnsJob {
+  const uint32_t* x;     // encryption: r; decryption: c
+  const uint32_t* m;     // encryption: plaintexts
+  uint32_t* out;
+  uint64_t first;
+  uint32_t count, pos0;
+  int m_limbs;
+};
+struct RnsJobs {
+  RnsJob one;
+  const RnsJob* many;    // null: `one`
+  int n;
+  uint32_t npos;
+};
+
 // A launch of k_rns_pow: nmod moduli (1, or the two primes' squares), each
 // with its program and its groups' inputs; item i is group i / nmod of
 // modulus i % nmod.
