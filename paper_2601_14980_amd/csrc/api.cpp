@@ -17,6 +17,13 @@
 
 using pc2h::Limbs;
 
+// Launch shape of k_rns_pow for one call (rns_plan).
+struct RnsPlan {
+  int T = 0, nb = 0, grid = 0, w = 0;
+  size_t ngroups = 0, group_bytes = 0, table_bytes = 0;
+  size_t stage_bytes() const { return ngroups * group_bytes; }  // one input, one modulus
+};
+
 struct pc2_ctx {
   int device = 0;
   int cus = 0;
@@ -35,6 +42,14 @@ struct pc2_ctx {
   int rocc[pc2k::RNS_NT][pc2k::RNS_NBMAX + 1] = {};  // RNS powering: workgroups per CU
 };
 
+// One key's jobs of a batch or runner launch on the RNS engine.
+struct RnsPart {
+  const pc2_pk* pk = nullptr;  // encryption
+  const pc2_sk* sk = nullptr;  // decryption
+  RnsPlan plan;
+  pc2k::RnsJobs jobs{};
+};
+
 struct pc2_runner {
   pc2_ctx* ctx = nullptr;
   int op = 0, max_cls = 0;
@@ -49,6 +64,8 @@ struct pc2_runner {
   uint32_t* stage = nullptr;  // decryption: CRT halves of one launch's groups
   uint8_t* mscratch = nullptr;  // encryption on the matrix cores: tables of the widest grid
   size_t mscratch_bytes = 0;
+  uint8_t* rscratch = nullptr;  // the RNS engine's tables and staging
+  size_t rscratch_bytes = 0, rjobs_b = 0;
   int mocc[pc2k::NUM_CLASSES] = {};  // resident workgroups per CU of k_batch_mfma per class
   hipEvent_t copied = nullptr;
   bool pending = false;
@@ -83,6 +100,10 @@ struct pc2_batch {
     int* queue = nullptr;
   } mp[2];
   uint8_t* mscratch = nullptr;
+  // jobs on the RNS engine, one part per key: its jobs, plan and scratch (one
+  // scratch for all parts, whose launches run in order on one stream)
+  std::vector<RnsPart> rparts;
+  uint8_t* rscratch = nullptr;
   hipGraphExec_t exec = nullptr;
   void* graph_stream = nullptr;
 };
@@ -698,11 +719,6 @@ int rns_window(const pc2_ctx* ctx, int T) { return ctx->window ? ctx->window : (
 
 // Column blocks per workgroup for `count` elements of nmod moduli: the least
 // time by rounds of resident workgroups.
-struct RnsPlan {
-  int T = 0, nb = 0, grid = 0, w = 0;
-  size_t ngroups = 0, group_bytes = 0, table_bytes = 0;
-  size_t stage_bytes() const { return ngroups * group_bytes; }  // one input, one modulus
-};
 RnsPlan rns_plan_nb(pc2_ctx* ctx, int T, int nmod, size_t count, int nb, int w) {
   RnsPlan p;
   p.T = T;
@@ -1638,6 +1654,90 @@ int pc2_enc_sum_dec(const pc2_sk* sk, const uint32_t* const* m_k, const uint32_t
 }
 
 // ---------------------------------------------------------------- batches
+namespace {
+// Positions of a part's jobs: each from the next multiple of 32.
+uint32_t round32(uint32_t v) { return (v + 31) & ~31u; }
+
+// The jobs that the RNS engine takes, by key: count[i] elements from element
+// first[i] of job i.  in_rns[i] tells which; hjobs receives their descriptors
+// (part after part, jobs.many holding an index until rns_parts_place).
+std::vector<RnsPart> rns_parts(pc2_ctx* ctx, int op, const pc2_job* jobs, const size_t* first,
+                               const size_t* count, size_t njobs, std::vector<bool>* in_rns,
+                               std::vector<pc2k::RnsJob>* hjobs) {
+  std::vector<RnsPart> parts;
+  in_rns->assign(njobs, false);
+  if (op != pc2k::OP_ENC && op != pc2k::OP_DEC) return parts;
+  std::vector<bool> seen(njobs, false);
+  for (size_t i = 0; i < njobs; ++i) {
+    if (seen[i] || count[i] == 0) continue;
+    RnsPart p;
+    const void* key = op == pc2k::OP_DEC ? (const void*)jobs[i].sk : (const void*)jobs[i].pk;
+    size_t total = 0;
+    for (size_t k = i; k < njobs; ++k) {
+      const void* other = op == pc2k::OP_DEC ? (const void*)jobs[k].sk : (const void*)jobs[k].pk;
+      if (count[k] == 0 || other != key) continue;
+      seen[k] = true;
+      total += count[k];
+    }
+    if (total >= ((size_t)1 << 31)) continue;
+    if (op == pc2k::OP_DEC ? !dec_rns(ctx, jobs[i].sk)
+                           : enc_engine(ctx, jobs[i].pk, total) != ENG_RNS)
+      continue;
+    p.pk = jobs[i].pk;
+    p.sk = jobs[i].sk;
+    const size_t at = hjobs->size();
+    uint32_t pos = 0;
+    for (size_t k = i; k < njobs; ++k) {
+      const void* other = op == pc2k::OP_DEC ? (const void*)jobs[k].sk : (const void*)jobs[k].pk;
+      if (count[k] == 0 || other != key) continue;
+      (*in_rns)[k] = true;
+      const pc2_job& j = jobs[k];
+      const bool dec = op == pc2k::OP_DEC;
+      hjobs->push_back({dec ? j.in0 : j.in1, dec ? nullptr : j.in0, j.out, first[k],
+                        (uint32_t)count[k], pos, (int)j.m_limbs});
+      pos = round32(pos + (uint32_t)count[k]);
+    }
+    p.jobs.n = (int)(hjobs->size() - at);
+    p.jobs.many = reinterpret_cast<const pc2k::RnsJob*>(at * sizeof(pc2k::RnsJob));
+    p.jobs.npos = pos;
+    p.plan = op == pc2k::OP_DEC ? rns_plan(ctx, p.sk->dec[0].T, 2, pos)
+                                : rns_plan(ctx, p.pk->rn.T, 1, pos);
+    parts.push_back(p);
+  }
+  return parts;
+}
+void rns_parts_place(std::vector<RnsPart>& parts, const void* dev) {
+  for (RnsPart& p : parts)
+    p.jobs.many = reinterpret_cast<const pc2k::RnsJob*>((const char*)dev +
+                                                        (size_t)p.jobs.many);
+}
+// A class whose (only) encryption jobs outside the RNS engine would run on the
+// VALU engine, but are few enough for an element a wavefront (enc_engine's
+// rule); -1: none.
+int few_elements_class(const pc2_ctx* ctx, int op, const pc2_job* jobs, const size_t* count,
+                       size_t njobs, const std::vector<bool>& in_rns) {
+  if (op != pc2k::OP_ENC || ctx->modmul != PC2_MODMUL_AUTO || ctx->tile) return -1;
+  int cls = -1;
+  size_t total = 0;
+  for (size_t i = 0; i < njobs; ++i) {
+    if (count[i] == 0 || in_rns[i] || use_mfma(ctx, jobs[i].pk->cls)) continue;
+    if (cls >= 0 && cls != jobs[i].pk->cls) return -1;
+    cls = jobs[i].pk->cls;
+    total += count[i];
+  }
+  return cls >= 0 && total <= ELEM_MAX_COUNT[cls] ? cls : -1;
+}
+size_t rns_part_bytes(const RnsPart& p, int op) {
+  return op == pc2k::OP_DEC
+             ? rns_decrypt_bytes(p.plan, p.jobs.npos, p.sk->c.h[0].Ls, p.sk->c.h[0].s2.nl)
+             : rns_encrypt_bytes(p.plan);
+}
+int rns_part_run(pc2_ctx* ctx, const RnsPart& p, int op, uint8_t* scratch, void* stream) {
+  return op == pc2k::OP_DEC ? rns_decrypt_run(ctx, p.sk, p.jobs, p.plan, scratch, stream)
+                            : rns_encrypt_run(ctx, p.pk, p.jobs, p.plan, scratch, stream);
+}
+}  // namespace
+
 // Work-queue counters at the end of a batch's or runner's descriptor
 // allocation: the VALU launch's, then one per matrix-core class, each on
 // its own 128-byte line.
@@ -1704,6 +1804,17 @@ int pc2_batch_create(pc2_ctx* ctx, const pc2_job* jobs, size_t njobs, pc2_batch*
   }
   pc2_batch* b = new (std::nothrow) pc2_batch();
   if (!b) return PC2_E_NOMEM;
+  std::vector<size_t> zero(njobs, 0), counts(njobs);
+  for (size_t i = 0; i < njobs; ++i) counts[i] = jobs[i].count;
+  std::vector<bool> in_rns;
+  std::vector<pc2k::RnsJob> rjobs;
+  b->rparts = rns_parts(ctx, op, jobs, zero.data(), counts.data(), njobs, &in_rns, &rjobs);
+  const int few = few_elements_class(ctx, op, jobs, counts.data(), njobs, in_rns);
+  if (few >= 0 && mcb < 0) {
+    (mca < 0 ? mca : mcb) = few;
+    if (mcb > mca) std::swap(mca, mcb);
+    pair = -1;
+  }
   b->ctx = ctx;
   b->op = op;
   b->pair = pair;
@@ -1723,7 +1834,7 @@ int pc2_batch_create(pc2_ctx* ctx, const pc2_job* jobs, size_t njobs, pc2_batch*
   std::vector<bool> mjob;      // runs on the matrix cores
   for (size_t i = 0; i < njobs; ++i) {
     const pc2_job& j = jobs[i];
-    if (j.count == 0) continue;
+    if (j.count == 0 || in_rns[i]) continue;
     pc2k::BatchJob d{};
     const pc2_pk* pk = (op == pc2k::OP_DEC) ? &j.sk->pk : j.pk;
     const bool mf = op == pc2k::OP_ENC && (pk->cls == mca || pk->cls == mcb);
@@ -1787,7 +1898,8 @@ int pc2_batch_create(pc2_ctx* ctx, const pc2_job* jobs, size_t njobs, pc2_batch*
   const size_t jobs_b = (dj.size() * sizeof(pc2k::BatchJob) + 255) & ~(size_t)255;
   const size_t items_b = (items.size() * sizeof(pc2k::BatchItem) + 255) & ~(size_t)255;
   const size_t ptr_b = (ptrbuf.size() * sizeof(size_t) + 255) & ~(size_t)255;
-  const size_t total = jobs_b + items_b + ptr_b + QUEUE_BYTES;
+  const size_t rjobs_b = (rjobs.size() * sizeof(pc2k::RnsJob) + 255) & ~(size_t)255;
+  const size_t total = jobs_b + items_b + ptr_b + QUEUE_BYTES + rjobs_b;
   int rc = PC2_OK;
   if (hipSetDevice(ctx->device) != hipSuccess) rc = PC2_E_DEVICE;
   if (!rc && hipMalloc(&b->dev, total) != hipSuccess) rc = PC2_E_NOMEM;
@@ -1813,10 +1925,15 @@ int pc2_batch_create(pc2_ctx* ctx, const pc2_job* jobs, size_t njobs, pc2_batch*
         dj[ji].inputs = (const uint32_t* const*)(dptr + ptr_off[ji]);
         dj[ji].lengths = dptr + ptr_off[ji] + dj[ji].K;
       }
-    if (hipMemcpy(b->jobs, dj.data(), dj.size() * sizeof(pc2k::BatchJob),
-                  hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(b->items, items.data(), items.size() * sizeof(pc2k::BatchItem),
-                  hipMemcpyHostToDevice) != hipSuccess ||
+    void* rdev = base + jobs_b + items_b + ptr_b + QUEUE_BYTES;
+    rns_parts_place(b->rparts, rdev);
+    if ((!dj.empty() && hipMemcpy(b->jobs, dj.data(), dj.size() * sizeof(pc2k::BatchJob),
+                                  hipMemcpyHostToDevice) != hipSuccess) ||
+        (!items.empty() && hipMemcpy(b->items, items.data(),
+                                     items.size() * sizeof(pc2k::BatchItem),
+                                     hipMemcpyHostToDevice) != hipSuccess) ||
+        (!rjobs.empty() && hipMemcpy(rdev, rjobs.data(), rjobs.size() * sizeof(pc2k::RnsJob),
+                                     hipMemcpyHostToDevice) != hipSuccess) ||
         (!ptrbuf.empty() && hipMemcpy(dptr, ptrbuf.data(), ptrbuf.size() * sizeof(size_t),
                                       hipMemcpyHostToDevice) != hipSuccess))
       rc = PC2_E_DEVICE;
@@ -1831,6 +1948,9 @@ int pc2_batch_create(pc2_ctx* ctx, const pc2_job* jobs, size_t njobs, pc2_batch*
     mbytes = std::max(mbytes, (size_t)m.grid * (pc2k::mfma_digit_bytes(m.cls) << m.w));
   }
   if (!rc && mbytes && hipMalloc(&b->mscratch, mbytes) != hipSuccess) rc = PC2_E_NOMEM;
+  size_t rbytes = 0;
+  for (const RnsPart& p : b->rparts) rbytes = std::max(rbytes, rns_part_bytes(p, op));
+  if (!rc && rbytes && hipMalloc(&b->rscratch, rbytes) != hipSuccess) rc = PC2_E_NOMEM;
   if (!rc && b->nitems) {
     int occ = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, pc2k::batch_kernel(op, pair), 64, 0) !=
@@ -1851,6 +1971,7 @@ int pc2_batch_create(pc2_ctx* ctx, const pc2_job* jobs, size_t njobs, pc2_batch*
     if (b->dev) (void)hipFree(b->dev);
     if (b->scratch) (void)hipFree(b->scratch);
     if (b->mscratch) (void)hipFree(b->mscratch);
+    if (b->rscratch) (void)hipFree(b->rscratch);
     if (b->stage) (void)hipFree(b->stage);
     delete b;
     return rc;
@@ -1871,6 +1992,9 @@ int pc2_batch_run(pc2_batch* b, void* hip_stream) {
       if (e == hipSuccess && m.nitems)
         e = pc2k::launch_batch_mfma(m.cls, m.grid, b->jobs, m.items, m.nitems, m.sub, m.queue,
                                     b->mscratch, m.w, b->ctx->err, st);
+    for (const RnsPart& p : b->rparts)
+      if (e == hipSuccess && rns_part_run(b->ctx, p, b->op, b->rscratch, st) != PC2_OK)
+        e = hipErrorLaunchFailure;
     return e;
   };
   if (!hip_stream) return status_of(launch(nullptr));
@@ -1908,6 +2032,7 @@ int pc2_batch_destroy(pc2_batch* b) {
   if (b->dev) (void)hipFree(b->dev);
   if (b->scratch) (void)hipFree(b->scratch);
   if (b->mscratch) (void)hipFree(b->mscratch);
+  if (b->rscratch) (void)hipFree(b->rscratch);
   if (b->stage) (void)hipFree(b->stage);
   delete b;
   return PC2_OK;
@@ -2026,7 +2151,8 @@ int pc2_runner_create(pc2_ctx* ctx, int op_abi, uint32_t max_nbits, size_t max_j
   const size_t max_items = (op == pc2k::OP_DEC ? 2 : 1) * max_groups;
   r->items_b = (max_items * sizeof(pc2k::BatchItem) + 255) & ~(size_t)255;
   r->ptr_b = (r->max_ptrs * sizeof(size_t) + 255) & ~(size_t)255;
-  const size_t total = r->jobs_b + r->items_b + r->ptr_b + QUEUE_BYTES;
+  r->rjobs_b = op == pc2k::OP_SUM ? 0 : (max_jobs * sizeof(pc2k::RnsJob) + 255) & ~(size_t)255;
+  const size_t total = r->jobs_b + r->items_b + r->ptr_b + QUEUE_BYTES + r->rjobs_b;
   int rc = PC2_OK;
   if (hipMalloc(&r->dev, total) != hipSuccess || hipHostMalloc(&r->host, total) != hipSuccess ||
       hipEventCreateWithFlags(&r->copied, hipEventDisableTiming) != hipSuccess)
@@ -2071,6 +2197,29 @@ int pc2_runner_create(pc2_ctx* ctx, int op_abi, uint32_t max_nbits, size_t max_j
     }
     if (!rc && r->mscratch_bytes && hipMalloc(&r->mscratch, r->mscratch_bytes) != hipSuccess)
       rc = PC2_E_NOMEM;
+    // the RNS engine: one launch's positions under any key up to max_nbits
+    if (!rc && op != pc2k::OP_SUM && cls >= RNS_MIN_CLASS) {
+      size_t elems = 0;
+      for (int g = 0; g < pc2k::NUM_GEOS; ++g)
+        if (pc2k::GEO_CLASS[g] >= RNS_MIN_CLASS && pc2k::GEO_CLASS[g] <= cls)
+          elems = std::max(elems, (size_t)std::max(0, pc2k::batch_group_elems(op, g)));
+      const size_t npos = std::min(max_groups * elems + 32 * max_jobs, (size_t)1 << 31);
+      const pc2k::ClassGeo cg = pc2k::CLASS_GEO[cls];
+      const int p2bits = cg.pD * cg.pK * cg.pT - 2;
+      const int tmax = pc2h::rns_tiles(op == pc2k::OP_DEC ? p2bits : 64 * L);
+      for (int T : pc2k::RNS_T)
+        for (int nb = 1; nb <= pc2k::RNS_NBMAX; ++nb) {
+          if (T > tmax || !rns_slots(ctx, T, nb)) continue;
+          const RnsPlan p =
+              rns_plan_nb(ctx, T, op == pc2k::OP_DEC ? 2 : 1, npos, nb, pc2k::SCHED_WMAX);
+          r->rscratch_bytes = std::max(
+              r->rscratch_bytes, op == pc2k::OP_DEC
+                                     ? rns_decrypt_bytes(p, npos, Ls, (p2bits + 31) / 32)
+                                     : rns_encrypt_bytes(p));
+        }
+      if (r->rscratch_bytes && hipMalloc(&r->rscratch, r->rscratch_bytes) != hipSuccess)
+        rc = PC2_E_NOMEM;
+    }
     if (!rc && op == pc2k::OP_DEC) {  // CRT halves of up to max_groups groups
       size_t per = 0;
       for (int g = 0; g < pc2k::NUM_GEOS; ++g)
@@ -2084,6 +2233,7 @@ int pc2_runner_create(pc2_ctx* ctx, int op_abi, uint32_t max_nbits, size_t max_j
     if (r->host) (void)hipHostFree(r->host);
     if (r->scratch) (void)hipFree(r->scratch);
     if (r->mscratch) (void)hipFree(r->mscratch);
+    if (r->rscratch) (void)hipFree(r->rscratch);
     if (r->stage) (void)hipFree(r->stage);
     if (r->copied) (void)hipEventDestroy(r->copied);
     delete r;
@@ -2150,6 +2300,31 @@ int pc2_runner_launch(pc2_runner* r, const pc2_job* jobs, const size_t* first,
     pair = pc2k::batch_pair(ca, cb);
     if (pair < 0) return PC2_E_UNSUPPORTED;
   }
+  // the jobs that the RNS engine takes (whatever fits the launcher's scratch;
+  // the others stay on the persistent kernels)
+  std::vector<size_t> relem(njobs), rcount(njobs);
+  for (size_t i = 0; i < njobs; ++i) {
+    const pc2_pk* pk = (op == pc2k::OP_DEC) ? &jobs[i].sk->pk : jobs[i].pk;
+    const size_t epw = (size_t)pc2k::batch_group_elems(op, job_geo(ctx, pk, op));
+    relem[i] = first[i] * epw;
+    rcount[i] = std::min(ngroups[i] * epw, jobs[i].count - std::min(jobs[i].count, relem[i]));
+  }
+  std::vector<bool> in_rns;
+  std::vector<pc2k::RnsJob> rjobs;
+  std::vector<RnsPart> parts =
+      rns_parts(ctx, op, jobs, relem.data(), rcount.data(), njobs, &in_rns, &rjobs);
+  for (const RnsPart& p : parts)
+    if (!r->rscratch || rns_part_bytes(p, op) > r->rscratch_bytes) {
+      parts.clear();
+      rjobs.clear();
+      in_rns.assign(njobs, false);
+      break;
+    }
+  const int few = few_elements_class(ctx, op, jobs, rcount.data(), njobs, in_rns);
+  if (few >= 0 && mcb < 0 && r->mscratch) {
+    (mca < 0 ? mca : mcb) = few;
+    pair = -1;
+  }
   if (hipSetDevice(ctx->device) != hipSuccess) return PC2_E_DEVICE;
   // the previous launch's copies must have read the staging buffers
   if (r->pending && hipEventSynchronize(r->copied) != hipSuccess) return PC2_E_DEVICE;
@@ -2203,7 +2378,7 @@ int pc2_runner_launch(pc2_runner* r, const pc2_job* jobs, const size_t* first,
     const int want = pass == 0 ? first_geo : (first_geo == pa ? pb : pa);
     if (pass == 1 && pa == pb) break;
     for (size_t i = 0; i < njobs; ++i) {
-      if (on_mfma(i) || hj[i].geo != want) continue;
+      if (in_rns[i] || on_mfma(i) || hj[i].geo != want) continue;
       for (size_t g = 0; g < ngroups[i]; ++g) {
         hi[it++] = pc2k::BatchItem{(int)i, 0, first[i] + g};
         if (op == pc2k::OP_DEC) hi[it++] = pc2k::BatchItem{(int)i, 1, first[i] + g};
@@ -2217,18 +2392,24 @@ int pc2_runner_launch(pc2_runner* r, const pc2_job* jobs, const size_t* first,
   for (int part = 0; part < 2; ++part) {
     mfirst[part] = it;
     for (size_t i = 0; mcls[part] >= 0 && i < njobs; ++i)
-      if (on_mfma(i) && hj[i].geo == mcls[part]) {
+      if (!in_rns[i] && on_mfma(i) && hj[i].geo == mcls[part]) {
         msub[part] = std::max(msub[part], hj[i].group);
         for (size_t g = 0; g < ngroups[i]; ++g)
           hi[it++] = pc2k::BatchItem{(int)i, 0, first[i] + g};
       }
     mfirst[part + 1] = it;
   }
+  const size_t rofs = r->jobs_b + r->items_b + r->ptr_b + QUEUE_BYTES;
+  std::copy(rjobs.begin(), rjobs.end(), (pc2k::RnsJob*)(hb + rofs));
+  rns_parts_place(parts, db + rofs);
   hipStream_t st = (hipStream_t)hip_stream;
   if (hipMemcpyAsync(db, hb, njobs * sizeof(pc2k::BatchJob), hipMemcpyHostToDevice, st) !=
           hipSuccess ||
-      hipMemcpyAsync(db + r->jobs_b, hb + r->jobs_b, it * sizeof(pc2k::BatchItem),
-                     hipMemcpyHostToDevice, st) != hipSuccess ||
+      (it && hipMemcpyAsync(db + r->jobs_b, hb + r->jobs_b, it * sizeof(pc2k::BatchItem),
+                            hipMemcpyHostToDevice, st) != hipSuccess) ||
+      (!rjobs.empty() && hipMemcpyAsync(db + rofs, hb + rofs,
+                                        rjobs.size() * sizeof(pc2k::RnsJob),
+                                        hipMemcpyHostToDevice, st) != hipSuccess) ||
       (pofs && hipMemcpyAsync(dp, hp, pofs * sizeof(size_t), hipMemcpyHostToDevice, st) !=
                    hipSuccess) ||
       hipEventRecord(r->copied, st) != hipSuccess)
@@ -2257,7 +2438,10 @@ int pc2_runner_launch(pc2_runner* r, const pc2_job* jobs, const size_t* first,
                                 r->mscratch, w,
                                 ctx->err, st);
   }
-  return status_of(e);
+  int rc = status_of(e);
+  for (const RnsPart& p : parts)
+    if (!rc) rc = rns_part_run(ctx, p, op, r->rscratch, hip_stream);
+  return rc;
 }
 
 int pc2_runner_destroy(pc2_runner* r) {
@@ -2268,6 +2452,7 @@ int pc2_runner_destroy(pc2_runner* r) {
   if (r->host) (void)hipHostFree(r->host);
   if (r->scratch) (void)hipFree(r->scratch);
   if (r->mscratch) (void)hipFree(r->mscratch);
+  if (r->rscratch) (void)hipFree(r->rscratch);
   if (r->stage) (void)hipFree(r->stage);
   if (r->copied) (void)hipEventDestroy(r->copied);
   delete r;
