@@ -40,6 +40,7 @@ struct pc2_ctx {
   int tuned[pc2k::NUM_GEOS][pc2k::OP_COUNT] = {};  // autotuned windows (0 = none)
   int tuned_geo[pc2k::NUM_CLASSES] = {-1, -1, -1, -1, -1, -1, -1, -1, -1};  // encryption tile
   int rocc[pc2k::RNS_NT][pc2k::RNS_NBMAX + 1] = {};  // RNS powering: workgroups per CU
+  int gocc[pc2k::RNS_NGATHER][pc2k::RNS_NT][pc2k::RNS_NBMAX + 1] = {};  // and the gather kernels'
 };
 
 // One key's jobs of a batch or runner launch on the RNS engine.
@@ -118,6 +119,15 @@ struct pc2_matvec {
   size_t parts_bytes = 0;
   int cap_table = 1, cap_apply = 1;  // resident workgroups of the two kernels
   bool loaded = false;
+  // on the RNS engine (rw > 0): digits of rw bits, rnw of them, entries d < 2^rw
+  // in tab; the running values of rblocks blocks of 32 rows, and a flag per row
+  int rw = 0, rnw = 0;
+  uint8_t* rstage = nullptr;
+  uint32_t* rbad = nullptr;
+  size_t rblocks = 0;
+  hipEvent_t done = nullptr;  // after the last call that used them, on done_stream
+  void* done_stream = nullptr;
+  bool done_valid = false;
 };
 
 struct pc2_colsplit {
@@ -418,7 +428,8 @@ pc2k::PkConst pk_const_alt(const uint32_t* base, const PkOffsets& o, const pc2k:
 struct RnsOffsets {
   int T = 0;
   size_t E1, E2, c2, kb, ka;
-  struct To { size_t P, add, m; int nhalf; } x, gm;
+  struct To { size_t P, add, m; int nhalf; } x, gm, c;
+  size_t one;
   struct From { size_t C, D, O, N28, F; int S, nblk; double ntop_inv; } from;
   size_t ops[5];
 };
@@ -431,11 +442,12 @@ RnsOffsets::To add_rns_to(DevBuf& buf, const pc2h::RnsToHost& h) {
 }
 // Powers x^e modulo N (N of `tiles`), x of nhalf 16-bit halves; f2 != null: a
 // second input 1 + m f2 (m of mhalf halves) closes the product, else the
-// result leaves Montgomery form on output.  E2, c2, kb and ka depend on the
+// result leaves Montgomery form on output; chalf > 0: also what products of
+// ciphertexts of chalf halves need.  E2, c2, kb and ka depend on the
 // tile count alone: `same` (null: none) names a modulus whose copies to use.
 // T = 0 in the result: the engine does not take this modulus.
 RnsOffsets add_rns(DevBuf& buf, const Limbs& N, int T, const Limbs& e, int nhalf, const Limbs* f2,
-                   int mhalf, const RnsOffsets* same) {
+                   int mhalf, const RnsOffsets* same, int chalf = 0) {
   RnsOffsets o;
   if (T == 0) return o;
   const pc2h::RnsBase& R = pc2h::rns_base(T);
@@ -460,6 +472,15 @@ RnsOffsets add_rns(DevBuf& buf, const Limbs& N, int T, const Limbs& e, int nhalf
   }
   o.x = add_rns_to(buf, pc2h::rns_to(R, N, R.MA, nhalf, false));
   if (f2) o.gm = add_rns_to(buf, pc2h::rns_to(R, N, *f2, mhalf, true));
+  if (chalf) {
+    o.c = add_rns_to(buf, pc2h::rns_to(R, N, Limbs{1}, chalf, false));
+    std::vector<uint32_t> one;
+    for (const Limbs& v : {R.MA, pc2h::mul(R.MA, R.MA), Limbs{1}}) {
+      const std::vector<uint32_t> w = pc2h::rns_entry(R, N, v);
+      one.insert(one.end(), w.begin(), w.end());
+    }
+    o.one = add_aligned(buf, one);
+  }
   const pc2h::RnsFromHost h = pc2h::rns_from(R, N, f2 == nullptr);
   std::vector<uint32_t> F;
   for (int64_t v : h.F) {
@@ -483,6 +504,10 @@ pc2k::RnsKey rns_const(const uint32_t* base, const RnsOffsets& o, int nw) {
          (const int32_t*)(base + o.c2), base + o.kb, base + o.ka};
   k.x = rns_to_const(base, o.x);
   if (o.gm.nhalf) k.gm = rns_to_const(base, o.gm);
+  if (o.c.nhalf) {
+    k.c = rns_to_const(base, o.c);
+    k.one = (const uint8_t*)(base + o.one);
+  }
   k.from = {base + o.from.C, base + o.from.D, base + o.from.O, base + o.from.N28,
             (const int64_t*)(base + o.from.F), o.from.S, o.from.nblk, nw, o.from.ntop_inv};
   for (int i = 0; i < 5; ++i) k.ops[i] = base + o.ops[i];
@@ -500,7 +525,7 @@ int rns_tiles_for(int cls, const Limbs& N) {
 RnsOffsets add_rns_public(DevBuf& buf, const Limbs& n, int cls, int L) {
   Limbs n2 = pc2h::mul(n, n);
   pc2h::trim(n2);
-  return add_rns(buf, n2, rns_tiles_for(cls, n2), n, 2 * L, &n, 2 * L, nullptr);
+  return add_rns(buf, n2, rns_tiles_for(cls, n2), n, 2 * L, &n, 2 * L, nullptr, 4 * L);
 }
 
 struct HalfOffsets {
@@ -698,11 +723,12 @@ int rns_index(int T) {
     if (pc2k::RNS_T[i] == T) return i;
   return 0;
 }
-// resident workgroups of k_rns_pow<T, nb> (0: not compiled)
-int rns_slots(pc2_ctx* ctx, int T, int nb) {
-  int& o = ctx->rocc[rns_index(T)][nb];
+// resident workgroups of k_rns_pow<T, nb>, or of a kernel with a multiplier per
+// element (0: not compiled)
+int rns_slots(pc2_ctx* ctx, int T, int nb, int gather = -1) {
+  int& o = gather < 0 ? ctx->rocc[rns_index(T)][nb] : ctx->gocc[gather][rns_index(T)][nb];
   if (o == 0) {
-    const void* k = pc2k::rns_pow_kernel(T, nb);
+    const void* k = gather < 0 ? pc2k::rns_pow_kernel(T, nb) : pc2k::rns_gather_kernel(T, nb, gather);
     int v = 0;
     if (!k)
       o = -1;
@@ -719,25 +745,26 @@ int rns_window(const pc2_ctx* ctx, int T) { return ctx->window ? ctx->window : (
 
 // Column blocks per workgroup for `count` elements of nmod moduli: the least
 // time by rounds of resident workgroups.
-RnsPlan rns_plan_nb(pc2_ctx* ctx, int T, int nmod, size_t count, int nb, int w) {
+RnsPlan rns_plan_nb(pc2_ctx* ctx, int T, int nmod, size_t count, int nb, int w, int gather = -1) {
   RnsPlan p;
   p.T = T;
   p.nb = nb;
   p.w = w;
   p.ngroups = (count + 32 * nb - 1) / (32 * nb);
   p.group_bytes = pc2k::rns_group_bytes(T, nb);
-  p.grid = (int)std::min<size_t>(p.ngroups * nmod, (size_t)rns_slots(ctx, T, nb));
-  p.table_bytes = (size_t)p.grid * ((size_t)1 << (w - 1)) * p.group_bytes;
+  p.grid = (int)std::min<size_t>(p.ngroups * nmod, (size_t)rns_slots(ctx, T, nb, gather));
+  const size_t entries = gather < 0 ? (size_t)1 << (w - 1) : 16;
+  p.table_bytes = (size_t)p.grid * entries * p.group_bytes;
   return p;
 }
-RnsPlan rns_plan(pc2_ctx* ctx, int T, int nmod, size_t count) {
+RnsPlan rns_plan(pc2_ctx* ctx, int T, int nmod, size_t count, int gather = -1) {
   const int w = rns_window(ctx, T);
   RnsPlan best;
   double best_cost = 0;
   for (int nb = 1; nb <= pc2k::RNS_NBMAX; ++nb) {
-    const int slots = rns_slots(ctx, T, nb);
+    const int slots = rns_slots(ctx, T, nb, gather);
     if (!slots) continue;
-    RnsPlan p = rns_plan_nb(ctx, T, nmod, count, nb, w);
+    RnsPlan p = rns_plan_nb(ctx, T, nmod, count, nb, w, gather);
     // a round of w workgroups per CU measured 1.45 + w nb, in units of what a
     // column block adds (2048-bit decryption halves, nb 1 / 2 / 4: 4.1 / 5.9 /
     // 8.8 ms one per CU, nb 2 / 4: 9.4 / 15.6 ms two per CU; 2048-bit n^2, one
@@ -761,6 +788,9 @@ size_t rns_encrypt_bytes(const RnsPlan& p) { return p.table_bytes + 2 * p.stage_
 size_t rns_decrypt_bytes(const RnsPlan& p, size_t chunk, int Ls, int nl2) {
   return p.table_bytes + 2 * p.stage_bytes() + align256(chunk * 2 * (size_t)(nl2 + 1) * 4) +
          align256(chunk * 2 * (size_t)(Ls + 1) * 4);
+}
+size_t rns_smul_bytes(const RnsPlan& p, size_t chunk) {
+  return p.table_bytes + p.stage_bytes() + align256(chunk * 4);
 }
 size_t rns_encrypt_sk_bytes(const RnsPlan& p, size_t chunk, int nl2) {
   return p.table_bytes + 4 * p.stage_bytes() + align256(chunk * 2 * (size_t)(nl2 + 1) * 4);
@@ -801,6 +831,10 @@ size_t class_scratch_need(pc2_ctx* ctx, int cls, int L, int Ls, int nl2) {
     for (int T : pc2k::RNS_T)
       for (int nb = 1; nb <= pc2k::RNS_NBMAX; ++nb) {
         if (T > tn || !rns_slots(ctx, T, nb)) continue;
+        for (int g = 0; g < pc2k::RNS_NGATHER; ++g) (void)rns_slots(ctx, T, nb, g);
+        if (rns_slots(ctx, T, nb, pc2k::RNS_SMUL))
+          need = std::max(need,
+                          rns_smul_bytes(rns_plan_nb(ctx, T, 1, ch, nb, w, pc2k::RNS_SMUL), ch));
         const RnsPlan p = rns_plan_nb(ctx, T, 2, ch, nb, w);
         need = std::max(need, rns_encrypt_bytes(p) + 2 * align256(ch * 8 * (size_t)L));
         if (T <= tp) {
@@ -919,6 +953,43 @@ int rns_encrypt_run(pc2_ctx* ctx, const pc2_pk* pk, const pc2k::RnsJobs& J, cons
   if (e == hipSuccess)
     e = pc2k::launch_rns_enc_check(pk->c, J, nullptr, 0, ctx->err, stream);
   return status_of(e);
+}
+
+// out[i] = c[i]^k[i], at any count (ms, RNS against VALU: 1024 bits, 1 element
+// 0.30 / 1.25, 20000: 0.88 / 1.39; 2048 bits, 1: 0.58 / 2.57, 20000: 2.4 / 4.6;
+// 4096 bits, 1: 2.05 / 4.9, 20000: 9.4 / 13.4)
+int rns_scalar_mul(const pc2_pk* pk, const uint32_t* c, const uint64_t* k, uint32_t* out,
+                   size_t count, void* stream) {
+  pc2_ctx* ctx = pk->ctx;
+  const pc2k::RnsKey& K = pk->rn;
+  const size_t chunk = std::min(count, pc2k::DEC_CHUNK), L2 = 2 * (size_t)pk->L;
+  const RnsPlan p = rns_plan(ctx, K.T, 1, chunk, pc2k::RNS_SMUL);
+  if (!p.T || !ctx->scratch || rns_smul_bytes(p, chunk) > ctx->scratch_bytes) return PC2_E_NOMEM;
+  pc2k::RnsSmul s{};
+  s.M = K.M;
+  s.one = K.one;
+  s.table = reinterpret_cast<uint8_t*>(ctx->scratch);
+  s.in = s.table + p.table_bytes;
+  uint32_t* bad = reinterpret_cast<uint32_t*>(s.in + p.stage_bytes());
+  int rc = scratch_begin(ctx, stream);
+  for (size_t at = 0; at < count && !rc; at += chunk) {
+    const size_t n = std::min(chunk, count - at);
+    const pc2k::RnsJobs J = one_job(c + at * L2, nullptr, 0, out + at * L2, n);
+    s.k = k + at;
+    s.count = n;
+    s.ngroups = (int)((n + 32 * p.nb - 1) / (32 * p.nb));
+    hipError_t e = pc2k::launch_rns_to(K.c, K.T, p.nb, J, false, (int)L2, s.in, stream);
+    if (e == hipSuccess)
+      e = pc2k::launch_rns_row_check(c + at * L2, pk->c.n2.Nl, (int)L2, bad, n, stream);
+    if (e == hipSuccess)
+      e = pc2k::launch_rns_gather(K.T, p.nb, pc2k::RNS_SMUL, std::min(p.grid, s.ngroups), &s,
+                                  stream);
+    if (e == hipSuccess) e = pc2k::launch_rns_from(K.from, K.T, p.nb, s.in, J, nullptr, 0, stream);
+    if (e == hipSuccess)
+      e = pc2k::launch_rns_row_clear(bad, out + at * L2, (int)L2, n, ctx->err, stream);
+    rc = status_of(e);
+  }
+  return scratch_end(ctx, stream, rc);
 }
 
 int rns_decrypt_run(pc2_ctx* ctx, const pc2_sk* sk, const pc2k::RnsJobs& J, const RnsPlan& p,
@@ -1561,6 +1632,8 @@ int pc2_hom_scalar_mul(const pc2_pk* pk, const uint32_t* c, const uint64_t* k, u
     if (partial_overlap(out, cb, c, cb) || partial_overlap(out, cb, k, 8 * count))
       return PC2_E_INVAL;
   }
+  if (pk->rn.T && pk->ctx->modmul != PC2_MODMUL_VALU)
+    return rns_scalar_mul(pk, c, k, out, count, stream);
   pc2k::Launch l{};
   int rc = prepare(pk->ctx, pk->cls, pc2k::OP_SMUL, count, 0, pk->L, &l, stream);
   if (!rc) rc = scratch_begin(pk->ctx, stream);
@@ -2497,6 +2570,174 @@ void pick_chunks(const pc2_matvec* mv, size_t rows, size_t max_chunks, size_t* n
 }
 }  // namespace
 
+namespace {
+// Column blocks per row group (nb) and column chunks of `rows` rows on the RNS
+// engine, their running values at most `blocks` blocks of 32: the least time
+// by rounds of resident workgroups (a product measured 1.45 + nb, see
+// rns_plan), plus the products that join the chunks.
+struct RnsMvShape {
+  int nb = 0;
+  size_t groups = 0, nch = 0, chunk_cols = 0;
+  double cost = 0;
+};
+RnsMvShape rns_mv_shape(pc2_ctx* ctx, int T, size_t cols, int nw, size_t rows, size_t blocks) {
+  RnsMvShape best;
+  for (int nb = 1; nb <= pc2k::RNS_NBMAX; ++nb) {
+    const size_t slots = (size_t)rns_slots(ctx, T, nb, pc2k::RNS_MV);
+    const size_t G = (rows + 32 * nb - 1) / (32 * nb);
+    if (!slots || (G * nb > blocks && best.nb)) continue;
+    for (size_t c = 1; c <= std::min(cols, (size_t)256) && (c == 1 || G * nb * c <= blocks); ++c) {
+      const size_t cc = (cols + c - 1) / c;
+      if ((cols + cc - 1) / cc != c) continue;  // the same split as a smaller count
+      const double t = ((double)((G * c + slots - 1) / slots) * (double)(cc * nw) +
+                        (c > 1 ? (double)c : 0.0)) * (1.45 + nb);
+      if (!best.nb || t < best.cost) best = {nb, G, c, cc, t};
+    }
+  }
+  return best;
+}
+
+// The RNS engine for a plan: the digit width of the least time among those
+// whose tables take no more than the plan's table bytes or 128 MB; false if
+// there is none or the device has no memory for it.  It is the faster one from a single
+// row up (load / apply in ms, RNS against VALU, ebits 50: 1024 bits, 64 rows x
+// 16 columns 0.18 / 0.16 against 1.03 / 2.1; 4096 bits, 64 x 16: 1.2 / 1.05
+// against 4.1 / 1.4; 2048 bits, 256 x 256: 0.42 / 1.4 against 2.2 / 4.8).
+bool rns_matvec_create(pc2_matvec* mv, size_t rows_hint) {
+  pc2_ctx* ctx = mv->ctx;
+  const int T = mv->pk->rn.T;
+  if (!T || ctx->modmul == PC2_MODMUL_VALU) return false;
+  const size_t slots = (size_t)rns_slots(ctx, T, 1, pc2k::RNS_MV);
+  const size_t tslots = (size_t)rns_slots(ctx, T, 1, pc2k::RNS_MVTAB);
+  if (!slots || !tslots) return false;
+  const size_t Gc = (mv->cols + 31) / 32, most = 2 * slots;
+  // (no hint: rows enough that the tables' cost is small, as for the window)
+  const size_t rows = std::min(rows_hint ? rows_hint : (size_t)8192, most * 32);
+  auto table = [&](int w) {
+    return mv->cols * (size_t)((mv->ebits + w - 1) / w) * ((size_t)64 * T << w);
+  };
+  double best = 0;
+  for (int w = 1; w <= 12; ++w) {
+    const size_t nw = (size_t)((mv->ebits + w - 1) / w);
+    if (table(w) > std::max(mv->table_bytes, (size_t)128 << 20)) break;
+    const double cost =
+        rns_mv_shape(ctx, T, mv->cols, (int)nw, rows, most).cost +
+        2.45 * (double)((Gc * nw + tslots - 1) / tslots) *
+            (double)(((size_t)1 << w) + (size_t)w * (nw - 1));
+    if (mv->rw == 0 || cost < best) {
+      best = cost;
+      mv->rw = w;
+      mv->rnw = (int)nw;
+    }
+  }
+  if (mv->rw == 0) return false;
+  mv->rblocks = std::max(most, Gc + std::min(tslots, Gc * mv->rnw));
+  const size_t stage = mv->rblocks * pc2k::rns_group_bytes(T, 1);
+  if (hipMalloc(&mv->tab, table(mv->rw)) != hipSuccess ||
+      hipMalloc(&mv->rstage, stage + mv->rblocks * 32 * 4) != hipSuccess ||
+      hipEventCreateWithFlags(&mv->done, hipEventDisableTiming) != hipSuccess) {
+    (void)hipGetLastError();
+    if (mv->tab) (void)hipFree(mv->tab);
+    if (mv->rstage) (void)hipFree(mv->rstage);
+    mv->tab = nullptr;
+    mv->rstage = nullptr;
+    mv->rw = 0;
+    return false;
+  }
+  mv->rbad = reinterpret_cast<uint32_t*>(mv->rstage + stage);
+  return true;
+}
+// the plan's staging is used by one call after another, whatever their streams
+// (as the context's scratch: scratch_begin, scratch_end)
+int stage_begin(pc2_matvec* mv, void* stream) {
+  if (!mv->done_valid || mv->done_stream == stream || capturing(stream)) return PC2_OK;
+  return hipStreamWaitEvent((hipStream_t)stream, mv->done, 0) == hipSuccess ? PC2_OK
+                                                                           : PC2_E_DEVICE;
+}
+int stage_end(pc2_matvec* mv, void* stream, int rc) {
+  if (rc || capturing(stream)) return rc;
+  if (hipEventRecord(mv->done, (hipStream_t)stream) != hipSuccess) return PC2_E_DEVICE;
+  mv->done_stream = stream;
+  mv->done_valid = true;
+  return PC2_OK;
+}
+
+int rns_matvec_load(pc2_matvec* mv, const uint32_t* c, void* stream) {
+  pc2_ctx* ctx = mv->ctx;
+  const pc2k::RnsKey& K = mv->pk->rn;
+  const int L2 = 2 * mv->pk->L;
+  const size_t gb = pc2k::rns_group_bytes(K.T, 1), slots = (size_t)rns_slots(ctx, K.T, 1, pc2k::RNS_MVTAB);
+  const size_t Gc = (mv->cols + 31) / 32;
+  int rc = stage_begin(mv, stream);
+  if (rc) return rc;
+  pc2k::RnsMvTab t{};
+  t.M = K.M;
+  t.one = K.one;
+  t.in = mv->rstage;
+  t.table = mv->rstage + Gc * gb;
+  t.tab = reinterpret_cast<uint8_t*>(mv->tab);
+  t.c = c;
+  t.n2 = mv->pk->c.n2.Nl;
+  t.L2 = L2;
+  t.w = mv->rw;
+  t.nw = mv->rnw;
+  t.ngroups = (int)Gc;
+  t.cols = mv->cols;
+  t.err = ctx->err;
+  hipError_t e = pc2k::launch_rns_to(K.c, K.T, 1, one_job(c, nullptr, 0, nullptr, mv->cols), false,
+                                     L2, mv->rstage, stream);
+  if (e == hipSuccess)
+    e = pc2k::launch_rns_gather(K.T, 1, pc2k::RNS_MVTAB,
+                                (int)std::min<size_t>(slots, Gc * mv->rnw), &t, stream);
+  return stage_end(mv, stream, status_of(e));
+}
+
+int rns_matvec_apply(pc2_matvec* mv, const uint64_t* B, const uint32_t* alpha, uint32_t* out,
+                     size_t rows, void* stream) {
+  pc2_ctx* ctx = mv->ctx;
+  const pc2k::RnsKey& K = mv->pk->rn;
+  const size_t L2 = 2 * (size_t)mv->pk->L;
+  int rc = stage_begin(mv, stream);
+  for (size_t at = 0; at < rows && !rc; at += mv->rblocks * 32) {
+    const size_t n = std::min(rows - at, mv->rblocks * 32);
+    const RnsMvShape S = rns_mv_shape(ctx, K.T, mv->cols, mv->rnw, n, mv->rblocks);
+    const uint32_t* a = alpha ? alpha + at * L2 : nullptr;
+    const pc2k::RnsJobs J = one_job(a, nullptr, 0, out + at * L2, n);
+    pc2k::RnsMv m{};
+    m.M = K.M;
+    m.one = K.one;
+    m.in = mv->rstage;
+    m.tab = reinterpret_cast<const uint8_t*>(mv->tab);
+    m.B = B + at * mv->cols;
+    m.bad = mv->rbad;
+    m.rows = n;
+    m.cols = mv->cols;
+    m.chunk_cols = S.chunk_cols;
+    m.alpha = alpha != nullptr;
+    m.ebits = mv->ebits;
+    m.w = mv->rw;
+    m.nw = mv->rnw;
+    m.nch = (int)S.nch;
+    m.ngroups = (int)S.groups;
+    hipError_t e = pc2k::launch_rns_row_check(a, mv->pk->c.n2.Nl, (int)L2, mv->rbad, n, stream);
+    if (e == hipSuccess && a)
+      e = pc2k::launch_rns_to(K.c, K.T, S.nb, J, false, (int)L2, mv->rstage, stream);
+    auto gather = [&](int which, size_t items) {
+      const size_t slots = (size_t)rns_slots(ctx, K.T, S.nb, which);
+      return pc2k::launch_rns_gather(K.T, S.nb, which, (int)std::min(slots, items), &m, stream);
+    };
+    if (e == hipSuccess) e = gather(pc2k::RNS_MV, S.groups * S.nch);
+    if (e == hipSuccess && S.nch > 1) e = gather(pc2k::RNS_CHAIN, S.groups);
+    if (e == hipSuccess)
+      e = pc2k::launch_rns_from(K.from, K.T, S.nb, mv->rstage, J, nullptr, 0, stream);
+    if (e == hipSuccess)
+      e = pc2k::launch_rns_row_clear(mv->rbad, out + at * L2, (int)L2, n, ctx->err, stream);
+    rc = status_of(e);
+  }
+  return stage_end(mv, stream, rc);
+}
+}  // namespace
+
 int pc2_matvec_create(const pc2_pk* pk, size_t cols, uint32_t ebits, uint32_t window,
                       size_t rows_hint, pc2_matvec** out) {
   if (!pk || !pk->ctx || !out || cols == 0 || ebits < 1 || ebits > 64 || window > 12)
@@ -2531,6 +2772,10 @@ int pc2_matvec_create(const pc2_pk* pk, size_t cols, uint32_t ebits, uint32_t wi
   mv->ebits = (int)ebits;
   mv->cols = cols;
   mv->table_bytes = matvec_table_bytes(pk->cls, cols, (int)ebits, w);
+  if (rns_matvec_create(mv, rows_hint)) {
+    *out = mv;
+    return PC2_OK;
+  }
   if (hipMalloc(&mv->tab, mv->table_bytes) != hipSuccess) {
     delete mv;
     return PC2_E_NOMEM;
@@ -2566,6 +2811,11 @@ int pc2_matvec_info(const pc2_matvec* mv, uint32_t* window, size_t* table_bytes)
 int pc2_matvec_load(pc2_matvec* mv, const uint32_t* c, void* hip_stream) {
   if (!mv || !mv->ctx || !c) return PC2_E_INVAL;
   if (hipSetDevice(mv->ctx->device) != hipSuccess) return PC2_E_DEVICE;
+  if (mv->rw) {
+    const int rc = rns_matvec_load(mv, c, hip_stream);
+    if (!rc) mv->loaded = true;
+    return rc;
+  }
   const int cls = mv->pk->cls;
   const size_t epw = (size_t)pc2k::elems_per_block(cls);
   const size_t groups = (mv->cols + epw - 1) / epw * (size_t)mv->nw;
@@ -2590,6 +2840,7 @@ int pc2_matvec_apply(pc2_matvec* mv, const uint64_t* B, const uint32_t* alpha, u
     if (a0 < o0 + rows * row_bytes && o0 < a0 + rows * row_bytes) return PC2_E_INVAL;
   }
   if (hipSetDevice(ctx->device) != hipSuccess) return PC2_E_DEVICE;
+  if (mv->rw) return rns_matvec_apply(mv, B, alpha, out, rows, hip_stream);
   // column chunks, as many as the plan's staging holds for this many rows
   const size_t epw = (size_t)pc2k::elems_per_block(cls);
   const size_t gpc = (rows + epw - 1) / epw;
@@ -2622,6 +2873,8 @@ int pc2_matvec_destroy(pc2_matvec* mv) {
   (void)hipDeviceSynchronize();
   if (mv->tab) (void)hipFree(mv->tab);
   if (mv->parts) (void)hipFree(mv->parts);
+  if (mv->rstage) (void)hipFree(mv->rstage);
+  if (mv->done) (void)hipEventDestroy(mv->done);
   delete mv;
   return PC2_OK;
 }

@@ -18,28 +18,22 @@
 
 using namespace pc2r;
 using pc2k::RnsFrom;
+using pc2k::RnsMv;
+using pc2k::RnsMvTab;
 using pc2k::RnsPow;
+using pc2k::RnsSmul;
 using pc2k::RnsTo;
 
 namespace {
 
-// One wavefront's run over its workgroup's groups; SIDE 0: X (or the only
-// group of wavefronts), 1: Y.  Both sides meet at the same barriers; see RGeo.
+// A program over the workgroup's groups: table of odd powers, sliding windows
+// and the closing product.
 template <class G, int SIDE>
 __device__ __forceinline__ void pow_run(const RnsPow& P, RWork<G>& ws, int wave, int lane) {
-  constexpr bool X = SIDE == 0;
-  constexpr bool U = (X ? G::RX : G::RY) > 0;
   constexpr size_t GB = 2 * (size_t)G::PART * 16;  // bytes of one group's residues
-  const int w = X ? wave : wave - G::W / 2;
-  const int t0 = (X ? 0 : G::NX) + w * G::MT;
-  const bool unit = w < (X ? G::RX : G::RY) * G::NB;
-  const int u = unit ? w : 0;
-  const int tu = (X ? 0 : G::NX) + (G::XY ? G::W / 2 : G::W) * G::MT + (U ? u / G::NB : 0);
-  const int bu = U ? u % G::NB : 0;
-  const bool first = (int)threadIdx.x < G::NB * 32;  // (X wavefronts) clears beta
-  uint8_t* slot = P.table + (size_t)blockIdx.x * P.entries * GB;
+  using OP = Operands<G>;
+  Stepper<G, SIDE, OP> st(wave, lane);
   const int nitems = P.ngroups * P.nmod;
-  Share<G, U> h;
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
     const int mod = P.nmod == 2 ? (it & 1) : 0;
     const int g = P.nmod == 2 ? it >> 1 : it;
@@ -47,114 +41,40 @@ __device__ __forceinline__ void pow_run(const RnsPow& P, RWork<G>& ws, int wave,
     const uint32_t* ops = P.ops[mod];
     uint8_t* in = P.in[mod] + (size_t)g * GB;
     uint8_t* gm = P.gm[mod] ? P.gm[mod] + (size_t)g * GB : in;
+    uint8_t* slot = P.table + ((size_t)blockIdx.x * P.entries - 1) * GB;
     auto entry = [&](uint32_t e) {
-      uint8_t* p = slot + (size_t)(e - 1) * GB;
+      uint8_t* p = slot + (size_t)e * GB;
       if (e == pc2k::RNS_GM) p = gm;
       if (e == 0 || e >= pc2k::RNS_OUT) p = in;
       return Buf(p, (uint32_t)GB);
     };
     auto is_mul = [](uint32_t op) { return op >> 16 == pc2k::RNS_MUL && (op & 0xFF) != pc2k::RNS_SQ; };
     auto stores = [](uint32_t op) { return ((op >> 8) & 0xFF) != pc2k::RNS_NODST; };
-    // operands of the reductions of product `op` in base B, and in base A,
-    // where the multiplier is the next product's
-    auto ops_b = [&](uint32_t op) {
-      return Operands{is_mul(op), stores(op), entry(op & 0xFF), entry((op >> 8) & 0xFF)};
-    };
-    auto ops_a = [&](uint32_t op, uint32_t next) {
-      return Operands{is_mul(next), stores(op), entry(next & 0xFF), entry((op >> 8) & 0xFF)};
-    };
-    int par = 0;
-    int k = 0;
-    uint32_t op = ops[0], prev = 0;
-    for (;;) {
-      // op is a load: every wavefront its own tiles
-      {
-        const uint32_t next = ops[k + 1];
+    uint32_t op = ops[0];
+    for (int k = 1;; ++k) {
+      const uint32_t next = ops[k];
+      if (op >> 16 == pc2k::RNS_LOAD) {
         const Buf e = entry(op & 0xFF), y = entry(next & 0xFF);
-        for (int m = 0; m < G::MT; ++m)
-          for (int b = 0; b < G::NB; ++b)
-            load_unit<G>(M, ws, t0 + m, b, e, is_mul(next), y, lane);
-        if (U && unit) load_unit<G>(M, ws, tu, bu, e, is_mul(next), y, lane);
-        for (int i = threadIdx.x; i < 2 * G::NB * 32; i += G::W * 64) (&ws.beta[0][0])[i] = 0;
-        op = next;
-        ++k;
-        if (X) h.prime(M.E1, t0, tu, lane);
-        lds_barrier();
+        const bool mul = is_mul(next);
+        st.load(
+            M, ws,
+            [&](int t, int b, bool, v4u& x) {
+              const uint32_t at = (t * G::NB + b) * 1024;
+              x = e.load(lane * 16, G::PART * 16 + at);
+              return e.load(lane * 16, at);
+            },
+            [&](int t, int b, bool, const v4u& x) {
+              return mul ? y.load(lane * 16, G::PART * 16 + (t * G::NB + b) * 1024) : x;
+            });
+      } else {
+        OP o{is_mul(op), stores(op), entry(op & 0xFF), entry((op >> 8) & 0xFF)};
+        OP n{is_mul(next), stores(op), entry(next & 0xFF), entry((op >> 8) & 0xFF)};
+        const bool last = next >> 16 == pc2k::RNS_END;
+        st.product(M, ws, o, n, last);
+        if (last) break;
       }
-      bool pending = false;  // Y: the last product's reductions in base A
-      for (;;) {
-        // products: A -> B
-        const uint32_t next = ops[++k];
-        if constexpr (!G::XY) {
-          h.template init<false>(ws.c2, M.c2, t0, tu, lane);
-          h.template part<0, G::T>(M.E1, ws.kb, M.kb, ws.xi, t0, tu, bu, lane);
-          finish_b(h, M, ws, par, t0, unit, tu, bu, ops_b(op), lane);
-          h.prime(M.E2, t0, tu, lane);
-          lds_barrier();
-          if (next >> 16 == pc2k::RNS_END) break;
-          h.template init<true>(ws.c2, M.c2, t0, tu, lane);
-          h.template part<0, G::T>(M.E2, ws.ka, M.ka, ws.om, t0, tu, bu, lane);
-          finish_a(h, M, ws, par, t0, unit, tu, bu, ops_a(op, next), lane);
-          par ^= 1;
-          if (first) ws.beta[par][threadIdx.x] = 0;
-          h.prime(M.E1, t0, tu, lane);
-          lds_barrier();
-        } else if constexpr (X) {
-          __builtin_amdgcn_s_setprio(1);
-          h.template init<false>(ws.c2, M.c2, t0, tu, lane);
-          h.template part<0, G::NX>(M.E1, ws.kb, M.kb, ws.xi, t0, tu, bu, lane);
-          lds_barrier();
-          __builtin_amdgcn_s_setprio(2);
-          h.template part<G::NX, G::T>(M.E1, ws.kb, M.kb, ws.xi, t0, tu, bu, lane);
-          __builtin_amdgcn_s_setprio(0);
-          finish_b(h, M, ws, par, t0, unit, tu, bu, ops_b(op), lane);
-          h.prime(M.E2, t0, tu, lane);
-          lds_barrier();
-          if (next >> 16 == pc2k::RNS_END) break;
-          __builtin_amdgcn_s_setprio(1);
-          h.template init<true>(ws.c2, M.c2, t0, tu, lane);
-          h.template part<0, G::NX>(M.E2, ws.ka, M.ka, ws.om, t0, tu, bu, lane);
-          lds_barrier();
-          __builtin_amdgcn_s_setprio(2);
-          h.template part<G::NX, G::T>(M.E2, ws.ka, M.ka, ws.om, t0, tu, bu, lane);
-          __builtin_amdgcn_s_setprio(0);
-          finish_a(h, M, ws, par, t0, unit, tu, bu, ops_a(op, next), lane);
-          par ^= 1;
-          if (first) ws.beta[par][threadIdx.x] = 0;
-          h.prime(M.E1, t0, tu, lane);
-          lds_barrier();
-        } else {
-          if (pending) finish_a(h, M, ws, par ^ 1, t0, unit, tu, bu, ops_a(prev, op), lane);
-          h.prime(M.E1, t0, tu, lane);
-          lds_barrier();
-          __builtin_amdgcn_s_setprio(1);
-          h.template init<false>(ws.c2, M.c2, t0, tu, lane);
-          h.template part<0, G::T>(M.E1, ws.kb, M.kb, ws.xi, t0, tu, bu, lane);
-          __builtin_amdgcn_s_setprio(0);
-          lds_barrier();
-          finish_b(h, M, ws, par, t0, unit, tu, bu, ops_b(op), lane);
-          if (next >> 16 == pc2k::RNS_END) break;
-          h.prime(M.E2, t0, tu, lane);
-          lds_barrier();
-          __builtin_amdgcn_s_setprio(1);
-          h.template init<true>(ws.c2, M.c2, t0, tu, lane);
-          h.template part<0, G::T>(M.E2, ws.ka, M.ka, ws.om, t0, tu, bu, lane);
-          __builtin_amdgcn_s_setprio(0);
-          par ^= 1;
-          pending = true;
-          lds_barrier();
-        }
-        prev = op;
-        op = next;
-        if (op >> 16 != pc2k::RNS_MUL) break;
-      }
-      if (ops[k] >> 16 == pc2k::RNS_END) break;
-      if constexpr (G::XY) {
-        if (!X) finish_a(h, M, ws, par ^ 1, t0, unit, tu, bu, ops_a(prev, op), lane);
-        lds_barrier();  // beta is read before the load clears it
-      }
+      op = next;
     }
-    lds_barrier();  // the next group's load overwrites the residues
   }
 }
 
@@ -163,15 +83,382 @@ __global__ __launch_bounds__(G::W * 64, 2) void k_rns_pow(RnsPow P) {
   __shared__ __align__(16) RWork<G> ws;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   load_constants<G>(P.M[0], ws);
-  lds_barrier();
-  if constexpr (G::XY) {
-    if (wave < G::W / 2)
-      pow_run<G, 0>(P, ws, wave, lane);
-    else
-      pow_run<G, 1>(P, ws, wave, lane);
-  } else {
-    pow_run<G, 0>(P, ws, wave, lane);
+  PC2R_SIDES(G, wave, (pow_run<G, SIDE>(P, ws, wave, lane)));
+}
+
+// c^k with a 64-bit k per element (fixed windows of 4 bits): in holds c, the
+// result replaces its residues in base B.
+template <class G, int SIDE>
+__device__ __forceinline__ void smul_run(const RnsSmul& P, RWork<G>& ws, int wave, int lane) {
+  constexpr size_t GB = 2 * (size_t)G::PART * 16;
+  using OP = Gather<G, true>;
+  Stepper<G, SIDE, OP> st(wave, lane);
+  const RConst<G> M(P.M);
+  const int n = lane & 31, h = lane >> 5;
+  uint8_t* slot = P.table + (size_t)blockIdx.x * 16 * GB;  // entry d: c^d MA
+  const Buf tab(slot, (uint32_t)(16 * GB));
+  const Buf one(P.one, G::T * 64), r2(P.one + G::T * 64, G::T * 64),
+      unit(P.one + 2 * G::T * 64, G::T * 64);
+  for (int g = blockIdx.x; g < P.ngroups; g += gridDim.x) {
+    const Buf in(P.in + (size_t)g * GB, (uint32_t)GB);
+    uint64_t e[G::NB], eu = 0;
+#pragma unroll
+    for (int b = 0; b < G::NB; ++b) {
+      const size_t i = ((size_t)g * G::NB + b) * 32 + n;
+      e[b] = P.k[i < P.count ? i : P.count - 1];
+      if (b == st.bu) eu = e[b];
+    }
+    auto entry = [&](OP& o, uint32_t d, uint32_t du, int b) {
+      o.off[b] = d * (uint32_t)GB + lane * 16 + b * 1024;
+      if (b == st.bu) o.offu = du * (uint32_t)GB + lane * 16 + b * 1024;
+    };
+    auto group = [&](OP& o) {
+      o.y = tab;
+      o.ts = G::NB * 1024;
+      o.ps = G::PART * 16;
+    };
+    // entry 0: one
+    st.each([&](int t, int b, bool) {
+      const uint32_t at = (t * G::NB + b) * 1024;
+      tab.store(one.load(h * 16, t * 32), lane * 16, at);
+      tab.store(one.load(h * 16, (G::T + t) * 32), lane * 16, G::PART * 16 + at);
+    });
+    // entry 1: c MA^2 / MA, then products by it
+    st.load(
+        M, ws,
+        [&](int t, int b, bool, v4u& x) {
+          const uint32_t at = (t * G::NB + b) * 1024;
+          x = in.load(lane * 16, G::PART * 16 + at);
+          return in.load(lane * 16, at);
+        },
+        [&](int t, int, bool, const v4u&) { return r2.load(h * 16, (G::T + t) * 32); });
+    OP o, nx;
+    o.single(r2, lane);
+    group(nx);
+#pragma unroll
+    for (int b = 0; b < G::NB; ++b) entry(nx, 1, 1, b);
+    o.store = nx.store = true;
+#pragma unroll 1
+    for (int d = 1; d < 16; ++d) {
+      o.mul = d != 2;  // (the square)
+      nx.mul = d >= 2;
+      o.dst = nx.dst = Buf(slot + (size_t)d * GB, (uint32_t)GB);
+      st.product(M, ws, o, nx, false);
+      if (d == 2) {
+        group(o);
+#pragma unroll
+        for (int b = 0; b < G::NB; ++b) o.off[b] = nx.off[b];
+        o.offu = nx.offu;
+      }
+    }
+    // the top digit's entry, four squarings and a product per digit, and the
+    // product by 1 that leaves Montgomery form
+    st.load(
+        M, ws,
+        [&](int t, int b, bool u, v4u& x) {
+          const uint32_t d = (uint32_t)((u ? eu : e[b]) >> 60);
+          const uint32_t off = d * (uint32_t)GB + lane * 16, at = (t * G::NB + b) * 1024;
+          x = tab.load(off, G::PART * 16 + at);
+          return tab.load(off, at);
+        },
+        [&](int, int, bool, const v4u& x) { return x; });
+    group(o);
+    o.store = nx.store = o.mul = false;
+    o.dst = nx.dst = in;
+    int sh = 56, s = 0;  // s: squarings done for the digit at sh
+#pragma unroll 1
+    for (;;) {
+      const bool last = sh < 0;
+      nx.mul = s == 3 || (s == 4 && sh == 0);
+      if (s == 3) {
+        group(nx);
+#pragma unroll
+        for (int b = 0; b < G::NB; ++b)
+          entry(nx, (uint32_t)(e[b] >> sh) & 15u, (uint32_t)(eu >> sh) & 15u, b);
+      } else if (nx.mul) {
+        nx.single(unit, lane);
+      }
+      o.store = last;
+      st.product(M, ws, o, nx, last);
+      if (last) break;
+      o.mul = nx.mul;
+      o.y = nx.y;
+      o.ts = nx.ts;
+      o.ps = nx.ps;
+      o.offu = nx.offu;
+#pragma unroll
+      for (int b = 0; b < G::NB; ++b) o.off[b] = nx.off[b];
+      if (++s == 5) {
+        s = 0;
+        sh -= 4;
+      }
+    }
   }
+}
+
+template <class G>
+__global__ __launch_bounds__(G::W * 64, 2) void k_rns_smul(RnsSmul P) {
+  __shared__ __align__(16) RWork<G> ws;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  load_constants<G>(P.M, ws);
+  PC2R_SIDES(G, wave, (smul_run<G, SIDE>(P, ws, wave, lane)));
+}
+
+// Fixed-base tables of the ciphertext matrix-vector product: item (window t,
+// column group) takes the columns' c_j to c_j^(2^(w t)) and writes its powers
+// d < 2^w in Montgomery form, each element's entry on its own (2 T x 32
+// bytes: base B, base A).  A column with c_j >= n^2 gets zeros (entry 0, the
+// Montgomery one, apart).
+template <class G, int SIDE>
+__device__ __forceinline__ void mvtab_run(const RnsMvTab& P, RWork<G>& ws, int wave, int lane) {
+  constexpr size_t GB = 2 * (size_t)G::PART * 16;
+  constexpr size_t EB = (size_t)G::T * 64;
+  using OP = Scatter<G>;
+  Stepper<G, SIDE, OP> st(wave, lane);
+  const RConst<G> M(P.M);
+  const int n = lane & 31, h = lane >> 5;
+  const Buf base(P.table + (size_t)blockIdx.x * GB, (uint32_t)GB);
+  const Buf one(P.one, G::T * 64), r2(P.one + G::T * 64, G::T * 64);
+  const int per = 1 << P.w;
+  for (int it = blockIdx.x; it < P.ngroups * P.nw; it += gridDim.x) {
+    const int win = P.nw - 1 - it / P.ngroups, g = it % P.ngroups;  // the longest first
+    const Buf in(P.in + (size_t)g * GB, (uint32_t)GB);
+    uint8_t *ent[G::NB], *entu = nullptr;  // entry 0 of the lane's element
+    bool ok[G::NB], oku = false;
+    auto where = [&](int b, bool& good) -> uint8_t* {
+      const size_t j = ((size_t)g * G::NB + b) * 32 + n;
+      good = j < P.cols && pc2d::sc_cmp(P.c + j * P.L2, P.L2, P.n2, P.L2) < 0;
+      return j < P.cols ? P.tab + ((j * P.nw + win) << P.w) * EB + h * 16 : nullptr;
+    };
+#pragma unroll
+    for (int b = 0; b < G::NB; ++b) ent[b] = where(b, ok[b]);
+    entu = where(st.bu, oku);
+    if (win == 0 && wave == 0 && h == 0)
+#pragma unroll
+      for (int b = 0; b < G::NB; ++b)
+        if (ent[b] && !ok[b]) atomicOr(P.err, pc2k::ERR_RANGE);
+    st.each([&](int t, int b, bool u) {
+      uint8_t* p = u ? entu : ent[b];
+      if (!p) return;
+      *reinterpret_cast<v4u*>(p + t * 32) = one.load(h * 16, t * 32);
+      *reinterpret_cast<v4u*>(p + (G::T + t) * 32) = one.load(h * 16, (G::T + t) * 32);
+    });
+    st.load(
+        M, ws,
+        [&](int t, int b, bool, v4u& x) {
+          const uint32_t at = (t * G::NB + b) * 1024;
+          x = in.load(lane * 16, G::PART * 16 + at);
+          return in.load(lane * 16, at);
+        },
+        [&](int t, int, bool, const v4u&) { return r2.load(h * 16, (G::T + t) * 32); });
+    // products: c MA, w t squarings (the last result is entry 1), then by the base
+    const int nsq = P.w * win;
+    OP o{}, nx{};
+    o.dst = nx.dst = nx.y = base;
+#pragma unroll 1
+    for (int s = 0; s < nsq + per - 1; ++s) {
+      const int d = s - nsq + 1;  // the entry that product s makes (d >= 1)
+      o.mul = s == 0 || d > 2;    // (entry 2 squares the base)
+      nx.mul = d >= 2;
+      o.y = s == 0 ? r2 : base;
+      o.store = nx.store = d >= 1;
+      o.group = nx.group = d == 1;
+      const size_t at = d >= 1 ? (size_t)d * EB : 0;
+#pragma unroll
+      for (int b = 0; b < G::NB; ++b) {
+        o.p[b] = nx.p[b] = ent[b] ? ent[b] + at : nullptr;
+        o.ok[b] = nx.ok[b] = ok[b];
+      }
+      o.pu = nx.pu = entu ? entu + at : nullptr;
+      o.oku = nx.oku = oku;
+      o.single = s == 0;
+      nx.single = false;
+      st.product(M, ws, o, nx, false);
+    }
+    st.flush(M, ws);
+  }
+}
+
+template <class G>
+__global__ __launch_bounds__(G::W * 64, 2) void k_rns_mvtab(RnsMvTab P) {
+  __shared__ __align__(16) RWork<G> ws;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  load_constants<G>(P.M, ws);
+  PC2R_SIDES(G, wave, (mvtab_run<G, SIDE>(P, ws, wave, lane)));
+}
+
+// Rows of the ciphertext matrix-vector product: item (column chunk, row group)
+// multiplies its rows' start values (the first chunk's in place if there is an
+// alpha, else 1; the other chunks' the Montgomery one) by one table entry per
+// w-bit digit of each of the chunk's constants.  A digit that is zero in the
+// whole group is skipped (every wavefront of a workgroup sees the same digits).
+template <class G, int SIDE>
+__device__ __forceinline__ void mv_run(const RnsMv& P, RWork<G>& ws, int wave, int lane) {
+  constexpr size_t GB = 2 * (size_t)G::PART * 16;
+  constexpr size_t EB = (size_t)G::T * 64;
+  using OP = Gather<G, (G::MT <= 2)>;
+  Stepper<G, SIDE, OP> st(wave, lane);
+  const RConst<G> M(P.M);
+  const int n = lane & 31, h = lane >> 5;
+  const uint32_t dmask = (1u << P.w) - 1;
+  for (int it = blockIdx.x; it < P.ngroups * P.nch; it += gridDim.x) {
+    const int ch = it / P.ngroups, g = it % P.ngroups;
+    const Buf in(P.in + (size_t)it * GB, (uint32_t)GB);
+    const bool own = ch == 0 && P.alpha;
+    const Buf from(own ? P.in + (size_t)it * GB : P.one + (ch == 0 ? 2 * EB : 0),
+                   own ? (uint32_t)GB : (uint32_t)EB);
+    auto start = [&](int t, int b, int part) {
+      return own ? from.load(lane * 16, part * G::PART * 16 + (t * G::NB + b) * 1024)
+                 : from.load(h * 16, (part * G::T + t) * 32);
+    };
+    const size_t j0 = (size_t)ch * P.chunk_cols;
+    const size_t j1 = j0 + P.chunk_cols < P.cols ? j0 + P.chunk_cols : P.cols;
+    const uint64_t* row[G::NB];
+    bool bad[G::NB];
+    uint64_t e[G::NB], en[G::NB];  // the constants of column j, and of j + 1 in flight
+#pragma unroll
+    for (int b = 0; b < G::NB; ++b) {
+      const size_t i = ((size_t)g * G::NB + b) * 32 + n;
+      row[b] = P.B + (i < P.rows ? i : P.rows - 1) * P.cols;
+      bad[b] = false;
+      e[b] = 0;
+      en[b] = row[b][j0];
+    }
+    size_t j = j0 - 1;
+    int win = P.nw - 1;
+    // the next digit with work into o; false at the end
+    auto advance = [&](OP& o) -> bool {
+      for (;;) {
+        if (++win == P.nw) {
+          if (++j == j1) return false;
+          win = 0;
+#pragma unroll
+          for (int b = 0; b < G::NB; ++b) {
+            e[b] = en[b];
+            if (P.ebits < 64 && (e[b] >> P.ebits) != 0) bad[b] = true;
+            if (j + 1 < j1) en[b] = row[b][j + 1];
+          }
+        }
+        uint32_t any = 0;
+#pragma unroll
+        for (int b = 0; b < G::NB; ++b) {
+          const uint32_t d = (uint32_t)(e[b] >> (P.w * win)) & dmask;
+          any |= d;
+          o.off[b] = d * (uint32_t)EB + h * 16;
+          if (b == st.bu) o.offu = o.off[b];
+        }
+        if (__ballot(any != 0) == 0) continue;
+        o.y = Buf(P.tab + ((j * P.nw + win) << P.w) * EB, (uint32_t)(EB << P.w));
+        return true;
+      }
+    };
+    OP o, nx;
+    o.ts = nx.ts = 32;
+    o.ps = nx.ps = G::T * 32;
+    o.dst = nx.dst = in;
+    o.store = nx.store = false;
+    bool more = advance(nx);
+    if (more) {
+      st.load(
+          M, ws,
+          [&](int t, int b, bool, v4u& x) {
+            x = start(t, b, 1);
+            return start(t, b, 0);
+          },
+          [&](int t, int b, bool u, const v4u&) {
+            return nx.y.load(u ? nx.offu : nx.off[b], (G::T + t) * 32);
+          });
+    } else if (!own) {  // every digit zero: the start value stands
+      st.each([&](int t, int b, bool) {
+        const uint32_t at = (t * G::NB + b) * 1024;
+        in.store(start(t, b, 0), lane * 16, at);
+        in.store(start(t, b, 1), lane * 16, G::PART * 16 + at);
+      });
+    }
+    o.mul = true;
+#pragma unroll 1
+    while (more) {
+      o.y = nx.y;
+      o.offu = nx.offu;
+#pragma unroll
+      for (int b = 0; b < G::NB; ++b) o.off[b] = nx.off[b];
+      nx.mul = more = advance(nx);
+      o.store = nx.store = !more;
+      st.product(M, ws, o, nx, false);
+    }
+    st.flush(M, ws);
+    if (wave == 0 && h == 0)
+#pragma unroll
+      for (int b = 0; b < G::NB; ++b) {
+        const size_t i = ((size_t)g * G::NB + b) * 32 + n;
+        if (bad[b] && i < P.rows) P.bad[i] = 1;
+      }
+  }
+}
+
+template <class G>
+__global__ __launch_bounds__(G::W * 64, 2) void k_rns_mv(RnsMv P) {
+  __shared__ __align__(16) RWork<G> ws;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  load_constants<G>(P.M, ws);
+  PC2R_SIDES(G, wave, (mv_run<G, SIDE>(P, ws, wave, lane)));
+}
+
+// The chunks' values of each row group multiplied together (base B of the
+// result in the first chunk's place).
+template <class G, int SIDE>
+__device__ __forceinline__ void chain_run(const RnsMv& P, RWork<G>& ws, int wave, int lane) {
+  constexpr size_t GB = 2 * (size_t)G::PART * 16;
+  using OP = Operands<G>;
+  Stepper<G, SIDE, OP> st(wave, lane);
+  const RConst<G> M(P.M);
+  for (int g = blockIdx.x; g < P.ngroups; g += gridDim.x) {
+    auto value = [&](int ch) {
+      return Buf(P.in + ((size_t)ch * P.ngroups + g) * GB, (uint32_t)GB);
+    };
+    const Buf v0 = value(0), v1 = value(1);
+    st.load(
+        M, ws,
+        [&](int t, int b, bool, v4u& x) {
+          const uint32_t at = (t * G::NB + b) * 1024;
+          x = v0.load(lane * 16, G::PART * 16 + at);
+          return v0.load(lane * 16, at);
+        },
+        [&](int t, int b, bool, const v4u&) {
+          return v1.load(lane * 16, G::PART * 16 + (t * G::NB + b) * 1024);
+        });
+#pragma unroll 1
+    for (int ch = 1; ch < P.nch; ++ch) {
+      const bool last = ch + 1 == P.nch;
+      OP o{true, last, value(ch), v0}, nx{!last, false, value(last ? ch : ch + 1), v0};
+      st.product(M, ws, o, nx, last);
+    }
+  }
+}
+
+template <class G>
+__global__ __launch_bounds__(G::W * 64, 2) void k_rns_chain(RnsMv P) {
+  __shared__ __align__(16) RWork<G> ws;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  load_constants<G>(P.M, ws);
+  PC2R_SIDES(G, wave, (chain_run<G, SIDE>(P, ws, wave, lane)));
+}
+
+// bad[i] = alpha_i >= n^2 (one lane per row; alpha null: 0)
+__global__ __launch_bounds__(64) void k_rns_row_check(const uint32_t* __restrict__ alpha,
+                                                      const uint32_t* __restrict__ n2, int L2,
+                                                      uint32_t* __restrict__ bad, size_t rows) {
+  const size_t i = (size_t)blockIdx.x * 64 + threadIdx.x;
+  if (i < rows) bad[i] = alpha ? pc2d::sc_cmp(alpha + i * L2, L2, n2, L2) >= 0 : 0;
+}
+// rows with bad[i] are zeroed and ERR_RANGE latched
+__global__ __launch_bounds__(64) void k_rns_row_clear(const uint32_t* __restrict__ bad,
+                                                      uint32_t* __restrict__ out, int L2,
+                                                      size_t rows, int* err) {
+  const size_t i = (size_t)blockIdx.x * 64 + threadIdx.x;
+  if (i >= rows || !bad[i]) return;
+  for (int k = 0; k < L2; ++k) out[i * L2 + k] = 0u;
+  atomicOr(err, pc2k::ERR_RANGE);
 }
 
 // the job and element at a position; false if there is none
@@ -481,6 +768,24 @@ const void* rns_pow_kernel(int t, int nb) {
 #undef PC2_RNS_DO
   return nullptr;
 }
+// The kernels with a multiplier per element.  Scalar products take one or two
+// column blocks (two where their multipliers fit the registers); mat-vecs one,
+// as their items are few and their multipliers come from HBM.
+const void* rns_gather_kernel(int t, int nb, int which) {
+#define PC2_RNS_DO                                                                        \
+  if constexpr (G::T >= 9 && (G::NB == 1 || (G::NB == 2 && (G::T == 9 || G::T == 17)))) { \
+    if (which == RNS_SMUL) return (const void*)&k_rns_smul<G>;                            \
+    if (which == RNS_MV) return (const void*)&k_rns_mv<G>;                                \
+    if (which == RNS_CHAIN) return (const void*)&k_rns_chain<G>;                          \
+  }                                                                                       \
+  if constexpr (G::T >= 9 && G::NB == 1) {                                                \
+    if (which == RNS_MVTAB) return (const void*)&k_rns_mvtab<G>;                          \
+  }                                                                                       \
+  return nullptr
+  PC2_RNS_GEOS(PC2_RNS_CASE)
+#undef PC2_RNS_DO
+  return nullptr;
+}
 
 int rns_pow_threads(int t, int nb) {
 #define PC2_RNS_DO return G::W * 64
@@ -504,6 +809,26 @@ hipError_t launch_rns_pow(int t, int nb, int grid, const RnsPow& p, void* stream
   void* args[] = {(void*)&p};
   return hipLaunchKernel(k, dim3(grid), dim3(rns_pow_threads(t, nb)), args, 0,
                          (hipStream_t)stream);
+}
+
+hipError_t launch_rns_gather(int t, int nb, int which, int grid, const void* p, void* stream) {
+  const void* k = rns_gather_kernel(t, nb, which);
+  if (!k) return hipErrorInvalidValue;
+  void* args[] = {const_cast<void*>(p)};
+  return hipLaunchKernel(k, dim3(grid), dim3(rns_pow_threads(t, nb)), args, 0,
+                         (hipStream_t)stream);
+}
+hipError_t launch_rns_row_check(const uint32_t* x, const uint32_t* n2, int L2, uint32_t* bad,
+                                size_t rows, void* stream) {
+  hipLaunchKernelGGL(k_rns_row_check, dim3((unsigned)((rows + 63) / 64)), dim3(64), 0,
+                     (hipStream_t)stream, x, n2, L2, bad, rows);
+  return hipGetLastError();
+}
+hipError_t launch_rns_row_clear(const uint32_t* bad, uint32_t* out, int L2, size_t rows, int* err,
+                                void* stream) {
+  hipLaunchKernelGGL(k_rns_row_clear, dim3((unsigned)((rows + 63) / 64)), dim3(64), 0,
+                     (hipStream_t)stream, bad, out, L2, rows, err);
+  return hipGetLastError();
 }
 
 hipError_t launch_rns_from(const RnsFrom& c, int T, int nb, const uint8_t* in,

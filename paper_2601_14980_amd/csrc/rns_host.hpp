@@ -393,6 +393,23 @@ inline RnsToHost rns_to(const RnsBase& R, const Limbs& N0, const Limbs& f, int n
   return o;
 }
 
+// v mod N as one entry: 16-bit residues by base B's channels (times s_j), then
+// base A's, centred.
+inline std::vector<uint32_t> rns_entry(const RnsBase& R, const Limbs& N, const Limbs& v0) {
+  const Limbs v = mod_words(v0, N);
+  std::vector<uint32_t> o;
+  for (int p = 0; p < 2; ++p)
+    for (int c = 0; c < R.n; c += 2) {
+      int32_t r[2];
+      for (int k = 0; k < 2; ++k) {
+        const uint32_t m = p ? R.a[c + k] : R.b[c + k];
+        r[k] = centred((int64_t)mod_small(v, m) * (p ? 1 : R.s[c + k]), m);
+      }
+      o.push_back(pair16(r[0], r[1]));
+    }
+  return o;
+}
+
 // Output conversion; mont: of values in Montgomery form (divides by MA).
 struct RnsFromHost {
   std::vector<uint32_t> C, D, O, N28;

@@ -26,4 +26,15 @@ hipError_t launch_rns_dec_finish(const SkConst& sk, const RnsJobs& jobs, const u
 hipError_t launch_rns_garner_crt(const SkConst& sk, const RnsJobs& jobs, const uint32_t* stage,
                                  int* err, void* stream);
 
+// kernels with a multiplier per element (null if not compiled for (T, nb));
+// rns_pow_threads threads; p: the kernel's argument (RnsSmul, RnsMvTab, RnsMv)
+enum { RNS_SMUL, RNS_MVTAB, RNS_MV, RNS_CHAIN, RNS_NGATHER };
+const void* rns_gather_kernel(int T, int nb, int which);
+hipError_t launch_rns_gather(int T, int nb, int which, int grid, const void* p, void* stream);
+// bad[i] = x_i >= n2 (x null: 0); rows with bad[i] zeroed and ERR_RANGE latched
+hipError_t launch_rns_row_check(const uint32_t* x, const uint32_t* n2, int L2, uint32_t* bad,
+                                size_t rows, void* stream);
+hipError_t launch_rns_row_clear(const uint32_t* bad, uint32_t* out, int L2, size_t rows, int* err,
+                                void* stream);
+
 }  // namespace pc2k

@@ -144,6 +144,7 @@ __device__ __forceinline__ void lds_barrier() {
 // lane offset, so that no vector register holds an address.
 struct Buf {
   __amdgpu_buffer_rsrc_t r;
+  Buf() = default;
   __device__ __forceinline__ Buf(const void* p, uint32_t bytes)
       : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000)) {}
   __device__ __forceinline__ v4u load(uint32_t lane_off, uint32_t off) const {
@@ -294,26 +295,133 @@ struct Share {
 };
 
 // The multiplier of a product (mul; else the running value itself) and the
-// destination of a copy of its result (store).
+// destination of a copy of its result (store), both in a group's layout.
+// pre_b / pre_a run before the matrix product whose reductions use the
+// multiplier's residues in that base, f_b / f_a in them (m: the tile's index in
+// the wavefront's share, MT for its unit).
+template <class G>
 struct Operands {
   bool mul, store;
   Buf y, dst;
+  __device__ __forceinline__ void pre_b(int, int, int, int) {}
+  __device__ __forceinline__ void pre_a(int, int, int, int) {}
+  template <int NBN>
+  __device__ __forceinline__ void f_b(v4u (&f)[NBN], int, int t, int nb0, int lane) const {
+#pragma unroll
+    for (int b = 0; b < NBN; ++b) f[b] = y.load(lane * 16, ((t * G::NB + nb0 + b) * 64) * 16);
+  }
+  template <int NBN>
+  __device__ __forceinline__ void f_a(v4u (&f)[NBN], int, int t, int nb0, int lane) const {
+#pragma unroll
+    for (int b = 0; b < NBN; ++b)
+      f[b] = y.load(lane * 16, (G::PART + (t * G::NB + nb0 + b) * 64) * 16);
+  }
+  __device__ __forceinline__ void st_b(const v4u& z, int t, int b, bool, int lane) const {
+    dst.store(z, lane * 16, ((t * G::NB + b) * 64) * 16);
+  }
+  __device__ __forceinline__ void st_a(const v4u& z, int t, int b, bool, int lane) const {
+    dst.store(z, lane * 16, (G::PART + (t * G::NB + b) * 64) * 16);
+  }
+};
+
+// A multiplier per element: lane's element of column block b has its residues
+// at y + off[b] (offu: of the unit's block), tile stride ts, base A at ps.
+// PRE (where the registers allow it): they are loaded a matrix product ahead
+// of their use, which hides the latency of entries that come from HBM.
+template <class G, bool PRE>
+struct Gather {
+  bool mul, store;
+  Buf y, dst;
+  uint32_t off[G::NB], offu, ts, ps;
+  v4u pre[PRE ? G::MT + 1 : 1][G::NB];
+  __device__ __forceinline__ void pre_any(uint32_t part, int t0, bool unit, int tu) {
+    if (!PRE || !mul) return;
+#pragma unroll
+    for (int m = 0; m < G::MT; ++m)
+#pragma unroll
+      for (int b = 0; b < G::NB; ++b) pre[m][b] = y.load(off[b], part + (t0 + m) * ts);
+    if (unit) pre[PRE ? G::MT : 0][0] = y.load(offu, part + tu * ts);
+  }
+  __device__ __forceinline__ void pre_b(int t0, bool unit, int tu, int) { pre_any(0, t0, unit, tu); }
+  __device__ __forceinline__ void pre_a(int t0, bool unit, int tu, int) {
+    pre_any(ps, t0, unit, tu);
+  }
+  template <int NBN>
+  __device__ __forceinline__ void get(v4u (&f)[NBN], int m, int t, uint32_t part) const {
+#pragma unroll
+    for (int b = 0; b < NBN; ++b) {
+      if constexpr (PRE)
+        f[b] = pre[m][b];
+      else
+        f[b] = y.load(m == G::MT ? offu : off[b], part + t * ts);
+    }
+  }
+  template <int NBN>
+  __device__ __forceinline__ void f_b(v4u (&f)[NBN], int m, int t, int, int) const {
+    get(f, m, t, 0);
+  }
+  template <int NBN>
+  __device__ __forceinline__ void f_a(v4u (&f)[NBN], int m, int t, int, int) const {
+    get(f, m, t, ps);
+  }
+  // one entry for every element
+  __device__ __forceinline__ void single(const Buf& e, int lane) {
+    y = e;
+    ts = 32;
+    ps = G::T * 32;
+    offu = (lane >> 5) * 16;
+#pragma unroll
+    for (int b = 0; b < G::NB; ++b) off[b] = offu;
+  }
+  __device__ __forceinline__ void st_b(const v4u& z, int t, int b, bool, int lane) const {
+    dst.store(z, lane * 16, ((t * G::NB + b) * 64) * 16);
+  }
+  __device__ __forceinline__ void st_a(const v4u& z, int t, int b, bool, int lane) const {
+    dst.store(z, lane * 16, (G::PART + (t * G::NB + b) * 64) * 16);
+  }
+};
+
+// The multiplier as in Operands; the results go to an entry of each element's
+// own at p[b] (pu: of the unit's block; null: none), zero where ok is not
+// set, and (group) to dst as well.
+template <class G>
+struct Scatter : Operands<G> {
+  bool group, single;  // single: y is one entry, the same for every element
+  uint8_t* p[G::NB];
+  uint8_t* pu;
+  bool ok[G::NB], oku;
+  template <int NBN>
+  __device__ __forceinline__ void f_b(v4u (&f)[NBN], int m, int t, int nb0, int lane) const {
+    if (!single) return Operands<G>::template f_b<NBN>(f, m, t, nb0, lane);
+#pragma unroll
+    for (int b = 0; b < NBN; ++b) f[b] = this->y.load((lane >> 5) * 16, t * 32);
+  }
+  __device__ __forceinline__ void put(const v4u& z, uint32_t at, int b, bool unit) const {
+    uint8_t* q = unit ? pu : p[b];
+    const bool good = unit ? oku : ok[b];
+    if (q) *reinterpret_cast<v4u*>(q + at) = good ? z : v4u{0u, 0u, 0u, 0u};
+  }
+  __device__ __forceinline__ void st_b(const v4u& z, int t, int b, bool unit, int lane) const {
+    if (group) Operands<G>::st_b(z, t, b, unit, lane);
+    put(z, t * 32, b, unit);
+  }
+  __device__ __forceinline__ void st_a(const v4u& z, int t, int b, bool unit, int lane) const {
+    if (group) Operands<G>::st_a(z, t, b, unit, lane);
+    put(z, (G::T + t) * 32, b, unit);
+  }
 };
 
 // The reductions after A -> B, tile t over column blocks nb0 ..: w <- w y +
 // acc, and the tile's share of beta into s1, s2.
-template <class G, int NBN>
+template <class G, int NBN, class OP>
 __device__ __forceinline__ void reduce_b(const v16i (&acc)[NBN], const ChanConst<G>& k, RWork<G>& ws,
-                                         int t, int nb0, const Operands& o, int (&s1)[NBN],
+                                         int m, int t, int nb0, const OP& o, int (&s1)[NBN],
                                          int (&s2)[NBN], int lane) {
   const int at = (t * G::NB + nb0) * 64;
   v4u x[NBN], f[NBN];
 #pragma unroll
   for (int b = 0; b < NBN; ++b) x[b] = f[b] = ws.om[at + b * 64 + lane] ^ FLIP;
-  if (o.mul) {
-#pragma unroll
-    for (int b = 0; b < NBN; ++b) f[b] = o.y.load(lane * 16, (at + b * 64) * 16);
-  }
+  if (o.mul) o.template f_b<NBN>(f, m, t, nb0, lane);
 #pragma unroll
   for (int b = 0; b < NBN; ++b) {
     v4u z;
@@ -329,7 +437,7 @@ __device__ __forceinline__ void reduce_b(const v16i (&acc)[NBN], const ChanConst
       s1[b] = mad16<1>(z[i], k.w[16 + i], mad16<0>(z[i], k.w[16 + i], s1[b]));
       s2[b] = mad16<1>(z[i], k.w[20 + i], mad16<0>(z[i], k.w[20 + i], s2[b]));
     }
-    if (o.store) o.dst.store(z, lane * 16, (at + b * 64) * 16);
+    if (o.store) o.st_b(z, t, nb0 + b, m == G::MT, lane);
     ws.om[at + b * 64 + lane] = z ^ FLIP;
   }
 }
@@ -339,10 +447,10 @@ __device__ __forceinline__ void add_beta(RWork<G>& ws, int par, int b, int s1, i
   __hip_atomic_fetch_add(&ws.beta[par][b * 32 + (lane & 31)], (unsigned long long)s,
                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
-template <class G, bool U>
+template <class G, bool U, class OP>
 __device__ __forceinline__ void finish_b(Share<G, U>& h, const RConst<G>& M, RWork<G>& ws,
                                          int par, int t0, bool unit, int tu, int bu,
-                                         const Operands& o, int lane) {
+                                         const OP& o, int lane) {
   int s1[G::NB] = {}, s2[G::NB] = {};
   ChanConst<G> k[2];
   k[0] = h.k;
@@ -352,7 +460,7 @@ __device__ __forceinline__ void finish_b(Share<G, U>& h, const RConst<G>& M, RWo
       k[(m + 1) & 1].load(ws.kb, M.kb, t0 + m + 1, lane);
     else if (U)
       k[(m + 1) & 1].load(ws.kb, M.kb, tu, lane);
-    reduce_b<G, G::NB>(h.acc[m], k[m & 1], ws, t0 + m, 0, o, s1, s2, lane);
+    reduce_b<G, G::NB>(h.acc[m], k[m & 1], ws, m, t0 + m, 0, o, s1, s2, lane);
   }
 #pragma unroll
   for (int b = 0; b < G::NB; ++b) add_beta<G>(ws, par, b, s1[b], s2[b], lane);
@@ -360,7 +468,7 @@ __device__ __forceinline__ void finish_b(Share<G, U>& h, const RConst<G>& M, RWo
     if (unit) {
       int u1[1] = {}, u2[1] = {};
       const v16i au[1] = {h.accu};
-      reduce_b<G, 1>(au, k[G::MT & 1], ws, tu, bu, o, u1, u2, lane);
+      reduce_b<G, 1>(au, k[G::MT & 1], ws, G::MT, tu, bu, o, u1, u2, lane);
       add_beta<G>(ws, par, bu, u1[0], u2[0], lane);
     }
   }
@@ -377,10 +485,10 @@ __device__ __forceinline__ uint32_t read_beta(const RWork<G>& ws, int par, int b
 
 // The reductions after B -> A: x <- acc - beta MB, then xi <- x y for the next
 // product, whose multiplier o names (o.dst: where this product's x goes).
-template <class G, int NBN>
+template <class G, int NBN, class OP>
 __device__ __forceinline__ void reduce_a(const v16i (&acc)[NBN], const uint32_t (&bp)[NBN],
-                                         const ChanConst<G>& k, RWork<G>& ws, int t, int nb0,
-                                         const Operands& o, int lane) {
+                                         const ChanConst<G>& k, RWork<G>& ws, int m, int t,
+                                         int nb0, const OP& o, int lane) {
   const int at = (t * G::NB + nb0) * 64;
   v4u x[NBN], f[NBN];
 #pragma unroll
@@ -401,12 +509,9 @@ __device__ __forceinline__ void reduce_a(const v16i (&acc)[NBN], const uint32_t 
   }
   if (o.store) {
 #pragma unroll
-    for (int b = 0; b < NBN; ++b) o.dst.store(x[b], lane * 16, (G::PART + at + b * 64) * 16);
+    for (int b = 0; b < NBN; ++b) o.st_a(x[b], t, nb0 + b, m == G::MT, lane);
   }
-  if (o.mul) {
-#pragma unroll
-    for (int b = 0; b < NBN; ++b) f[b] = o.y.load(lane * 16, (G::PART + at + b * 64) * 16);
-  }
+  if (o.mul) o.template f_a<NBN>(f, m, t, nb0, lane);
 #pragma unroll
   for (int b = 0; b < NBN; ++b) {
     v4u z;
@@ -417,10 +522,10 @@ __device__ __forceinline__ void reduce_a(const v16i (&acc)[NBN], const uint32_t 
     ws.xi[at + b * 64 + lane] = z ^ FLIP;
   }
 }
-template <class G, bool U>
+template <class G, bool U, class OP>
 __device__ __forceinline__ void finish_a(Share<G, U>& h, const RConst<G>& M, RWork<G>& ws,
                                          int par, int t0, bool unit, int tu, int bu,
-                                         const Operands& o, int lane) {
+                                         const OP& o, int lane) {
   uint32_t bp[G::NB];
 #pragma unroll
   for (int b = 0; b < G::NB; ++b) bp[b] = read_beta<G>(ws, par, b, lane);
@@ -432,34 +537,166 @@ __device__ __forceinline__ void finish_a(Share<G, U>& h, const RConst<G>& M, RWo
       k[(m + 1) & 1].load(ws.ka, M.ka, t0 + m + 1, lane);
     else if (U)
       k[(m + 1) & 1].load(ws.ka, M.ka, tu, lane);
-    reduce_a<G, G::NB>(h.acc[m], bp, k[m & 1], ws, t0 + m, 0, o, lane);
+    reduce_a<G, G::NB>(h.acc[m], bp, k[m & 1], ws, m, t0 + m, 0, o, lane);
   }
   if constexpr (U) {
     if (unit) {
       const uint32_t bpu[1] = {read_beta<G>(ws, par, bu, lane)};
       const v16i au[1] = {h.accu};
-      reduce_a<G, 1>(au, bpu, k[G::MT & 1], ws, tu, bu, o, lane);
+      reduce_a<G, 1>(au, bpu, k[G::MT & 1], ws, G::MT, tu, bu, o, lane);
     }
   }
 }
 
-// Load a value: w, and xi for the next product (as in ext2).
-template <class G>
-__device__ __forceinline__ void load_unit(const RConst<G>& M, RWork<G>& ws, int t, int b,
-                                          const Buf& e, bool mul, const Buf& yb, int lane) {
-  const int at = (t * G::NB + b) * 64;
-  ws.om[at + lane] = e.load(lane * 16, at * 16) ^ FLIP;
-  const v4u x = e.load(lane * 16, (G::PART + at) * 16);
-  v4u y = x;
-  if (mul) y = yb.load(lane * 16, (G::PART + at) * 16);
-  ChanConst<G> k;
-  k.load(ws.ka, M.ka, t, lane);
-  v4u o;
+// One wavefront's run of products over its workgroup's current group; SIDE 0:
+// X (or the only group of wavefronts), 1: Y.  Both sides meet at the same
+// barriers (see RGeo), so every wavefront of a workgroup makes the same calls.
+template <class G, int SIDE, class OP>
+struct Stepper {
+  static constexpr bool X = SIDE == 0;
+  static constexpr bool U = (X ? G::RX : G::RY) > 0;
+  int lane, t0, tu, bu, par = 0;
+  bool unit, first;
+  bool pending = false;  // Y: the last product's reductions in base A (with def)
+  OP def;
+  Share<G, U> h;
+
+  __device__ __forceinline__ Stepper(int wave, int lane_) : lane(lane_) {
+    const int w = X ? wave : wave - G::W / 2;
+    t0 = (X ? 0 : G::NX) + w * G::MT;
+    unit = w < (X ? G::RX : G::RY) * G::NB;
+    const int u = unit ? w : 0;
+    tu = (X ? 0 : G::NX) + (G::XY ? G::W / 2 : G::W) * G::MT + (U ? u / G::NB : 0);
+    bu = U ? u % G::NB : 0;
+    first = (int)threadIdx.x < G::NB * 32;  // (X wavefronts) clears beta
+  }
+
+  // f(tile, column block, index in the share) over the wavefront's units
+  template <class F>
+  __device__ __forceinline__ void each(F f) const {
+#pragma unroll 1
+    for (int m = 0; m < G::MT; ++m)
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-    o[i] = pack16(reduce(mul16_biased<0>(x[i], y[i], BIAS), k.w[2 * i], k.w[8 + 2 * i]),
-                  reduce(mul16_biased<1>(x[i], y[i], BIAS), k.w[2 * i + 1], k.w[9 + 2 * i]));
-  ws.xi[at + lane] = o ^ FLIP;
-}
+      for (int b = 0; b < G::NB; ++b) f(t0 + m, b, false);
+    if (U && unit) f(tu, bu, true);
+  }
+
+  // the running value <- w and x as load(tile, block, unit, x) gives them, with
+  // xi for a product by mul(tile, block, unit, x)
+  template <class L, class F>
+  __device__ __forceinline__ void load(const RConst<G>& M, RWork<G>& ws, L value, F mul) {
+    if constexpr (G::XY && !X) {
+      if (pending) {
+        finish_a(h, M, ws, par ^ 1, t0, unit, tu, bu, def, lane);
+        pending = false;
+      }
+    }
+    lds_barrier();  // beta is read, and the residues, before they are overwritten
+    each([&](int t, int b, bool u) {
+      const int at = (t * G::NB + b) * 64;
+      v4u x;
+      ws.om[at + lane] = value(t, b, u, x) ^ FLIP;
+      const v4u y = mul(t, b, u, x);
+      ChanConst<G> k;
+      k.load(ws.ka, M.ka, t, lane);
+      v4u o;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        o[i] = pack16(reduce(mul16_biased<0>(x[i], y[i], BIAS), k.w[2 * i], k.w[8 + 2 * i]),
+                      reduce(mul16_biased<1>(x[i], y[i], BIAS), k.w[2 * i + 1], k.w[9 + 2 * i]));
+      ws.xi[at + lane] = o ^ FLIP;
+    });
+    for (int i = threadIdx.x; i < 2 * G::NB * 32; i += G::W * 64) (&ws.beta[0][0])[i] = 0;
+    par = 0;
+    if (X) h.prime(M.E1, t0, tu, lane);
+    lds_barrier();
+  }
+
+  // One product: o names its multiplier and where its w goes, n the next
+  // product's multiplier and where this product's x goes.  last: w only.
+  __device__ __forceinline__ void product(const RConst<G>& M, RWork<G>& ws, OP& o, OP& n,
+                                          bool last) {
+    if constexpr (!G::XY || X) {
+      o.pre_b(t0, unit, tu, lane);
+      h.template init<false>(ws.c2, M.c2, t0, tu, lane);
+      if constexpr (G::XY) {
+        __builtin_amdgcn_s_setprio(1);
+        h.template part<0, G::NX>(M.E1, ws.kb, M.kb, ws.xi, t0, tu, bu, lane);
+        lds_barrier();
+        __builtin_amdgcn_s_setprio(2);
+      }
+      h.template part<G::XY ? G::NX : 0, G::T>(M.E1, ws.kb, M.kb, ws.xi, t0, tu, bu, lane);
+      if constexpr (G::XY) __builtin_amdgcn_s_setprio(0);
+      finish_b(h, M, ws, par, t0, unit, tu, bu, o, lane);
+      h.prime(M.E2, t0, tu, lane);
+      lds_barrier();
+      if (last) return;
+      n.pre_a(t0, unit, tu, lane);
+      h.template init<true>(ws.c2, M.c2, t0, tu, lane);
+      if constexpr (G::XY) {
+        __builtin_amdgcn_s_setprio(1);
+        h.template part<0, G::NX>(M.E2, ws.ka, M.ka, ws.om, t0, tu, bu, lane);
+        lds_barrier();
+        __builtin_amdgcn_s_setprio(2);
+      }
+      h.template part<G::XY ? G::NX : 0, G::T>(M.E2, ws.ka, M.ka, ws.om, t0, tu, bu, lane);
+      if constexpr (G::XY) __builtin_amdgcn_s_setprio(0);
+      finish_a(h, M, ws, par, t0, unit, tu, bu, n, lane);
+      par ^= 1;
+      if (first) ws.beta[par][threadIdx.x] = 0;
+      h.prime(M.E1, t0, tu, lane);
+      lds_barrier();
+    } else {
+      if (pending) finish_a(h, M, ws, par ^ 1, t0, unit, tu, bu, def, lane);
+      pending = false;
+      h.prime(M.E1, t0, tu, lane);
+      lds_barrier();
+      o.pre_b(t0, unit, tu, lane);
+      __builtin_amdgcn_s_setprio(1);
+      h.template init<false>(ws.c2, M.c2, t0, tu, lane);
+      h.template part<0, G::T>(M.E1, ws.kb, M.kb, ws.xi, t0, tu, bu, lane);
+      __builtin_amdgcn_s_setprio(0);
+      lds_barrier();
+      finish_b(h, M, ws, par, t0, unit, tu, bu, o, lane);
+      if (last) return;
+      h.prime(M.E2, t0, tu, lane);
+      lds_barrier();
+      n.pre_a(t0, unit, tu, lane);
+      __builtin_amdgcn_s_setprio(1);
+      h.template init<true>(ws.c2, M.c2, t0, tu, lane);
+      h.template part<0, G::T>(M.E2, ws.ka, M.ka, ws.om, t0, tu, bu, lane);
+      __builtin_amdgcn_s_setprio(0);
+      par ^= 1;
+      pending = true;
+      def = n;
+      lds_barrier();
+    }
+  }
+
+  // after the last product if its x is wanted
+  __device__ __forceinline__ void flush(const RConst<G>& M, RWork<G>& ws) {
+    if constexpr (G::XY && !X) {
+      if (pending) finish_a(h, M, ws, par ^ 1, t0, unit, tu, bu, def, lane);
+      pending = false;
+    }
+  }
+};
+
+// run R<SIDE>::go(...) of a workgroup's wavefronts
+#define PC2R_SIDES(G, wave, CALL)   \
+  do {                              \
+    if constexpr (G::XY) {          \
+      if ((wave) < G::W / 2) {      \
+        constexpr int SIDE = 0;     \
+        CALL;                       \
+      } else {                      \
+        constexpr int SIDE = 1;     \
+        CALL;                       \
+      }                             \
+    } else {                        \
+      constexpr int SIDE = 0;       \
+      CALL;                         \
+    }                               \
+  } while (0)
 
 }  // namespace pc2r

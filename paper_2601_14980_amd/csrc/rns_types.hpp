@@ -81,6 +81,39 @@ struct RnsPow {
   int nmod, ngroups, entries;
 };
 
+// one: single values, the same for every element (an entry of 2 T x 32 bytes
+// each: base B, base A): MA, MA^2 and 1 mod N.
+struct RnsSmul {         // c^k, k_rns_smul
+  RnsMod M;
+  const uint8_t* one;
+  uint8_t* in;           // c, and the result (base B)
+  uint8_t* table;        // 16 entries per workgroup
+  const uint64_t* k;
+  size_t count;
+  int ngroups;
+};
+struct RnsMvTab {        // k_rns_mvtab
+  RnsMod M;
+  const uint8_t* one;
+  const uint8_t* in;     // c_j
+  uint8_t* table;        // one entry per workgroup
+  uint8_t* tab;          // [cols][nw][2^w] entries
+  const uint32_t *c, *n2;
+  int L2, w, nw, ngroups;
+  size_t cols;
+  int* err;
+};
+struct RnsMv {           // k_rns_mv, k_rns_chain
+  RnsMod M;
+  const uint8_t* one;
+  uint8_t* in;           // [chunk][row group]: the running values
+  const uint8_t* tab;
+  const uint64_t* B;
+  uint32_t* bad;         // per row
+  size_t rows, cols, chunk_cols;
+  int alpha, ebits, w, nw, nch, ngroups;  // alpha: the first chunk's values are set; ngroups: of rows
+};
+
 constexpr int RNS_NT = 6, RNS_NBMAX = 4;
 constexpr int RNS_T[RNS_NT] = {5, 9, 13, 17, 26, 34};  // compiled tile counts
 
@@ -90,6 +123,8 @@ struct RnsKey {
   RnsMod M;
   RnsTo x, gm;              // the power's base (times MA); 1 + m n
   RnsFrom from;
+  RnsTo c;                  // modulo n^2: ciphertexts as they are,
+  const uint8_t* one;       // and the single values MA, MA^2, 1 (see RnsSmul)
   const uint32_t* ops[5];
 };
 
