@@ -12,66 +12,6 @@
 
 namespace pc2h {
 
-// x mod m by word-wise long division (Knuth's algorithm D)
-inline Limbs mod_words(const Limbs& x0, const Limbs& m0) {
-  Limbs x = x0, m = m0;
-  trim(x);
-  trim(m);
-  if (cmp(x, m) < 0) return resized(x, m.size());
-  const size_t n = m.size();
-  const int sh = __builtin_clz(m[n - 1]);
-  if (n == 1) {
-    uint64_t r = 0;
-    for (size_t i = x.size(); i-- > 0;) r = ((r << 32) | x[i]) % m[0];
-    return Limbs{(uint32_t)r};
-  }
-  auto shl = [&](const Limbs& a, size_t len) {
-    Limbs r(len, 0);
-    for (size_t i = 0; i < len; ++i) {
-      const uint64_t lo = i > 0 && i - 1 < a.size() ? a[i - 1] : 0, hi = i < a.size() ? a[i] : 0;
-      r[i] = (uint32_t)((((hi << 32) | lo) << sh) >> 32);
-    }
-    return r;
-  };
-  const Limbs d = shl(m, n);
-  Limbs u = shl(x, x.size() + 1);
-  for (size_t j = u.size() - n; j-- > 0;) {
-    const uint64_t num = ((uint64_t)u[j + n] << 32) | u[j + n - 1];
-    uint64_t q = u[j + n] >= d[n - 1] ? 0xFFFFFFFFull : num / d[n - 1];
-    uint64_t r = num - q * d[n - 1];
-    while (r >> 32 == 0 && q * d[n - 2] > ((r << 32) | u[j + n - 2])) {
-      --q;
-      r += d[n - 1];
-    }
-    int64_t borrow = 0;
-    uint64_t c = 0;
-    for (size_t i = 0; i < n; ++i) {
-      c += q * d[i];
-      const int64_t t = (int64_t)u[i + j] - (int64_t)(uint32_t)c + borrow;
-      u[i + j] = (uint32_t)t;
-      borrow = t >> 32;
-      c >>= 32;
-    }
-    const int64_t t = (int64_t)u[j + n] - (int64_t)c + borrow;
-    u[j + n] = (uint32_t)t;
-    if (t < 0) {
-      uint64_t k = 0;
-      for (size_t i = 0; i < n; ++i) {
-        k += (uint64_t)u[i + j] + d[i];
-        u[i + j] = (uint32_t)k;
-        k >>= 32;
-      }
-      u[j + n] += (uint32_t)k;
-    }
-  }
-  Limbs out(n, 0);
-  for (size_t i = 0; i < n; ++i) {
-    const uint64_t lo = u[i], hi = i + 1 < n ? u[i + 1] : 0;
-    out[i] = (uint32_t)(((hi << 32) | lo) >> sh);
-  }
-  return out;
-}
-
 inline uint32_t mod_small(const Limbs& x, uint32_t m) {
   uint64_t r = 0;
   for (size_t i = x.size(); i-- > 0;) r = ((r << 32) | x[i]) % m;
@@ -114,12 +54,25 @@ inline uint32_t inv_small(uint32_t a, uint32_t m) {  // a^-1 mod m, 0 if not inv
   return (uint32_t)(t0 < 0 ? t0 + m : t0);
 }
 
-// v mod m in (-m/2, m/2]
-inline int32_t centred(int64_t v, uint32_t m) {
-  int64_t r = v % (int64_t)m;
-  if (r < 0) r += m;
-  return (int32_t)(2 * r > (int64_t)m ? r - m : r);
-}
+// Residues modulo a channel's m of |v| < 2^50: in [0, m), and centred in
+// (-m/2, m/2].  The quotient in double is exact to +-1; a key's tables take some
+// 10^5 of these, which the division instruction made half of its creation.
+struct Mod {
+  int64_t m;
+  double inv;
+  explicit Mod(uint32_t m_) : m(m_), inv(1.0 / (double)m_) {}
+  uint32_t operator()(int64_t v) const {
+    int64_t r = v - m * (int64_t)((double)v * inv);
+    r += r < 0 ? m : 0;
+    r -= r >= m ? m : 0;
+    return (uint32_t)r;
+  }
+  int32_t centred(int64_t v) const {
+    const int64_t r = (*this)(v);
+    return (int32_t)(2 * r > m ? r - m : r);
+  }
+};
+inline int32_t centred(int64_t v, uint32_t m) { return Mod(m).centred(v); }
 
 // largest prime allowed per tile count: small enough for the bounds on the
 // 32-bit sums, large enough that 16 T of them hold the modulus and 2^30
@@ -136,7 +89,6 @@ struct RnsBase {
   std::vector<uint32_t> iMAi;      // (MA / a_i)^-1 mod a_i
   std::vector<uint32_t> ia;        // [j][i] a_i^-1 mod b_j
   std::vector<int32_t> g;          // MA (MB / b_j)^-1 mod b_j, centred
-  std::vector<Limbs> gMB;          // |g_j| MB / b_j
   std::vector<uint32_t> E2;        // fragments (T T 256 words)
   std::vector<uint32_t> c2, kb, ka;
   bool ok = false;
@@ -156,9 +108,10 @@ inline bool rns_pack(const std::vector<int32_t>& E, const std::vector<uint32_t>&
   for (int j = 0; j < n; ++j) {
     const int t = j / 16, H = (j >> 3) & 1, u = j & 7;
     int64_t sum = 0, bound = 0;
+    const Mod M(mrow[j]);
     for (int i = 0; i < n; ++i) {
       const int32_t e = E[(size_t)j * n + i];
-      const int32_t f = centred((int64_t)e * 256, mrow[j]);
+      const int32_t f = M.centred((int64_t)e * 256);
       sum += e;
       const int64_t hmax = (int64_t)((0.52 * mcol[i] + 128) / 256) + 1;
       bound += 128 * (int64_t)std::abs(e) + hmax * std::abs(f);
@@ -215,10 +168,11 @@ inline RnsBase make_rns_base(int T) {
   trim(R.MB);
   // products of a base's other moduli, and of the other base, per channel
   auto prod_mod = [](const std::vector<uint32_t>& v, uint32_t m, int skip) {
-    uint64_t r = 1;
+    const Mod M(m);
+    uint32_t r = 1;
     for (int i = 0; i < (int)v.size(); ++i)
-      if (i != skip) r = r * v[i] % m;
-    return (uint32_t)r;
+      if (i != skip) r = M((int64_t)r * v[i]);
+    return r;
   };
   R.s.resize(n);
   R.iMAi.resize(n);
@@ -228,34 +182,31 @@ inline RnsBase make_rns_base(int T) {
   for (int i = 0; i < n; ++i) R.iMAi[i] = inv_small(prod_mod(R.a, R.a[i], i), R.a[i]);
   for (int j = 0; j < n; ++j) {
     const uint32_t m = R.b[j];
+    const Mod M(m);
     pre[0] = 1;
-    for (int i = 0; i < n; ++i) pre[i + 1] = (uint32_t)((uint64_t)pre[i] * (R.a[i] % m) % m);
+    for (int i = 0; i < n; ++i) pre[i + 1] = M((int64_t)pre[i] * R.a[i]);
     R.s[j] = inv_small(pre[n], m);
-    uint64_t run = R.s[j];
+    uint32_t run = R.s[j];
     for (int i = n; i-- > 0;) {  // inverse of every a_i from one inverse of their product
-      R.ia[(size_t)j * n + i] = (uint32_t)(run * pre[i] % m);
-      run = run * (R.a[i] % m) % m;
+      R.ia[(size_t)j * n + i] = M((int64_t)run * pre[i]);
+      run = M((int64_t)run * R.a[i]);
     }
     R.g[j] = centred((int64_t)((uint64_t)pre[n] * inv_small(prod_mod(R.b, m, j), m) % m), m);
   }
   std::vector<int32_t> E2((size_t)n * n);
   for (int i = 0; i < n; ++i) {
     const uint32_t m = R.a[i];
+    const Mod M(m);
     std::vector<uint32_t> suf(n + 1);
     suf[n] = 1;
-    for (int j = n; j-- > 0;) suf[j] = (uint32_t)((uint64_t)suf[j + 1] * R.b[j] % m);
-    uint64_t p = 1;
+    for (int j = n; j-- > 0;) suf[j] = M((int64_t)suf[j + 1] * R.b[j]);
+    uint32_t p = 1;
     for (int j = 0; j < n; ++j) {
-      const uint64_t mbj = p * suf[j + 1] % m;
-      E2[(size_t)i * n + j] = centred((int64_t)mbj * R.g[j], m);
-      p = p * R.b[j] % m;
+      E2[(size_t)i * n + j] = M.centred((int64_t)M((int64_t)p * suf[j + 1]) * R.g[j]);
+      p = M((int64_t)p * R.b[j]);
     }
   }
   R.ok = rns_pack(E2, R.a, R.b, false, &R.E2, &R.c2);
-  for (int j = 0; j < n; ++j) {
-    const uint32_t ag = (uint32_t)std::abs(R.g[j]);
-    R.gMB.push_back(mul_small(div_small(R.MB, R.b[j]), ag));
-  }
   R.kb.assign((size_t)T * 48, 0);
   R.ka.assign((size_t)T * 48, 0);
   for (int c = 0; c < n; ++c) {
@@ -310,21 +261,20 @@ inline bool rns_e1(const RnsBase& R, const Limbs& N, std::vector<uint32_t>* frag
                    std::vector<uint32_t>* cst) {
   const int n = R.n;
   std::vector<int32_t> E((size_t)n * n);
-  std::vector<uint32_t> k(n);
+  std::vector<int64_t> ki(n);  // centred, as q's bound wants
   for (int i = 0; i < n; ++i) {
     const uint32_t a = R.a[i], inv = inv_small(mod_small(N, a), a);
     if (!inv) return false;
-    k[i] = (uint32_t)((uint64_t)(a - inv) * R.iMAi[i] % a);
+    ki[i] = centred((int64_t)(a - inv) * R.iMAi[i], a);
   }
   for (int j = 0; j < n; ++j) {
     const uint32_t m = R.b[j];
     const uint64_t Nj = mod_small(N, m);
     if (!Nj) return false;
-    const uint64_t f = Nj * R.s[j] % m;
+    const Mod M(m);
+    const int64_t f = M((int64_t)(Nj * R.s[j]));
     for (int i = 0; i < n; ++i) {
-      const int64_t ki = centred(k[i], R.a[i]);  // centred, as q's bound wants
-      const int64_t t = (int64_t)(f * R.ia[(size_t)j * n + i] % m);
-      E[(size_t)j * n + i] = centred(ki * t, m);
+      E[(size_t)j * n + i] = M.centred(ki[i] * M.centred(f * R.ia[(size_t)j * n + i]));
     }
   }
   return rns_pack(E, R.b, R.a, true, frag, cst);
@@ -347,7 +297,8 @@ inline RnsToHost rns_to(const RnsBase& R, const Limbs& N0, const Limbs& f, int n
   o.m.assign((size_t)4 * T * 8, 0);
   std::vector<uint32_t> m(2 * n), r(2 * n), Nm(2 * n);
   for (int c = 0; c < 2 * n; ++c) m[c] = c < n ? R.b[c] : R.a[c - n];  // part 0: base B
-  Limbs v = mod_words(f, N);
+  const std::vector<Mod> Ms(m.begin(), m.end());
+  Limbs v = mod(f, N);
   v = resized(v, N.size());
   for (int c = 0; c < 2 * n; ++c) {
     r[c] = mod_small(v, m[c]);
@@ -358,7 +309,7 @@ inline RnsToHost rns_to(const RnsBase& R, const Limbs& N0, const Limbs& f, int n
   for (int i = 0; i < nhalf; ++i) {
     for (int c = 0; c < 2 * n; ++c) {
       const uint64_t sc = c < n ? R.s[c] : 1;
-      o.P[((size_t)(c / 8) * nhalf + i) * 8 + (c & 7)] = (uint32_t)(r[c] * sc % m[c]);
+      o.P[((size_t)(c / 8) * nhalf + i) * 8 + (c & 7)] = Ms[c]((int64_t)(r[c] * sc));
     }
     if (i + 1 == nhalf) break;
     // v <- 2^16 v mod N, on the limbs and on the residues
@@ -382,8 +333,7 @@ inline RnsToHost rns_to(const RnsBase& R, const Limbs& N0, const Limbs& f, int n
     }
     v = resized(w, nl);
     for (int c = 0; c < 2 * n; ++c) {
-      int64_t t = ((int64_t)r[c] * 65536 - q * (int64_t)Nm[c]) % (int64_t)m[c];
-      r[c] = (uint32_t)(t < 0 ? t + m[c] : t);
+      r[c] = Ms[c]((int64_t)r[c] * 65536 - q * (int64_t)Nm[c]);
     }
   }
   for (int c = 0; c < 2 * n; ++c) {
@@ -396,7 +346,7 @@ inline RnsToHost rns_to(const RnsBase& R, const Limbs& N0, const Limbs& f, int n
 // v mod N as one entry: 16-bit residues by base B's channels (times s_j), then
 // base A's, centred.
 inline std::vector<uint32_t> rns_entry(const RnsBase& R, const Limbs& N, const Limbs& v0) {
-  const Limbs v = mod_words(v0, N);
+  const Limbs v = mod(v0, N);
   std::vector<uint32_t> o;
   for (int p = 0; p < 2; ++p)
     for (int c = 0; c < R.n; c += 2) {
@@ -435,38 +385,26 @@ inline RnsFromHost rns_from(const RnsBase& R, const Limbs& N0, bool mont) {
   o.S = (bitlen(N) + 27 + 27) / 28;
   o.nblk = (o.S + 7) / 8;
   const int SB = 8 * o.nblk;
-  const Mont32 M(N);
-  Limbs iMA;  // MA^-1 mod N
-  if (mont) {
-    // the product of the a_i^-1 mod N, each (1 + N t) / a_i with
-    // t = -N^-1 mod a_i
-    iMA = M.to(Limbs{1});
-    for (int i = 0; i < n; ++i) {
-      const uint32_t a = R.a[i];
-      const uint32_t t = (a - inv_small(mod_small(N, a), a)) % a;
-      Limbs x = mul_small(N, t);
-      x = add(x, Limbs{1});
-      iMA = M.mm(iMA, M.to(div_small(x, a)));
-    }
-    iMA = M.from(iMA);
-  }
-  const Limbs f = mont ? M.to(iMA) : Limbs{};
-  auto scaled = [&](const Limbs& x) {
-    Limbs r = resized(mod_words(x, N), N.size());
-    return mont ? M.mm(r, f) : r;
+  // x / a mod N, exactly divided after adding the multiple of N that makes it
+  // divisible
+  auto div_mod = [&](const Limbs& x, uint32_t a) {
+    const uint64_t ninv = inv_small(mod_small(N, a), a);
+    const uint32_t t = (uint32_t)((a - mod_small(x, a)) * ninv % a);
+    return div_small(add(mul_small(N, t), x), a);
   };
+  Limbs f = mod(R.MB, N);  // MB, or MB / MA
+  if (mont)
+    for (int i = 0; i < n; ++i) f = div_mod(f, R.a[i]);
   o.C.assign((size_t)o.nblk * n * 8, 0);
-  for (int j = 0; j < n; ++j) {
-    Limbs c = scaled(R.gMB[j]);
-    if (R.g[j] < 0 && !is_zero(c)) c = sub(resized(N, N.size()), c);
+  for (int j = 0; j < n; ++j) {  // g_j f / b_j
+    Limbs c = mod(mul_small(div_mod(f, R.b[j]), (uint32_t)std::abs(R.g[j])), N);
+    if (R.g[j] < 0 && !is_zero(c)) c = sub(N, c);
     const std::vector<uint32_t> l = limbs28(c, SB);
     for (int i = 0; i < SB; ++i) o.C[((size_t)(i / 8) * n + j) * 8 + i % 8] = l[i];
     o.F.push_back((int64_t)std::nearbyintl((long double)R.g[j] / (long double)R.b[j] *
                                            68719476736.0L));
   }
-  Limbs d = scaled(R.MB);
-  if (!is_zero(d)) d = sub(resized(N, N.size()), d);
-  o.D = limbs28(d, SB);
+  o.D = limbs28(is_zero(f) ? f : sub(N, f), SB);
   Limbs off(N.size() + 1, 0);
   off = resized(mul_small(N, 1u << 26), N.size() + 1);
   o.O = limbs28(off, SB);
