@@ -618,7 +618,7 @@ int auto_window(int geo, int op) {
 
 int window_for(const pc2_ctx* ctx, int geo, int op) {
   if (ctx->window) return ctx->window;
-  if (op == pc2k::OP_FUSED_MFMA) op = pc2k::OP_ENC_MFMA;
+  if (op == pc2k::OP_FUSED_MFMA || op == pc2k::OP_ENC_TEAM) op = pc2k::OP_ENC_MFMA;
   const int t = ctx->tuned[geo][op == pc2k::OP_FUSED ? pc2k::OP_ENC : op];
   // (matrix-core engine, 2048-bit keys: w = 6 measured 1 % faster than 5)
   if (op == pc2k::OP_ENC_MFMA) return t ? t : (geo >= 6 ? 6 : (geo >= 5 ? 5 : 4));
@@ -663,10 +663,12 @@ int occupancy(pc2_ctx* ctx, int geo, int op) {
   int& o = ctx->occ[geo][op];
   if (o == 0) {
     int v = 0;
-    const void* k = op == pc2k::OP_ENC_MFMA     ? pc2k::kernel_encrypt_mfma(geo)
+    int threads = 64;
+    const void* k = op == pc2k::OP_ENC_TEAM     ? pc2k::kernel_encrypt_team(geo, &threads)
+                    : op == pc2k::OP_ENC_MFMA   ? pc2k::kernel_encrypt_mfma(geo)
                     : op == pc2k::OP_FUSED_MFMA ? pc2k::kernel_encrypt_mfma(geo, true)
                                                 : pc2k::kernel_for(geo, op);
-    if (!k || hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k, 64, 0) != hipSuccess ||
+    if (!k || hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k, threads, 0) != hipSuccess ||
         v <= 0)
       v = 1;
     o = v;
@@ -681,7 +683,7 @@ int occupancy(pc2_ctx* ctx, int geo, int op) {
 // every launch that asks for the same amount), then the tables.
 size_t plan_launch(pc2_ctx* ctx, int geo, int op, size_t count, int Ls, int L, int w,
                    pc2k::Launch* l, void* stream, size_t aux_words) {
-  const bool mf = op == pc2k::OP_ENC_MFMA || op == pc2k::OP_FUSED_MFMA;
+  const bool mf = op == pc2k::OP_ENC_MFMA || op == pc2k::OP_FUSED_MFMA || op == pc2k::OP_ENC_TEAM;
   const size_t epb = mf ? 1 : (size_t)pc2k::elems_per_block(geo);
   const size_t groups = (count + epb - 1) / epb;
   const size_t cap = (size_t)ctx->cus * occupancy(ctx, geo, op);
@@ -815,6 +817,7 @@ size_t class_scratch_need(pc2_ctx* ctx, int cls, int L, int Ls, int nl2) {
   if (pc2k::ALT_GEO[cls] >= 0) take(pc2k::ALT_GEO[cls], pc2k::OP_ENC, 0);
   take(cls, pc2k::OP_SMUL, 0);
   take(cls, pc2k::OP_ENC_MFMA, 0);
+  take(cls, pc2k::OP_ENC_TEAM, 0);
   take(cls, pc2k::OP_DEC, ch * 2 * (size_t)(Ls + 1));
   const size_t acc_words =
       std::max(pc2k::chunk_words(cls), pc2k::mfma_digit_bytes(cls) / 4);  // either engine
@@ -917,6 +920,17 @@ Engine enc_engine(const pc2_ctx* ctx, const pc2_pk* pk, size_t count) {
   if (use_mfma(ctx, pk->cls)) return ENG_ELEM;
   // (a tile asked for by option is a tile of the VALU engine)
   return !ctx->tile && count <= ELEM_MAX_COUNT[pk->cls] ? ENG_ELEM : ENG_VALU;
+}
+// The matrix-core encryption of `count` elements by workgroups of several
+// wavefronts per element (mfma_team.hpp): while one round of them holds all
+// elements.  A second round takes as long as the first, and then a wavefront
+// per element is no slower (ms, team / wavefront, at one full round and past
+// it: 1024 bits, 512 elements 1.25 / 1.6, 2048 bits, 256: 2.9 / 5.4 and 257: 5.9
+// / 5.4, 3072 bits, 256: 5.5 / 11.3).
+bool enc_team(pc2_ctx* ctx, int cls, size_t count) {
+  int threads;
+  return pc2k::kernel_encrypt_team(cls, &threads) &&
+         count <= (size_t)ctx->cus * occupancy(ctx, cls, pc2k::OP_ENC_TEAM);
 }
 bool dec_rns(const pc2_ctx* ctx, const pc2_sk* sk) {
   return sk->dec[1].T && ctx->modmul != PC2_MODMUL_VALU;
@@ -1475,11 +1489,13 @@ int pc2_encrypt(const pc2_pk* pk, const uint32_t* m, uint32_t m_limbs, const uin
   const Engine eng = enc_engine(ctx, pk, count);
   if (eng == ENG_RNS) return rns_encrypt(pk, m, (int)m_limbs, r, c, count, stream);
   if (eng == ENG_ELEM) {
-    int rc = prepare(ctx, pk->cls, pc2k::OP_ENC_MFMA, count, 0, pk->L, &l, stream);
+    const bool team = enc_team(ctx, pk->cls, count);
+    int rc = prepare(ctx, pk->cls, team ? pc2k::OP_ENC_TEAM : pc2k::OP_ENC_MFMA, count, 0, pk->L,
+                     &l, stream);
     if (!rc) rc = scratch_begin(ctx, stream);
     if (rc) return rc;
     return scratch_end(ctx, stream, status_of(pc2k::launch_encrypt_mfma(
-                                        pk->cls, l, pk->c, m, (int)m_limbs, r, c, count)));
+                                        pk->cls, l, pk->c, m, (int)m_limbs, r, c, count, team)));
   }
   const int geo = enc_geo(ctx, pk->cls, count);
   int rc = prepare(ctx, geo, pc2k::OP_ENC, count, 0, pk->L, &l, stream);

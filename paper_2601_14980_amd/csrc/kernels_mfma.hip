@@ -15,6 +15,7 @@
 #include "engine.hpp"
 #include "launch.hpp"
 #include "mfma_mont.hpp"
+#include "mfma_team.hpp"
 #include "paillier_ops.hpp"
 
 namespace {
@@ -83,29 +84,10 @@ __device__ __forceinline__ void store_canonical(pc2m::MWork<G>& ws, const pc2m::
     if (gi >= 0 && gi < G::S) u[gi] = (uint32_t)U[q];
   }
   pc2m::wave_sync();
-  if (lane == 0) {
-    int32_t cy = 0;
-    for (int i = 0; i < G::S; ++i) {
-      const int32_t t = (int32_t)u[i] + cy;
-      u[i] = (uint32_t)t & pc2m::M28;
-      cy = t >> 28;
-    }
-    if (cy < 0) {
-      uint32_t cr = 0;
-      for (int i = 0; i < G::S; ++i) {
-        const uint32_t t = u[i] + K.N28[i] + cr;
-        u[i] = t & pc2m::M28;
-        cr = t >> 28;
-      }
-    }
-  }
+  if (lane == 0) pc2m::canonical_limbs<G>(u, K);
   pc2m::wave_sync();
   for (int j = lane; j < L2; j += 64) {
-    const int b = 32 * j, i = b / 28, s = b % 28;
-    const uint64_t acc = (uint64_t)(i < G::S ? u[i] : 0u) |
-                         ((uint64_t)(i + 1 < G::S ? u[i + 1] : 0u) << 28) |
-                         ((uint64_t)(i + 2 < G::S ? u[i + 2] : 0u) << 56);
-    out[j] = ok ? (uint32_t)(acc >> s) : 0u;
+    out[j] = ok ? pc2m::canonical_word<G>(u, j) : 0u;
   }
   pc2m::wave_sync();
 }
@@ -131,6 +113,113 @@ __global__ __launch_bounds__(64, S <= 160 ? 3 : 2) void k_encrypt_mfma(
     store_canonical<G>(ws, pk.mf, U, lane, c + e * 2 * (size_t)L, 2 * L, ok);
     if (lane == 0 && !ok) atomicOr(err, pc2k::ERR_RANGE);
   }
+}
+
+// The same encryption with a workgroup of several wavefronts per element
+// (mfma_team.hpp); the steps are those of encrypt_element, as one loop around
+// one product.
+template <class G, int ROLE>
+__device__ __forceinline__ void team_run(pc2m::TeamWork<G>& ws, const PkConst& pk,
+                                         const uint32_t* m, int m_limbs, const uint32_t* r,
+                                         uint32_t* c, size_t count, uint8_t* table, int w,
+                                         int* err) {
+  using P = pc2m::Tile<G, ROLE>;
+  const int lane = threadIdx.x & 63;
+  const int half = 1 << (w - 1);
+  uint8_t* sq = table + (size_t)half * G::FB;
+  uint8_t* gm = sq + G::FB;
+  const uint32_t* sched = pk.nsch.p[w - pc2k::SCHED_WMIN];
+  const int nsched = pk.nsch.n[w - pc2k::SCHED_WMIN];
+  const int L2 = 2 * pk.L;
+  const uint8_t* kp = P::LOW ? pk.mf.Np : pk.mf.N;
+  pc2m::v4i KB[P::NK];
+#pragma unroll
+  for (int k = 0; k < P::NK; ++k) KB[k] = pc2m::team_b_global<G, P>(kp, lane, k);
+  int32_t U = 0;
+  for (size_t e = blockIdx.x; e < count; e += gridDim.x) {
+    const uint32_t* me = m + e * m_limbs;
+    const uint32_t* re = r + e * pk.L;
+    if (threadIdx.x == 0) ws.ok = pc2ops::encrypt_inputs_ok(pk, me, m_limbs, re);
+    pc2m::team_load_x<G>(ws, me, m_limbs);
+    // steps: 0 g^m, 1 entry 0, 2 the square, 3 .. half + 1 the entries, then
+    // the schedule (si, its squarings left, its product), then by g^m
+    int si = 0;
+    uint32_t left = 0, dig = 0;
+#pragma unroll 1
+    for (int step = 0;; ++step) {
+      const uint8_t* y = nullptr;
+      uint8_t* out = nullptr;
+      bool last = false;
+      if (step == 0) {
+        y = pk.mf.nR;
+        out = gm;
+      } else if (step == 1) {
+        pc2m::team_load_x<G>(ws, re, pk.L);
+        y = pk.mf.R2;
+        out = table;
+      } else if (step == 2) {
+        out = sq;
+      } else if (step < half + 2) {
+        if (step == 3) pc2m::team_load_fwd<G>(ws, table);
+        y = sq;
+        out = table + (size_t)(step - 2) * G::FB;
+      } else {
+        if (si == 0) pc2m::team_load_fwd<G>(ws, table + (size_t)((sched[0] & 0xFFFFu) >> 1) * G::FB);
+        while (left == 0 && dig == 0 && ++si < nsched) {
+          left = sched[si] >> 16;
+          dig = sched[si] & 0xFFFFu;
+        }
+        if (left) {
+          --left;
+        } else if (dig) {
+          y = table + (size_t)(dig >> 1) * G::FB;
+          dig = 0;
+        } else {
+          y = gm;
+          last = true;
+        }
+      }
+      pc2m::team_mul<G, ROLE>(ws, KB, kp, y, lane, out, step == 0, U);
+      if (last) break;
+    }
+    if constexpr (!P::LOW) {
+      const int gi = P::BASE - G::S + lane;
+      if (gi < G::S && lane >= P::OWN) ws.u[gi] = (uint32_t)U;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) pc2m::canonical_limbs<G>(ws.u, pk.mf);
+    __syncthreads();
+    const uint32_t ok = ws.ok;
+    for (int j = threadIdx.x; j < L2; j += G::W * 64)
+      c[e * L2 + j] = ok ? pc2m::canonical_word<G>(ws.u, j) : 0u;
+    if (threadIdx.x == 0 && !ok) atomicOr(err, pc2k::ERR_RANGE);
+    __syncthreads();  // ws.ok and ws.u are read
+  }
+}
+
+template <int S>
+__global__ __launch_bounds__(pc2m::TeamGeo<S>::W * 64, 2) void k_encrypt_team(
+    PkConst pk, const uint32_t* __restrict__ m, int m_limbs, const uint32_t* __restrict__ r,
+    uint32_t* __restrict__ c, size_t count, uint8_t* scratch, int w, int* err) {
+  using G = pc2m::TeamGeo<S>;
+  static_assert(G::W <= 10, "roles below");
+  __shared__ __align__(16) pc2m::TeamWork<G> ws;
+  uint8_t* table = scratch + (size_t)blockIdx.x * ((size_t)G::FB << w);
+  uint32_t* z = reinterpret_cast<uint32_t*>(&ws);
+  for (int i = threadIdx.x; i < (int)(sizeof(ws) / 4); i += G::W * 64) z[i] = 0u;
+  // the table's pads (see init_table; the tails are zero too)
+  for (int k = 0; k < (1 << (w - 1)) + 2; ++k)
+    for (int i = threadIdx.x; i < G::FB / 4; i += G::W * 64)
+      reinterpret_cast<uint32_t*>(table + (size_t)k * G::FB)[i] = 0u;
+  __syncthreads();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#define PC2_ROLE(R)                                                             \
+  if constexpr (R < G::W) {                                                     \
+    if (wave == R) team_run<G, R>(ws, pk, m, m_limbs, r, c, count, table, w, err); \
+  }
+  PC2_ROLE(0) PC2_ROLE(1) PC2_ROLE(2) PC2_ROLE(3) PC2_ROLE(4) PC2_ROLE(5) PC2_ROLE(6) PC2_ROLE(7)
+  PC2_ROLE(8) PC2_ROLE(9)
+#undef PC2_ROLE
 }
 
 // Step `step` of the fused encrypt -> K-way product (Def. 1 applied K - 1
@@ -239,6 +328,22 @@ const void* kernel_encrypt_mfma(int cls, bool fused) {
   return nullptr;
 }
 
+// few elements: a workgroup of several wavefronts each (from 1024-bit keys)
+const void* kernel_encrypt_team(int cls, int* threads) {
+#define PC2_TEAM(C)                                       \
+  case C:                                                 \
+    *threads = pc2m::TeamGeo<MFMA_S[C]>::W * 64;          \
+    return (const void*)&k_encrypt_team<MFMA_S[C]>
+  switch (cls) {
+    PC2_TEAM(5);
+    PC2_TEAM(6);
+    PC2_TEAM(7);
+    PC2_TEAM(8);
+  }
+#undef PC2_TEAM
+  return nullptr;
+}
+
 const void* batch_mfma_kernel(int cls) {
   switch (cls) {
     case 0: return (const void*)&k_batch_mfma<MFMA_S[0]>;
@@ -274,14 +379,15 @@ size_t mfma_digit_bytes(int cls) {  // a forward digit array, with its zero pads
 }
 
 hipError_t launch_encrypt_mfma(int cls, const Launch& l, const PkConst& pk, const uint32_t* m,
-                               int m_limbs, const uint32_t* r, uint32_t* c, size_t count) {
-  const void* k = kernel_encrypt_mfma(cls);
+                               int m_limbs, const uint32_t* r, uint32_t* c, size_t count, bool team) {
+  int threads = 64;
+  const void* k = team ? kernel_encrypt_team(cls, &threads) : kernel_encrypt_mfma(cls);
   if (!k) return hipErrorInvalidValue;
   uint8_t* scratch = reinterpret_cast<uint8_t*>(l.scratch);
   int w = l.window;
   void* args[] = {(void*)&pk, (void*)&m, (void*)&m_limbs, (void*)&r, (void*)&c,
                   (void*)&count, (void*)&scratch, (void*)&w, (void*)&l.err};
-  return hipLaunchKernel(k, dim3(l.grid), dim3(64), args, 0, (hipStream_t)l.stream);
+  return hipLaunchKernel(k, dim3(l.grid), dim3(threads), args, 0, (hipStream_t)l.stream);
 }
 
 hipError_t launch_enc_prod_mfma(int cls, const Launch& l, const PkConst& pk, const PtrList& ms,

@@ -11,7 +11,8 @@ enum Op {
   OP_ENC_MFMA = 5,  // encryption with the matrix-core product (kernels_mfma.hip)
   OP_ENC_CRT = 6,   // key-holder encryption through p^2 and q^2
   OP_FUSED_MFMA = 7,  // OP_FUSED with the matrix-core product
-  OP_COUNT = 8
+  OP_ENC_TEAM = 8,  // OP_ENC_MFMA by a workgroup of several wavefronts per element
+  OP_COUNT = 9
 };
 
 // kernel_for, slot_shape, elems_per_block and launch_encrypt take a geometry
@@ -50,8 +51,9 @@ size_t chunk_words(int geo);  // words of one n^2 residue in the geometry's chun
 // kernel of one step of the fused path
 const void* kernel_encrypt_mfma(int cls, bool fused = false);
 size_t mfma_digit_bytes(int cls);
+const void* kernel_encrypt_team(int cls, int* threads);  // null: none for the class
 hipError_t launch_encrypt_mfma(int cls, const Launch& l, const PkConst& pk, const uint32_t* m,
-                               int m_limbs, const uint32_t* r, uint32_t* c, size_t count);
+                               int m_limbs, const uint32_t* r, uint32_t* c, size_t count, bool team);
 // persistent batch encryption over the matrix cores for jobs of key class
 // cls: queue reset, then grid workgroups (one wavefront each) pulling single
 // elements of the items (job.group elements of one job; sub >= every

@@ -343,6 +343,35 @@ __device__ __forceinline__ void mont_mul(MWork<G>& ws, const MConst& K, const ui
   wave_sync();
 }
 
+// Signed limbs u of a value of magnitude below 0.52 N -> the canonical residue's
+// 28-bit limbs, in place (one lane): the carries in one pass, and N once for a
+// negative value (a borrow out of the top limb).
+template <class G>
+__device__ __forceinline__ void canonical_limbs(uint32_t* u, const MConst& K) {
+  int32_t cy = 0;
+  for (int i = 0; i < G::S; ++i) {
+    const int32_t t = (int32_t)u[i] + cy;
+    u[i] = (uint32_t)t & M28;
+    cy = t >> 28;
+  }
+  if (cy >= 0) return;
+  uint32_t cr = 0;
+  for (int i = 0; i < G::S; ++i) {
+    const uint32_t t = u[i] + K.N28[i] + cr;
+    u[i] = t & M28;
+    cr = t >> 28;
+  }
+}
+// word j of canonical limbs
+template <class G>
+__device__ __forceinline__ uint32_t canonical_word(const uint32_t* u, int j) {
+  const int b = 32 * j, i = b / 28, s = b % 28;
+  const uint64_t acc = (uint64_t)(i < G::S ? u[i] : 0u) |
+                       ((uint64_t)(i + 1 < G::S ? u[i + 1] : 0u) << 28) |
+                       ((uint64_t)(i + 2 < G::S ? u[i + 2] : 0u) << 56);
+  return (uint32_t)(acc >> s);
+}
+
 // bits [28 i, 28 i + 28) of a little-endian uint32 array of n words
 __device__ __forceinline__ uint32_t limb28_of(const uint32_t* a, int n, int i) {
   const int b = 28 * i, w = b >> 5, s = b & 31;
