@@ -787,9 +787,8 @@ RnsPlan rns_plan(pc2_ctx* ctx, int T, int nmod, size_t count, int gather = -1) {
 // aligned parts)
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 size_t rns_encrypt_bytes(const RnsPlan& p) { return p.table_bytes + 2 * p.stage_bytes(); }
-size_t rns_decrypt_bytes(const RnsPlan& p, size_t chunk, int Ls, int nl2) {
-  return p.table_bytes + 2 * p.stage_bytes() + align256(chunk * 2 * (size_t)(nl2 + 1) * 4) +
-         align256(chunk * 2 * (size_t)(Ls + 1) * 4);
+size_t rns_decrypt_bytes(const RnsPlan& p, size_t chunk, int nl2) {
+  return p.table_bytes + 2 * p.stage_bytes() + align256(chunk * 2 * (size_t)(nl2 + 1) * 4);
 }
 size_t rns_smul_bytes(const RnsPlan& p, size_t chunk) {
   return p.table_bytes + p.stage_bytes() + align256(chunk * 4);
@@ -841,8 +840,8 @@ size_t class_scratch_need(pc2_ctx* ctx, int cls, int L, int Ls, int nl2) {
         const RnsPlan p = rns_plan_nb(ctx, T, 2, ch, nb, w);
         need = std::max(need, rns_encrypt_bytes(p) + 2 * align256(ch * 8 * (size_t)L));
         if (T <= tp) {
-          need = std::max(need, rns_decrypt_bytes(p, ch, Ls, nl2) + align256(ch * 8 * (size_t)L));
-          need = std::max(need, rns_decrypt_bytes(p, ch, Ls, nl2));
+          need = std::max(need, rns_decrypt_bytes(p, ch, nl2) + align256(ch * 8 * (size_t)L));
+          need = std::max(need, rns_decrypt_bytes(p, ch, nl2));
           need = std::max(need, rns_encrypt_sk_bytes(p, ch, nl2));
         }
       }
@@ -1012,7 +1011,6 @@ int rns_decrypt_run(pc2_ctx* ctx, const pc2_sk* sk, const pc2k::RnsJobs& J, cons
   uint8_t* in = base + p.table_bytes;
   uint32_t* ys = reinterpret_cast<uint32_t*>(in + 2 * p.stage_bytes());
   const size_t stride = nl2 + 1;
-  uint32_t* halves = ys + align256(J.npos * 2 * stride * 4) / 4;
   pc2k::RnsPow pw{};
   pw.table = base;
   pw.nmod = 2;
@@ -1031,7 +1029,7 @@ int rns_decrypt_run(pc2_ctx* ctx, const pc2_sk* sk, const pc2k::RnsJobs& J, cons
     e = pc2k::launch_rns_from(sk->dec[i].from, T, p.nb, pw.in[i], J, ys + i * stride, 2 * stride,
                               stream);
   if (e == hipSuccess)
-    e = pc2k::launch_rns_dec_finish(sk->c, J, ys, stride, halves, ctx->err, stream);
+    e = pc2k::launch_rns_dec_finish(sk->c, J, ys, stride, ctx->err, stream);
   return status_of(e);
 }
 
@@ -1088,7 +1086,7 @@ int rns_decrypt(const pc2_sk* sk, const uint32_t* c, uint32_t* m, size_t count, 
   const size_t chunk = std::min(count, pc2k::DEC_CHUNK), L = sk->pk.L;
   const RnsPlan p = rns_plan(ctx, sk->dec[0].T, 2, chunk);
   if (!ctx->scratch ||
-      rns_decrypt_bytes(p, chunk, sk->c.h[0].Ls, sk->c.h[0].s2.nl) > ctx->scratch_bytes)
+      rns_decrypt_bytes(p, chunk, sk->c.h[0].s2.nl) > ctx->scratch_bytes)
     return PC2_E_NOMEM;
   int rc = scratch_begin(ctx, stream);
   for (size_t b = 0; b < count && !rc; b += chunk)
@@ -1351,6 +1349,7 @@ int pc2_sk_create(pc2_ctx* ctx, uint32_t nbits, const uint32_t* p_limbs, const u
   Limbs phi = pc2h::mul(p, pc2h::sub(p, Limbs{1}));
   pc2h::trim(phi);
   Limbs q2inv = MP2.pow(pc2h::mod(q2, p2), pc2h::sub(phi, Limbs{1}));
+  size_t p2inv = buf.add(pc2h::inv_pow2(p2, nl2));
   size_t q2i = buf.add(pc2h::resized(pc2h::shl_mod(q2inv, (uint64_t)32 * nl2, p2), nl2));
   // the RNS engine modulo p^2 and q^2: decryption and key-holder encryption
   // (both primes on one tile count, or neither)
@@ -1391,6 +1390,7 @@ int pc2_sk_create(pc2_ctx* ctx, uint32_t nbits, const uint32_t* p_limbs, const u
   sk->c.h[1] = half_const(base, hq);
   sk->c.QI = base + qi;
   sk->c.Q2I = base + q2i;
+  sk->c.P2inv = base + p2inv;
   sk->c.p2_n0 = 0u - pc2h::inv32(p2[0]);
   sk->pk.rn = rns_const(base, rn, 2 * L);
   for (int i = 0; i < 2; ++i) {
@@ -1685,7 +1685,7 @@ int pc2_enc_sum_dec(const pc2_sk* sk, const uint32_t* const* m_k, const uint32_t
     const RnsPlan pe = rns_plan(ctx, sk->pk.rn.T, 1, chunk);
     const RnsPlan pd = rns_plan(ctx, sk->dec[0].T, 2, chunk);
     if (!ctx->scratch || 2 * cb + rns_encrypt_bytes(pe) > ctx->scratch_bytes ||
-        cb + rns_decrypt_bytes(pd, chunk, Ls, sk->c.h[0].s2.nl) > ctx->scratch_bytes)
+        cb + rns_decrypt_bytes(pd, chunk, sk->c.h[0].s2.nl) > ctx->scratch_bytes)
       return PC2_E_NOMEM;
     uint32_t* prod = ctx->scratch;
     uint8_t* rest = reinterpret_cast<uint8_t*>(ctx->scratch) + cb;
@@ -1818,7 +1818,7 @@ int few_elements_class(const pc2_ctx* ctx, int op, const pc2_job* jobs, const si
 }
 size_t rns_part_bytes(const RnsPart& p, int op) {
   return op == pc2k::OP_DEC
-             ? rns_decrypt_bytes(p.plan, p.jobs.npos, p.sk->c.h[0].Ls, p.sk->c.h[0].s2.nl)
+             ? rns_decrypt_bytes(p.plan, p.jobs.npos, p.sk->c.h[0].s2.nl)
              : rns_encrypt_bytes(p.plan);
 }
 int rns_part_run(pc2_ctx* ctx, const RnsPart& p, int op, uint8_t* scratch, void* stream) {
@@ -2303,7 +2303,7 @@ int pc2_runner_create(pc2_ctx* ctx, int op_abi, uint32_t max_nbits, size_t max_j
               rns_plan_nb(ctx, T, op == pc2k::OP_DEC ? 2 : 1, npos, nb, pc2k::SCHED_WMAX);
           r->rscratch_bytes = std::max(
               r->rscratch_bytes, op == pc2k::OP_DEC
-                                     ? rns_decrypt_bytes(p, npos, Ls, (p2bits + 31) / 32)
+                                     ? rns_decrypt_bytes(p, npos, (p2bits + 31) / 32)
                                      : rns_encrypt_bytes(p));
         }
       if (r->rscratch_bytes && hipMalloc(&r->rscratch, r->rscratch_bytes) != hipSuccess)

@@ -79,6 +79,7 @@ struct SkConst {
   HalfConst h[2];        // [0] = p, [1] = q
   const uint32_t* QI;    // q^-1 2^(32 Ls) mod p
   const uint32_t* Q2I;   // (q^2)^-1 2^(32 nl2) mod p^2 (nl2 = limbs of p^2)
+  const uint32_t* P2inv; // (p^2)^-1 mod 2^(32 nl2)
   uint32_t p2_n0;        // -(p^2)^-1 mod 2^32
   int ebits;             // max bit length of p-1, q-1
 };

@@ -20,9 +20,10 @@ hipError_t launch_rns_from(const RnsFrom& c, int T, int nb, const uint8_t* in,
 // checks to both halves' words okw[(2 position + half) stride]
 hipError_t launch_rns_enc_check(const PkConst& pk, const RnsJobs& jobs, uint32_t* okw,
                                 size_t stride, int* err, void* stream);
-// the scalar end of both decryption halves, then the recombinations
+// the end of a decryption (both halves' y to m), and the recombination of
+// key-holder encryption halves
 hipError_t launch_rns_dec_finish(const SkConst& sk, const RnsJobs& jobs, const uint32_t* ys,
-                                 size_t stride, uint32_t* halves, int* err, void* stream);
+                                 size_t stride, int* err, void* stream);
 hipError_t launch_rns_garner_crt(const SkConst& sk, const RnsJobs& jobs, const uint32_t* stage,
                                  int* err, void* stream);
 

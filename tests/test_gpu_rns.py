@@ -272,3 +272,33 @@ def test_batch_of_several_jobs(gpu_ctx, op):
         for j in jobs:
             j["out"].zero_()
     b.close()
+
+
+def _prime(bits, seed):
+    rng = random.Random(seed)
+    small = [p for p in range(3, 2000, 2) if all(p % d for d in range(3, int(p ** 0.5) + 1, 2))]
+    while True:
+        x = rng.getrandbits(bits) | 1 | (3 << (bits - 2))
+        if all(x % p for p in small) and pow(2, x - 1, x) == 1 and pow(3, x - 1, x) == 1:
+            return x
+
+
+# primes of unequal lengths: limbs of p past a wavefront's (33 and 65 words),
+# and a q^2 of fewer limbs than p^2
+@pytest.mark.parametrize("pbits,qbits", [(1034, 1014), (2068, 2028)])
+def test_unequal_primes(gpu_ctx, pbits, qbits):
+    from paper_2601_14980_amd import pc2
+    p, q = _prime(pbits, 1), _prime(qbits, 2)
+    n = p * q
+    opk, osk = O.derive_keys(p, q)
+    sk = pc2.SecretKey(gpu_ctx, n.bit_length(), p, q)
+    ms, rs = _ms_rs(n, 9, 5)
+    cs, st = gpu_encrypt(gpu_ctx, sk.public, ms, rs)
+    assert st == 0 and cs == [O.encrypt(opk, m, r) for m, r in zip(ms, rs)]
+    assert gpu_decrypt(gpu_ctx, sk, cs) == (ms, 0)
+    # not coprime to p: refused alike
+    bad = [cs[0], p * 3, q * q, cs[1]]
+    got = gpu_decrypt(gpu_ctx, sk, bad)
+    with _valu(gpu_ctx):
+        assert got == gpu_decrypt(gpu_ctx, sk, bad)
+    assert got[0][0] == ms[0] and got[0][1] == got[0][2] == 0
