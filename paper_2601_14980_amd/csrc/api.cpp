@@ -428,7 +428,7 @@ pc2k::PkConst pk_const_alt(const uint32_t* base, const PkOffsets& o, const pc2k:
 struct RnsOffsets {
   int T = 0;
   size_t E1, E2, c2, kb, ka;
-  struct To { size_t P, add, m; int nhalf; } x, gm, c;
+  struct To { size_t E = 0, cst = 0; int nchunk = 0; } x, gm, c;
   size_t one;
   struct From { size_t C, D, O, N28, F; int S, nblk; double ntop_inv; } from;
   size_t ops[5];
@@ -438,7 +438,7 @@ size_t add_aligned(DevBuf& buf, const std::vector<uint32_t>& w) {
   return buf.add(w);
 }
 RnsOffsets::To add_rns_to(DevBuf& buf, const pc2h::RnsToHost& h) {
-  return {add_aligned(buf, h.P), add_aligned(buf, h.add), add_aligned(buf, h.m), h.nhalf};
+  return {add_aligned(buf, h.E), add_aligned(buf, h.cst), h.nchunk};
 }
 // Powers x^e modulo N (N of `tiles`), x of nhalf 16-bit halves; f2 != null: a
 // second input 1 + m f2 (m of mhalf halves) closes the product, else the
@@ -493,8 +493,8 @@ RnsOffsets add_rns(DevBuf& buf, const Limbs& N, int T, const Limbs& e, int nhalf
   o.T = T;
   return o;
 }
-pc2k::RnsTo rns_to_const(const uint32_t* base, const RnsOffsets::To& t) {
-  return {base + t.P, base + t.add, base + t.m, t.nhalf};
+pc2k::RnsTo rns_to_const(const uint32_t* base, const RnsOffsets::To& t, const pc2k::RnsMod& M) {
+  return {(const uint8_t*)(base + t.E), (const int32_t*)(base + t.cst), M.kb, M.ka, t.nchunk};
 }
 pc2k::RnsKey rns_const(const uint32_t* base, const RnsOffsets& o, int nw) {
   pc2k::RnsKey k{};
@@ -502,10 +502,10 @@ pc2k::RnsKey rns_const(const uint32_t* base, const RnsOffsets& o, int nw) {
   k.T = o.T;
   k.M = {(const uint8_t*)(base + o.E1), (const uint8_t*)(base + o.E2),
          (const int32_t*)(base + o.c2), base + o.kb, base + o.ka};
-  k.x = rns_to_const(base, o.x);
-  if (o.gm.nhalf) k.gm = rns_to_const(base, o.gm);
-  if (o.c.nhalf) {
-    k.c = rns_to_const(base, o.c);
+  k.x = rns_to_const(base, o.x, k.M);
+  if (o.gm.nchunk) k.gm = rns_to_const(base, o.gm, k.M);
+  if (o.c.nchunk) {
+    k.c = rns_to_const(base, o.c, k.M);
     k.one = (const uint8_t*)(base + o.one);
   }
   k.from = {base + o.from.C, base + o.from.D, base + o.from.O, base + o.from.N28,

@@ -482,58 +482,97 @@ __device__ __forceinline__ bool find_job(const pc2k::RnsJobs& J, uint32_t pos, p
   return pos - j.pos0 < j.count;
 }
 
-// Residues of one wavefront's slot (part, tile, half: eight channels) for 64
-// positions, one per lane: sum_i half_i P[i] + add.  The constants are uniform
-// (scalar loads).
-__global__ __launch_bounds__(256) void k_rns_to(RnsTo C, pc2k::RnsJobs J, bool plain, int limbs,
+// Residues of both bases for 64 positions: the block's input bytes (less 128)
+// go to LDS as the matrix product's column operand, and its wavefronts share
+// the 2 T row tiles.  After 512 bytes a channel's sum is reduced, as 512 * 128 *
+// 24500 is what 32 bits hold.  As sums on the vector ALUs this took 250 us for
+// 10007 ciphertexts of 2048-bit keys and 2 x 700 us for the halves of 65536
+// decryptions, now 37 and 2 x 46.
+__global__ __launch_bounds__(512) void k_rns_to(RnsTo C, pc2k::RnsJobs J, bool plain, int limbs,
                                                 int T, int nb, uint8_t* __restrict__ out) {
+  extern __shared__ __align__(16) uint32_t lds[];
+  v4u* sb = reinterpret_cast<v4u*>(lds);  // [chunk][2 column blocks][64]
+  __shared__ int top;
   const int lane = threadIdx.x & 63;
-  const int slot = __builtin_amdgcn_readfirstlane(blockIdx.y * 4 + (threadIdx.x >> 6));
-  if (slot >= 4 * T) return;
-  const uint32_t pos = blockIdx.x * 64 + lane;
-  const uint32_t per = nb * 32;
-  if (pos >= (J.npos + per - 1) / per * per) return;
-  pc2k::RnsJob j;
-  size_t e;
-  const bool live = find_job(J, pos, j, e);
-  if (plain) limbs = j.m_limbs;
-  const int nhalf = !live ? 0 : 2 * limbs < C.nhalf ? 2 * limbs : C.nhalf;
-  const uint32_t* P = C.P + (size_t)slot * C.nhalf * 8;
-  const uint32_t* xe = (plain ? j.m : j.x) + e * limbs;
-  uint64_t acc[8];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t per = nb * 32, total = (J.npos + per - 1) / per * per;
+  int kc;
+  {
+    const int p = threadIdx.x >> 3;
+    const uint32_t pos = blockIdx.x * 64 + p;
+    pc2k::RnsJob j{};
+    size_t e = 0;
+    const bool live = pos < J.npos && find_job(J, pos, j, e);
+    if (plain) limbs = j.m_limbs;
+    const int words = live ? limbs : 0;
+    if (threadIdx.x == 0) top = 1;
+    __syncthreads();
+    if ((threadIdx.x & 7) == 0) atomicMax(&top, words);
+    __syncthreads();
+    kc = (top + 7) / 8;
+    if (kc > C.nchunk) kc = C.nchunk;
+    const uint32_t* xe = (plain ? j.m : j.x) + e * (size_t)limbs;
+    for (int q = threadIdx.x & 7; q < 2 * kc; q += 8) {
+      v4u v = {0u, 0u, 0u, 0u};
+      if (4 * q + 3 < words) {
+        __builtin_memcpy(&v, xe + 4 * q, 16);
+      } else {
 #pragma unroll
-  for (int c = 0; c < 8; ++c) acc[c] = C.add[slot * 8 + c];
-  // (uniform bound: lanes of shorter or no inputs add zeros)
-  const int top = plain ? C.nhalf : 2 * limbs < C.nhalf ? 2 * limbs : C.nhalf;
-  for (int i = 0; i < top; i += 2) {
-    if (plain && __ballot(i < nhalf) == 0) break;
-    const uint32_t w = i < nhalf ? xe[i >> 1] : 0u;
-    const uint32_t lo = w & 0xFFFFu, hi = w >> 16;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] += (uint64_t)lo * P[i * 8 + c];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] += (uint64_t)hi * P[i * 8 + 8 + c];
+        for (int i = 0; i < 4; ++i)
+          if (4 * q + i < words) v[i] = xe[4 * q + i];
+      }
+      sb[((q >> 1) * 2 + (p >> 5)) * 64 + (q & 1) * 32 + (p & 31)] = v ^ 0x80808080u;
+    }
   }
-  v4u o;
-  uint32_t r[8];
+  kc = __builtin_amdgcn_readfirstlane(kc);
+  __syncthreads();
+  const v4i* s = reinterpret_cast<const v4i*>(sb) + lane;
+  const int h = lane >> 5, n = lane & 31;
+  for (int tt = wave; tt < 2 * T; tt += 8) {
+    const bool part = tt >= T;
+    const int t = part ? tt - T : tt;
+    const v4i* E = reinterpret_cast<const v4i*>(C.E) + (size_t)tt * C.nchunk * 64 + lane;
+    const uint32_t* k = (part ? C.ka : C.kb) + (t * 2 + h) * 24;
+    const int32_t* cst = C.cst + ((size_t)kc * 2 * T + tt) * 16 + h * 8;
+    v16i acc[2];
+    uint32_t inv[8], negm[8];
 #pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    // acc < 2^42: the quotient by the modulus is exact to +-1 in double
-    const uint32_t m = C.m[slot * 8 + c];
-    const uint64_t q = (uint64_t)((double)acc[c] * (1.0 / (double)m));
-    int v = (int)(uint32_t)(acc[c] - q * m);  // in [-m, 2 m)
-    if (v < 0) v += (int)m;
-    if (v >= (int)m) v -= (int)m;
-    if (2 * v > (int)m) v -= (int)m;
-    r[c] = (uint32_t)v;
+    for (int u = 0; u < 8; ++u) {
+      inv[u] = k[u];
+      negm[u] = k[8 + u];
+      acc[0][2 * u] = acc[1][2 * u] = cst[u];
+      acc[0][2 * u + 1] = acc[1][2 * u + 1] = 0;
+    }
+    for (int c0 = 0; c0 < kc; c0 += 16) {
+      const int c1 = c0 + 16 < kc ? c0 + 16 : kc;
+#pragma unroll 4
+      for (int c = c0; c < c1; ++c) {
+        const v4i a = E[c * 64];
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+          acc[b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, s[(c * 2 + b) * 64], acc[b], 0, 0, 0);
+      }
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int w = (acc[b][2 * u + 1] << 8) + acc[b][2 * u];
+          acc[b][2 * u] = (int)(int16_t)reduce(w, inv[u], negm[u]);
+          acc[b][2 * u + 1] = 0;
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const uint32_t pos = blockIdx.x * 64 + b * 32;
+      if (pos >= total) break;
+      v4u o;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] = pack16((uint32_t)acc[b][4 * i], (uint32_t)acc[b][4 * i + 2]);
+      const uint32_t grp = pos / per, blk = pos % per / 32;
+      uint8_t* g = out + grp * pc2k::rns_group_bytes(T, nb);
+      reinterpret_cast<v4u*>(g)[((size_t)tt * nb + blk) * 64 + h * 32 + n] = o;
+    }
   }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) o[i] = pack16(r[2 * i], r[2 * i + 1]);
-  // slot = (part T + tile) 2 + half
-  const int h = slot & 1, pt = slot >> 1;
-  const uint32_t grp = pos / per, b = pos % per / 32, n = pos & 31;
-  uint8_t* g = out + grp * pc2k::rns_group_bytes(T, nb);
-  reinterpret_cast<v4u*>(g)[((size_t)pt * nb + b) * 64 + h * 32 + n] = o;
 }
 
 // The value of base-B residues mod N, canonical.  A block handles 64
@@ -851,7 +890,8 @@ hipError_t launch_rns_to(const RnsTo& c, int T, int nb, const RnsJobs& jobs, boo
                          int limbs, uint8_t* out, void* stream) {
   const uint32_t per = nb * 32;
   const uint32_t total = (jobs.npos + per - 1) / per * per;
-  hipLaunchKernelGGL(k_rns_to, dim3((total + 63) / 64, (unsigned)T), dim3(256), 0,
+  const int chunks = plain ? c.nchunk : std::min(c.nchunk, (limbs + 7) / 8);
+  hipLaunchKernelGGL(k_rns_to, dim3((total + 63) / 64), dim3(512), (size_t)chunks * 2048,
                      (hipStream_t)stream, c, jobs, plain, limbs, T, nb, out);
   return hipGetLastError();
 }

@@ -280,37 +280,57 @@ inline bool rns_e1(const RnsBase& R, const Limbs& N, std::vector<uint32_t>* frag
   return rns_pack(E, R.b, R.a, true, frag, cst);
 }
 
-// Input conversion by the constant f: rows 2^(16 i) f mod N (add: plus 1).
+// Input conversion by the constant f (RnsTo): V_(2 i) = 2^(16 i) f mod N for
+// each of nhalf 16-bit halves, V_(2 i + 1) = 256 V_(2 i), so that the value is
+// below 2^25 nhalf N; add_one: plus 1.
 struct RnsToHost {
-  std::vector<uint32_t> P, add, m;
-  int nhalf = 0;
+  std::vector<uint32_t> E, cst;
+  int nchunk = 0;
 };
 inline RnsToHost rns_to(const RnsBase& R, const Limbs& N0, const Limbs& f, int nhalf,
                         bool add_one) {
   RnsToHost o;
   Limbs N = N0;
   trim(N);
-  const int n = R.n, T = R.T;
-  o.nhalf = nhalf;
-  o.P.assign((size_t)4 * T * nhalf * 8, 0);
-  o.add.assign((size_t)4 * T * 8, 0);
-  o.m.assign((size_t)4 * T * 8, 0);
-  std::vector<uint32_t> m(2 * n), r(2 * n), Nm(2 * n);
-  for (int c = 0; c < 2 * n; ++c) m[c] = c < n ? R.b[c] : R.a[c - n];  // part 0: base B
-  const std::vector<Mod> Ms(m.begin(), m.end());
+  const int n = R.n, T = R.T, KC = o.nchunk = (nhalf + 15) / 16;
+  o.E.assign((size_t)2 * T * KC * 256, 0);
+  o.cst.assign((size_t)(KC + 1) * 2 * n, 0);
+  uint8_t* E = reinterpret_cast<uint8_t*>(o.E.data());
+  std::vector<uint32_t> r(2 * n), Nm(2 * n), sc(2 * n), x(2 * n);
+  std::vector<int64_t> sum(2 * n, 0);
+  std::vector<Mod> Ms;
+  for (int c = 0; c < 2 * n; ++c) Ms.emplace_back(c < n ? R.b[c] : R.a[c - n]);  // base B first
   Limbs v = mod(f, N);
-  v = resized(v, N.size());
   for (int c = 0; c < 2 * n; ++c) {
-    r[c] = mod_small(v, m[c]);
-    Nm[c] = mod_small(N, m[c]);
+    r[c] = mod_small(v, (uint32_t)Ms[c].m);
+    Nm[c] = mod_small(N, (uint32_t)Ms[c].m);
+    sc[c] = c < n ? R.s[c] : 1u;
   }
+  auto constants = [&](int chunks) {
+    for (int c = 0; c < 2 * n; ++c)
+      o.cst[(size_t)chunks * 2 * n + c] =
+          (uint32_t)Ms[c].centred(128 * sum[c] + (add_one ? (int64_t)sc[c] : 0));
+  };
+  constants(0);
   const size_t nl = N.size();
   const double Ntop = (double)N[nl - 1] * 4294967296.0 + (nl > 1 ? N[nl - 2] : 0);
   for (int i = 0; i < nhalf; ++i) {
+    for (int c = 0; c < 2 * n; ++c) x[c] = Ms[c]((int64_t)r[c] * sc[c]);
     for (int c = 0; c < 2 * n; ++c) {
-      const uint64_t sc = c < n ? R.s[c] : 1;
-      o.P[((size_t)(c / 8) * nhalf + i) * 8 + (c & 7)] = Ms[c]((int64_t)(r[c] * sc));
+      const int row = c >> 4, u = c & 7, H = (c >> 3) & 1;
+      for (int k = 0; k < 2; ++k) {
+        const int32_t e = Ms[c].centred((int64_t)x[c] << (8 * k));
+        const int32_t lo = (int32_t)(int8_t)(e & 255), hi = (e - lo) >> 8;
+        sum[c] += e;
+        const int at = 2 * i + k;  // input byte
+        for (int part = 0; part < 2; ++part) {
+          const int q = 2 * u + part, rho = 8 * (q >> 2) + 4 * H + (q & 3);
+          E[(((size_t)row * KC + at / 32) * 64 + 32 * ((at >> 4) & 1) + rho) * 16 + (at & 15)] =
+              (uint8_t)(part ? hi : lo);
+        }
+      }
     }
+    if (i % 16 == 15 || i + 1 == nhalf) constants(i / 16 + 1);
     if (i + 1 == nhalf) break;
     // v <- 2^16 v mod N, on the limbs and on the residues
     Limbs w(nl + 1, 0);
@@ -332,13 +352,7 @@ inline RnsToHost rns_to(const RnsBase& R, const Limbs& N0, const Limbs& f, int n
       w = sub(w, N);
     }
     v = resized(w, nl);
-    for (int c = 0; c < 2 * n; ++c) {
-      r[c] = Ms[c]((int64_t)r[c] * 65536 - q * (int64_t)Nm[c]);
-    }
-  }
-  for (int c = 0; c < 2 * n; ++c) {
-    o.m[c] = m[c];
-    if (add_one) o.add[c] = c < n ? R.s[c] : 1u;
+    for (int c = 0; c < 2 * n; ++c) r[c] = Ms[c]((int64_t)r[c] * 65536 - q * (int64_t)Nm[c]);
   }
   return o;
 }

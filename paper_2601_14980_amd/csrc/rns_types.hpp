@@ -18,13 +18,15 @@ struct RnsMod {
   const uint32_t* ka;   // [T][2][24]: 1/a_i (8 floats), -a_i (8), -MB pairs (8)
 };
 
-// Input conversion: sum_i half_i P[i] over the 16-bit halves of the input,
-// P[i] one residue per channel, plus a constant `add` per channel.
+// Input conversion: sum_i byte_i V_i + add over the input's bytes, V_i = 2^(8 i)
+// f, as a product of the matrix cores: E holds the V_i's channel residues, two
+// bytes each, as fragments of 32 rows (16 channels) by 32 input bytes; the
+// input bytes go in less 128, and cst has what that takes away, and add.
 struct RnsTo {
-  const uint32_t* P;    // [2 parts][T][2 halves][nhalf][8]
-  const uint32_t* add;  // [2 parts][T][2 halves][8]
-  const uint32_t* m;    // [2 parts][T][2 halves][8] channel moduli
-  int nhalf;            // halves of the longest input
+  const uint8_t* E;     // [2 parts][T][nchunk][64 lanes][16]
+  const int32_t* cst;   // [chunks used: 0 .. nchunk][2 parts][T][2 halves][8]
+  const uint32_t *kb, *ka;  // channel constants (RnsMod)
+  int nchunk;           // 32-byte chunks of the longest input
 };
 
 // Output conversion: the value mod N (canonical) from the residues mod b_j.
