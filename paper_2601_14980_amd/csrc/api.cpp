@@ -21,6 +21,7 @@ using pc2h::Limbs;
 struct RnsPlan {
   int T = 0, nb = 0, grid = 0, w = 0;
   size_t ngroups = 0, group_bytes = 0, table_bytes = 0;
+  double cost = 0;  // of a product, over all rounds of workgroups (rns_plan)
   size_t stage_bytes() const { return ngroups * group_bytes; }  // one input, one modulus
 };
 
@@ -49,6 +50,7 @@ struct RnsPart {
   const pc2_sk* sk = nullptr;  // decryption
   RnsPlan plan;
   pc2k::RnsJobs jobs{};
+  bool side = false;           // batches: runs beside the others
 };
 
 struct pc2_runner {
@@ -101,10 +103,13 @@ struct pc2_batch {
     int* queue = nullptr;
   } mp[2];
   uint8_t* mscratch = nullptr;
-  // jobs on the RNS engine, one part per key: its jobs, plan and scratch (one
-  // scratch for all parts, whose launches run in order on one stream)
+  // jobs on the RNS engine, one part per key: its jobs and plan.  The parts run
+  // one after another on the caller's stream (one scratch for all), or two of
+  // them side by side, the second on `side` (rns_parts_pair)
   std::vector<RnsPart> rparts;
-  uint8_t* rscratch = nullptr;
+  uint8_t *rscratch = nullptr, *rscratch2 = nullptr;
+  hipStream_t side = nullptr;
+  hipEvent_t forked = nullptr, joined = nullptr;
   hipGraphExec_t exec = nullptr;
   void* graph_stream = nullptr;
 };
@@ -762,7 +767,6 @@ RnsPlan rns_plan_nb(pc2_ctx* ctx, int T, int nmod, size_t count, int nb, int w, 
 RnsPlan rns_plan(pc2_ctx* ctx, int T, int nmod, size_t count, int gather = -1) {
   const int w = rns_window(ctx, T);
   RnsPlan best;
-  double best_cost = 0;
   for (int nb = 1; nb <= pc2k::RNS_NBMAX; ++nb) {
     const int slots = rns_slots(ctx, T, nb, gather);
     if (!slots) continue;
@@ -775,9 +779,9 @@ RnsPlan rns_plan(pc2_ctx* ctx, int T, int nmod, size_t count, int gather = -1) {
     const size_t full = items / slots, rest = (items % slots + ctx->cus - 1) / ctx->cus;
     const double cost = (double)full * (1.45 + (double)(occ * nb)) +
                         (rest ? 1.45 + (double)(rest * nb) : 0.0);
-    if (!best.T || cost < best_cost) {
+    if (!best.T || cost < best.cost) {
       best = p;
-      best_cost = cost;
+      best.cost = cost;
     }
   }
   return best;
@@ -1795,6 +1799,42 @@ std::vector<RnsPart> rns_parts(pc2_ctx* ctx, int op, const pc2_job* jobs, const 
   }
   return parts;
 }
+// Two parts that together have no more workgroups than there are compute units
+// run side by side, each on units of its own, with the column blocks per
+// workgroup that make the later of the two earliest: a part of few groups would
+// leave most of the device idle.  (A product's time goes with T, the products
+// with T.  6100 elements of a 2048-bit key and 8000 of a 1024-bit key, ms: one
+// after the other 15.7 + 4.5, beside each other with the plans of either
+// alone 18.6, with the second in 63 workgroups 15.9.)
+void rns_parts_pair(pc2_ctx* ctx, std::vector<RnsPart>& parts, int nmod) {
+  if (parts.size() != 2) return;
+  RnsPlan best[2];
+  double best_time = 0, serial = 0;
+  for (const RnsPart& p : parts) serial += p.plan.cost * p.plan.T * p.plan.T;
+  for (int n0 = 1; n0 <= pc2k::RNS_NBMAX; ++n0)
+    for (int n1 = 1; n1 <= pc2k::RNS_NBMAX; ++n1) {
+      const int nb[2] = {n0, n1};
+      RnsPlan p[2];
+      double time = 0;
+      size_t groups = 0;
+      for (int i = 0; i < 2; ++i) {
+        const int T = parts[i].plan.T;
+        if (!rns_slots(ctx, T, nb[i])) break;
+        p[i] = rns_plan_nb(ctx, T, nmod, parts[i].jobs.npos, nb[i], parts[i].plan.w);
+        groups += p[i].ngroups * nmod;
+        time = std::max(time, (1.45 + nb[i]) * T * T);
+      }
+      if (!p[1].T || groups > (size_t)ctx->cus) continue;
+      if (best_time == 0 || time < best_time) {
+        best_time = time;
+        best[0] = p[0];
+        best[1] = p[1];
+      }
+    }
+  if (best_time == 0 || best_time > 0.95 * serial) return;
+  for (int i = 0; i < 2; ++i) parts[i].plan = best[i];
+  parts[1].side = true;
+}
 void rns_parts_place(std::vector<RnsPart>& parts, const void* dev) {
   for (RnsPart& p : parts)
     p.jobs.many = reinterpret_cast<const pc2k::RnsJob*>((const char*)dev +
@@ -1839,6 +1879,20 @@ int occupancy_of(const void* k) {
       occ <= 0)
     occ = 1;
   return occ;
+}
+
+static void batch_free(pc2_batch* b) {
+  if (b->exec) (void)hipGraphExecDestroy(b->exec);
+  if (b->dev) (void)hipFree(b->dev);
+  if (b->scratch) (void)hipFree(b->scratch);
+  if (b->mscratch) (void)hipFree(b->mscratch);
+  if (b->rscratch) (void)hipFree(b->rscratch);
+  if (b->rscratch2) (void)hipFree(b->rscratch2);
+  if (b->stage) (void)hipFree(b->stage);
+  if (b->forked) (void)hipEventDestroy(b->forked);
+  if (b->joined) (void)hipEventDestroy(b->joined);
+  if (b->side) (void)hipStreamDestroy(b->side);
+  delete b;
 }
 
 int pc2_batch_create(pc2_ctx* ctx, const pc2_job* jobs, size_t njobs, pc2_batch** out) {
@@ -2037,9 +2091,21 @@ int pc2_batch_create(pc2_ctx* ctx, const pc2_job* jobs, size_t njobs, pc2_batch*
     mbytes = std::max(mbytes, (size_t)m.grid * (pc2k::mfma_digit_bytes(m.cls) << m.w));
   }
   if (!rc && mbytes && hipMalloc(&b->mscratch, mbytes) != hipSuccess) rc = PC2_E_NOMEM;
-  size_t rbytes = 0;
-  for (const RnsPart& p : b->rparts) rbytes = std::max(rbytes, rns_part_bytes(p, op));
-  if (!rc && rbytes && hipMalloc(&b->rscratch, rbytes) != hipSuccess) rc = PC2_E_NOMEM;
+  if (!rc && !b->rparts.empty()) {
+    rns_parts_pair(ctx, b->rparts, op == pc2k::OP_DEC ? 2 : 1);
+    size_t rbytes[2] = {0, 0};
+    for (const RnsPart& p : b->rparts)
+      rbytes[p.side] = std::max(rbytes[p.side], rns_part_bytes(p, op));
+    if (hipMalloc(&b->rscratch, rbytes[0]) != hipSuccess) rc = PC2_E_NOMEM;
+    if (!rc && rbytes[1]) {
+      if (hipMalloc(&b->rscratch2, rbytes[1]) != hipSuccess)
+        rc = PC2_E_NOMEM;
+      else if (hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking) != hipSuccess ||
+               hipEventCreateWithFlags(&b->forked, hipEventDisableTiming) != hipSuccess ||
+               hipEventCreateWithFlags(&b->joined, hipEventDisableTiming) != hipSuccess)
+        rc = PC2_E_DEVICE;
+    }
+  }
   if (!rc && b->nitems) {
     int occ = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, pc2k::batch_kernel(op, pair), 64, 0) !=
@@ -2057,12 +2123,7 @@ int pc2_batch_create(pc2_ctx* ctx, const pc2_job* jobs, size_t njobs, pc2_batch*
     if (bytes && hipMalloc(&b->scratch, bytes) != hipSuccess) rc = PC2_E_NOMEM;
   }
   if (rc) {
-    if (b->dev) (void)hipFree(b->dev);
-    if (b->scratch) (void)hipFree(b->scratch);
-    if (b->mscratch) (void)hipFree(b->mscratch);
-    if (b->rscratch) (void)hipFree(b->rscratch);
-    if (b->stage) (void)hipFree(b->stage);
-    delete b;
+    batch_free(b);
     return rc;
   }
   *out = b;
@@ -2074,7 +2135,11 @@ int pc2_batch_run(pc2_batch* b, void* hip_stream) {
   if (hipSetDevice(b->ctx->device) != hipSuccess) return PC2_E_DEVICE;
   auto launch = [&](void* st) {
     hipError_t e = hipSuccess;
-    if (b->nitems)
+    if (b->side) {
+      e = hipEventRecord(b->forked, (hipStream_t)st);
+      if (e == hipSuccess) e = hipStreamWaitEvent(b->side, b->forked, 0);
+    }
+    if (e == hipSuccess && b->nitems)
       e = pc2k::launch_batch(b->op, b->pair, b->grid, b->jobs, b->items, b->nitems, b->queue,
                              b->scratch, b->slot_words, b->w_a, b->w_b, b->ctx->err, st);
     for (const auto& m : b->mp)
@@ -2082,8 +2147,14 @@ int pc2_batch_run(pc2_batch* b, void* hip_stream) {
         e = pc2k::launch_batch_mfma(m.cls, m.grid, b->jobs, m.items, m.nitems, m.sub, m.queue,
                                     b->mscratch, m.w, b->ctx->err, st);
     for (const RnsPart& p : b->rparts)
-      if (e == hipSuccess && rns_part_run(b->ctx, p, b->op, b->rscratch, st) != PC2_OK)
+      if (e == hipSuccess && rns_part_run(b->ctx, p, b->op, p.side ? b->rscratch2 : b->rscratch,
+                                          p.side ? (void*)b->side : st) != PC2_OK)
         e = hipErrorLaunchFailure;
+    if (b->side) {  // joined whatever happened, as a capture ends with no open branch
+      const hipError_t j = hipEventRecord(b->joined, b->side);
+      const hipError_t w = hipStreamWaitEvent((hipStream_t)st, b->joined, 0);
+      if (e == hipSuccess) e = j != hipSuccess ? j : w;
+    }
     return e;
   };
   if (!hip_stream) return status_of(launch(nullptr));
@@ -2117,13 +2188,7 @@ int pc2_batch_destroy(pc2_batch* b) {
   if (!b || !b->ctx) return PC2_E_INVAL;
   (void)hipSetDevice(b->ctx->device);
   (void)hipDeviceSynchronize();
-  if (b->exec) (void)hipGraphExecDestroy(b->exec);
-  if (b->dev) (void)hipFree(b->dev);
-  if (b->scratch) (void)hipFree(b->scratch);
-  if (b->mscratch) (void)hipFree(b->mscratch);
-  if (b->rscratch) (void)hipFree(b->rscratch);
-  if (b->stage) (void)hipFree(b->stage);
-  delete b;
+  batch_free(b);
   return PC2_OK;
 }
 
