@@ -771,14 +771,14 @@ RnsPlan rns_plan(pc2_ctx* ctx, int T, int nmod, size_t count, int gather = -1) {
     const int slots = rns_slots(ctx, T, nb, gather);
     if (!slots) continue;
     RnsPlan p = rns_plan_nb(ctx, T, nmod, count, nb, w, gather);
-    // a round of w workgroups per CU measured 1.45 + w nb, in units of what a
-    // column block adds (2048-bit decryption halves, nb 1 / 2 / 4: 4.1 / 5.9 /
-    // 8.8 ms one per CU, nb 2 / 4: 9.4 / 15.6 ms two per CU; 2048-bit n^2, one
-    // per CU: 16.9 / 24.7 / 41.3 ms)
+    // a round of w workgroups per CU measured 1.2 + 0.3 w + w nb, in units of
+    // what a column block adds (2048-bit decryption halves, nb 1 / 2 / 4: 4.1 /
+    // 5.9 / 8.8 ms one per CU, nb 2 / 4: 9.4 / 15.6 ms two per CU; 2048-bit
+    // n^2, one per CU: 16.9 / 24.7 / 41.3 ms)
     const size_t items = p.ngroups * nmod, occ = (size_t)slots / ctx->cus;
     const size_t full = items / slots, rest = (items % slots + ctx->cus - 1) / ctx->cus;
-    const double cost = (double)full * (1.45 + (double)(occ * nb)) +
-                        (rest ? 1.45 + (double)(rest * nb) : 0.0);
+    auto round = [&](size_t w) { return w ? 1.2 + (double)w * (0.3 + nb) : 0.0; };
+    const double cost = (double)full * round(occ) + round(rest);
     if (!best.T || cost < best.cost) {
       best = p;
       best.cost = cost;

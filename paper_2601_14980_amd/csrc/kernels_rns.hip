@@ -834,9 +834,9 @@ template <int T, int NB>
 struct Pick;
 #define PC2_RNS_GEOS(D)                                                       \
   D(5, 1, 4, false) D(5, 2, 4, false) D(5, 4, 4, false)                       \
-  D(9, 1, 8, false) D(9, 2, 4, false) D(9, 4, 4, false)                       \
+  D(9, 1, 8, false) D(9, 2, 4, false) D(9, 3, 4, false) D(9, 4, 4, false)     \
   D(13, 1, 8, false) D(13, 2, 4, false)                                       \
-  D(17, 1, 8, true) D(17, 2, 8, true) D(17, 4, 8, true)                       \
+  D(17, 1, 8, true) D(17, 2, 8, true) D(17, 3, 8, true) D(17, 4, 8, true)     \
   D(26, 1, 8, true) D(26, 2, 8, true)                                         \
   D(34, 1, 8, true) D(34, 2, 8, true)
 #define PC2_RNS_PICK(T, NB, W, XY) \
