@@ -143,6 +143,26 @@ def roofline_mfma(nbits_n: int, mm: int, count: int, secs: float) -> dict:
             "mfma_per_product": mfma_per_product(2 * nbits_n)}
 
 
+# tiles of 16 channels per base of the residue-number-system engine, by bits of
+# n^2 (keys from 1024 bits; encryptions of thousands of elements)
+RNS_T = {2048: 9, 4096: 17, 6144: 26, 8192: 34}
+
+
+def roofline_rns(nbits_n: int, mm: int, count: int, secs: float) -> dict:
+    """Residue-number-system engine on the i8 matrix cores: the same
+    algorithmic work as roofline_mfma; issued: two base extensions per product,
+    T x T matrix instructions of 32 x 32 x 32 for 32 elements each."""
+    d = 2 * nbits_n // 8
+    per = 2 * RNS_T[2 * nbits_n] ** 2
+    ops = 2.0 * count * mm * 2 * d * d / secs
+    issued = 2.0 * count * mm * per * 32 * 32 * 32 / 32 / secs
+    return {"bound": "mfma", "unit": "TOP/s (int8, 2 per multiply-accumulate)",
+            "achieved": round(ops / 1e12, 1), "peak": round(2 * PEAK_I8_MACS / 1e12, 1),
+            "frac": round(ops / (2 * PEAK_I8_MACS), 4),
+            "issued_frac": round(issued / (2 * PEAK_I8_MACS), 4),
+            "mfma_per_product_of_32": per}
+
+
 # ------------------------------------------------------- measured HBM traffic
 # Per kernel: the committed FETCH_SIZE / WRITE_SIZE record and the sources
 # that define the kernel; a record counts only while they are unchanged
@@ -154,6 +174,8 @@ TRAFFIC = {
     "k_encrypt_mfma": ("k_encrypt_mfma_2048bit_traffic.json",
                        ["kernels_mfma.hip", "mfma_mont.hpp", "paillier_ops.hpp", "pc2_types.hpp",
                         "launch.hpp"]),
+    "k_rns_pow": ("k_rns_pow_2048bit_traffic.json",
+                  ["kernels_rns.hip", "rns_mont.hpp", "rns_types.hpp"]),
 }
 
 
@@ -664,7 +686,7 @@ def run_key4096(pc2, gen, ctx, torch, np, args) -> dict:
     mm_e, prod_e = montgomery_products_per_encrypt(nbits, sk.n, AUTO_WINDOW)
     mm_d, prod_d = montgomery_products_per_decrypt(p, q, AUTO_WINDOW)
     me, md = float(np.median(te)) / 1e3, float(np.median(td)) / 1e3
-    roof = (roofline_mfma(nbits, mm_e, count, me) if mfma
+    roof = (roofline_rns(nbits, mm_e - 2, count, me) if mfma
             else roofline_valu(prod_e * count, me))
     log(f"4096-bit: encrypt {count} in {me * 1e3:.1f} ms ({'mfma' if mfma else 'valu'} engine), "
         f"decrypt in {md * 1e3:.1f} ms, round trip exact {ok}")
@@ -828,7 +850,7 @@ def run_admm(pc2, gen, ctx, torch, np, args, engines) -> dict:
         mt = float(np.median(times))
         enc_s = float(np.median(enc_ms)) / 1e3
         mm, prod = montgomery_products_per_encrypt(ADMM_BITS, p * q, AUTO_WINDOW)
-        roof = (roofline_mfma(ADMM_BITS, mm, K * N, enc_s) if engine == "mfma"
+        roof = (roofline_rns(ADMM_BITS, mm - 2, K * N, enc_s) if engine == "mfma"
                 else roofline_valu(K * N * prod, enc_s))
         roof["mm_per_encrypt"] = mm
         out[engine] = {"iterations_timed": len(times), "ms_per_iteration": round(mt * 1e3, 1),
@@ -1112,16 +1134,19 @@ def main() -> int:
     enc_avg_s = sum(enc_ms) / len(enc_ms) / 1e3
 
     def engine_roofline(engine, secs):
+        mm = mm_enc
         if engine == "mfma":
-            r = {"kernel": f"k_encrypt_mfma<{MFMA_S[2 * NBITS]}>",
-                 **roofline_mfma(NBITS, mm_enc, total, secs),
-                 "traffic": measured_traffic("k_encrypt_mfma", total),
-                 "per_launch_macs": total * mm_enc * 2 * (NBITS // 4) ** 2}
+            # (the powering itself; the two products before it are conversions)
+            mm = mm_enc - 2
+            r = {"kernel": f"k_rns_pow<{RNS_T[2 * NBITS]}, 4>",
+                 **roofline_rns(NBITS, mm, total, secs),
+                 "traffic": measured_traffic("k_rns_pow", total),
+                 "per_launch_macs": total * mm * 2 * (NBITS // 4) ** 2}
         else:
             r = {"kernel": "k_encrypt", **roofline_valu(prod_enc * total, secs),
                  "traffic": measured_traffic("k_encrypt", total),
                  "per_launch_products": prod_enc * total}
-        r.update({"mm_per_encrypt": mm_enc, "avg_launch_ms": round(secs * 1e3, 3)})
+        r.update({"mm_per_encrypt": mm, "avg_launch_ms": round(secs * 1e3, 3)})
         return r
 
     roofline = engine_roofline(main_engine, enc_avg_s)
@@ -1154,12 +1179,11 @@ def main() -> int:
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        # encryption (most of a step) multiplies 7-bit digits as i8 on the
-        # matrix cores with i32 accumulation, or 32-bit limbs on the VALU;
-        # decryption always runs on 32-bit limbs
+        # encryption and decryption multiply the bytes of 16-bit residues as i8
+        # on the matrix cores with i32 accumulation, or 32-bit limbs on the VALU
         "dtype": "i8" if main_engine == "mfma" else "u32",
-        "dtypes": {"encrypt": "i8 x i8 -> i32" if main_engine == "mfma" else "u32 x u32 -> u64",
-                   "decrypt": "u32 x u32 -> u64"},
+        "dtypes": {op: "i8 x i8 -> i32" if main_engine == "mfma" else "u32 x u32 -> u64"
+                   for op in ("encrypt", "decrypt")},
         "data": "synthetic",
         "config": {"workload": "2048-bit key, 8 nodes x 65536 float64 ~ N(0,1), scale 2^20, "
                                "offset 2^23: quantize, encrypt 524288, 8-way sum, decrypt 65536, "

@@ -103,18 +103,24 @@ int pc2_ctx_reserve(pc2_ctx *ctx, uint32_t max_nbits);
 
 /* Options.  PC2_OPT_WINDOW: window width w in {0 (auto), 2..6} of the
  * modular exponentiations (sliding windows over the key's exponents n,
- * p - 1, q - 1; fixed windows over per-element exponents).
- * PC2_OPT_MODMUL: limb-product engine for the Montgomery products of
- * public-key encryption (pc2_encrypt, pc2_enc_sum_dec, and the encryption
- * jobs of batches and runners): PC2_MODMUL_VALU (27/28-bit digits, one
- * v_mad_u64_u32 per limb product), PC2_MODMUL_MFMA (7-bit digits in signed
- * redundant 28-bit limbs, the three limb-product matrices of each product on
- * the i8 matrix cores with int32 accumulation, one carry split per column on
- * the vector ALUs) or PC2_MODMUL_AUTO (the default: the MFMA engine for
- * keys of 2048 bits and more, where it is the faster one on the MI355X, the
- * VALU engine otherwise).  All give identical results; the other operations
- * always use the VALU engine.  A batch or runner launch holds encryption
- * jobs of at most two key classes per engine.
+ * p - 1, q - 1; fixed windows over the VALU engine's per-element exponents).
+ * PC2_OPT_MODMUL: the engine of the modular products.  Three exist:
+ *   VALU         27/28-bit digits, one v_mad_u64_u32 per limb product;
+ *   per element  7-bit digits in signed redundant 28-bit limbs, the three
+ *                limb-product matrices of each product on the i8 matrix cores,
+ *                a wavefront (few elements: several) per ciphertext;
+ *   residues     a residue number system of 16-bit primes, two base extensions
+ *                per product on the i8 matrix cores with constant matrices
+ *                shared by 32 ciphertexts and more (keys from 1024 bits).
+ * PC2_MODMUL_VALU: the VALU engine everywhere.  PC2_MODMUL_MFMA: public-key
+ * encryptions on the matrix cores (per element below some thousands of
+ * elements and below 1024 bits, else residues).  PC2_MODMUL_AUTO (the default):
+ * whichever of the three is the fastest for the key's size and the call's
+ * count.  With MFMA and AUTO, decryption, key-holder encryption, scalar
+ * products and mat-vec plans under keys from 1024 bits run on residues, and
+ * sums on the VALU.  All engines give identical results.  A batch or runner
+ * launch holds encryption jobs of at most two key classes per engine; its jobs
+ * on residues run as one launch sequence per key.
  * PC2_OPT_TILE: the limb tile of the VALU encryption kernels (pc2_encrypt,
  * batches and runners of encryptions), i.e. how many lanes of a wavefront
  * share one ciphertext.  1024-bit keys run with 2 (own) or 4 lanes,
@@ -257,7 +263,11 @@ int pc2_enc_sum_dec(const pc2_sk *sk, const uint32_t *const *m_k, const uint32_t
  * (c_j^(2^(w t)))^d for d = 1 .. 2^w - 1 in Montgomery form, so that a row
  * costs one modular product per nonzero w-bit digit of its constants and no
  * squarings; the tables take cols * ceil(ebits / w) * (2^w - 1) entries of
- * the n^2 digit layout (640 B at 2048 bits).
+ * the n^2 digit layout (640 B at 2048 bits).  A plan whose products run on
+ * residues (PC2_OPT_MODMUL at its creation, keys from 1024 bits) chooses a
+ * digit width of its own, of the least time among those whose tables (2^w
+ * entries of 1088 B at 2048 bits) take no more than that or 128 MB, and holds
+ * staging for the rows beside them.
  *
  * pc2_matvec_create: cols >= 1; ebits in 1..64 bounds the constants
  * (B_ij < 2^ebits); window w in 1..12, or 0 = automatic: the w minimising
@@ -274,7 +284,8 @@ int pc2_enc_sum_dec(const pc2_sk *sk, const uint32_t *const *m_k, const uint32_t
  *   B_ij >= 2^ebits or alpha_i >= n^2 is written as zero with PC2_E_RANGE
  *   latched; rows that use a zeroed column come out zero.  Staging for
  *   partial products (rows split over column chunks to fill the device) is
- *   allocated on the first call that needs more than the plan holds.
+ *   allocated with the plan; more rows than it holds run in several passes, or
+ *   in fewer chunks.
  * The plan's device memory is owned by the plan; the caller owns c, B, alpha,
  * out.  A plan is used from one host thread at a time. */
 typedef struct pc2_matvec pc2_matvec;

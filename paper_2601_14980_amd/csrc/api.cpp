@@ -630,10 +630,10 @@ int window_for(const pc2_ctx* ctx, int geo, int op) {
   return t ? t : auto_window(geo, op);
 }
 
-// The Montgomery engine of an encryption (pc2_encrypt, pc2_enc_sum_dec)
-// under a key of class cls: the matrix cores when asked for, or
-// automatically from 2048-bit keys (class 6) on, where they measured faster
-// than the VALU engine on the MI355X.
+// Whether an encryption under a key of class cls that the RNS engine does not
+// take (enc_engine) runs on the matrix cores, a wavefront per element, also when
+// it fills the device: when asked for, or automatically from 2048-bit keys
+// (class 6) on, where that measured faster than the VALU engine.
 constexpr int MFMA_AUTO_CLASS = 6;
 bool use_mfma(const pc2_ctx* ctx, int cls) {
   return ctx->modmul == PC2_MODMUL_MFMA ||

@@ -1,14 +1,17 @@
 // Powering kernels of the RNS engine (rns_mont.hpp) and its conversions.
 //
-//   k_rns_to    integers (32-bit limbs) -> residues of both bases, in
-//               Montgomery form (times MA) or times another constant
-//   k_rns_pow   runs a program of Montgomery products over groups of 32 NB
-//               elements, one group at a time per workgroup: the table of
-//               odd powers, sliding windows, the closing product
-//   k_rns_from  residues of base B -> the canonical integer mod N
-//
-// Both conversions are plain sums over constants on the vector ALUs (together
-// a few products' worth of a powering of thousands).
+//   k_rns_to      integers (32-bit limbs) -> residues of both bases, times a
+//                 constant (a matrix product of the input's bytes)
+//   k_rns_pow     runs a program of Montgomery products over groups of 32 NB
+//                 elements, one group at a time per workgroup: the table of
+//                 odd powers, sliding windows, the closing product
+//   k_rns_smul    powers with a 64-bit exponent per element
+//   k_rns_mvtab, k_rns_mv, k_rns_chain  fixed-base tables, rows and the join of
+//                 column chunks of the ciphertext matrix-vector product
+//   k_rns_from    residues of base B -> the canonical integer mod N (sums on the
+//                 vector ALUs: 0.1 ms, its carries one wavefront's serial chain)
+//   k_rns_dec_finish, k_rns_garner_crt  the ends of decryption and of key-holder
+//                 encryption
 #include <hip/hip_runtime.h>
 
 #include "bn_scalar.hpp"

@@ -282,7 +282,7 @@ inline bool rns_e1(const RnsBase& R, const Limbs& N, std::vector<uint32_t>* frag
 
 // Input conversion by the constant f (RnsTo): V_(2 i) = 2^(16 i) f mod N for
 // each of nhalf 16-bit halves, V_(2 i + 1) = 256 V_(2 i), so that the value is
-// below 2^25 nhalf N; add_one: plus 1.
+// below 2^16 nhalf N; add_one: plus 1.
 struct RnsToHost {
   std::vector<uint32_t> E, cst;
   int nchunk = 0;
