@@ -266,8 +266,8 @@ int pc2_enc_sum_dec(const pc2_sk *sk, const uint32_t *const *m_k, const uint32_t
  * the n^2 digit layout (640 B at 2048 bits).  A plan whose products run on
  * residues (PC2_OPT_MODMUL at its creation, keys from 1024 bits) chooses a
  * digit width of its own, of the least time among those whose tables (2^w
- * entries of 1088 B at 2048 bits) take no more than that or 128 MB, and holds
- * staging for the rows beside them.
+ * entries of 1088 B at 2048 bits) take no more than that and a sixteenth, or
+ * 128 MB, and holds staging for the rows beside them.
  *
  * pc2_matvec_create: cols >= 1; ebits in 1..64 bounds the constants
  * (B_ij < 2^ebits); window w in 1..12, or 0 = automatic: the w minimising

@@ -2679,8 +2679,9 @@ RnsMvShape rns_mv_shape(pc2_ctx* ctx, int T, size_t cols, int nw, size_t rows, s
 }
 
 // The RNS engine for a plan: the digit width of the least time among those
-// whose tables take no more than the plan's table bytes or 128 MB; false if
-// there is none or the device has no memory for it.  It is the faster one from a single
+// whose tables take no more than the plan's table bytes and a sixteenth (which
+// lets 9-bit digits stand for 10-bit ones) or 128 MB; false if there is none or
+// the device has no memory for it.  It is the faster one from a single
 // row up (load / apply in ms, RNS against VALU, ebits 50: 1024 bits, 64 rows x
 // 16 columns 0.18 / 0.16 against 1.03 / 2.1; 4096 bits, 64 x 16: 1.2 / 1.05
 // against 4.1 / 1.4; 2048 bits, 256 x 256: 0.42 / 1.4 against 2.2 / 4.8).
@@ -2700,7 +2701,7 @@ bool rns_matvec_create(pc2_matvec* mv, size_t rows_hint) {
   double best = 0;
   for (int w = 1; w <= 12; ++w) {
     const size_t nw = (size_t)((mv->ebits + w - 1) / w);
-    if (table(w) > std::max(mv->table_bytes, (size_t)128 << 20)) break;
+    if (table(w) > std::max(mv->table_bytes + mv->table_bytes / 16, (size_t)128 << 20)) break;
     const double cost =
         rns_mv_shape(ctx, T, mv->cols, (int)nw, rows, most).cost +
         2.45 * (double)((Gc * nw + tslots - 1) / tslots) *
