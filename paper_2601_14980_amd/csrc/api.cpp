@@ -20,6 +20,7 @@ using pc2h::Limbs;
 // Launch shape of k_rns_pow for one call (rns_plan).
 struct RnsPlan {
   int T = 0, nb = 0, grid = 0, w = 0;
+  bool wide = false;
   size_t ngroups = 0, group_bytes = 0, table_bytes = 0;
   double cost = 0;  // of a product, over all rounds of workgroups (rns_plan)
   size_t stage_bytes() const { return ngroups * group_bytes; }  // one input, one modulus
@@ -40,7 +41,7 @@ struct pc2_ctx {
   int occ[pc2k::NUM_GEOS][pc2k::OP_COUNT] = {};    // workgroups per CU (0 = not queried)
   int tuned[pc2k::NUM_GEOS][pc2k::OP_COUNT] = {};  // autotuned windows (0 = none)
   int tuned_geo[pc2k::NUM_CLASSES] = {-1, -1, -1, -1, -1, -1, -1, -1, -1};  // encryption tile
-  int rocc[pc2k::RNS_NT][pc2k::RNS_NBMAX + 1] = {};  // RNS powering: workgroups per CU
+  int rocc[2][pc2k::RNS_NT][pc2k::RNS_NBMAX + 1] = {};  // RNS powering (wide): workgroups per CU
   int gocc[pc2k::RNS_NGATHER][pc2k::RNS_NT][pc2k::RNS_NBMAX + 1] = {};  // and the gather kernels'
 };
 
@@ -732,14 +733,16 @@ int rns_index(int T) {
 }
 // resident workgroups of k_rns_pow<T, nb>, or of a kernel with a multiplier per
 // element (0: not compiled)
-int rns_slots(pc2_ctx* ctx, int T, int nb, int gather = -1) {
-  int& o = gather < 0 ? ctx->rocc[rns_index(T)][nb] : ctx->gocc[gather][rns_index(T)][nb];
+int rns_slots(pc2_ctx* ctx, int T, int nb, int gather = -1, bool wide = false) {
+  int& o =
+      gather < 0 ? ctx->rocc[wide][rns_index(T)][nb] : ctx->gocc[gather][rns_index(T)][nb];
   if (o == 0) {
-    const void* k = gather < 0 ? pc2k::rns_pow_kernel(T, nb) : pc2k::rns_gather_kernel(T, nb, gather);
+    const void* k =
+        gather < 0 ? pc2k::rns_pow_kernel(T, nb, wide) : pc2k::rns_gather_kernel(T, nb, gather);
     int v = 0;
     if (!k)
       o = -1;
-    else if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k, pc2k::rns_pow_threads(T, nb),
+    else if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k, pc2k::rns_pow_threads(T, nb, wide),
                                                           0) != hipSuccess || v <= 0)
       o = 1;
     else
@@ -752,37 +755,45 @@ int rns_window(const pc2_ctx* ctx, int T) { return ctx->window ? ctx->window : (
 
 // Column blocks per workgroup for `count` elements of nmod moduli: the least
 // time by rounds of resident workgroups.
-RnsPlan rns_plan_nb(pc2_ctx* ctx, int T, int nmod, size_t count, int nb, int w, int gather = -1) {
+RnsPlan rns_plan_nb(pc2_ctx* ctx, int T, int nmod, size_t count, int nb, int w, int gather = -1,
+                    bool wide = false) {
   RnsPlan p;
   p.T = T;
   p.nb = nb;
+  p.wide = wide;
   p.w = w;
   p.ngroups = (count + 32 * nb - 1) / (32 * nb);
   p.group_bytes = pc2k::rns_group_bytes(T, nb);
-  p.grid = (int)std::min<size_t>(p.ngroups * nmod, (size_t)rns_slots(ctx, T, nb, gather));
+  p.grid = (int)std::min<size_t>(p.ngroups * nmod, (size_t)rns_slots(ctx, T, nb, gather, wide));
   const size_t entries = gather < 0 ? (size_t)1 << (w - 1) : 16;
   p.table_bytes = (size_t)p.grid * entries * p.group_bytes;
   return p;
 }
+// Time of a product of w workgroups of nb column blocks per CU, in units of what
+// a column block adds.  As two sides (T >= 17, wide): 1.1 + nb, one a CU
+// (2048-bit n^2, nb 1 .. 4: 16.9 / 24.7 / 33.5 / 41.3 ms; 2048-bit decryption
+// halves, wide, nb 2 / 3 / 4: 5.5 / 7.1 / 8.9 ms).  Else 1.2 + w (0.3 + nb)
+// (decryption halves, nb 1 .. 4: 4.1 / 5.9 / 7.5 / 9.2 ms one a CU, nb 2 / 4: 9.4 /
+// 15.6 ms two a CU).
+double rns_round(int T, int nb, bool wide, size_t w) {
+  if (w == 0) return 0.0;
+  return T >= 17 || wide ? (double)w * (1.1 + nb) : 1.2 + (double)w * (0.3 + nb);
+}
+
 RnsPlan rns_plan(pc2_ctx* ctx, int T, int nmod, size_t count, int gather = -1) {
   const int w = rns_window(ctx, T);
   RnsPlan best;
-  for (int nb = 1; nb <= pc2k::RNS_NBMAX; ++nb) {
-    const int slots = rns_slots(ctx, T, nb, gather);
+  for (int k = 2; k <= 2 * pc2k::RNS_NBMAX + 1; ++k) {
+    const int nb = k / 2;
+    const bool wide = k & 1;
+    if (wide && gather >= 0) continue;
+    const int slots = rns_slots(ctx, T, nb, gather, wide);
     if (!slots) continue;
-    RnsPlan p = rns_plan_nb(ctx, T, nmod, count, nb, w, gather);
-    // a round of w workgroups per CU measured 1.2 + 0.3 w + w nb, in units of
-    // what a column block adds (2048-bit decryption halves, nb 1 / 2 / 4: 4.1 /
-    // 5.9 / 8.8 ms one per CU, nb 2 / 4: 9.4 / 15.6 ms two per CU; 2048-bit
-    // n^2, one per CU: 16.9 / 24.7 / 41.3 ms)
+    RnsPlan p = rns_plan_nb(ctx, T, nmod, count, nb, w, gather, wide);
     const size_t items = p.ngroups * nmod, occ = (size_t)slots / ctx->cus;
     const size_t full = items / slots, rest = (items % slots + ctx->cus - 1) / ctx->cus;
-    auto round = [&](size_t w) { return w ? 1.2 + (double)w * (0.3 + nb) : 0.0; };
-    const double cost = (double)full * round(occ) + round(rest);
-    if (!best.T || cost < best.cost) {
-      best = p;
-      best.cost = cost;
-    }
+    p.cost = (double)full * rns_round(T, nb, wide, occ) + rns_round(T, nb, wide, rest);
+    if (!best.T || p.cost < best.cost) best = p;
   }
   return best;
 }
@@ -837,6 +848,7 @@ size_t class_scratch_need(pc2_ctx* ctx, int cls, int L, int Ls, int nl2) {
     for (int T : pc2k::RNS_T)
       for (int nb = 1; nb <= pc2k::RNS_NBMAX; ++nb) {
         if (T > tn || !rns_slots(ctx, T, nb)) continue;
+        (void)rns_slots(ctx, T, nb, -1, true);
         for (int g = 0; g < pc2k::RNS_NGATHER; ++g) (void)rns_slots(ctx, T, nb, g);
         if (rns_slots(ctx, T, nb, pc2k::RNS_SMUL))
           need = std::max(need,
@@ -964,7 +976,7 @@ int rns_encrypt_run(pc2_ctx* ctx, const pc2_pk* pk, const pc2k::RnsJobs& J, cons
   hipError_t e = pc2k::launch_rns_to(K.x, K.T, p.nb, J, false, pk->L, pw.in[0], stream);
   if (e == hipSuccess) e = pc2k::launch_rns_to(K.gm, K.T, p.nb, J, true, 0, pw.gm[0], stream);
   if (e == hipSuccess)
-    e = pc2k::launch_rns_pow(K.T, p.nb, std::min(p.grid, pw.ngroups), pw, stream);
+    e = pc2k::launch_rns_pow(K.T, p.nb, p.wide, std::min(p.grid, pw.ngroups), pw, stream);
   if (e == hipSuccess)
     e = pc2k::launch_rns_from(K.from, K.T, p.nb, pw.in[0], J, nullptr, 0, stream);
   if (e == hipSuccess)
@@ -1028,7 +1040,7 @@ int rns_decrypt_run(pc2_ctx* ctx, const pc2_sk* sk, const pc2k::RnsJobs& J, cons
     e = pc2k::launch_rns_to(sk->dec[i].x, T, p.nb, J, false, 2 * sk->pk.L, pw.in[i], stream);
   }
   if (e == hipSuccess)
-    e = pc2k::launch_rns_pow(T, p.nb, std::min(p.grid, 2 * pw.ngroups), pw, stream);
+    e = pc2k::launch_rns_pow(T, p.nb, p.wide, std::min(p.grid, 2 * pw.ngroups), pw, stream);
   for (int i = 0; i < 2 && e == hipSuccess; ++i)
     e = pc2k::launch_rns_from(sk->dec[i].from, T, p.nb, pw.in[i], J, ys + i * stride, 2 * stride,
                               stream);
@@ -1059,7 +1071,7 @@ int rns_encrypt_sk_run(pc2_ctx* ctx, const pc2_sk* sk, const pc2k::RnsJobs& J, c
       e = pc2k::launch_rns_to(sk->enc[i].gm, T, p.nb, J, true, 0, pw.gm[i], stream);
   }
   if (e == hipSuccess)
-    e = pc2k::launch_rns_pow(T, p.nb, std::min(p.grid, 2 * pw.ngroups), pw, stream);
+    e = pc2k::launch_rns_pow(T, p.nb, p.wide, std::min(p.grid, 2 * pw.ngroups), pw, stream);
   for (int i = 0; i < 2 && e == hipSuccess; ++i)
     e = pc2k::launch_rns_from(sk->enc[i].from, T, p.nb, pw.in[i], J, stage + i * stride,
                               2 * stride, stream);
@@ -1820,9 +1832,10 @@ void rns_parts_pair(pc2_ctx* ctx, std::vector<RnsPart>& parts, int nmod) {
       for (int i = 0; i < 2; ++i) {
         const int T = parts[i].plan.T;
         if (!rns_slots(ctx, T, nb[i])) break;
-        p[i] = rns_plan_nb(ctx, T, nmod, parts[i].jobs.npos, nb[i], parts[i].plan.w);
+        const bool wide = rns_slots(ctx, T, nb[i], -1, true) > 0;
+        p[i] = rns_plan_nb(ctx, T, nmod, parts[i].jobs.npos, nb[i], parts[i].plan.w, -1, wide);
         groups += p[i].ngroups * nmod;
-        time = std::max(time, (1.45 + nb[i]) * T * T);
+        time = std::max(time, rns_round(T, nb[i], wide, 1) * T * T);
       }
       if (!p[1].T || groups > (size_t)ctx->cus) continue;
       if (best_time == 0 || time < best_time) {
@@ -2654,8 +2667,8 @@ void pick_chunks(const pc2_matvec* mv, size_t rows, size_t max_chunks, size_t* n
 namespace {
 // Column blocks per row group (nb) and column chunks of `rows` rows on the RNS
 // engine, their running values at most `blocks` blocks of 32: the least time
-// by rounds of resident workgroups (a product measured 1.45 + nb, see
-// rns_plan), plus the products that join the chunks.
+// by rounds of resident workgroups (a product measured 1.45 + nb, as its
+// multipliers come from HBM; else see rns_round), plus the products that join the chunks.
 struct RnsMvShape {
   int nb = 0;
   size_t groups = 0, nch = 0, chunk_cols = 0;

@@ -831,10 +831,11 @@ __global__ __launch_bounds__(64) void k_rns_garner_crt(pc2k::SkConst sk, pc2k::R
 
 namespace pc2k {
 
-namespace {
-// (T, NB) -> geometry: wavefronts, and whether they run as two sides.
-template <int T, int NB>
-struct Pick;
+// The geometries (T, NB, wavefronts, two sides), one per T and NB, and the wide
+// ones beside them for T = 9: eight wavefronts as two sides finish a group
+// sooner, four alone leave room for a second workgroup on the unit (65536
+// decryptions of 2048 bits: 35.9 ms wide, 32.7; 8192: 5.5 wide, 6.0; 10000:
+// 6.4 wide, 7.4; rns_plan chooses).
 #define PC2_RNS_GEOS(D)                                                       \
   D(5, 1, 4, false) D(5, 2, 4, false) D(5, 4, 4, false)                       \
   D(9, 1, 8, false) D(9, 2, 4, false) D(9, 3, 4, false) D(9, 4, 4, false)     \
@@ -842,30 +843,25 @@ struct Pick;
   D(17, 1, 8, true) D(17, 2, 8, true) D(17, 3, 8, true) D(17, 4, 8, true)     \
   D(26, 1, 8, true) D(26, 2, 8, true)                                         \
   D(34, 1, 8, true) D(34, 2, 8, true)
-#define PC2_RNS_PICK(T, NB, W, XY) \
-  template <>                      \
-  struct Pick<T, NB> {             \
-    using G = RGeo<T, NB, W, XY>;  \
-  };
-PC2_RNS_GEOS(PC2_RNS_PICK)
-#undef PC2_RNS_PICK
-}  // namespace
-
-#define PC2_RNS_CASE(T, NB, W, XY) \
-  if (t == T && nb == NB) {        \
-    using G = Pick<T, NB>::G;      \
-    PC2_RNS_DO;                    \
+#define PC2_RNS_WIDE_GEOS(D) D(9, 2, 8, true) D(9, 3, 8, true) D(9, 4, 8, true)
+#define PC2_RNS_CASE(T, NB, W, XY)  \
+  if (t == T && nb == NB) {         \
+    using G = RGeo<T, NB, W, XY>;   \
+    PC2_RNS_DO;                     \
   }
 
-const void* rns_pow_kernel(int t, int nb) {
+const void* rns_pow_kernel(int t, int nb, bool wide) {
 #define PC2_RNS_DO return (const void*)&k_rns_pow<G>
-  PC2_RNS_GEOS(PC2_RNS_CASE)
+  if (wide) {
+    PC2_RNS_WIDE_GEOS(PC2_RNS_CASE)
+  } else {
+    PC2_RNS_GEOS(PC2_RNS_CASE)
+  }
 #undef PC2_RNS_DO
   return nullptr;
 }
-// The kernels with a multiplier per element.  Scalar products take one or two
-// column blocks (two where their multipliers fit the registers); mat-vecs one,
-// as their items are few and their multipliers come from HBM.
+// The kernels with a multiplier per element: one or two column blocks (two where
+// the multipliers fit the registers), the fixed-base tables one.
 const void* rns_gather_kernel(int t, int nb, int which) {
 #define PC2_RNS_DO                                                                        \
   if constexpr (G::T >= 9 && (G::NB == 1 || (G::NB == 2 && (G::T == 9 || G::T == 17)))) { \
@@ -882,9 +878,13 @@ const void* rns_gather_kernel(int t, int nb, int which) {
   return nullptr;
 }
 
-int rns_pow_threads(int t, int nb) {
+int rns_pow_threads(int t, int nb, bool wide) {
 #define PC2_RNS_DO return G::W * 64
-  PC2_RNS_GEOS(PC2_RNS_CASE)
+  if (wide) {
+    PC2_RNS_WIDE_GEOS(PC2_RNS_CASE)
+  } else {
+    PC2_RNS_GEOS(PC2_RNS_CASE)
+  }
 #undef PC2_RNS_DO
   return 0;
 }
@@ -899,11 +899,11 @@ hipError_t launch_rns_to(const RnsTo& c, int T, int nb, const RnsJobs& jobs, boo
   return hipGetLastError();
 }
 
-hipError_t launch_rns_pow(int t, int nb, int grid, const RnsPow& p, void* stream) {
-  const void* k = rns_pow_kernel(t, nb);
+hipError_t launch_rns_pow(int t, int nb, bool wide, int grid, const RnsPow& p, void* stream) {
+  const void* k = rns_pow_kernel(t, nb, wide);
   if (!k) return hipErrorInvalidValue;
   void* args[] = {(void*)&p};
-  return hipLaunchKernel(k, dim3(grid), dim3(rns_pow_threads(t, nb)), args, 0,
+  return hipLaunchKernel(k, dim3(grid), dim3(rns_pow_threads(t, nb, wide)), args, 0,
                          (hipStream_t)stream);
 }
 
@@ -911,7 +911,7 @@ hipError_t launch_rns_gather(int t, int nb, int which, int grid, const void* p, 
   const void* k = rns_gather_kernel(t, nb, which);
   if (!k) return hipErrorInvalidValue;
   void* args[] = {const_cast<void*>(p)};
-  return hipLaunchKernel(k, dim3(grid), dim3(rns_pow_threads(t, nb)), args, 0,
+  return hipLaunchKernel(k, dim3(grid), dim3(rns_pow_threads(t, nb, false)), args, 0,
                          (hipStream_t)stream);
 }
 hipError_t launch_rns_row_check(const uint32_t* x, const uint32_t* n2, int L2, uint32_t* bad,

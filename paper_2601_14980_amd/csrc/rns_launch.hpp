@@ -5,13 +5,14 @@
 
 namespace pc2k {
 
-const void* rns_pow_kernel(int T, int nb);   // null if (T, nb) is not compiled
-int rns_pow_threads(int T, int nb);
+// null (0) if (T, nb) is not compiled; wide: the geometry for one workgroup a CU
+const void* rns_pow_kernel(int T, int nb, bool wide);
+int rns_pow_threads(int T, int nb, bool wide);
 
 // the jobs' x (or m) as residues of both bases; limbs: words of an x
 hipError_t launch_rns_to(const RnsTo& c, int T, int nb, const RnsJobs& jobs, bool plain,
                          int limbs, uint8_t* out, void* stream);
-hipError_t launch_rns_pow(int T, int nb, int grid, const RnsPow& p, void* stream);
+hipError_t launch_rns_pow(int T, int nb, bool wide, int grid, const RnsPow& p, void* stream);
 // residues of base B -> canonical words: at the jobs' outputs (stage null), or
 // at stage + position stride
 hipError_t launch_rns_from(const RnsFrom& c, int T, int nb, const uint8_t* in,
@@ -28,7 +29,7 @@ hipError_t launch_rns_garner_crt(const SkConst& sk, const RnsJobs& jobs, const u
                                  int* err, void* stream);
 
 // kernels with a multiplier per element (null if not compiled for (T, nb));
-// rns_pow_threads threads; p: the kernel's argument (RnsSmul, RnsMvTab, RnsMv)
+// rns_pow_threads (not wide) threads; p: the kernel's argument (RnsSmul, RnsMvTab, RnsMv)
 enum { RNS_SMUL, RNS_MVTAB, RNS_MV, RNS_CHAIN, RNS_NGATHER };
 const void* rns_gather_kernel(int T, int nb, int which);
 hipError_t launch_rns_gather(int T, int nb, int which, int grid, const void* p, void* stream);

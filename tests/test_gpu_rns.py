@@ -51,7 +51,7 @@ def _ms_rs(n, count, seed):
 # counts from which a public-key encryption takes the engine (one element
 # below, at it), and a ragged one of several groups
 @pytest.mark.parametrize("nbits,count", [
-    (1024, 3583), (1024, 3584), (1120, 3617), (1536, 3871), (2048, 3839), (2048, 3841),
+    (1024, 3583), (1024, 3584), (1120, 3617), (1024, 12001), (1536, 3871), (2048, 3839), (2048, 3841),
     (2048, 16385), (2048, 20001), (3072, 6657), (4096, 7425)])
 def test_encrypt_counts(gpu_ctx, nbits, count):
     sk, opk, _ = _key(gpu_ctx, nbits)
@@ -81,7 +81,7 @@ def test_encrypt_windows(gpu_ctx, window):
 
 
 @pytest.mark.parametrize("nbits,count", [
-    (1024, 1), (1024, 33), (1120, 31), (1536, 65), (2048, 32), (2048, 129), (2048, 8193),
+    (1024, 1), (1024, 33), (1120, 31), (1536, 65), (2048, 32), (2048, 129), (2048, 5000), (2048, 8193),
     (2048, 10001), (3072, 31), (3072, 4097), (4096, 5)])
 def test_decrypt_and_key_holder_counts(gpu_ctx, nbits, count):
     from paper_2601_14980_amd import pc2
