@@ -111,14 +111,15 @@ int pc2_ctx_reserve(pc2_ctx *ctx, uint32_t max_nbits);
  *                a wavefront (few elements: several) per ciphertext;
  *   residues     a residue number system of 16-bit primes, two base extensions
  *                per product on the i8 matrix cores with constant matrices
- *                shared by 32 ciphertexts and more (keys from 1024 bits).
+ *                shared by 32 ciphertexts and more (keys from 512 bits).
  * PC2_MODMUL_VALU: the VALU engine everywhere.  PC2_MODMUL_MFMA: public-key
  * encryptions on the matrix cores (per element below some thousands of
- * elements and below 1024 bits, else residues).  PC2_MODMUL_AUTO (the default):
+ * elements and below 512 bits, else residues).  PC2_MODMUL_AUTO (the default):
  * whichever of the three is the fastest for the key's size and the call's
  * count.  With MFMA and AUTO, decryption, key-holder encryption, scalar
- * products and mat-vec plans under keys from 1024 bits run on residues, and
- * sums on the VALU.  All engines give identical results.  A batch or runner
+ * products and mat-vec plans under keys from 1024 bits run on residues (under
+ * 512-bit keys, decryptions and key-holder encryptions of some thousands and
+ * fewer), and sums on the VALU.  All engines give identical results.  A batch or runner
  * launch holds encryption jobs of at most two key classes per engine; its jobs
  * on residues run as one launch sequence per key.
  * PC2_OPT_TILE: the limb tile of the VALU encryption kernels (pc2_encrypt,
@@ -264,7 +265,7 @@ int pc2_enc_sum_dec(const pc2_sk *sk, const uint32_t *const *m_k, const uint32_t
  * costs one modular product per nonzero w-bit digit of its constants and no
  * squarings; the tables take cols * ceil(ebits / w) * (2^w - 1) entries of
  * the n^2 digit layout (640 B at 2048 bits).  A plan whose products run on
- * residues (PC2_OPT_MODMUL at its creation, keys from 1024 bits) chooses a
+ * residues (PC2_OPT_MODMUL at its creation, keys from 512 bits) chooses a
  * digit width of its own, of the least time among those whose tables (2^w
  * entries of 1088 B at 2048 bits) take no more than that and a sixteenth, or
  * 128 MB, and holds staging for the rows beside them.

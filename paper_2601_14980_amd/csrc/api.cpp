@@ -519,10 +519,10 @@ pc2k::RnsKey rns_const(const uint32_t* base, const RnsOffsets& o, int nw) {
   for (int i = 0; i < 5; ++i) k.ops[i] = base + o.ops[i];
   return k;
 }
-// Tile count of a modulus of a key of class cls, 0 below 1024-bit keys (where
+// Tile count of a modulus of a key of class cls, 0 below 512-bit keys (where
 // the VALU engine's products are short) and for a modulus far below its
 // class's size (the output conversion reads its four top limbs).
-constexpr int RNS_MIN_CLASS = 5;
+constexpr int RNS_MIN_CLASS = 4;
 int rns_tiles_for(int cls, const Limbs& N) {
   const int bits = pc2h::bitlen(N);
   return cls >= RNS_MIN_CLASS && bits >= 512 ? pc2h::rns_tiles(bits) : 0;
@@ -922,12 +922,12 @@ int status_of(hipError_t e) { return e == hipSuccess ? PC2_OK : PC2_E_DEVICE; }
 // with a wavefront of its own finishes sooner (one launch, ms, per-element /
 // RNS: 1024 bits, 2048 elements 1.9 / 3.2, 4096: 3.6 / 3.4; 2048 bits, 2048:
 // 6.7 / 13.1, 4096: 13.7 / 13.3; 3072 bits, 4096: 27.6 / 43.6, 8192: 55.6 /
-// 49.6; 4096 bits, 8192: 115 / 106).  Keys below 1024 bits stay on the VALU
-// engine once it fills the device (VALU / per-element: 256 bits, 4096: 0.62 /
-// 0.40, 16384: 0.68 / 1.46; 512 bits, 4096: 2.67 / 1.14, 16384: 2.71 / 4.05);
-// so does a 1024-bit key that the RNS engine does not take (16384: 9.6 / 11.6).
+// 49.6; 4096 bits, 8192: 115 / 106; 512 bits, 4096: 1.14 / 1.26, 8192: 2.0 /
+// 1.34).  256-bit keys stay on the VALU engine once it fills the device (VALU /
+// per-element: 4096: 0.62 / 0.40, 16384: 0.68 / 1.46), and so do keys that the
+// RNS engine does not take (512 bits, 16384: 2.71 / 4.05; 1024: 9.6 / 11.6).
 enum Engine { ENG_VALU, ENG_ELEM, ENG_RNS };
-constexpr size_t RNS_MIN_COUNT[pc2k::NUM_CLASSES] = {0, 0, 0, 0, 0, 3584, 3840, 6656, 7424};
+constexpr size_t RNS_MIN_COUNT[pc2k::NUM_CLASSES] = {0, 0, 0, 0, 4097, 3584, 3840, 6656, 7424};
 constexpr size_t ELEM_MAX_COUNT[pc2k::NUM_CLASSES] = {0, 0, 0, 4096, 8192, 12288};
 Engine enc_engine(const pc2_ctx* ctx, const pc2_pk* pk, size_t count) {
   if (ctx->modmul == PC2_MODMUL_VALU) return ENG_VALU;
@@ -947,8 +947,17 @@ bool enc_team(pc2_ctx* ctx, int cls, size_t count) {
   return pc2k::kernel_encrypt_team(cls, &threads) &&
          count <= (size_t)ctx->cus * occupancy(ctx, cls, pc2k::OP_ENC_TEAM);
 }
-bool dec_rns(const pc2_ctx* ctx, const pc2_sk* sk) {
-  return sk->dec[1].T && ctx->modmul != PC2_MODMUL_VALU;
+// Decryption and key-holder encryption of `count` elements: on the RNS engine at
+// any count from 1024-bit keys.  512-bit keys' squares of 512 bits fill half of
+// the smallest bases, which pays only while the VALU engine is latency-bound (ms,
+// RNS / VALU: decryption, 4096 elements 0.76 / 0.87, 8192 0.98 / 0.88, 65536 4.0 /
+// 1.6; key-holder encryption, 4096 1.38 / 1.64, 8192 1.81 / 1.65).
+constexpr size_t HALF_RNS_MAX_512 = 5632;
+bool half_rns(const pc2_ctx* ctx, const pc2_sk* sk, size_t count) {
+  return ctx->modmul != PC2_MODMUL_VALU && (sk->pk.cls > 4 || count <= HALF_RNS_MAX_512);
+}
+bool dec_rns(const pc2_ctx* ctx, const pc2_sk* sk, size_t count) {
+  return sk->dec[1].T && half_rns(ctx, sk, count);
 }
 
 pc2k::RnsJobs one_job(const uint32_t* x, const uint32_t* m, int m_limbs, uint32_t* out,
@@ -986,7 +995,8 @@ int rns_encrypt_run(pc2_ctx* ctx, const pc2_pk* pk, const pc2k::RnsJobs& J, cons
 
 // out[i] = c[i]^k[i], at any count (ms, RNS against VALU: 1024 bits, 1 element
 // 0.30 / 1.25, 20000: 0.88 / 1.39; 2048 bits, 1: 0.58 / 2.57, 20000: 2.4 / 4.6;
-// 4096 bits, 1: 2.05 / 4.9, 20000: 9.4 / 13.4)
+// 4096 bits, 1: 2.05 / 4.9, 20000: 9.4 / 13.4; 512 bits, 1: 0.18 / 0.41, 65536:
+// 0.80 / 0.82)
 int rns_scalar_mul(const pc2_pk* pk, const uint32_t* c, const uint64_t* k, uint32_t* out,
                    size_t count, void* stream) {
   pc2_ctx* ctx = pk->ctx;
@@ -1527,7 +1537,7 @@ int pc2_decrypt(const pc2_sk* sk, const uint32_t* c, uint32_t* m, size_t count, 
   if (!c || !m) return PC2_E_INVAL;
   if (partial_overlap(c, 8 * (size_t)sk->pk.L * count, m, 4 * (size_t)sk->pk.L * count))
     return PC2_E_INVAL;
-  if (dec_rns(sk->ctx, sk)) return rns_decrypt(sk, c, m, count, stream);
+  if (dec_rns(sk->ctx, sk, count)) return rns_decrypt(sk, c, m, count, stream);
   // the two CRT halves of up to DEC_CHUNK elements are staged between the
   // per-prime phase and the recombination
   const int Ls = sk->c.h[0].Ls;
@@ -1605,7 +1615,7 @@ int pc2_encrypt_sk(const pc2_sk* sk, const uint32_t* m, uint32_t m_limbs, const 
       return PC2_E_INVAL;
   }
   if (!sk->crt_ok) return PC2_E_UNSUPPORTED;
-  if (sk->enc[1].T && sk->ctx->modmul != PC2_MODMUL_VALU)
+  if (sk->enc[1].T && half_rns(sk->ctx, sk, count))
     return rns_encrypt_sk(sk, m, (int)m_limbs, r, c, count, stream);
   // the two halves of up to DEC_CHUNK elements are staged before the recombination
   const int nl2 = sk->c.h[0].s2.nl, L = sk->pk.L, cls = sk->pk.cls;
@@ -1696,7 +1706,7 @@ int pc2_enc_sum_dec(const pc2_sk* sk, const uint32_t* const* m_k, const uint32_t
   const int Ls = sk->c.h[0].Ls, L = sk->pk.L, cls = sk->pk.cls;
   const size_t chunk = std::min(count, pc2k::DEC_CHUNK);
   const Engine eng = enc_engine(ctx, &sk->pk, chunk);
-  if (eng == ENG_RNS && dec_rns(ctx, sk)) {
+  if (eng == ENG_RNS && dec_rns(ctx, sk, chunk)) {
     const size_t cb = align256(chunk * 8 * (size_t)L);
     const RnsPlan pe = rns_plan(ctx, sk->pk.rn.T, 1, chunk);
     const RnsPlan pd = rns_plan(ctx, sk->dec[0].T, 2, chunk);
@@ -1785,7 +1795,7 @@ std::vector<RnsPart> rns_parts(pc2_ctx* ctx, int op, const pc2_job* jobs, const 
       total += count[k];
     }
     if (total >= ((size_t)1 << 31)) continue;
-    if (op == pc2k::OP_DEC ? !dec_rns(ctx, jobs[i].sk)
+    if (op == pc2k::OP_DEC ? !dec_rns(ctx, jobs[i].sk, total)
                            : enc_engine(ctx, jobs[i].pk, total) != ENG_RNS)
       continue;
     p.pk = jobs[i].pk;

@@ -864,12 +864,12 @@ const void* rns_pow_kernel(int t, int nb, bool wide) {
 // the multipliers fit the registers), the fixed-base tables one.
 const void* rns_gather_kernel(int t, int nb, int which) {
 #define PC2_RNS_DO                                                                        \
-  if constexpr (G::T >= 9 && (G::NB == 1 || (G::NB == 2 && (G::T == 9 || G::T == 17)))) { \
+  if constexpr (G::NB == 1 || (G::NB == 2 && (G::T == 5 || G::T == 9 || G::T == 17))) {   \
     if (which == RNS_SMUL) return (const void*)&k_rns_smul<G>;                            \
     if (which == RNS_MV) return (const void*)&k_rns_mv<G>;                                \
     if (which == RNS_CHAIN) return (const void*)&k_rns_chain<G>;                          \
   }                                                                                       \
-  if constexpr (G::T >= 9 && G::NB == 1) {                                                \
+  if constexpr (G::NB == 1) {                                                             \
     if (which == RNS_MVTAB) return (const void*)&k_rns_mvtab<G>;                          \
   }                                                                                       \
   return nullptr

@@ -1,4 +1,4 @@
-"""The residue-number-system engine (keys of 1024 bits and up) against the VALU
+"""The residue-number-system engine (keys from 512 bits) against the VALU
 engine on the same context and against the oracle: counts on both sides of
 a block of 32 elements and of every choice that a call's shape depends on, key
 sizes of every tile count, and the values at the ends of the input ranges.
@@ -51,7 +51,8 @@ def _ms_rs(n, count, seed):
 # counts from which a public-key encryption takes the engine (one element
 # below, at it), and a ragged one of several groups
 @pytest.mark.parametrize("nbits,count", [
-    (1024, 3583), (1024, 3584), (1120, 3617), (1024, 12001), (1536, 3871), (2048, 3839), (2048, 3841),
+    (512, 4096), (512, 4097), (480, 9001), (1024, 3583), (1024, 3584), (1120, 3617),
+    (1024, 12001), (1536, 3871), (2048, 3839), (2048, 3841),
     (2048, 16385), (2048, 20001), (3072, 6657), (4096, 7425)])
 def test_encrypt_counts(gpu_ctx, nbits, count):
     sk, opk, _ = _key(gpu_ctx, nbits)
@@ -81,7 +82,8 @@ def test_encrypt_windows(gpu_ctx, window):
 
 
 @pytest.mark.parametrize("nbits,count", [
-    (1024, 1), (1024, 33), (1120, 31), (1536, 65), (2048, 32), (2048, 129), (2048, 5000), (2048, 8193),
+    (512, 1), (512, 5632), (512, 5633), (1024, 1), (1024, 33), (1120, 31), (1536, 65),
+    (2048, 32), (2048, 129), (2048, 5000), (2048, 8193),
     (2048, 10001), (3072, 31), (3072, 4097), (4096, 5)])
 def test_decrypt_and_key_holder_counts(gpu_ctx, nbits, count):
     from paper_2601_14980_amd import pc2
@@ -138,7 +140,8 @@ def test_bad_inputs(gpu_ctx, nbits):
 
 
 @pytest.mark.parametrize("nbits,count", [
-    (1024, 1), (1024, 33), (1120, 32), (1536, 65), (2048, 31), (2048, 97), (2048, 16400),
+    (400, 33), (512, 65), (512, 20001), (1024, 1), (1024, 33), (1120, 32), (1536, 65),
+    (2048, 31), (2048, 97), (2048, 16400),
     (3072, 33), (4096, 32)])
 def test_scalar_mul_counts(gpu_ctx, nbits, count):
     sk, opk, _ = _key(gpu_ctx, nbits)
@@ -158,6 +161,7 @@ def test_scalar_mul_counts(gpu_ctx, nbits, count):
 # rows: one group, both numbers of column blocks, several row batches (the last
 # two are more rows than the plan's staging holds at once)
 @pytest.mark.parametrize("nbits,rows,cols,ebits,window,hint,with_alpha", [
+    (512, 33, 5, 50, 0, 33, True), (512, 700, 40, 50, 0, 700, True),
     (1024, 1, 1, 1, 0, 0, True), (1024, 33, 3, 64, 0, 33, False), (1120, 32, 5, 17, 0, 1, True),
     (1536, 65, 4, 50, 4, 65, True), (2048, 31, 33, 7, 0, 31, True),
     (2048, 700, 40, 50, 0, 700, True), (2048, 700, 40, 50, 0, 0, False),
