@@ -680,13 +680,7 @@ __global__ __launch_bounds__(512) void k_rns_from(RnsFrom C, const uint8_t* __re
     size_t el;
     if (!find_job(J, p, job, el)) continue;
     uint32_t* out = stage ? stage + p * stride : job.out + el * C.nw;
-    for (int j = lane; j < C.nw; j += 64) {
-      const int bit = 32 * j, i = bit / 28, sh = bit % 28;
-      uint64_t v = limb[i * 64 + e];
-      if (i + 1 < 8 * nblk) v |= (uint64_t)limb[(i + 1) * 64 + e] << 28;
-      if (i + 2 < 8 * nblk) v |= (uint64_t)limb[(i + 2) * 64 + e] << 56;
-      out[j] = (uint32_t)(v >> sh);
-    }
+    for (int j = lane; j < C.nw; j += 64) out[j] = pc2k::rns_word28(limb + e, 8 * nblk, 64, j);
   }
 }
 

@@ -42,6 +42,18 @@ struct RnsFrom {
   double ntop_inv;      // 1 / (N's limbs S - 4 .. S - 1 as a number)
 };
 
+// Word j of a number in n 28-bit limbs, `stride` words apart; zero past them.  A
+// result's words come from the key's declared size, its limbs from the modulus,
+// which may be shorter by any amount.
+__host__ __device__ inline uint32_t rns_word28(const uint32_t* limb, int n, int stride, int j) {
+  const int bit = 32 * j, i = bit / 28, sh = bit % 28;
+  uint64_t v = 0;
+  if (i < n) v = limb[(size_t)i * stride];
+  if (i + 1 < n) v |= (uint64_t)limb[(size_t)(i + 1) * stride] << 28;
+  if (i + 2 < n) v |= (uint64_t)limb[(size_t)(i + 2) * stride] << 56;
+  return (uint32_t)(v >> sh);
+}
+
 // Powering programs (rns_mont.hpp): one word per operation.
 constexpr uint32_t RNS_SQ = 0xFF;                          // multiplier: the running value
 constexpr uint32_t RNS_GM = 0xFD;                          // multiplier: the second input
