@@ -957,7 +957,7 @@ bool half_rns(const pc2_ctx* ctx, const pc2_sk* sk, size_t count) {
   return ctx->modmul != PC2_MODMUL_VALU && (sk->pk.cls > 4 || count <= HALF_RNS_MAX_512);
 }
 bool dec_rns(const pc2_ctx* ctx, const pc2_sk* sk, size_t count) {
-  return sk->dec[1].T && half_rns(ctx, sk, count);
+  return sk->dec[0].T && half_rns(ctx, sk, count);
 }
 
 pc2k::RnsJobs one_job(const uint32_t* x, const uint32_t* m, int m_limbs, uint32_t* out,
@@ -1377,20 +1377,22 @@ int pc2_sk_create(pc2_ctx* ctx, uint32_t nbits, const uint32_t* p_limbs, const u
   Limbs q2inv = MP2.pow(pc2h::mod(q2, p2), pc2h::sub(phi, Limbs{1}));
   size_t p2inv = buf.add(pc2h::inv_pow2(p2, nl2));
   size_t q2i = buf.add(pc2h::resized(pc2h::shl_mod(q2inv, (uint64_t)32 * nl2, p2), nl2));
-  // the RNS engine modulo p^2 and q^2: decryption and key-holder encryption
-  // (both primes on one tile count, or neither)
+  // the RNS engine modulo p^2 and q^2, each operation on one tile count for both
+  // primes, or neither (a modulus that shares a factor with a channel is refused)
   RnsOffsets rd[2], re[2];
   const int rt = rns_tiles_for(cls, p2), rtq = rns_tiles_for(cls, q2);
   if (rt && rtq && rtq <= rt) {
     const Limbs* sq[2] = {&p2, &q2};
     const Limbs* pr[2] = {&p, &q};
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < 2 && (i == 0 || rd[0].T); ++i) {
       const Limbs sm1 = pc2h::sub(*pr[i], Limbs{1});
       Limbs order = pc2h::mul(*pr[i], sm1);
       rd[i] = add_rns(buf, *sq[i], rt, sm1, 4 * L, nullptr, 0, i ? &rd[0] : nullptr);
-      if (rd[0].T)
+      if (rd[i].T)
         re[i] = add_rns(buf, *sq[i], rt, pc2h::mod(n, order), 2 * L, &n, 2 * L, &rd[0]);
     }
+    if (!rd[1].T) rd[0].T = 0;
+    if (!re[0].T || !re[1].T) re[0].T = re[1].T = 0;
   }
   // the key-holder encryption needs r, m < n < 2 q^2, i.e. p < 2 q
   const bool crt_ok = pc2h::cmp(p, pc2h::add(q, q)) < 0;
@@ -1615,7 +1617,7 @@ int pc2_encrypt_sk(const pc2_sk* sk, const uint32_t* m, uint32_t m_limbs, const 
       return PC2_E_INVAL;
   }
   if (!sk->crt_ok) return PC2_E_UNSUPPORTED;
-  if (sk->enc[1].T && half_rns(sk->ctx, sk, count))
+  if (sk->enc[0].T && half_rns(sk->ctx, sk, count))
     return rns_encrypt_sk(sk, m, (int)m_limbs, r, c, count, stream);
   // the two halves of up to DEC_CHUNK elements are staged before the recombination
   const int nl2 = sk->c.h[0].s2.nl, L = sk->pk.L, cls = sk->pk.cls;
