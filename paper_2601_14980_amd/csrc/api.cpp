@@ -6,6 +6,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "../../include/pc2.h"
@@ -1775,6 +1776,109 @@ namespace {
 // Positions of a part's jobs: each from the next multiple of 32.
 uint32_t round32(uint32_t v) { return (v + 31) & ~31u; }
 
+// The jobs of one key in a launch.
+struct KeyJobs {
+  const pc2_pk* pk = nullptr;
+  const pc2_sk* sk = nullptr;
+  std::vector<size_t> jobs;
+  size_t total = 0;
+  bool takes = false;  // the RNS engine takes them (enc_engine, dec_rns)
+  bool rns = false;
+};
+int key_ebits(const KeyJobs& k) { return k.sk ? k.sk->c.ebits : (int)k.pk->nbits; }
+
+// Estimates in microseconds for the choice between the engines where a launch
+// holds several keys (rns_choose), all per bit of the exponents.  On residues
+// every key is a launch sequence of its own, however few its elements (16
+// decryptions of 1024 / 2048 / 3072 / 4096 bits: 1.24 / 3.3 / 7.3 / 13.1 ms a
+// key).  A unit of RnsPlan::cost by tile count: with a few workgroups, with one on
+// every compute unit, and how steeply it falls from there, as the units then
+// stream fewer copies of the constants (encryptions of 3072 bits on 129 / 208 / 256
+// units: 5.3 / 7.6 / 8.1; 4096 bits on 129 / 232 / 256: 8.4 / 13.1 / 14).
+struct RnsUnit { double few, full, drop; };
+constexpr RnsUnit RNS_UNIT[pc2k::RNS_NT] = {{0.97, 1.1, 0.3},  {1.30, 1.6, 0.6},
+                                            {1.91, 2.4, 1.0},  {3.05, 3.9, 1.45},
+                                            {5.0, 8.1, 5.6},   {8.0, 14.0, 11.3}};
+double rns_time(const pc2_ctx* ctx, const RnsPlan& p, int nmod, int ebits) {
+  const RnsUnit u = RNS_UNIT[rns_index(p.T)];
+  const double fill = std::min(1.0, (double)(p.ngroups * nmod) / ctx->cus);
+  return p.cost * std::max(u.few, u.full - (1 - fill) * u.drop) * ebits;
+}
+// The persistent kernels run all keys of a launch together: no sooner than one
+// element's chain of products, and than the device does the products of all
+// (ms, few elements / an element in a full device: VALU decryption 1024 bits 4.7
+// / 0.00014, 2048: 16.4 / 0.00095, 3072: 31 / 0.003, 4096: 72 / 0.007; VALU
+// encryption 1024: 17 / 0.00065; per-element encryption 1024: 1.5 / 0.0007, 2048:
+// 5.2 / 0.0028, 3072: 9.5 / 0.0066, 4096: 19.4 / 0.0135).
+struct PersistentUnit { double chain, each; };
+constexpr PersistentUnit VALU_DEC[4] = {{9.2, 0.00027}, {16.0, 0.00093}, {20.2, 0.0020},
+                                        {35.2, 0.0034}};
+constexpr PersistentUnit VALU_ENC_1024 = {16.6, 0.00064};
+constexpr PersistentUnit ELEM_ENC[4] = {{1.46, 0.00069}, {2.56, 0.00135}, {3.10, 0.00216},
+                                        {4.74, 0.00329}};
+PersistentUnit persistent_unit(const pc2_ctx* ctx, int op, int cls) {
+  if (cls < 5) return {0, 0};  // (no launch holds these beside a key that the RNS engine takes)
+  if (op == pc2k::OP_DEC) return VALU_DEC[cls - 5];
+  return use_mfma(ctx, cls) ? ELEM_ENC[cls - 5] : VALU_ENC_1024;
+}
+
+// Which keys of a launch run on residues: the one key of a launch of its own
+// whenever the engine takes it, else those of the most elements, as many as
+// make the launch's estimated time the least (decryption batches, 2048 bits, 16
+// elements a key, 4 / 8 / 16 keys: 13.4 / 26.9 / 53.7 ms as sequences, 16.5 in the
+// persistent kernel; encryptions of 3840 elements, 4 keys: 53.8 against 45.7).
+void rns_choose(pc2_ctx* ctx, int op, std::vector<KeyJobs>& keys) {
+  if (keys.size() == 1) {
+    keys[0].rns = keys[0].takes;
+    return;
+  }
+  const int nmod = op == pc2k::OP_DEC ? 2 : 1;
+  struct Load { double chain = 0, each = 0; size_t keys = 0; } load[pc2k::NUM_CLASSES];
+  auto load_of = [&](const KeyJobs& k) -> Load& { return load[k.sk ? k.sk->pk.cls : k.pk->cls]; };
+  std::vector<size_t> order;
+  for (size_t i = 0; i < keys.size(); ++i) {
+    const KeyJobs& k = keys[i];
+    const int cls = k.sk ? k.sk->pk.cls : k.pk->cls;
+    const PersistentUnit u = persistent_unit(ctx, op, cls);
+    load_of(k).chain = std::max(load_of(k).chain, u.chain * key_ebits(k));
+    load_of(k).each += u.each * key_ebits(k) * (double)k.total;
+    ++load_of(k).keys;
+    if (k.takes) order.push_back(i);
+  }
+  // the VALU classes in one launch, each class on the matrix cores in its own
+  auto persistent = [&] {
+    double chain = 0, each = 0, elem = 0;
+    for (int c = 0; c < pc2k::NUM_CLASSES; ++c) {
+      if (!load[c].keys) continue;
+      if (op == pc2k::OP_ENC && use_mfma(ctx, c)) {
+        elem += std::max(load[c].chain, load[c].each);
+      } else {
+        chain = std::max(chain, load[c].chain);
+        each += load[c].each;
+      }
+    }
+    return std::max(chain, each) + elem;
+  };
+  std::stable_sort(order.begin(), order.end(),
+                   [&](size_t a, size_t b) { return keys[a].total > keys[b].total; });
+  double best = persistent(), rns = 0;
+  size_t take = 0;
+  for (size_t m = 0; m < order.size(); ++m) {
+    const KeyJobs& k = keys[order[m]];
+    const int T = op == pc2k::OP_DEC ? k.sk->dec[0].T : k.pk->rn.T;
+    const PersistentUnit u = persistent_unit(ctx, op, k.sk ? k.sk->pk.cls : k.pk->cls);
+    rns += rns_time(ctx, rns_plan(ctx, T, nmod, k.total), nmod, key_ebits(k));
+    load_of(k).each -= u.each * key_ebits(k) * (double)k.total;
+    --load_of(k).keys;
+    const double time = rns + persistent();
+    if (time < best) {
+      best = time;
+      take = m + 1;
+    }
+  }
+  for (size_t m = 0; m < take; ++m) keys[order[m]].rns = true;
+}
+
 // The jobs that the RNS engine takes, by key: count[i] elements from element
 // first[i] of job i.  in_rns[i] tells which; hjobs receives their descriptors
 // (part after part, jobs.many holding an index until rns_parts_place).
@@ -1784,41 +1888,44 @@ std::vector<RnsPart> rns_parts(pc2_ctx* ctx, int op, const pc2_job* jobs, const 
   std::vector<RnsPart> parts;
   in_rns->assign(njobs, false);
   if (op != pc2k::OP_ENC && op != pc2k::OP_DEC) return parts;
-  std::vector<bool> seen(njobs, false);
+  const bool dec = op == pc2k::OP_DEC;
+  std::vector<KeyJobs> keys;  // by first appearance
+  std::unordered_map<const void*, size_t> at;
   for (size_t i = 0; i < njobs; ++i) {
-    if (seen[i] || count[i] == 0) continue;
+    if (count[i] == 0) continue;
+    const void* key = dec ? (const void*)jobs[i].sk : (const void*)jobs[i].pk;
+    const auto ins = at.emplace(key, keys.size());
+    if (ins.second) {
+      keys.emplace_back();
+      keys.back().pk = dec ? nullptr : jobs[i].pk;
+      keys.back().sk = dec ? jobs[i].sk : nullptr;
+    }
+    KeyJobs& k = keys[ins.first->second];
+    k.jobs.push_back(i);
+    k.total += count[i];
+  }
+  for (KeyJobs& k : keys)
+    k.takes = k.total < ((size_t)1 << 31) &&
+              (dec ? dec_rns(ctx, k.sk, k.total) : enc_engine(ctx, k.pk, k.total) == ENG_RNS);
+  rns_choose(ctx, op, keys);
+  for (const KeyJobs& k : keys) {
+    if (!k.rns) continue;
     RnsPart p;
-    const void* key = op == pc2k::OP_DEC ? (const void*)jobs[i].sk : (const void*)jobs[i].pk;
-    size_t total = 0;
-    for (size_t k = i; k < njobs; ++k) {
-      const void* other = op == pc2k::OP_DEC ? (const void*)jobs[k].sk : (const void*)jobs[k].pk;
-      if (count[k] == 0 || other != key) continue;
-      seen[k] = true;
-      total += count[k];
-    }
-    if (total >= ((size_t)1 << 31)) continue;
-    if (op == pc2k::OP_DEC ? !dec_rns(ctx, jobs[i].sk, total)
-                           : enc_engine(ctx, jobs[i].pk, total) != ENG_RNS)
-      continue;
-    p.pk = jobs[i].pk;
-    p.sk = jobs[i].sk;
-    const size_t at = hjobs->size();
+    p.pk = k.pk;
+    p.sk = k.sk;
+    const size_t from = hjobs->size();
     uint32_t pos = 0;
-    for (size_t k = i; k < njobs; ++k) {
-      const void* other = op == pc2k::OP_DEC ? (const void*)jobs[k].sk : (const void*)jobs[k].pk;
-      if (count[k] == 0 || other != key) continue;
-      (*in_rns)[k] = true;
-      const pc2_job& j = jobs[k];
-      const bool dec = op == pc2k::OP_DEC;
-      hjobs->push_back({dec ? j.in0 : j.in1, dec ? nullptr : j.in0, j.out, first[k],
-                        (uint32_t)count[k], pos, (int)j.m_limbs});
-      pos = round32(pos + (uint32_t)count[k]);
+    for (size_t i : k.jobs) {
+      const pc2_job& j = jobs[i];
+      (*in_rns)[i] = true;
+      hjobs->push_back({dec ? j.in0 : j.in1, dec ? nullptr : j.in0, j.out, first[i],
+                        (uint32_t)count[i], pos, (int)j.m_limbs});
+      pos = round32(pos + (uint32_t)count[i]);
     }
-    p.jobs.n = (int)(hjobs->size() - at);
-    p.jobs.many = reinterpret_cast<const pc2k::RnsJob*>(at * sizeof(pc2k::RnsJob));
+    p.jobs.n = (int)(hjobs->size() - from);
+    p.jobs.many = reinterpret_cast<const pc2k::RnsJob*>(from * sizeof(pc2k::RnsJob));
     p.jobs.npos = pos;
-    p.plan = op == pc2k::OP_DEC ? rns_plan(ctx, p.sk->dec[0].T, 2, pos)
-                                : rns_plan(ctx, p.pk->rn.T, 1, pos);
+    p.plan = rns_plan(ctx, dec ? k.sk->dec[0].T : k.pk->rn.T, dec ? 2 : 1, pos);
     parts.push_back(p);
   }
   return parts;
