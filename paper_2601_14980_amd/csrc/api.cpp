@@ -1776,6 +1776,11 @@ namespace {
 // Positions of a part's jobs: each from the next multiple of 32.
 uint32_t round32(uint32_t v) { return (v + 31) & ~31u; }
 
+// A part holds at most RNS_PART positions, and a key's jobs are cut into as many
+// parts as they need, which share one scratch: a launch's staging (2.2 KB a
+// position at 2048 bits) stays bounded whatever its jobs' lengths.
+constexpr uint32_t RNS_PART = (uint32_t)pc2k::DEC_CHUNK;
+
 // The jobs of one key in a launch.
 struct KeyJobs {
   const pc2_pk* pk = nullptr;
@@ -1905,28 +1910,45 @@ std::vector<RnsPart> rns_parts(pc2_ctx* ctx, int op, const pc2_job* jobs, const 
     k.total += count[i];
   }
   for (KeyJobs& k : keys)
-    k.takes = k.total < ((size_t)1 << 31) &&
-              (dec ? dec_rns(ctx, k.sk, k.total) : enc_engine(ctx, k.pk, k.total) == ENG_RNS);
+    k.takes = dec ? dec_rns(ctx, k.sk, k.total) : enc_engine(ctx, k.pk, k.total) == ENG_RNS;
   rns_choose(ctx, op, keys);
   for (const KeyJobs& k : keys) {
     if (!k.rns) continue;
     RnsPart p;
-    p.pk = k.pk;
-    p.sk = k.sk;
-    const size_t from = hjobs->size();
+    size_t from = 0;
     uint32_t pos = 0;
+    auto start = [&] {
+      p = RnsPart();
+      p.pk = k.pk;
+      p.sk = k.sk;
+      from = hjobs->size();
+      pos = 0;
+    };
+    auto close = [&] {
+      p.jobs.n = (int)(hjobs->size() - from);
+      p.jobs.many = reinterpret_cast<const pc2k::RnsJob*>(from * sizeof(pc2k::RnsJob));
+      p.jobs.npos = pos;
+      p.plan = rns_plan(ctx, dec ? k.sk->dec[0].T : k.pk->rn.T, dec ? 2 : 1, pos);
+      parts.push_back(p);
+    };
+    start();
     for (size_t i : k.jobs) {
       const pc2_job& j = jobs[i];
       (*in_rns)[i] = true;
-      hjobs->push_back({dec ? j.in0 : j.in1, dec ? nullptr : j.in0, j.out, first[i],
-                        (uint32_t)count[i], pos, (int)j.m_limbs});
-      pos = round32(pos + (uint32_t)count[i]);
+      for (size_t done = 0; done < count[i];) {
+        if (round32(pos) >= RNS_PART) {
+          close();
+          start();
+        }
+        pos = round32(pos);
+        const size_t n = std::min<size_t>(count[i] - done, RNS_PART - pos);
+        hjobs->push_back({dec ? j.in0 : j.in1, dec ? nullptr : j.in0, j.out, first[i] + done,
+                          (uint32_t)n, pos, (int)j.m_limbs});
+        pos += (uint32_t)n;
+        done += n;
+      }
     }
-    p.jobs.n = (int)(hjobs->size() - from);
-    p.jobs.many = reinterpret_cast<const pc2k::RnsJob*>(from * sizeof(pc2k::RnsJob));
-    p.jobs.npos = pos;
-    p.plan = rns_plan(ctx, dec ? k.sk->dec[0].T : k.pk->rn.T, dec ? 2 : 1, pos);
-    parts.push_back(p);
+    close();
   }
   return parts;
 }
@@ -2013,18 +2035,44 @@ int occupancy_of(const void* k) {
   return occ;
 }
 
+static void batch_rns_free(pc2_batch* b) {
+  if (b->rscratch) (void)hipFree(b->rscratch);
+  if (b->rscratch2) (void)hipFree(b->rscratch2);
+  if (b->forked) (void)hipEventDestroy(b->forked);
+  if (b->joined) (void)hipEventDestroy(b->joined);
+  if (b->side) (void)hipStreamDestroy(b->side);
+  b->rscratch = b->rscratch2 = nullptr;
+  b->forked = b->joined = nullptr;
+  b->side = nullptr;
+}
 static void batch_free(pc2_batch* b) {
   if (b->exec) (void)hipGraphExecDestroy(b->exec);
   if (b->dev) (void)hipFree(b->dev);
   if (b->scratch) (void)hipFree(b->scratch);
   if (b->mscratch) (void)hipFree(b->mscratch);
-  if (b->rscratch) (void)hipFree(b->rscratch);
-  if (b->rscratch2) (void)hipFree(b->rscratch2);
   if (b->stage) (void)hipFree(b->stage);
-  if (b->forked) (void)hipEventDestroy(b->forked);
-  if (b->joined) (void)hipEventDestroy(b->joined);
-  if (b->side) (void)hipStreamDestroy(b->side);
+  batch_rns_free(b);
   delete b;
+}
+
+// What a batch's parts on the RNS engine run in; false if the device has no
+// memory for it (the jobs then stay on the persistent kernels).
+static bool batch_rns_alloc(pc2_batch* b, pc2_ctx* ctx, int op) {
+  rns_parts_pair(ctx, b->rparts, op == pc2k::OP_DEC ? 2 : 1);
+  size_t bytes[2] = {0, 0};
+  for (const RnsPart& p : b->rparts)
+    bytes[p.side] = std::max(bytes[p.side], rns_part_bytes(p, op));
+  if (hipSetDevice(ctx->device) == hipSuccess &&
+      hipMalloc(&b->rscratch, bytes[0]) == hipSuccess &&
+      (!bytes[1] ||
+       (hipMalloc(&b->rscratch2, bytes[1]) == hipSuccess &&
+        hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking) == hipSuccess &&
+        hipEventCreateWithFlags(&b->forked, hipEventDisableTiming) == hipSuccess &&
+        hipEventCreateWithFlags(&b->joined, hipEventDisableTiming) == hipSuccess)))
+    return true;
+  (void)hipGetLastError();
+  batch_rns_free(b);
+  return false;
 }
 
 int pc2_batch_create(pc2_ctx* ctx, const pc2_job* jobs, size_t njobs, pc2_batch** out) {
@@ -2084,6 +2132,11 @@ int pc2_batch_create(pc2_ctx* ctx, const pc2_job* jobs, size_t njobs, pc2_batch*
   std::vector<bool> in_rns;
   std::vector<pc2k::RnsJob> rjobs;
   b->rparts = rns_parts(ctx, op, jobs, zero.data(), counts.data(), njobs, &in_rns, &rjobs);
+  if (!b->rparts.empty() && !batch_rns_alloc(b, ctx, op)) {
+    b->rparts.clear();
+    rjobs.clear();
+    in_rns.assign(njobs, false);
+  }
   const int few = few_elements_class(ctx, op, jobs, counts.data(), njobs, in_rns);
   if (few >= 0 && mcb < 0) {
     (mca < 0 ? mca : mcb) = few;
@@ -2223,21 +2276,6 @@ int pc2_batch_create(pc2_ctx* ctx, const pc2_job* jobs, size_t njobs, pc2_batch*
     mbytes = std::max(mbytes, (size_t)m.grid * (pc2k::mfma_digit_bytes(m.cls) << m.w));
   }
   if (!rc && mbytes && hipMalloc(&b->mscratch, mbytes) != hipSuccess) rc = PC2_E_NOMEM;
-  if (!rc && !b->rparts.empty()) {
-    rns_parts_pair(ctx, b->rparts, op == pc2k::OP_DEC ? 2 : 1);
-    size_t rbytes[2] = {0, 0};
-    for (const RnsPart& p : b->rparts)
-      rbytes[p.side] = std::max(rbytes[p.side], rns_part_bytes(p, op));
-    if (hipMalloc(&b->rscratch, rbytes[0]) != hipSuccess) rc = PC2_E_NOMEM;
-    if (!rc && rbytes[1]) {
-      if (hipMalloc(&b->rscratch2, rbytes[1]) != hipSuccess)
-        rc = PC2_E_NOMEM;
-      else if (hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking) != hipSuccess ||
-               hipEventCreateWithFlags(&b->forked, hipEventDisableTiming) != hipSuccess ||
-               hipEventCreateWithFlags(&b->joined, hipEventDisableTiming) != hipSuccess)
-        rc = PC2_E_DEVICE;
-    }
-  }
   if (!rc && b->nitems) {
     int occ = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, pc2k::batch_kernel(op, pair), 64, 0) !=
@@ -2407,6 +2445,14 @@ int pc2_autotune(const pc2_sk* sk, void* hip_stream, int* w_enc, int* w_dec, int
 
 // ---------------------------------------------------------------- runners
 namespace {
+// elements of the largest group of a key up to class cls
+size_t runner_group_max(int op, int cls) {
+  size_t elems = 0;
+  for (int g = 0; g < pc2k::NUM_GEOS; ++g)
+    if (pc2k::GEO_CLASS[g] >= RNS_MIN_CLASS && pc2k::GEO_CLASS[g] <= cls)
+      elems = std::max(elems, (size_t)std::max(0, pc2k::batch_group_elems(op, g)));
+  return elems;
+}
 int op_from_abi(int op_abi) {
   if (op_abi == PC2_OP_ENCRYPT) return pc2k::OP_ENC;
   if (op_abi == PC2_OP_DECRYPT) return pc2k::OP_DEC;
@@ -2437,7 +2483,11 @@ int pc2_runner_create(pc2_ctx* ctx, int op_abi, uint32_t max_nbits, size_t max_j
   const size_t max_items = (op == pc2k::OP_DEC ? 2 : 1) * max_groups;
   r->items_b = (max_items * sizeof(pc2k::BatchItem) + 255) & ~(size_t)255;
   r->ptr_b = (r->max_ptrs * sizeof(size_t) + 255) & ~(size_t)255;
-  r->rjobs_b = op == pc2k::OP_SUM ? 0 : (max_jobs * sizeof(pc2k::RnsJob) + 255) & ~(size_t)255;
+  // the RNS engine's jobs, of which each part's end may cut one in two
+  const size_t max_pos = max_groups * runner_group_max(op, cls) + 32 * max_jobs;
+  if (op != pc2k::OP_SUM && cls >= RNS_MIN_CLASS)
+    r->rjobs_b =
+        ((max_jobs + 2 * (max_pos / RNS_PART) + 1) * sizeof(pc2k::RnsJob) + 255) & ~(size_t)255;
   const size_t total = r->jobs_b + r->items_b + r->ptr_b + QUEUE_BYTES + r->rjobs_b;
   int rc = PC2_OK;
   if (hipMalloc(&r->dev, total) != hipSuccess || hipHostMalloc(&r->host, total) != hipSuccess ||
@@ -2483,13 +2533,10 @@ int pc2_runner_create(pc2_ctx* ctx, int op_abi, uint32_t max_nbits, size_t max_j
     }
     if (!rc && r->mscratch_bytes && hipMalloc(&r->mscratch, r->mscratch_bytes) != hipSuccess)
       rc = PC2_E_NOMEM;
-    // the RNS engine: one launch's positions under any key up to max_nbits
-    if (!rc && op != pc2k::OP_SUM && cls >= RNS_MIN_CLASS) {
-      size_t elems = 0;
-      for (int g = 0; g < pc2k::NUM_GEOS; ++g)
-        if (pc2k::GEO_CLASS[g] >= RNS_MIN_CLASS && pc2k::GEO_CLASS[g] <= cls)
-          elems = std::max(elems, (size_t)std::max(0, pc2k::batch_group_elems(op, g)));
-      const size_t npos = std::min(max_groups * elems + 32 * max_jobs, (size_t)1 << 31);
+    // the RNS engine: a part's positions under any key up to max_nbits (without
+    // memory for it, launches stay on the persistent kernels)
+    if (!rc && r->rjobs_b) {
+      const size_t npos = std::min<size_t>(max_pos, RNS_PART);
       const pc2k::ClassGeo cg = pc2k::CLASS_GEO[cls];
       const int p2bits = cg.pD * cg.pK * cg.pT - 2;
       const int tmax = pc2h::rns_tiles(op == pc2k::OP_DEC ? p2bits : 64 * L);
@@ -2503,8 +2550,10 @@ int pc2_runner_create(pc2_ctx* ctx, int op_abi, uint32_t max_nbits, size_t max_j
                                      ? rns_decrypt_bytes(p, npos, (p2bits + 31) / 32)
                                      : rns_encrypt_bytes(p));
         }
-      if (r->rscratch_bytes && hipMalloc(&r->rscratch, r->rscratch_bytes) != hipSuccess)
-        rc = PC2_E_NOMEM;
+      if (r->rscratch_bytes && hipMalloc(&r->rscratch, r->rscratch_bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        r->rscratch = nullptr;
+      }
     }
     if (!rc && op == pc2k::OP_DEC) {  // CRT halves of up to max_groups groups
       size_t per = 0;
@@ -2600,7 +2649,8 @@ int pc2_runner_launch(pc2_runner* r, const pc2_job* jobs, const size_t* first,
   std::vector<RnsPart> parts =
       rns_parts(ctx, op, jobs, relem.data(), rcount.data(), njobs, &in_rns, &rjobs);
   for (const RnsPart& p : parts)
-    if (!r->rscratch || rns_part_bytes(p, op) > r->rscratch_bytes) {
+    if (!r->rscratch || rns_part_bytes(p, op) > r->rscratch_bytes ||
+        rjobs.size() * sizeof(pc2k::RnsJob) > r->rjobs_b) {
       parts.clear();
       rjobs.clear();
       in_rns.assign(njobs, false);
