@@ -781,9 +781,29 @@ double rns_round(int T, int nb, bool wide, size_t w) {
   return T >= 17 || wide ? (double)w * (1.1 + nb) : 1.2 + (double)w * (0.3 + nb);
 }
 
+// Microseconds of a unit of RnsPlan::cost per bit of the exponent, by tile count:
+// with a few workgroups, with one on every compute unit, and how steeply it falls
+// from there, as the units then stream fewer copies of the constants (16
+// decryptions of 1024 / 2048 / 3072 / 4096 bits: 1.24 / 3.3 / 7.3 / 13.1 ms;
+// encryptions of 3072 bits on 129 / 208 / 256 units: 5.3 / 7.6 / 8.1 us, 4096
+// bits on 129 / 232 / 256: 8.4 / 13.1 / 14).
+struct RnsUnit { double few, full, drop; };
+constexpr RnsUnit RNS_UNIT[pc2k::RNS_NT] = {{0.97, 1.1, 0.3},  {1.30, 1.6, 0.6},
+                                            {1.91, 2.4, 1.0},  {3.05, 3.9, 1.45},
+                                            {5.0, 8.1, 5.6},   {8.0, 14.0, 11.3}};
+double rns_unit(const pc2_ctx* ctx, const RnsPlan& p, int nmod) {
+  const RnsUnit u = RNS_UNIT[rns_index(p.T)];
+  const double fill = std::min(1.0, (double)(p.ngroups * nmod) / ctx->cus);
+  return std::max(u.few, u.full - (1 - fill) * u.drop);
+}
+
+// The plan of the least time.  From T = 26 a workgroup's streamed constants weigh
+// so much that two column blocks on half of the units beat one on all (8192
+// encryptions of 3072 / 4096 bits: 50.5 / 106 against 56.6 / 121 ms).
 RnsPlan rns_plan(pc2_ctx* ctx, int T, int nmod, size_t count, int gather = -1) {
   const int w = rns_window(ctx, T);
   RnsPlan best;
+  double least = 0;
   for (int k = 2; k <= 2 * pc2k::RNS_NBMAX + 1; ++k) {
     const int nb = k / 2;
     const bool wide = k & 1;
@@ -794,7 +814,11 @@ RnsPlan rns_plan(pc2_ctx* ctx, int T, int nmod, size_t count, int gather = -1) {
     const size_t items = p.ngroups * nmod, occ = (size_t)slots / ctx->cus;
     const size_t full = items / slots, rest = (items % slots + ctx->cus - 1) / ctx->cus;
     p.cost = (double)full * rns_round(T, nb, wide, occ) + rns_round(T, nb, wide, rest);
-    if (!best.T || p.cost < best.cost) best = p;
+    const double time = T >= 26 ? p.cost * rns_unit(ctx, p, nmod) : p.cost;
+    if (!best.T || time < least) {
+      best = p;
+      least = time;
+    }
   }
   return best;
 }
@@ -922,13 +946,14 @@ int status_of(hipError_t e) { return e == hipSuccess ? PC2_OK : PC2_E_DEVICE; }
 // RNS engine needs a device-filling number of elements; below that an element
 // with a wavefront of its own finishes sooner (one launch, ms, per-element /
 // RNS: 1024 bits, 2048 elements 1.9 / 3.2, 4096: 3.6 / 3.4; 2048 bits, 2048:
-// 6.7 / 13.1, 4096: 13.7 / 13.3; 3072 bits, 4096: 27.6 / 43.6, 8192: 55.6 /
-// 49.6; 4096 bits, 8192: 115 / 106; 512 bits, 4096: 1.14 / 1.26, 8192: 2.0 /
+// 6.7 / 13.1, 4096: 13.7 / 13.3; 3072 bits, 7168, which fill the device's wavefronts
+// once more: 48.3 / 51.4, 7500: 55.4 / 50.4; 4096 bits, 6900: 98 / 105, 7424: 115 /
+// 105; 512 bits, 4096: 1.14 / 1.26, 8192: 2.0 /
 // 1.34).  256-bit keys stay on the VALU engine once it fills the device (VALU /
 // per-element: 4096: 0.62 / 0.40, 16384: 0.68 / 1.46), and so do keys that the
 // RNS engine does not take (512 bits, 16384: 2.71 / 4.05; 1024: 9.6 / 11.6).
 enum Engine { ENG_VALU, ENG_ELEM, ENG_RNS };
-constexpr size_t RNS_MIN_COUNT[pc2k::NUM_CLASSES] = {0, 0, 0, 0, 4097, 3584, 3840, 6656, 7424};
+constexpr size_t RNS_MIN_COUNT[pc2k::NUM_CLASSES] = {0, 0, 0, 0, 4097, 3584, 3840, 7169, 7169};
 constexpr size_t ELEM_MAX_COUNT[pc2k::NUM_CLASSES] = {0, 0, 0, 4096, 8192, 12288};
 Engine enc_engine(const pc2_ctx* ctx, const pc2_pk* pk, size_t count) {
   if (ctx->modmul == PC2_MODMUL_VALU) return ENG_VALU;
@@ -1792,22 +1817,11 @@ struct KeyJobs {
 };
 int key_ebits(const KeyJobs& k) { return k.sk ? k.sk->c.ebits : (int)k.pk->nbits; }
 
-// Estimates in microseconds for the choice between the engines where a launch
-// holds several keys (rns_choose), all per bit of the exponents.  On residues
-// every key is a launch sequence of its own, however few its elements (16
-// decryptions of 1024 / 2048 / 3072 / 4096 bits: 1.24 / 3.3 / 7.3 / 13.1 ms a
-// key).  A unit of RnsPlan::cost by tile count: with a few workgroups, with one on
-// every compute unit, and how steeply it falls from there, as the units then
-// stream fewer copies of the constants (encryptions of 3072 bits on 129 / 208 / 256
-// units: 5.3 / 7.6 / 8.1; 4096 bits on 129 / 232 / 256: 8.4 / 13.1 / 14).
-struct RnsUnit { double few, full, drop; };
-constexpr RnsUnit RNS_UNIT[pc2k::RNS_NT] = {{0.97, 1.1, 0.3},  {1.30, 1.6, 0.6},
-                                            {1.91, 2.4, 1.0},  {3.05, 3.9, 1.45},
-                                            {5.0, 8.1, 5.6},   {8.0, 14.0, 11.3}};
+// Estimates in microseconds per bit of the exponents for the choice between the
+// engines where a launch holds several keys (rns_choose).  On residues every key
+// is a launch sequence of its own, however few its elements (rns_unit).
 double rns_time(const pc2_ctx* ctx, const RnsPlan& p, int nmod, int ebits) {
-  const RnsUnit u = RNS_UNIT[rns_index(p.T)];
-  const double fill = std::min(1.0, (double)(p.ngroups * nmod) / ctx->cus);
-  return p.cost * std::max(u.few, u.full - (1 - fill) * u.drop) * ebits;
+  return p.cost * rns_unit(ctx, p, nmod) * ebits;
 }
 // The persistent kernels run all keys of a launch together: no sooner than one
 // element's chain of products, and than the device does the products of all

@@ -306,3 +306,19 @@ def test_unequal_primes(gpu_ctx, pbits, qbits):
     with _valu(gpu_ctx):
         assert got == gpu_decrypt(gpu_ctx, sk, bad)
     assert got[0][0] == ms[0] and got[0][1] == got[0][2] == 0
+
+
+# the last count on wavefronts of its own and the first on the engine from
+# 3072-bit keys on, where two column blocks a workgroup take half of the units
+@pytest.mark.parametrize("nbits,count", [
+    (3072, 7168), (3072, 7169), (3072, 8193), (4096, 7168), (4096, 7169), (4096, 8193)])
+def test_encrypt_engine_edges(gpu_ctx, nbits, count):
+    sk, opk, _ = _key(gpu_ctx, nbits)
+    ms, rs = _ms_rs(opk.n, 60, count)
+    reps = -(-count // 60)
+    ms, rs = (ms * reps)[:count], (rs * reps)[:count]
+    got, st = gpu_encrypt(gpu_ctx, sk.public, ms, rs)
+    assert st == 0 and got[:4] == [O.encrypt(opk, m, r) for m, r in zip(ms[:4], rs[:4])]
+    with _valu(gpu_ctx):
+        want, st = gpu_encrypt(gpu_ctx, sk.public, ms[:60], rs[:60])
+    assert st == 0 and got == (want * reps)[:count]
