@@ -144,7 +144,7 @@ def roofline_mfma(nbits_n: int, mm: int, count: int, secs: float) -> dict:
 
 
 # tiles of 16 channels per base of the residue-number-system engine, by bits of
-# n^2 (keys from 1024 bits; encryptions of thousands of elements)
+# n^2 (encryptions of thousands of elements; scalar products and mat-vecs)
 RNS_T = {2048: 9, 4096: 17, 6144: 26, 8192: 34}
 
 
@@ -731,7 +731,7 @@ def run_matvec(pc2, gen, ctx, sk, torch, np, args) -> dict:
     if ctx.sync() != 0:
         raise RuntimeError("device reported a data error while preparing the mat-vec")
     mv = pc2.MatVec(sk.public, D, MATVEC_EBITS, 0, rows_hint=D)
-    w, nw = mv.window, -(-MATVEC_EBITS // mv.window)
+    w, nw, residues, table_bytes = mv.window, mv.digits, mv.residues, mv.table_bytes
     stream = torch.cuda.current_stream()
     ev = [torch.cuda.Event(enable_timing=True) for _ in range(3)]
     t_tab, t_app = [], []
@@ -762,21 +762,25 @@ def run_matvec(pc2, gen, ctx, sk, torch, np, args) -> dict:
         want = (int(a[i]) + int(np.dot(Bh[i].astype(object), m))) % n
         got = sum(int(decs[i, k]) << (32 * k) for k in range(L))
         ok &= got == want
-    per_mm = 2 * (2 * L) ** 2 + 2 * L
-    mm_tab = D * sum(w * t + (1 << w) - 1 for t in range(nw))
+    # a plan on residues cuts the constants into digits as even as their bits
+    # allow, one on the VALU into digits of the window's bits
+    lo, wide = divmod(MATVEC_EBITS, nw) if residues else (w, 0)
+    widths = [lo + (t < wide) for t in range(nw)]
+    mm_tab = D * sum(sum(widths[:t]) + (1 << widths[t]) - 1 for t in range(nw))
     mm_app = D * D * nw
     tt, ta = float(np.median(t_tab)) / 1e3, float(np.median(t_app)) / 1e3
-    achieved = (mm_tab + mm_app) * per_mm / (tt + ta)
-    log(f"matvec {D}x{D}: w {w}, tables {tt * 1e3:.1f} ms, rows {ta * 1e3:.1f} ms, "
-        f"{achieved / 1e12:.2f} T products/s, exact {ok}")
+    products = mm_tab + mm_app
+    roof = (roofline_rns(NBITS, products, 1, tt + ta) if residues
+            else roofline_valu(products * (2 * (2 * L) ** 2 + 2 * L), tt + ta))
+    log(f"matvec {D}x{D}: {nw} digits on {'residues' if residues else 'the VALU'}, "
+        f"tables {tt * 1e3:.1f} ms, rows {ta * 1e3:.1f} ms, exact {ok}")
     return {"workload": f"2048-bit key, B {D}x{D} of {MATVEC_EBITS}-bit constants, c and alpha "
                         f"encryptions of quantized N(0,1) data: out = alpha * c^B mod n^2",
-            "window": w, "table_bytes": int(D * nw * ((1 << w) - 1) * 640),
+            "window": w, "digits": nw, "table_bytes": table_bytes,
             "tables_ms": round(tt * 1e3, 2), "rows_ms": round(ta * 1e3, 2),
-            "montgomery_products": mm_tab + mm_app,
+            "montgomery_products": products,
             "powers_per_s": round(D * D / (tt + ta), 1),
-            "achieved_T_products_per_s": round(achieved / 1e12, 3),
-            "frac_of_peak": round(achieved / PEAK_PRODUCTS, 4),
+            "roofline": roof,
             "sampled_rows_exact": bool(ok)}
 
 

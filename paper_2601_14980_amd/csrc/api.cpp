@@ -126,10 +126,11 @@ struct pc2_matvec {
   size_t parts_bytes = 0;
   int cap_table = 1, cap_apply = 1;  // resident workgroups of the two kernels
   bool loaded = false;
-  // on the RNS engine (rw > 0): digits of rw bits, rnw of them, entries d < 2^rw
+  // on the RNS engine (rdg.n > 0): the digits of the constants, whose entries are
   // in tab; the running values of rblocks blocks of 32 rows, and a flag per row
-  int rw = 0, rnw = 0;
+  pc2k::RnsDigits rdg{};
   uint8_t* rstage = nullptr;
+  size_t rstage_bytes = 0;
   uint32_t* rbad = nullptr;
   size_t rblocks = 0;
   hipEvent_t done = nullptr;  // after the last call that used them, on done_stream
@@ -2874,13 +2875,14 @@ RnsMvShape rns_mv_shape(pc2_ctx* ctx, int T, size_t cols, int nw, size_t rows, s
   return best;
 }
 
-// The RNS engine for a plan: the digit width of the least time among those
-// whose tables take no more than the plan's table bytes and a sixteenth (which
-// lets 9-bit digits stand for 10-bit ones) or 128 MB; false if there is none or
-// the device has no memory for it.  It is the faster one from a single
-// row up (load / apply in ms, RNS against VALU, ebits 50: 1024 bits, 64 rows x
-// 16 columns 0.18 / 0.16 against 1.03 / 2.1; 4096 bits, 64 x 16: 1.2 / 1.05
-// against 4.1 / 1.4; 2048 bits, 256 x 256: 0.42 / 1.4 against 2.2 / 4.8).
+// The RNS engine for a plan: the number of digits of the least time among those
+// whose tables fit the plan's table bytes; false if there is none or the device has
+// no memory for it.  Its entries are 1.7 times the VALU engine's, so windows of 1
+// and 2 bits stay there; otherwise it is the faster one from a single row up (load
+// / apply in ms, RNS against VALU, ebits 50: 1024 bits, 64 rows x 16 columns 0.16 /
+// 0.16 against 1.02 / 2.1; 2048 bits, 256 x 256: 0.39 / 1.17 against 2.2 / 4.8, window
+// 3: 0.36 / 2.0 against 1.6 / 5.6; 4096 bits, 64 x 16: 1.1 / 1.07 against 4.1 /
+// 1.44).
 bool rns_matvec_create(pc2_matvec* mv, size_t rows_hint) {
   pc2_ctx* ctx = mv->ctx;
   const int T = mv->pk->rn.T;
@@ -2891,35 +2893,31 @@ bool rns_matvec_create(pc2_matvec* mv, size_t rows_hint) {
   const size_t Gc = (mv->cols + 31) / 32, most = 2 * slots;
   // (no hint: rows enough that the tables' cost is small, as for the window)
   const size_t rows = std::min(rows_hint ? rows_hint : (size_t)8192, most * 32);
-  auto table = [&](int w) {
-    return mv->cols * (size_t)((mv->ebits + w - 1) / w) * ((size_t)64 * T << w);
-  };
   double best = 0;
-  for (int w = 1; w <= 12; ++w) {
-    const size_t nw = (size_t)((mv->ebits + w - 1) / w);
-    if (table(w) > std::max(mv->table_bytes + mv->table_bytes / 16, (size_t)128 << 20)) break;
-    const double cost =
-        rns_mv_shape(ctx, T, mv->cols, (int)nw, rows, most).cost +
-        2.45 * (double)((Gc * nw + tslots - 1) / tslots) *
-            (double)(((size_t)1 << w) + (size_t)w * (nw - 1));
-    if (mv->rw == 0 || cost < best) {
+  for (int nw = (mv->ebits + 11) / 12; nw <= mv->ebits; ++nw) {
+    const pc2k::RnsDigits dg = pc2k::RnsDigits::of(mv->ebits, nw);
+    if (mv->cols * (dg.entries() * (size_t)64 * T) > mv->table_bytes) continue;
+    const double cost = rns_mv_shape(ctx, T, mv->cols, nw, rows, most).cost +
+                        2.45 * (double)((Gc * nw + tslots - 1) / tslots) *
+                            (double)(((size_t)1 << dg.width(0)) + (size_t)dg.shift(nw - 1));
+    if (mv->rdg.n == 0 || cost < best) {
       best = cost;
-      mv->rw = w;
-      mv->rnw = (int)nw;
+      mv->rdg = dg;
     }
   }
-  if (mv->rw == 0) return false;
-  mv->rblocks = std::max(most, Gc + std::min(tslots, Gc * mv->rnw));
+  if (mv->rdg.n == 0) return false;
+  mv->rblocks = std::max(most, Gc + std::min(tslots, Gc * mv->rdg.n));
   const size_t stage = mv->rblocks * pc2k::rns_group_bytes(T, 1);
-  if (hipMalloc(&mv->tab, table(mv->rw)) != hipSuccess ||
-      hipMalloc(&mv->rstage, stage + mv->rblocks * 32 * 4) != hipSuccess ||
+  mv->rstage_bytes = stage + mv->rblocks * 32 * 4;
+  if (hipMalloc(&mv->tab, mv->table_bytes) != hipSuccess ||
+      hipMalloc(&mv->rstage, mv->rstage_bytes) != hipSuccess ||
       hipEventCreateWithFlags(&mv->done, hipEventDisableTiming) != hipSuccess) {
     (void)hipGetLastError();
     if (mv->tab) (void)hipFree(mv->tab);
     if (mv->rstage) (void)hipFree(mv->rstage);
     mv->tab = nullptr;
     mv->rstage = nullptr;
-    mv->rw = 0;
+    mv->rdg = {};
     return false;
   }
   mv->rbad = reinterpret_cast<uint32_t*>(mv->rstage + stage);
@@ -2957,8 +2955,7 @@ int rns_matvec_load(pc2_matvec* mv, const uint32_t* c, void* stream) {
   t.c = c;
   t.n2 = mv->pk->c.n2.Nl;
   t.L2 = L2;
-  t.w = mv->rw;
-  t.nw = mv->rnw;
+  t.dg = mv->rdg;
   t.ngroups = (int)Gc;
   t.cols = mv->cols;
   t.err = ctx->err;
@@ -2966,7 +2963,7 @@ int rns_matvec_load(pc2_matvec* mv, const uint32_t* c, void* stream) {
                                      L2, mv->rstage, stream);
   if (e == hipSuccess)
     e = pc2k::launch_rns_gather(K.T, 1, pc2k::RNS_MVTAB,
-                                (int)std::min<size_t>(slots, Gc * mv->rnw), &t, stream);
+                                (int)std::min<size_t>(slots, Gc * mv->rdg.n), &t, stream);
   return stage_end(mv, stream, status_of(e));
 }
 
@@ -2978,7 +2975,7 @@ int rns_matvec_apply(pc2_matvec* mv, const uint64_t* B, const uint32_t* alpha, u
   int rc = stage_begin(mv, stream);
   for (size_t at = 0; at < rows && !rc; at += mv->rblocks * 32) {
     const size_t n = std::min(rows - at, mv->rblocks * 32);
-    const RnsMvShape S = rns_mv_shape(ctx, K.T, mv->cols, mv->rnw, n, mv->rblocks);
+    const RnsMvShape S = rns_mv_shape(ctx, K.T, mv->cols, mv->rdg.n, n, mv->rblocks);
     const uint32_t* a = alpha ? alpha + at * L2 : nullptr;
     const pc2k::RnsJobs J = one_job(a, nullptr, 0, out + at * L2, n);
     pc2k::RnsMv m{};
@@ -2993,8 +2990,7 @@ int rns_matvec_apply(pc2_matvec* mv, const uint64_t* B, const uint32_t* alpha, u
     m.chunk_cols = S.chunk_cols;
     m.alpha = alpha != nullptr;
     m.ebits = mv->ebits;
-    m.w = mv->rw;
-    m.nw = mv->rnw;
+    m.dg = mv->rdg;
     m.nch = (int)S.nch;
     m.ngroups = (int)S.groups;
     hipError_t e = pc2k::launch_rns_row_check(a, mv->pk->c.n2.Nl, (int)L2, mv->rbad, n, stream);
@@ -3086,10 +3082,19 @@ int pc2_matvec_info(const pc2_matvec* mv, uint32_t* window, size_t* table_bytes)
   return PC2_OK;
 }
 
+int pc2_matvec_engine(const pc2_matvec* mv, int* residues, uint32_t* digits,
+                      size_t* staging_bytes) {
+  if (!mv) return PC2_E_INVAL;
+  if (residues) *residues = mv->rdg.n > 0;
+  if (digits) *digits = (uint32_t)(mv->rdg.n ? mv->rdg.n : mv->nw);
+  if (staging_bytes) *staging_bytes = mv->rdg.n ? mv->rstage_bytes : mv->parts_bytes;
+  return PC2_OK;
+}
+
 int pc2_matvec_load(pc2_matvec* mv, const uint32_t* c, void* hip_stream) {
   if (!mv || !mv->ctx || !c) return PC2_E_INVAL;
   if (hipSetDevice(mv->ctx->device) != hipSuccess) return PC2_E_DEVICE;
-  if (mv->rw) {
+  if (mv->rdg.n) {
     const int rc = rns_matvec_load(mv, c, hip_stream);
     if (!rc) mv->loaded = true;
     return rc;
@@ -3118,7 +3123,7 @@ int pc2_matvec_apply(pc2_matvec* mv, const uint64_t* B, const uint32_t* alpha, u
     if (a0 < o0 + rows * row_bytes && o0 < a0 + rows * row_bytes) return PC2_E_INVAL;
   }
   if (hipSetDevice(ctx->device) != hipSuccess) return PC2_E_DEVICE;
-  if (mv->rw) return rns_matvec_apply(mv, B, alpha, out, rows, hip_stream);
+  if (mv->rdg.n) return rns_matvec_apply(mv, B, alpha, out, rows, hip_stream);
   // column chunks, as many as the plan's staging holds for this many rows
   const size_t epw = (size_t)pc2k::elems_per_block(cls);
   const size_t gpc = (rows + epw - 1) / epw;

@@ -208,9 +208,9 @@ __global__ __launch_bounds__(G::W * 64, 2) void k_rns_smul(RnsSmul P) {
   PC2R_SIDES(G, wave, (smul_run<G, SIDE>(P, ws, wave, lane)));
 }
 
-// Fixed-base tables of the ciphertext matrix-vector product: item (window t,
-// column group) takes the columns' c_j to c_j^(2^(w t)) and writes its powers
-// d < 2^w in Montgomery form, each element's entry on its own (2 T x 32
+// Fixed-base tables of the ciphertext matrix-vector product: item (digit t,
+// column group) takes the columns' c_j to c_j^(2^shift(t)) and writes its powers
+// d < 2^width(t) in Montgomery form, each element's entry on its own (2 T x 32
 // bytes: base B, base A).  A column with c_j >= n^2 gets zeros (entry 0, the
 // Montgomery one, apart).
 template <class G, int SIDE>
@@ -223,16 +223,18 @@ __device__ __forceinline__ void mvtab_run(const RnsMvTab& P, RWork<G>& ws, int w
   const int n = lane & 31, h = lane >> 5;
   const Buf base(P.table + (size_t)blockIdx.x * GB, (uint32_t)GB);
   const Buf one(P.one, G::T * 64), r2(P.one + G::T * 64, G::T * 64);
-  const int per = 1 << P.w;
-  for (int it = blockIdx.x; it < P.ngroups * P.nw; it += gridDim.x) {
-    const int win = P.nw - 1 - it / P.ngroups, g = it % P.ngroups;  // the longest first
+  const pc2k::RnsDigits D = P.dg;
+  const size_t col = D.entries() * EB;
+  for (int it = blockIdx.x; it < P.ngroups * D.n; it += gridDim.x) {
+    const int win = D.n - 1 - it / P.ngroups, g = it % P.ngroups;  // the longest first
+    const int per = 1 << D.width(win);
     const Buf in(P.in + (size_t)g * GB, (uint32_t)GB);
-    uint8_t *ent[G::NB], *entu = nullptr;  // entry 0 of the lane's element
+    uint8_t *ent[G::NB], *entu = nullptr;  // the entry before the digit's first
     bool ok[G::NB], oku = false;
     auto where = [&](int b, bool& good) -> uint8_t* {
       const size_t j = ((size_t)g * G::NB + b) * 32 + n;
       good = j < P.cols && pc2d::sc_cmp(P.c + j * P.L2, P.L2, P.n2, P.L2) < 0;
-      return j < P.cols ? P.tab + ((j * P.nw + win) << P.w) * EB + h * 16 : nullptr;
+      return j < P.cols ? P.tab + j * col + D.before(win) * EB + h * 16 : nullptr;
     };
 #pragma unroll
     for (int b = 0; b < G::NB; ++b) ent[b] = where(b, ok[b]);
@@ -243,7 +245,7 @@ __device__ __forceinline__ void mvtab_run(const RnsMvTab& P, RWork<G>& ws, int w
         if (ent[b] && !ok[b]) atomicOr(P.err, pc2k::ERR_RANGE);
     st.each([&](int t, int b, bool u) {
       uint8_t* p = u ? entu : ent[b];
-      if (!p) return;
+      if (!p || win != 0) return;
       *reinterpret_cast<v4u*>(p + t * 32) = one.load(h * 16, t * 32);
       *reinterpret_cast<v4u*>(p + (G::T + t) * 32) = one.load(h * 16, (G::T + t) * 32);
     });
@@ -255,8 +257,8 @@ __device__ __forceinline__ void mvtab_run(const RnsMvTab& P, RWork<G>& ws, int w
           return in.load(lane * 16, at);
         },
         [&](int t, int, bool, const v4u&) { return r2.load(h * 16, (G::T + t) * 32); });
-    // products: c MA, w t squarings (the last result is entry 1), then by the base
-    const int nsq = P.w * win;
+    // products: c MA, the squarings (the last result is entry 1), then by the base
+    const int nsq = D.shift(win);
     OP o{}, nx{};
     o.dst = nx.dst = nx.y = base;
 #pragma unroll 1
@@ -294,7 +296,7 @@ __global__ __launch_bounds__(G::W * 64, 2) void k_rns_mvtab(RnsMvTab P) {
 // Rows of the ciphertext matrix-vector product: item (column chunk, row group)
 // multiplies its rows' start values (the first chunk's in place if there is an
 // alpha, else 1; the other chunks' the Montgomery one) by one table entry per
-// w-bit digit of each of the chunk's constants.  A digit that is zero in the
+// digit of each of the chunk's constants.  A digit that is zero in the
 // whole group is skipped (every wavefront of a workgroup sees the same digits).
 template <class G, int SIDE>
 __device__ __forceinline__ void mv_run(const RnsMv& P, RWork<G>& ws, int wave, int lane) {
@@ -304,7 +306,8 @@ __device__ __forceinline__ void mv_run(const RnsMv& P, RWork<G>& ws, int wave, i
   Stepper<G, SIDE, OP> st(wave, lane);
   const RConst<G> M(P.M);
   const int n = lane & 31, h = lane >> 5;
-  const uint32_t dmask = (1u << P.w) - 1;
+  const pc2k::RnsDigits D = P.dg;
+  const uint32_t col = D.entries() * (uint32_t)EB;
   for (int it = blockIdx.x; it < P.ngroups * P.nch; it += gridDim.x) {
     const int ch = it / P.ngroups, g = it % P.ngroups;
     const Buf in(P.in + (size_t)it * GB, (uint32_t)GB);
@@ -329,11 +332,11 @@ __device__ __forceinline__ void mv_run(const RnsMv& P, RWork<G>& ws, int wave, i
       en[b] = row[b][j0];
     }
     size_t j = j0 - 1;
-    int win = P.nw - 1;
+    int win = D.n - 1;
     // the next digit with work into o; false at the end
     auto advance = [&](OP& o) -> bool {
       for (;;) {
-        if (++win == P.nw) {
+        if (++win == D.n) {
           if (++j == j1) return false;
           win = 0;
 #pragma unroll
@@ -343,16 +346,18 @@ __device__ __forceinline__ void mv_run(const RnsMv& P, RWork<G>& ws, int wave, i
             if (j + 1 < j1) en[b] = row[b][j + 1];
           }
         }
+        const uint32_t mask = (1u << D.width(win)) - 1, before = D.before(win);
+        const int shift = D.shift(win);
         uint32_t any = 0;
 #pragma unroll
         for (int b = 0; b < G::NB; ++b) {
-          const uint32_t d = (uint32_t)(e[b] >> (P.w * win)) & dmask;
+          const uint32_t d = (uint32_t)(e[b] >> shift) & mask;
           any |= d;
-          o.off[b] = d * (uint32_t)EB + h * 16;
+          o.off[b] = (d ? before + d : 0u) * (uint32_t)EB + h * 16;
           if (b == st.bu) o.offu = o.off[b];
         }
         if (__ballot(any != 0) == 0) continue;
-        o.y = Buf(P.tab + ((j * P.nw + win) << P.w) * EB, (uint32_t)(EB << P.w));
+        o.y = Buf(P.tab + j * (size_t)col, col);
         return true;
       }
     };

@@ -106,14 +106,31 @@ struct RnsSmul {         // c^k, k_rns_smul
   size_t count;
   int ngroups;
 };
+// A constant of the mat-vec in n digits, as even as its bits allow: the first x
+// of them lo + 1 bits wide, the others lo, which holds the smallest tables for a
+// number of digits.  A column's table is entry 0, the Montgomery one, for every
+// digit that is zero, and then each digit's entries 1 .. 2^width - 1.
+struct RnsDigits {
+  int n, lo, x;
+  __host__ __device__ static RnsDigits of(int ebits, int n) { return {n, ebits / n, ebits % n}; }
+  __host__ __device__ int wide(int t) const { return t < x ? t : x; }  // of the digits below t
+  __host__ __device__ int width(int t) const { return lo + (t < x ? 1 : 0); }
+  __host__ __device__ int shift(int t) const { return lo * t + wide(t); }
+  // entry d >= 1 of digit t is before(t) + d
+  __host__ __device__ uint32_t before(int t) const {
+    return (uint32_t)t * ((1u << lo) - 1) + ((uint32_t)wide(t) << lo);
+  }
+  __host__ __device__ uint32_t entries() const { return before(n) + 1; }
+};
 struct RnsMvTab {        // k_rns_mvtab
   RnsMod M;
   const uint8_t* one;
   const uint8_t* in;     // c_j
   uint8_t* table;        // one entry per workgroup
-  uint8_t* tab;          // [cols][nw][2^w] entries
+  uint8_t* tab;          // [cols][dg.entries()]
   const uint32_t *c, *n2;
-  int L2, w, nw, ngroups;
+  RnsDigits dg;
+  int L2, ngroups;
   size_t cols;
   int* err;
 };
@@ -125,7 +142,8 @@ struct RnsMv {           // k_rns_mv, k_rns_chain
   const uint64_t* B;
   uint32_t* bad;         // per row
   size_t rows, cols, chunk_cols;
-  int alpha, ebits, w, nw, nch, ngroups;  // alpha: the first chunk's values are set; ngroups: of rows
+  RnsDigits dg;
+  int alpha, ebits, nch, ngroups;  // alpha: the first chunk's values are set; ngroups: of rows
 };
 
 constexpr int RNS_NT = 6, RNS_NBMAX = 4;

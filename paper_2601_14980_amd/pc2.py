@@ -50,7 +50,7 @@ EXPORTS = [
     "pc2_pk_info", "pc2_quantize", "pc2_dequantize", "pc2_encrypt", "pc2_encrypt_sk",
     "pc2_decrypt", "pc2_decrypt_static",
     "pc2_hom_add", "pc2_hom_scalar_mul", "pc2_hom_sum", "pc2_enc_sum_dec",
-    "pc2_matvec_create", "pc2_matvec_info", "pc2_matvec_load", "pc2_matvec_apply",
+    "pc2_matvec_create", "pc2_matvec_info", "pc2_matvec_engine", "pc2_matvec_load", "pc2_matvec_apply",
     "pc2_matvec_destroy", "pc2_colsplit_create", "pc2_colsplit_set_scale",
     "pc2_colsplit_iterate", "pc2_colsplit_destroy",
     "pc2_batch_create", "pc2_batch_run", "pc2_batch_destroy", "pc2_autotune",
@@ -115,6 +115,7 @@ def _load() -> ctypes.CDLL:
                                     c_size_t, P]),
         "pc2_matvec_create": (c_int, [P, c_size_t, c_uint32, c_uint32, c_size_t, POINTER(P)]),
         "pc2_matvec_info": (c_int, [P, POINTER(c_uint32), POINTER(c_size_t)]),
+        "pc2_matvec_engine": (c_int, [P, POINTER(c_int), POINTER(c_uint32), POINTER(c_size_t)]),
         "pc2_matvec_load": (c_int, [P, P, P]),
         "pc2_matvec_apply": (c_int, [P, P, P, P, c_size_t, P]),
         "pc2_matvec_destroy": (c_int, [P]),
@@ -419,6 +420,11 @@ class MatVec:
         _check(lib.pc2_matvec_info(h, byref(w), byref(nb)), "pc2_matvec_info")
         self.window = w.value
         self.table_bytes = nb.value
+        res, nd = c_int(), c_uint32()
+        _check(lib.pc2_matvec_engine(h, byref(res), byref(nd), byref(nb)), "pc2_matvec_engine")
+        self.residues = bool(res.value)
+        self.digits = nd.value
+        self.staging_bytes = nb.value
 
     def load(self, c: torch.Tensor, stream=None) -> None:
         if _rows(c, 2 * self.pk.L, "c") != self.cols:

@@ -74,6 +74,19 @@ int sim_from(const uint32_t* N0, int nn, const uint32_t* x0, int nx, int T, int 
   return 0;
 }
 
+// A constant's digits (RnsDigits): for each its shift, width, and the table entries
+// of its values 1 and 2^width - 1; returns the entries of a column.
+int sim_digits(int ebits, int n, int32_t* out) {
+  const pc2k::RnsDigits d = pc2k::RnsDigits::of(ebits, n);
+  for (int t = 0; t < n; ++t) {
+    out[4 * t] = d.shift(t);
+    out[4 * t + 1] = d.width(t);
+    out[4 * t + 2] = (int32_t)(d.before(t) + 1);
+    out[4 * t + 3] = (int32_t)(d.before(t) + ((1u << d.width(t)) - 1));
+  }
+  return (int)d.entries();
+}
+
 // MA of a tile count (its words; returns how many)
 int sim_ma(int T, uint32_t* out) {
   const Limbs& m = pc2h::rns_base(T).MA;
