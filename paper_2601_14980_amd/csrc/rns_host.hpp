@@ -2,6 +2,7 @@
 // everything that depends on them alone, once per tile count, and a modulus'
 // own matrices and conversion tables, once per key.
 #pragma once
+#include <array>
 #include <cmath>
 #include <cstdint>
 #include <mutex>
@@ -146,7 +147,8 @@ inline uint32_t pair16(int32_t lo, int32_t hi) {
   return ((uint32_t)lo & 0xFFFFu) | ((uint32_t)hi << 16);
 }
 
-inline RnsBase make_rns_base(int T) {
+// mt: tiles a wavefront owns, at most
+inline RnsBase make_rns_base(int T, int mt) {
   RnsBase R;
   R.T = T;
   const int n = R.n = 16 * T;
@@ -221,6 +223,7 @@ inline RnsBase make_rns_base(int T) {
     R.ka[at + 16 + u] = pair16(centred(-(int64_t)mb, R.a[c]), centred(-4096ll * mb, R.a[c]));
     if (R.a[c] >= 60000 || R.b[c] >= 60000) R.ok = false;
   }
+  std::vector<std::array<double, 2>> beta(2 * T, {0.0, 0.0});  // by tile half
   for (int c = 0; c < n; c += 2) {  // g_j / b_j = F1 2^-12 + F2 2^-25
     int32_t f1[2], f2[2];
     for (int k = 0; k < 2; ++k) {
@@ -232,7 +235,20 @@ inline RnsBase make_rns_base(int T) {
     const int u = (c & 7) / 2;
     R.kb[at + 16 + u] = pair16(f1[0], f1[1]);
     R.kb[at + 20 + u] = pair16(f2[0], f2[1]);
+    for (int k = 0; k < 2; ++k) {
+      // a lane's part of beta (s1, s2 of finish_b): its half of mt tiles, |w| < 0.52 b
+      const double z = 0.52 * R.b[c + k];
+      beta[c / 8][0] += z * std::abs(f1[k]);
+      beta[c / 8][1] += z * std::abs(f2[k]);
+    }
   }
+  for (int h = 0; h < 2; ++h)
+    for (int t = 0; t + mt <= T; ++t)
+      for (int i = 0; i < 2; ++i) {
+        double sum = 0;
+        for (int m = 0; m < mt; ++m) sum += beta[2 * (t + m) + h][i];
+        if (sum >= 2147483648.0) R.ok = false;
+      }
   return R;
 }
 
@@ -240,7 +256,7 @@ inline RnsBase make_rns_base(int T) {
 inline const RnsBase& rns_base(int T) {
   static std::once_flag once[64];
   static RnsBase* made[64];
-  std::call_once(once[T], [T] { made[T] = new RnsBase(make_rns_base(T)); });
+  std::call_once(once[T], [T] { made[T] = new RnsBase(make_rns_base(T, pc2k::rns_mt(T))); });
   return *made[T];
 }
 

@@ -84,6 +84,7 @@ struct RGeo {
   static constexpr int WG = W_ == 8 ? 1 : 2;           // workgroups a CU is planned for
   static constexpr bool KL = (LDS + T_ * 448) * WG <= 160 * 1024;
   static_assert(MT >= 1 && (!XY_ || W_ == 8), "wavefronts");
+  static_assert(MT <= pc2k::rns_mt(T_), "the bound on a lane's sums of beta");
   static_assert(RX * NB_ <= (XY_ ? W_ / 2 : W_) && RY * NB_ <= W_ / 2, "one unit a wavefront");
 };
 

@@ -148,6 +148,14 @@ struct RnsMv {           // k_rns_mv, k_rns_chain
 
 constexpr int RNS_NT = 6, RNS_NBMAX = 4;
 constexpr int RNS_T[RNS_NT] = {5, 9, 13, 17, 26, 34};  // compiled tile counts
+// the most tiles that a wavefront owns in their geometries: a lane sums over the
+// channels of that many tile halves in 32 bits (RGeo, make_rns_base)
+constexpr int RNS_MT[RNS_NT] = {1, 2, 3, 2, 3, 4};
+constexpr int rns_mt(int T) {
+  for (int i = 0; i < RNS_NT; ++i)
+    if (RNS_T[i] == T) return RNS_MT[i];
+  return 0;
+}
 
 // A modulus and its programs for window widths 2..6.
 struct RnsKey {

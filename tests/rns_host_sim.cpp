@@ -74,6 +74,10 @@ int sim_from(const uint32_t* N0, int nn, const uint32_t* x0, int nx, int T, int 
   return 0;
 }
 
+// Whether the bounds on 32-bit sums hold for tile count T with mt tiles a wavefront
+// (0: the compiled ones).
+int sim_bounds(int T, int mt) { return pc2h::make_rns_base(T, mt ? mt : pc2k::rns_mt(T)).ok; }
+
 // A constant's digits (RnsDigits): for each its shift, width, and the table entries
 // of its values 1 and 2^width - 1; returns the entries of a column.
 int sim_digits(int ebits, int n, int32_t* out) {

@@ -80,3 +80,12 @@ def test_matvec_digits(lib, ebits):
             shift, at = shift + w, last + 1
         assert shift == ebits and at == entries
         assert max(out[:, 1]) - min(out[:, 1]) <= 1
+
+
+# the compiled splits keep every 32-bit sum in range, and splits that would not are
+# refused (the sums of beta at T = 34 reach 0.78 of 2^31 with four tiles a wavefront)
+@pytest.mark.parametrize("T,mt,ok", [
+    (5, 0, 1), (9, 0, 1), (13, 0, 1), (17, 0, 1), (26, 0, 1), (34, 0, 1),
+    (34, 4, 1), (34, 6, 0), (34, 8, 0), (17, 4, 1), (17, 8, 0)])
+def test_bounds_of_the_splits(lib, T, mt, ok):
+    assert lib.sim_bounds(T, mt) == ok
