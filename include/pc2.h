@@ -124,7 +124,8 @@ int pc2_ctx_reserve(pc2_ctx *ctx, uint32_t max_nbits);
  * on residues run as one launch sequence per key.
  * PC2_OPT_TILE: the limb tile of the VALU encryption kernels (pc2_encrypt,
  * batches and runners of encryptions), i.e. how many lanes of a wavefront
- * share one ciphertext.  1024-bit keys run with 2 (own) or 4 lanes,
+ * share one ciphertext.  A tile asked for (not 0) also asks for these kernels
+ * where PC2_MODMUL_AUTO leaves the choice open, under keys of up to 1024 bits.  1024-bit keys run with 2 (own) or 4 lanes,
  * 2048-bit keys with 4 (own) or 8; other sizes have their own tile only.
  * Values: 0 = automatic (pc2_encrypt of at most one wavefront per SIMD of
  * the wider tile, i.e. count <= 4 * CUs * 64 / lanes, takes the wider tile,

@@ -958,10 +958,10 @@ constexpr size_t RNS_MIN_COUNT[pc2k::NUM_CLASSES] = {0, 0, 0, 0, 4097, 3584, 384
 constexpr size_t ELEM_MAX_COUNT[pc2k::NUM_CLASSES] = {0, 0, 0, 4096, 8192, 12288};
 Engine enc_engine(const pc2_ctx* ctx, const pc2_pk* pk, size_t count) {
   if (ctx->modmul == PC2_MODMUL_VALU) return ENG_VALU;
+  const bool mfma = use_mfma(ctx, pk->cls);
+  if (ctx->tile && !mfma) return ENG_VALU;  // a tile asked for is a tile of the VALU engine
   if (pk->rn.T && count >= RNS_MIN_COUNT[pk->cls]) return ENG_RNS;
-  if (use_mfma(ctx, pk->cls)) return ENG_ELEM;
-  // (a tile asked for by option is a tile of the VALU engine)
-  return !ctx->tile && count <= ELEM_MAX_COUNT[pk->cls] ? ENG_ELEM : ENG_VALU;
+  return mfma || count <= ELEM_MAX_COUNT[pk->cls] ? ENG_ELEM : ENG_VALU;
 }
 // The matrix-core encryption of `count` elements by workgroups of several
 // wavefronts per element (mfma_team.hpp): while one round of them holds all
