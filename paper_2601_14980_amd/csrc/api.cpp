@@ -2600,8 +2600,8 @@ int pc2_runner_group_size(const pc2_pk* pk, int op_abi, uint32_t* elems) {
   return PC2_OK;
 }
 
-int pc2_runner_launch(pc2_runner* r, const pc2_job* jobs, const size_t* first,
-                      const size_t* ngroups, size_t njobs, void* hip_stream) {
+static int runner_launch(pc2_runner* r, const pc2_job* jobs, const size_t* first,
+                         const size_t* ngroups, size_t njobs, void* hip_stream) {
   if (!r || !r->ctx || !jobs || !first || !ngroups || njobs == 0) return PC2_E_INVAL;
   if (njobs > r->max_jobs) return PC2_E_BUSY;
   pc2_ctx* ctx = r->ctx;
@@ -2793,6 +2793,15 @@ int pc2_runner_launch(pc2_runner* r, const pc2_job* jobs, const size_t* first,
   for (const RnsPart& p : parts)
     if (!rc) rc = rns_part_run(ctx, p, op, r->rscratch, hip_stream);
   return rc;
+}
+
+int pc2_runner_launch(pc2_runner* r, const pc2_job* jobs, const size_t* first,
+                      const size_t* ngroups, size_t njobs, void* hip_stream) {
+  try {  // (its job lists by key are host memory; nothing is enqueued before them)
+    return runner_launch(r, jobs, first, ngroups, njobs, hip_stream);
+  } catch (const std::bad_alloc&) {
+    return PC2_E_NOMEM;
+  }
 }
 
 int pc2_runner_destroy(pc2_runner* r) {
