@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <new>
 #include <string>
@@ -783,19 +784,20 @@ double rns_round(int T, int nb, bool wide, size_t w) {
 }
 
 // Microseconds of a unit of RnsPlan::cost per bit of the exponent, by tile count:
-// with a few workgroups, with one on every compute unit, and how steeply it falls
-// from there, as the units then stream fewer copies of the constants (16
-// decryptions of 1024 / 2048 / 3072 / 4096 bits: 1.24 / 3.3 / 7.3 / 13.1 ms;
-// encryptions of 3072 bits on 129 / 208 / 256 units: 5.3 / 7.6 / 8.1 us, 4096
-// bits on 129 / 232 / 256: 8.4 / 13.1 / 14).
-struct RnsUnit { double few, full, drop; };
-constexpr RnsUnit RNS_UNIT[pc2k::RNS_NT] = {{0.97, 1.1, 0.3},  {1.30, 1.6, 0.6},
-                                            {1.91, 2.4, 1.0},  {3.05, 3.9, 1.45},
-                                            {5.0, 8.1, 5.6},   {8.0, 14.0, 11.3}};
+// at least, with a workgroup on every compute unit, and how steeply it falls from
+// there, as the units then stream fewer copies of the constants (decryptions, ms,
+// 16 elements / a full device: 1024 bits 1.24 / 7.8 for 65536, 2048: 3.3 / 32 for
+// 65536, 3072: 7.3 / 48.5 for 32768, 4096: 13.1 / 88 for 32768; encryptions, 3072
+// bits on 129 / 208 / 256 units: 5.3 / 7.6 / 8.1 us, 4096 bits on 129 / 232 /
+// 256: 8.4 / 13.1 / 14).
+struct RnsUnit { double least, full, drop; };
+constexpr RnsUnit RNS_UNIT[pc2k::RNS_NT] = {{0.8, 0.8, -0.17},  {1.30, 1.6, 0.6},
+                                            {1.91, 2.75, 1.6},  {3.05, 4.1, 1.85},
+                                            {5.0, 8.1, 5.6},    {8.0, 14.0, 11.3}};
 double rns_unit(const pc2_ctx* ctx, const RnsPlan& p, int nmod) {
   const RnsUnit u = RNS_UNIT[rns_index(p.T)];
   const double fill = std::min(1.0, (double)(p.ngroups * nmod) / ctx->cus);
-  return std::max(u.few, u.full - (1 - fill) * u.drop);
+  return std::max(u.least, u.full - (1 - fill) * u.drop);
 }
 
 // The plan of the least time.  From T = 26 a workgroup's streamed constants weigh
@@ -1825,19 +1827,21 @@ double rns_time(const pc2_ctx* ctx, const RnsPlan& p, int nmod, int ebits) {
   return p.cost * rns_unit(ctx, p, nmod) * ebits;
 }
 // The persistent kernels run all keys of a launch together: no sooner than one
-// element's chain of products, and than the device does the products of all
-// (ms, few elements / an element in a full device: VALU decryption 1024 bits 4.7
-// / 0.00014, 2048: 16.4 / 0.00095, 3072: 31 / 0.003, 4096: 72 / 0.007; VALU
-// encryption 1024: 17 / 0.00065; per-element encryption 1024: 1.5 / 0.0007, 2048:
-// 5.2 / 0.0028, 3072: 9.5 / 0.0066, 4096: 19.4 / 0.0135).
-struct PersistentUnit { double chain, each; };
-constexpr PersistentUnit VALU_DEC[4] = {{9.2, 0.00027}, {16.0, 0.00093}, {20.2, 0.0020},
-                                        {35.2, 0.0034}};
-constexpr PersistentUnit VALU_ENC_1024 = {16.6, 0.00064};
-constexpr PersistentUnit ELEM_ENC[4] = {{1.46, 0.00069}, {2.56, 0.00135}, {3.10, 0.00216},
-                                        {4.74, 0.00329}};
+// element's chain of products, and than the device does the products of all, on
+// the VALU in rounds of as many elements as it holds (`round`).  Measured, ms, few
+// elements / a device-filling number of them: VALU decryption 1024 bits 4.7 / 5.7
+// for 32768 and 9.7 for 65536, 2048: 16.4 / 17.5 for 16384 and 58.5 for 65536,
+// 3072: 31 / 100.8 for 32768, 4096: 72 / 232.7 for 32768; VALU encryption 1024: 17 /
+// 30.3 for 65536; per-element encryption 1024: 1.5 / 0.0007 an element, 2048: 5.2 /
+// 0.0028, 3072: 9.5 / 0.0066, 4096: 19.4 / 0.0135.
+struct PersistentUnit { double chain, each, round; };
+constexpr PersistentUnit VALU_DEC[4] = {{9.2, 0.00027, 32768}, {16.0, 0.00086, 16384},
+                                        {20.2, 0.0020, 8192}, {35.2, 0.0034, 8192}};
+constexpr PersistentUnit VALU_ENC_1024 = {16.6, 0.00045, 32768};
+constexpr PersistentUnit ELEM_ENC[4] = {{1.46, 0.00069, 1}, {2.56, 0.00135, 1},
+                                        {3.10, 0.00216, 1}, {4.74, 0.00329, 1}};
 PersistentUnit persistent_unit(const pc2_ctx* ctx, int op, int cls) {
-  if (cls < 5) return {0, 0};  // (no launch holds these beside a key that the RNS engine takes)
+  if (cls < 5) return {0, 0, 1};  // (no launch holds these beside a key that the RNS engine takes)
   if (op == pc2k::OP_DEC) return VALU_DEC[cls - 5];
   return use_mfma(ctx, cls) ? ELEM_ENC[cls - 5] : VALU_ENC_1024;
 }
@@ -1853,7 +1857,7 @@ void rns_choose(pc2_ctx* ctx, int op, std::vector<KeyJobs>& keys) {
     return;
   }
   const int nmod = op == pc2k::OP_DEC ? 2 : 1;
-  struct Load { double chain = 0, each = 0; size_t keys = 0; } load[pc2k::NUM_CLASSES];
+  struct Load { double chain = 0, each = 0, round = 1; size_t keys = 0; } load[pc2k::NUM_CLASSES];
   auto load_of = [&](const KeyJobs& k) -> Load& { return load[k.sk ? k.sk->pk.cls : k.pk->cls]; };
   std::vector<size_t> order;
   for (size_t i = 0; i < keys.size(); ++i) {
@@ -1862,12 +1866,15 @@ void rns_choose(pc2_ctx* ctx, int op, std::vector<KeyJobs>& keys) {
     const PersistentUnit u = persistent_unit(ctx, op, cls);
     load_of(k).chain = std::max(load_of(k).chain, u.chain * key_ebits(k));
     load_of(k).each += u.each * key_ebits(k) * (double)k.total;
+    load_of(k).round = std::max(load_of(k).round, u.each * key_ebits(k) * u.round);
     ++load_of(k).keys;
     if (k.takes) order.push_back(i);
   }
-  // the VALU classes in one launch, each class on the matrix cores in its own
+  // the VALU classes in one launch (two fill each other's last round), each class
+  // on the matrix cores in its own
   auto persistent = [&] {
-    double chain = 0, each = 0, elem = 0;
+    double chain = 0, each = 0, round = 0, elem = 0;
+    int classes = 0;
     for (int c = 0; c < pc2k::NUM_CLASSES; ++c) {
       if (!load[c].keys) continue;
       if (op == pc2k::OP_ENC && use_mfma(ctx, c)) {
@@ -1875,8 +1882,11 @@ void rns_choose(pc2_ctx* ctx, int op, std::vector<KeyJobs>& keys) {
       } else {
         chain = std::max(chain, load[c].chain);
         each += load[c].each;
+        round = load[c].round;
+        ++classes;
       }
     }
+    if (classes == 1) each = std::ceil(each / round - 1e-9) * round;
     return std::max(chain, each) + elem;
   };
   std::stable_sort(order.begin(), order.end(),
