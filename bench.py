@@ -300,9 +300,10 @@ def run_batching(pc2, gen, ctx, torch, np, args, reps: int = 3) -> dict:
     1024-bit key and odd nodes under a 2048-bit key.  Phases: encrypt every
     node vector; per key group, multiply element j over the nodes whose
     vector reaches j; decrypt both aggregates.  Batched: one persistent
-    graph-captured launch per phase.  Plain: one launch per call.  The
-    encryption tile (lanes per ciphertext) and the windows of both key
-    sizes come from the autotuner first; both paths use them."""
+    graph-captured launch per phase.  Plain: one launch per call.  The VALU
+    engine's encryption tile (lanes per ciphertext) and windows of both key
+    sizes come from the autotuner first; both paths use them where they run on
+    that engine."""
     lengths = gen.log_uniform_lengths(BATCH_SEED, BATCH_NODES, 1024, 65536)
     keys = []
     tuned = {}
@@ -313,7 +314,8 @@ def run_batching(pc2, gen, ctx, torch, np, args, reps: int = 3) -> dict:
         we, wd, te = pc2.pc2_autotune(keys[-1])
         tuned[str(bits)] = {"enc_lanes": te, "enc_window": we, "dec_window": wd,
                             "tuning_s": round(time.perf_counter() - t1, 2)}
-        log(f"autotune {bits}-bit: encryption {te} lanes, w {we}; decryption w {wd}")
+        log(f"autotune {bits}-bit, VALU engine: encryption {te} lanes, w {we}; "
+            f"decryption w {wd}")
     xs = gen.normal_vectors(BATCH_SEED, lengths)
     qp = gen.Q_PLAIN
     nodes = []

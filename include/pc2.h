@@ -111,22 +111,26 @@ int pc2_ctx_reserve(pc2_ctx *ctx, uint32_t max_nbits);
  *                a wavefront (few elements: several) per ciphertext;
  *   residues     a residue number system of 16-bit primes, two base extensions
  *                per product on the i8 matrix cores with constant matrices
- *                shared by 32 ciphertexts and more (keys from 512 bits).
+ *                shared by 32 ciphertexts and more (keys declared with nbits >
+ *                256 whose modulus, n^2 or p^2 and q^2, has 512 bits and more).
  * PC2_MODMUL_VALU: the VALU engine everywhere.  PC2_MODMUL_MFMA: public-key
  * encryptions on the matrix cores (per element below some thousands of
- * elements and below 512 bits, else residues).  PC2_MODMUL_AUTO (the default):
- * whichever of the three is the fastest for the key's size and the call's
- * count.  With MFMA and AUTO, decryption, key-holder encryption, scalar
- * products and mat-vec plans under keys from 1024 bits run on residues (under
- * 512-bit keys, decryptions and key-holder encryptions of some thousands and
- * fewer), and sums on the VALU.  All engines give identical results.  A batch or runner
- * launch holds encryption jobs of at most two key classes per engine; its jobs
- * on residues run as one launch sequence per key.
+ * elements and where residues do not apply, else residues).  PC2_MODMUL_AUTO
+ * (the default): whichever of the three is the fastest for the key's size and
+ * the call's count.  With MFMA and AUTO, where they apply, scalar products and
+ * mat-vec plans run on residues at any count, decryptions and key-holder
+ * encryptions at any count with nbits > 512 and up to 5632 elements below;
+ * sums run on the VALU.  All engines give identical results.  A batch or runner
+ * launch holds encryption jobs of at most two key classes per engine; on
+ * residues every key's jobs are launches of their own, so a launch of several
+ * keys takes them there only for the keys whose elements make it the faster
+ * way, and holds the other keys in the persistent kernels.
  * PC2_OPT_TILE: the limb tile of the VALU encryption kernels (pc2_encrypt,
  * batches and runners of encryptions), i.e. how many lanes of a wavefront
  * share one ciphertext.  A tile asked for (not 0) also asks for these kernels
- * where PC2_MODMUL_AUTO leaves the choice open, under keys of up to 1024 bits.  1024-bit keys run with 2 (own) or 4 lanes,
- * 2048-bit keys with 4 (own) or 8; other sizes have their own tile only.
+ * where PC2_MODMUL_AUTO leaves the choice open, under keys of up to 1024 bits.
+ * 1024-bit keys run with 2 (own) or 4 lanes, 2048-bit keys with 4 (own) or 8;
+ * other sizes have their own tile only.
  * Values: 0 = automatic (pc2_encrypt of at most one wavefront per SIMD of
  * the wider tile, i.e. count <= 4 * CUs * 64 / lanes, takes the wider tile,
  * which has the shorter latency; larger calls, batches and runners take the
@@ -529,8 +533,9 @@ int pc2_admm_destroy(pc2_admm *admm);
  * {4, 5, 6}, and decryption with w in {4, 5, 6}, on the same synthetic
  * sample of a few device-filling waves (VALU engine).  Keeps the fastest
  * tile and windows in the context (used by later calls, batches and runners
- * of that class while PC2_OPT_TILE and PC2_OPT_WINDOW are 0) and reports
- * them: w_enc, w_dec, and tile_enc = lanes per ciphertext (any output may be
+ * of that class that run on the VALU engine, while PC2_OPT_TILE and
+ * PC2_OPT_WINDOW are 0; the engines on the matrix cores have windows of their
+ * own) and reports them: w_enc, w_dec, and tile_enc = lanes per ciphertext (any output may be
  * NULL).  Synchronises the stream; allocates temporary buffers. */
 int pc2_autotune(const pc2_sk *sk, void *hip_stream, int *w_enc, int *w_dec, int *tile_enc);
 

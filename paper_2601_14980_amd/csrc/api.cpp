@@ -522,9 +522,10 @@ pc2k::RnsKey rns_const(const uint32_t* base, const RnsOffsets& o, int nw) {
   for (int i = 0; i < 5; ++i) k.ops[i] = base + o.ops[i];
   return k;
 }
-// Tile count of a modulus of a key of class cls, 0 below 512-bit keys (where
-// the VALU engine's products are short) and for a modulus far below its
-// class's size (the output conversion reads its four top limbs).
+// Tile count of a modulus of a key of class cls, by the modulus' own length; 0 in
+// the classes below 512-bit keys (nbits <= 256) and for a modulus of fewer than 512
+// bits, whose products are short on the VALU engine (the output conversion's
+// quotient, too, wants four limbs and more).
 constexpr int RNS_MIN_CLASS = 4;
 int rns_tiles_for(int cls, const Limbs& N) {
   const int bits = pc2h::bitlen(N);
@@ -2390,7 +2391,8 @@ int pc2_batch_destroy(pc2_batch* b) {
 // -------------------------------------------------------------- autotune
 // Times encryption in each tile the key's class has (lanes per ciphertext)
 // with windows 4..6, and decryption with windows 4..6, on a few
-// device-filling waves of elements; keeps the fastest choices in the context.
+// device-filling waves of elements of the VALU engine; keeps the fastest choices in
+// the context, where that engine's calls read them.
 int pc2_autotune(const pc2_sk* sk, void* hip_stream, int* w_enc, int* w_dec, int* tile_enc) {
   if (!sk || !sk->ctx) return PC2_E_INVAL;
   pc2_ctx* ctx = sk->ctx;
