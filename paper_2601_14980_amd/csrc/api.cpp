@@ -1833,18 +1833,20 @@ double rns_time(const pc2_ctx* ctx, const RnsPlan& p, int nmod, int ebits) {
 // elements / a device-filling number of them: VALU decryption 1024 bits 4.7 / 5.7
 // for 32768 and 9.7 for 65536, 2048: 16.4 / 17.5 for 16384 and 58.5 for 65536,
 // 3072: 31 / 100.8 for 32768, 4096: 72 / 232.7 for 32768; VALU encryption 1024: 17 /
-// 30.3 for 65536; per-element encryption 1024: 1.5 / 0.0007 an element, 2048: 5.2 /
-// 0.0028, 3072: 9.5 / 0.0066, 4096: 19.4 / 0.0135.
+// 30.3 for 65536; per-element encryption 512: 0.49 / 0.00025 an element, 1024: 1.5 /
+// 0.0007, 2048: 5.2 / 0.0028, 3072: 9.5 / 0.0066, 4096: 19.4 / 0.0135.
 struct PersistentUnit { double chain, each, round; };
 constexpr PersistentUnit VALU_DEC[4] = {{9.2, 0.00027, 32768}, {16.0, 0.00086, 16384},
                                         {20.2, 0.0020, 8192}, {35.2, 0.0034, 8192}};
 constexpr PersistentUnit VALU_ENC_1024 = {16.6, 0.00045, 32768};
-constexpr PersistentUnit ELEM_ENC[4] = {{1.46, 0.00069, 1}, {2.56, 0.00135, 1},
-                                        {3.10, 0.00216, 1}, {4.74, 0.00329, 1}};
+constexpr PersistentUnit ELEM_ENC[5] = {{0.95, 0.00048, 1}, {1.46, 0.00069, 1},
+                                        {2.56, 0.00135, 1}, {3.10, 0.00216, 1},
+                                        {4.74, 0.00329, 1}};
 PersistentUnit persistent_unit(const pc2_ctx* ctx, int op, int cls) {
-  if (cls < 5) return {0, 0, 1};  // (no launch holds these beside a key that the RNS engine takes)
-  if (op == pc2k::OP_DEC) return VALU_DEC[cls - 5];
-  return use_mfma(ctx, cls) ? ELEM_ENC[cls - 5] : VALU_ENC_1024;
+  // (smaller keys stay in the persistent kernels whatever is chosen for the others)
+  if (cls < RNS_MIN_CLASS) return {0, 0, 1};
+  if (op == pc2k::OP_DEC) return cls < 5 ? PersistentUnit{0, 0, 1} : VALU_DEC[cls - 5];
+  return use_mfma(ctx, cls) ? ELEM_ENC[cls - RNS_MIN_CLASS] : VALU_ENC_1024;
 }
 
 // Which keys of a launch run on residues: the one key of a launch of its own

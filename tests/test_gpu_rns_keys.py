@@ -100,3 +100,27 @@ def test_many_keys_of_few_elements_are_not_a_sequence_each(gpu_ctx, keys, kind):
     with _valu(gpu_ctx):
         want = ms()
     assert got < 1.25 * want
+
+
+# keys of other classes beside one that the engine takes: on the VALU kernel, and
+# with the matrix cores asked for
+@pytest.mark.parametrize("modmul,other,counts", [
+    ("AUTO", 256, (9000, 700)), ("AUTO", 1024, (9000, 700)), ("AUTO", 1024, (4000, 20000)),
+    ("MFMA", 512, (9000, 9000)), ("MFMA", 512, (100, 5000)), ("MFMA", 256, (4000, 5000))])
+def test_other_classes(gpu_ctx, keys, modmul, other, counts):
+    from paper_2601_14980_amd import pc2
+    a, b = _prime(other // 2, 40), _prime(other // 2, 41)
+    sk = pc2.SecretKey(gpu_ctx, other, a, b)
+    jobs, want = _jobs(pc2, [keys[0], sk], counts, "encrypt")
+    gpu_ctx.set_option(pc2.PC2_OPT_MODMUL, getattr(pc2, "PC2_MODMUL_" + modmul))
+    try:
+        for kind in ("batch", "runner"):
+            run, handle = _launcher(pc2, gpu_ctx, jobs, kind)
+            run()
+            assert gpu_ctx.sync() == 0
+            for j, w in zip(jobs, want):
+                assert torch.equal(j["out"], w)
+                j["out"].zero_()
+            handle.close()
+    finally:
+        gpu_ctx.set_option(pc2.PC2_OPT_MODMUL, pc2.PC2_MODMUL_AUTO)
