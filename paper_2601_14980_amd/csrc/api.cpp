@@ -1817,6 +1817,7 @@ struct KeyJobs {
   std::vector<size_t> jobs;
   size_t total = 0;
   bool takes = false;  // the RNS engine takes them (enc_engine, dec_rns)
+  bool only = false;   // ... and the persistent kernels have none for the key's class
   bool rns = false;
 };
 int key_ebits(const KeyJobs& k) { return k.sk ? k.sk->c.ebits : (int)k.pk->nbits; }
@@ -1833,20 +1834,19 @@ double rns_time(const pc2_ctx* ctx, const RnsPlan& p, int nmod, int ebits) {
 // elements / a device-filling number of them: VALU decryption 1024 bits 4.7 / 5.7
 // for 32768 and 9.7 for 65536, 2048: 16.4 / 17.5 for 16384 and 58.5 for 65536,
 // 3072: 31 / 100.8 for 32768, 4096: 72 / 232.7 for 32768; VALU encryption 1024: 17 /
-// 30.3 for 65536; per-element encryption 512: 0.49 / 0.00025 an element, 1024: 1.5 /
-// 0.0007, 2048: 5.2 / 0.0028, 3072: 9.5 / 0.0066, 4096: 19.4 / 0.0135.
+// 30.3 for 65536; per-element encryption 1024: 1.5 / 0.0007 an element, 2048: 5.2 /
+// 0.0028, 3072: 9.5 / 0.0066, 4096: 19.4 / 0.0135.
 struct PersistentUnit { double chain, each, round; };
 constexpr PersistentUnit VALU_DEC[4] = {{9.2, 0.00027, 32768}, {16.0, 0.00086, 16384},
                                         {20.2, 0.0020, 8192}, {35.2, 0.0034, 8192}};
 constexpr PersistentUnit VALU_ENC_1024 = {16.6, 0.00045, 32768};
-constexpr PersistentUnit ELEM_ENC[5] = {{0.95, 0.00048, 1}, {1.46, 0.00069, 1},
-                                        {2.56, 0.00135, 1}, {3.10, 0.00216, 1},
-                                        {4.74, 0.00329, 1}};
+constexpr PersistentUnit ELEM_ENC[4] = {{1.46, 0.00069, 1}, {2.56, 0.00135, 1},
+                                        {3.10, 0.00216, 1}, {4.74, 0.00329, 1}};
 PersistentUnit persistent_unit(const pc2_ctx* ctx, int op, int cls) {
   // (smaller keys stay in the persistent kernels whatever is chosen for the others)
-  if (cls < RNS_MIN_CLASS) return {0, 0, 1};
-  if (op == pc2k::OP_DEC) return cls < 5 ? PersistentUnit{0, 0, 1} : VALU_DEC[cls - 5];
-  return use_mfma(ctx, cls) ? ELEM_ENC[cls - RNS_MIN_CLASS] : VALU_ENC_1024;
+  if (cls < 5) return {0, 0, 1};
+  if (op == pc2k::OP_DEC) return VALU_DEC[cls - 5];
+  return use_mfma(ctx, cls) ? ELEM_ENC[cls - 5] : VALU_ENC_1024;
 }
 
 // Which keys of a launch run on residues: the one key of a launch of its own
@@ -1855,8 +1855,13 @@ PersistentUnit persistent_unit(const pc2_ctx* ctx, int op, int cls) {
 // elements a key, 4 / 8 / 16 keys: 13.4 / 26.9 / 53.7 ms as sequences, 16.5 in the
 // persistent kernel; encryptions of 3840 elements, 4 keys: 53.8 against 45.7).
 void rns_choose(pc2_ctx* ctx, int op, std::vector<KeyJobs>& keys) {
-  if (keys.size() == 1) {
-    keys[0].rns = keys[0].takes;
+  size_t open = 0;
+  for (KeyJobs& k : keys) {
+    k.rns = k.only;
+    open += !k.only;
+  }
+  if (open <= 1) {
+    for (KeyJobs& k : keys) k.rns = k.takes;
     return;
   }
   const int nmod = op == pc2k::OP_DEC ? 2 : 1;
@@ -1865,6 +1870,7 @@ void rns_choose(pc2_ctx* ctx, int op, std::vector<KeyJobs>& keys) {
   std::vector<size_t> order;
   for (size_t i = 0; i < keys.size(); ++i) {
     const KeyJobs& k = keys[i];
+    if (k.only) continue;
     const int cls = k.sk ? k.sk->pk.cls : k.pk->cls;
     const PersistentUnit u = persistent_unit(ctx, op, cls);
     load_of(k).chain = std::max(load_of(k).chain, u.chain * key_ebits(k));
@@ -1937,8 +1943,11 @@ std::vector<RnsPart> rns_parts(pc2_ctx* ctx, int op, const pc2_job* jobs, const 
     k.jobs.push_back(i);
     k.total += count[i];
   }
-  for (KeyJobs& k : keys)
+  for (KeyJobs& k : keys) {
     k.takes = dec ? dec_rns(ctx, k.sk, k.total) : enc_engine(ctx, k.pk, k.total) == ENG_RNS;
+    k.only = k.takes &&
+             pc2k::batch_group_elems(op, job_geo(ctx, dec ? &k.sk->pk : k.pk, op)) == 0;
+  }
   rns_choose(ctx, op, keys);
   for (const KeyJobs& k : keys) {
     if (!k.rns) continue;
@@ -2160,10 +2169,19 @@ int pc2_batch_create(pc2_ctx* ctx, const pc2_job* jobs, size_t njobs, pc2_batch*
   std::vector<bool> in_rns;
   std::vector<pc2k::RnsJob> rjobs;
   b->rparts = rns_parts(ctx, op, jobs, zero.data(), counts.data(), njobs, &in_rns, &rjobs);
+  bool lost = false;
   if (!b->rparts.empty() && !batch_rns_alloc(b, ctx, op)) {
     b->rparts.clear();
     rjobs.clear();
     in_rns.assign(njobs, false);
+    lost = true;
+  }
+  for (size_t i = 0; i < njobs; ++i) {  // a class that no persistent kernel has
+    if (jobs[i].count == 0 || in_rns[i]) continue;
+    const pc2_pk* pk = (op == pc2k::OP_DEC) ? &jobs[i].sk->pk : jobs[i].pk;
+    if (pc2k::batch_group_elems(op, job_geo(ctx, pk, op)) > 0) continue;
+    batch_free(b);
+    return lost ? PC2_E_NOMEM : PC2_E_UNSUPPORTED;
   }
   const int few = few_elements_class(ctx, op, jobs, counts.data(), njobs, in_rns);
   if (few >= 0 && mcb < 0) {
@@ -2629,6 +2647,7 @@ static int runner_launch(pc2_runner* r, const pc2_job* jobs, const size_t* first
     if (!pk || pk->ctx != ctx || !j.out || pk->cls > r->max_cls) return PC2_E_INVAL;
     const int g = job_geo(ctx, pk, op);
     const size_t epw = (size_t)pc2k::batch_group_elems(op, g);
+    if (epw == 0) return PC2_E_UNSUPPORTED;  // no element groups under keys of this class
     if (first[i] + ngroups[i] > (j.count + epw - 1) / epw) return PC2_E_INVAL;
     if (op == pc2k::OP_ENC && (!j.in0 || !j.in1 || j.m_limbs < 1 || (int)j.m_limbs > pk->L))
       return PC2_E_INVAL;

@@ -114,7 +114,7 @@ def test_other_classes(gpu_ctx, keys, modmul, other, counts):
     jobs, want = _jobs(pc2, [keys[0], sk], counts, "encrypt")
     gpu_ctx.set_option(pc2.PC2_OPT_MODMUL, getattr(pc2, "PC2_MODMUL_" + modmul))
     try:
-        for kind in ("batch", "runner"):
+        for kind in ("batch", "runner") if other != 512 else ("batch",):
             run, handle = _launcher(pc2, gpu_ctx, jobs, kind)
             run()
             assert gpu_ctx.sync() == 0
@@ -124,3 +124,22 @@ def test_other_classes(gpu_ctx, keys, modmul, other, counts):
             handle.close()
     finally:
         gpu_ctx.set_option(pc2.PC2_OPT_MODMUL, pc2.PC2_MODMUL_AUTO)
+
+
+def test_class_without_element_groups(gpu_ctx, keys):
+    """512-bit keys have no persistent kernel: with the matrix cores asked for, a
+    batch of few elements under one is refused, and so is a runner's launch."""
+    from paper_2601_14980_amd import pc2
+    sk = pc2.SecretKey(gpu_ctx, 512, _prime(256, 40), _prime(256, 41))
+    jobs, _ = _jobs(pc2, [keys[0], sk], (100, 100), "encrypt")
+    r = pc2.Runner(gpu_ctx, pc2.PC2_OP_ENCRYPT, 2048, 2, 64)
+    gpu_ctx.set_option(pc2.PC2_OPT_MODMUL, pc2.PC2_MODMUL_MFMA)
+    try:
+        for call in (lambda: pc2.Batch(gpu_ctx, jobs), lambda: pc2.Batch(gpu_ctx, jobs[1:]),
+                     lambda: r.launch(jobs[1:], [0], [1])):
+            with pytest.raises(pc2.PC2Error) as e:
+                call()
+            assert e.value.status == pc2.PC2_E_UNSUPPORTED
+    finally:
+        gpu_ctx.set_option(pc2.PC2_OPT_MODMUL, pc2.PC2_MODMUL_AUTO)
+    r.close()
