@@ -734,6 +734,7 @@ def run_matvec(pc2, gen, ctx, sk, torch, np, args) -> dict:
         raise RuntimeError("device reported a data error while preparing the mat-vec")
     mv = pc2.MatVec(sk.public, D, MATVEC_EBITS, 0, rows_hint=D)
     w, nw, residues, table_bytes = mv.window, mv.digits, mv.residues, mv.table_bytes
+    blocks = mv.blocks
     stream = torch.cuda.current_stream()
     ev = [torch.cuda.Event(enable_timing=True) for _ in range(3)]
     t_tab, t_app = [], []
@@ -764,21 +765,23 @@ def run_matvec(pc2, gen, ctx, sk, torch, np, args) -> dict:
         want = (int(a[i]) + int(np.dot(Bh[i].astype(object), m))) % n
         got = sum(int(decs[i, k]) << (32 * k) for k in range(L))
         ok &= got == want
-    # a plan on residues cuts the constants into digits as even as their bits
-    # allow, one on the VALU into digits of the window's bits
-    lo, wide = divmod(MATVEC_EBITS, nw) if residues else (w, 0)
+    # a plan on residues cuts the constants into blocks of digits as even as the
+    # bits allow (squarings between blocks), one on the VALU into digits of the
+    # window's bits
+    bits = -(-MATVEC_EBITS // blocks)
+    lo, wide = divmod(bits, nw) if residues else (w, 0)
     widths = [lo + (t < wide) for t in range(nw)]
     mm_tab = D * sum(sum(widths[:t]) + (1 << widths[t]) - 1 for t in range(nw))
-    mm_app = D * D * nw
+    mm_app = D * (D * nw * blocks + bits * (blocks - 1))
     tt, ta = float(np.median(t_tab)) / 1e3, float(np.median(t_app)) / 1e3
     products = mm_tab + mm_app
     roof = (roofline_rns(NBITS, products, 1, tt + ta) if residues
             else roofline_valu(products * (2 * (2 * L) ** 2 + 2 * L), tt + ta))
-    log(f"matvec {D}x{D}: {nw} digits on {'residues' if residues else 'the VALU'}, "
+    log(f"matvec {D}x{D}: {blocks} x {nw} digits on {'residues' if residues else 'the VALU'}, "
         f"tables {tt * 1e3:.1f} ms, rows {ta * 1e3:.1f} ms, exact {ok}")
     return {"workload": f"2048-bit key, B {D}x{D} of {MATVEC_EBITS}-bit constants, c and alpha "
                         f"encryptions of quantized N(0,1) data: out = alpha * c^B mod n^2",
-            "window": w, "digits": nw, "table_bytes": table_bytes,
+            "window": w, "digits": nw, "blocks": blocks, "table_bytes": table_bytes,
             "tables_ms": round(tt * 1e3, 2), "rows_ms": round(ta * 1e3, 2),
             "montgomery_products": products,
             "powers_per_s": round(D * D / (tt + ta), 1),

@@ -271,9 +271,9 @@ int pc2_enc_sum_dec(const pc2_sk *sk, const uint32_t *const *m_k, const uint32_t
  * squarings; the tables take cols * ceil(ebits / w) * (2^w - 1) entries of
  * the n^2 digit layout (640 B at 2048 bits).  A plan whose products run on
  * residues (PC2_OPT_MODMUL at its creation) takes the same bytes for its tables,
- * whose entries are longer (1088 B at 2048 bits): it cuts the constants into as
- * many digits of its own as have the least time among those whose tables fit
- * (pc2_matvec_engine), and runs on the VALU where none fit.
+ * whose entries are longer (1088 B at 2048 bits): it cuts the constants into
+ * blocks and digits of its own, those of the least time among the ones whose
+ * tables fit (pc2_matvec_engine), and runs on the VALU where none do.
  *
  * pc2_matvec_create: cols >= 1; ebits in 1..64 bounds the constants
  * (B_ij < 2^ebits); window w in 1..12, or 0 = automatic: the w minimising
@@ -281,10 +281,12 @@ int pc2_enc_sum_dec(const pc2_sk *sk, const uint32_t *const *m_k, const uint32_t
  * tables fit in a quarter of the free device memory.  Allocates the tables
  * (PC2_E_NOMEM if they do not fit).
  * pc2_matvec_info: the window and the table bytes of a plan (either may be NULL).
- * pc2_matvec_engine: *residues = whether its products run on residues, *digits =
- *   the digits of a constant, i.e. the modular products per row and column, and
- *   *staging_bytes = the device bytes it holds beside its tables for partial
- *   products (any may be NULL).
+ * pc2_matvec_engine: *residues = whether its products run on residues; *blocks =
+ *   into how many blocks the bits of a constant are cut, which share the tables
+ *   (1 on the VALU); *digits = the digits of a block, so that a row costs digits *
+ *   blocks products per column and, between two blocks, a squaring per bit of a
+ *   block; *staging_bytes = the device bytes it holds beside its tables for
+ *   partial products (any may be NULL).
  * pc2_matvec_load: builds the tables of c ([cols][2L], device) on the stream.
  *   c_j >= n^2 latches PC2_E_RANGE and zeroes that column's tables.
  * pc2_matvec_apply: B: device uint64 [rows][cols] row-major; alpha: device
@@ -302,7 +304,7 @@ typedef struct pc2_matvec pc2_matvec;
 int pc2_matvec_create(const pc2_pk *pk, size_t cols, uint32_t ebits, uint32_t window,
                       size_t rows_hint, pc2_matvec **out);
 int pc2_matvec_info(const pc2_matvec *mv, uint32_t *window, size_t *table_bytes);
-int pc2_matvec_engine(const pc2_matvec *mv, int *residues, uint32_t *digits,
+int pc2_matvec_engine(const pc2_matvec *mv, int *residues, uint32_t *digits, uint32_t *blocks,
                       size_t *staging_bytes);
 int pc2_matvec_load(pc2_matvec *mv, const uint32_t *c, void *hip_stream);
 int pc2_matvec_apply(pc2_matvec *mv, const uint64_t *B, const uint32_t *alpha, uint32_t *out,

@@ -2894,37 +2894,47 @@ namespace {
 // Column blocks per row group (nb) and column chunks of `rows` rows on the RNS
 // engine, their running values at most `blocks` blocks of 32: the least time
 // by rounds of resident workgroups (a product measured 1.45 + nb, as its
-// multipliers come from HBM; else see rns_round), plus the products that join the chunks.
+// multipliers come from HBM, and 1.1 times that with constants in blocks; else see
+// rns_round), plus the products that join the chunks.
 struct RnsMvShape {
   int nb = 0;
   size_t groups = 0, nch = 0, chunk_cols = 0;
   double cost = 0;
 };
-RnsMvShape rns_mv_shape(pc2_ctx* ctx, int T, size_t cols, int nw, size_t rows, size_t blocks) {
+int rns_mv_kind(const pc2k::RnsDigits& dg) {
+  return dg.nblk > 1 ? pc2k::RNS_MVBLK : pc2k::RNS_MV;
+}
+RnsMvShape rns_mv_shape(pc2_ctx* ctx, int T, size_t cols, const pc2k::RnsDigits& dg, size_t rows,
+                        size_t blocks) {
   RnsMvShape best;
+  // products per column, and (constants in blocks) squarings and the last product
+  const int per = dg.n * dg.nblk, fix = dg.nblk > 1 ? dg.bits() * (dg.nblk - 1) + 1 : 0;
+  auto unit = [&](int nb) { return (1.45 + nb) * (dg.nblk > 1 ? 1.1 : 1.0); };
   for (int nb = 1; nb <= pc2k::RNS_NBMAX; ++nb) {
-    const size_t slots = (size_t)rns_slots(ctx, T, nb, pc2k::RNS_MV);
+    const size_t slots = (size_t)rns_slots(ctx, T, nb, rns_mv_kind(dg));
     const size_t G = (rows + 32 * nb - 1) / (32 * nb);
     if (!slots || (G * nb > blocks && best.nb)) continue;
     for (size_t c = 1; c <= std::min(cols, (size_t)256) && (c == 1 || G * nb * c <= blocks); ++c) {
       const size_t cc = (cols + c - 1) / c;
       if ((cols + cc - 1) / cc != c) continue;  // the same split as a smaller count
-      const double t = ((double)((G * c + slots - 1) / slots) * (double)(cc * nw) +
-                        (c > 1 ? (double)c : 0.0)) * (1.45 + nb);
+      const double t = ((double)((G * c + slots - 1) / slots) * (double)(cc * per + fix) +
+                        (c > 1 ? (double)c : 0.0)) * unit(nb);
       if (!best.nb || t < best.cost) best = {nb, G, c, cc, t};
     }
   }
   return best;
 }
 
-// The RNS engine for a plan: the number of digits of the least time among those
+// The RNS engine for a plan: the blocks and digits of the least time among those
 // whose tables fit the plan's table bytes; false if there is none or the device has
-// no memory for it.  Its entries are 1.7 times the VALU engine's, so windows of 1
-// and 2 bits stay there; otherwise it is the faster one from a single row up (load
-// / apply in ms, RNS against VALU, ebits 50: 1024 bits, 64 rows x 16 columns 0.16 /
-// 0.16 against 1.02 / 2.1; 2048 bits, 256 x 256: 0.39 / 1.17 against 2.2 / 4.8, window
-// 3: 0.36 / 2.0 against 1.6 / 5.6; 4096 bits, 64 x 16: 1.1 / 1.07 against 4.1 /
-// 1.44).
+// no memory for it.  Its entries are 1.7 times the VALU engine's.  Plans for many
+// rows, whose windows are wide, hold all digits of a constant; for few rows the
+// window is narrow, and blocks that share a small table do with a fraction of its
+// bytes.  It is the faster one from a single row up (load / apply in ms, RNS against
+// VALU, ebits 50: 1024 bits, 64 rows x 16 columns 0.16 / 0.16 against 1.02 / 2.1; 2048
+// bits, 256 x 256: 0.40 / 1.2 against 2.2 / 4.8, 1 x 1000: 0.16 / 1.8 against 3.1 / 9.4;
+// 4096 bits, 64 x 16: 1.1 / 1.07 against 4.1 / 1.44).  Constants of one bit, whose
+// tables hold one VALU entry, stay on the VALU.
 bool rns_matvec_create(pc2_matvec* mv, size_t rows_hint) {
   pc2_ctx* ctx = mv->ctx;
   const int T = mv->pk->rn.T;
@@ -2936,15 +2946,20 @@ bool rns_matvec_create(pc2_matvec* mv, size_t rows_hint) {
   // (no hint: rows enough that the tables' cost is small, as for the window)
   const size_t rows = std::min(rows_hint ? rows_hint : (size_t)8192, most * 32);
   double best = 0;
-  for (int nw = (mv->ebits + 11) / 12; nw <= mv->ebits; ++nw) {
-    const pc2k::RnsDigits dg = pc2k::RnsDigits::of(mv->ebits, nw);
-    if (mv->cols * (dg.entries() * (size_t)64 * T) > mv->table_bytes) continue;
-    const double cost = rns_mv_shape(ctx, T, mv->cols, nw, rows, most).cost +
-                        2.45 * (double)((Gc * nw + tslots - 1) / tslots) *
-                            (double)(((size_t)1 << dg.width(0)) + (size_t)dg.shift(nw - 1));
-    if (mv->rdg.n == 0 || cost < best) {
-      best = cost;
-      mv->rdg = dg;
+  for (int nblk = 1; nblk <= mv->ebits; ++nblk) {
+    const int bits = (mv->ebits + nblk - 1) / nblk;
+    for (int nw = (bits + 11) / 12; nw <= bits; ++nw) {
+      const pc2k::RnsDigits dg = pc2k::RnsDigits::of(mv->ebits, nw, nblk);
+      if (mv->cols * (dg.entries() * (size_t)64 * T) > mv->table_bytes ||
+          bits * (nblk - 1) + dg.shift(nw - 1) > 63)  // (the kernel shifts by it)
+        continue;
+      const double cost = rns_mv_shape(ctx, T, mv->cols, dg, rows, most).cost +
+                          2.45 * (double)((Gc * nw + tslots - 1) / tslots) *
+                              (double)(((size_t)1 << dg.width(0)) + (size_t)dg.shift(nw - 1));
+      if (mv->rdg.n == 0 || cost < best) {
+        best = cost;
+        mv->rdg = dg;
+      }
     }
   }
   if (mv->rdg.n == 0) return false;
@@ -3017,7 +3032,7 @@ int rns_matvec_apply(pc2_matvec* mv, const uint64_t* B, const uint32_t* alpha, u
   int rc = stage_begin(mv, stream);
   for (size_t at = 0; at < rows && !rc; at += mv->rblocks * 32) {
     const size_t n = std::min(rows - at, mv->rblocks * 32);
-    const RnsMvShape S = rns_mv_shape(ctx, K.T, mv->cols, mv->rdg.n, n, mv->rblocks);
+    const RnsMvShape S = rns_mv_shape(ctx, K.T, mv->cols, mv->rdg, n, mv->rblocks);
     const uint32_t* a = alpha ? alpha + at * L2 : nullptr;
     const pc2k::RnsJobs J = one_job(a, nullptr, 0, out + at * L2, n);
     pc2k::RnsMv m{};
@@ -3042,7 +3057,7 @@ int rns_matvec_apply(pc2_matvec* mv, const uint64_t* B, const uint32_t* alpha, u
       const size_t slots = (size_t)rns_slots(ctx, K.T, S.nb, which);
       return pc2k::launch_rns_gather(K.T, S.nb, which, (int)std::min(slots, items), &m, stream);
     };
-    if (e == hipSuccess) e = gather(pc2k::RNS_MV, S.groups * S.nch);
+    if (e == hipSuccess) e = gather(rns_mv_kind(mv->rdg), S.groups * S.nch);
     if (e == hipSuccess && S.nch > 1) e = gather(pc2k::RNS_CHAIN, S.groups);
     if (e == hipSuccess)
       e = pc2k::launch_rns_from(K.from, K.T, S.nb, mv->rstage, J, nullptr, 0, stream);
@@ -3124,9 +3139,10 @@ int pc2_matvec_info(const pc2_matvec* mv, uint32_t* window, size_t* table_bytes)
   return PC2_OK;
 }
 
-int pc2_matvec_engine(const pc2_matvec* mv, int* residues, uint32_t* digits,
+int pc2_matvec_engine(const pc2_matvec* mv, int* residues, uint32_t* digits, uint32_t* blocks,
                       size_t* staging_bytes) {
   if (!mv) return PC2_E_INVAL;
+  if (blocks) *blocks = (uint32_t)(mv->rdg.n ? mv->rdg.nblk : 1);
   if (residues) *residues = mv->rdg.n > 0;
   if (digits) *digits = (uint32_t)(mv->rdg.n ? mv->rdg.n : mv->nw);
   if (staging_bytes) *staging_bytes = mv->rdg.n ? mv->rstage_bytes : mv->parts_bytes;

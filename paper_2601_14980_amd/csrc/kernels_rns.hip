@@ -6,8 +6,9 @@
 //                 elements, one group at a time per workgroup: the table of
 //                 odd powers, sliding windows, the closing product
 //   k_rns_smul    powers with a 64-bit exponent per element
-//   k_rns_mvtab, k_rns_mv, k_rns_chain  fixed-base tables, rows and the join of
-//                 column chunks of the ciphertext matrix-vector product
+//   k_rns_mvtab, k_rns_mv, k_rns_mvblk, k_rns_chain  fixed-base tables, rows (with
+//                 constants whole, or in blocks) and the join of column chunks of
+//                 the ciphertext matrix-vector product
 //   k_rns_from    residues of base B -> the canonical integer mod N (sums on the
 //                 vector ALUs: 0.1 ms, its carries one wavefront's serial chain)
 //   k_rns_dec_finish, k_rns_garner_crt  the ends of decryption and of key-holder
@@ -411,6 +412,140 @@ __global__ __launch_bounds__(G::W * 64, 2) void k_rns_mv(RnsMv P) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   load_constants<G>(P.M, ws);
   PC2R_SIDES(G, wave, (mv_run<G, SIDE>(P, ws, wave, lane)));
+}
+
+// The same rows where the constants are taken in blocks of bits that share the
+// tables (RnsDigits), for plans made for few rows, whose tables have to be small:
+// item (column chunk, row group) starts from the Montgomery one, multiplies by the
+// entries of a block's digits over all its columns, squares the value once per bit
+// of a block and goes on with the next lower block.  The first chunk's value leaves
+// Montgomery form by a last product, with its alpha or 1.  One column block: with
+// two, the rows of a call are not few.  What bounds it is the chain of one item: a
+// chunk's products and, in every chunk, the squarings (50 of 50-bit constants less a
+// block's).  1000 columns made for one row, 2048 bits, tables / row: 0.16 / 1.8 ms
+// in 17 of the 32 KB a column; with all digits (8 of 6 to 7 bits, 1.1 MB a column)
+// 0.86 / 2.0; the same bytes on the VALU 3.1 / 9.4.
+template <class G, int SIDE>
+__device__ __forceinline__ void mvblk_run(const RnsMv& P, RWork<G>& ws, int wave, int lane) {
+  static_assert(G::NB == 1, "one column block");
+  constexpr size_t GB = 2 * (size_t)G::PART * 16;
+  constexpr size_t EB = (size_t)G::T * 64;
+  using OP = Gather<G, (G::MT <= 2)>;
+  Stepper<G, SIDE, OP> st(wave, lane);
+  const RConst<G> M(P.M);
+  const int n = lane & 31, h = lane >> 5;
+  const pc2k::RnsDigits D = P.dg;
+  const uint32_t col = D.entries() * (uint32_t)EB;
+  for (int it = blockIdx.x; it < P.ngroups * P.nch; it += gridDim.x) {
+    const int ch = it / P.ngroups, g = it % P.ngroups;
+    const Buf in(P.in + (size_t)it * GB, (uint32_t)GB), one(P.one, (uint32_t)EB);
+    const size_t j0 = (size_t)ch * P.chunk_cols;
+    const size_t j1 = j0 + P.chunk_cols < P.cols ? j0 + P.chunk_cols : P.cols;
+    const size_t i = (size_t)g * 32 + n;
+    const uint64_t* row = P.B + (i < P.rows ? i : P.rows - 1) * P.cols;
+    bool bad = false, begun = false;
+    uint64_t e = 0, en = row[j0];  // the constants of column j, and of j + 1 in flight
+    size_t j = j0 - 1;
+    int win = D.n - 1, blk = D.nblk - 1, squarings = 0;
+    bool close = ch == 0;
+    auto column = [&] {
+      e = en;
+      if (P.ebits < 64 && (e >> P.ebits) != 0) bad = true;
+      if (j + 1 < j1) en = row[j + 1];
+    };
+    // the next product's multiplier into o; false at the end
+    auto advance = [&](OP& o) -> bool {
+      for (;;) {
+        if (squarings) {
+          --squarings;
+          o.mul = false;
+          return true;
+        }
+        if (++win == D.n) {
+          win = 0;
+          if (++j == j1) {
+            j = j1 - 1;
+            win = D.n - 1;
+            if (blk > 0) {
+              --blk;
+              if (begun) squarings = D.bits();
+              j = j0;
+              win = -1;
+              en = row[j0];
+              column();
+              continue;
+            }
+            o.mul = close && begun;
+            if (!o.mul) return false;
+            close = false;
+            if (P.alpha) {
+              o.y = in;
+              o.ts = 1024;
+              o.ps = G::PART * 16;
+              o.offu = o.off[0] = lane * 16;
+            } else {
+              o.single(Buf(P.one + 2 * EB, (uint32_t)EB), lane);
+            }
+            return true;
+          }
+          column();
+        }
+        const uint32_t d =
+            (uint32_t)(e >> (blk * D.bits() + D.shift(win))) & ((1u << D.width(win)) - 1);
+        if (__ballot(d != 0) == 0) continue;
+        o.y = Buf(P.tab + j * (size_t)col, col);
+        o.offu = o.off[0] = (d ? D.before(win) + d : 0u) * (uint32_t)EB + h * 16;
+        o.ts = 32;
+        o.ps = G::T * 32;
+        o.mul = begun = true;
+        return true;
+      }
+    };
+    OP o, nx;
+    o.dst = nx.dst = in;
+    o.store = nx.store = false;
+    bool more = advance(nx);
+    if (more) {
+      st.load(
+          M, ws,
+          [&](int t, int, bool, v4u& x) {
+            x = one.load(h * 16, (G::T + t) * 32);
+            return one.load(h * 16, t * 32);
+          },
+          [&](int t, int, bool, const v4u&) {
+            return nx.y.load(nx.off[0], (G::T + t) * 32);
+          });
+    } else if (!(ch == 0 && P.alpha)) {  // every digit zero: 1, or the Montgomery one
+      const Buf s(P.one + (ch == 0 ? 2 * EB : 0), (uint32_t)EB);
+      st.each([&](int t, int b, bool) {
+        const uint32_t at = (t * G::NB + b) * 1024;
+        in.store(s.load(h * 16, t * 32), lane * 16, at);
+        in.store(s.load(h * 16, (G::T + t) * 32), lane * 16, G::PART * 16 + at);
+      });
+    }
+#pragma unroll 1
+    while (more) {
+      o.mul = nx.mul;
+      o.y = nx.y;
+      o.ts = nx.ts;
+      o.ps = nx.ps;
+      o.offu = nx.offu;
+      o.off[0] = nx.off[0];
+      more = advance(nx);
+      o.store = nx.store = !more;
+      st.product(M, ws, o, nx, false);
+    }
+    st.flush(M, ws);
+    if (wave == 0 && h == 0 && bad && i < P.rows) P.bad[i] = 1;
+  }
+}
+
+template <class G>
+__global__ __launch_bounds__(G::W * 64, 2) void k_rns_mvblk(RnsMv P) {
+  __shared__ __align__(16) RWork<G> ws;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  load_constants<G>(P.M, ws);
+  PC2R_SIDES(G, wave, (mvblk_run<G, SIDE>(P, ws, wave, lane)));
 }
 
 // The chunks' values of each row group multiplied together (base B of the
@@ -870,6 +1005,7 @@ const void* rns_gather_kernel(int t, int nb, int which) {
   }                                                                                       \
   if constexpr (G::NB == 1) {                                                             \
     if (which == RNS_MVTAB) return (const void*)&k_rns_mvtab<G>;                          \
+    if (which == RNS_MVBLK) return (const void*)&k_rns_mvblk<G>;                          \
   }                                                                                       \
   return nullptr
   PC2_RNS_GEOS(PC2_RNS_CASE)

@@ -30,7 +30,7 @@ hipError_t launch_rns_garner_crt(const SkConst& sk, const RnsJobs& jobs, const u
 
 // kernels with a multiplier per element (null if not compiled for (T, nb));
 // rns_pow_threads (not wide) threads; p: the kernel's argument (RnsSmul, RnsMvTab, RnsMv)
-enum { RNS_SMUL, RNS_MVTAB, RNS_MV, RNS_CHAIN, RNS_NGATHER };
+enum { RNS_SMUL, RNS_MVTAB, RNS_MV, RNS_MVBLK, RNS_CHAIN, RNS_NGATHER };
 const void* rns_gather_kernel(int T, int nb, int which);
 hipError_t launch_rns_gather(int T, int nb, int which, int grid, const void* p, void* stream);
 // bad[i] = x_i >= n2 (x null: 0); rows with bad[i] zeroed and ERR_RANGE latched

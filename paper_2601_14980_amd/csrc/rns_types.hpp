@@ -106,13 +106,19 @@ struct RnsSmul {         // c^k, k_rns_smul
   size_t count;
   int ngroups;
 };
-// A constant of the mat-vec in n digits, as even as its bits allow: the first x
-// of them lo + 1 bits wide, the others lo, which holds the smallest tables for a
-// number of digits.  A column's table is entry 0, the Montgomery one, for every
-// digit that is zero, and then each digit's entries 1 .. 2^width - 1.
+// A constant of the mat-vec, or (nblk > 1) a block of its bits, in n digits as even
+// as the bits allow: the first x of them lo + 1 bits wide, the others lo, which
+// holds the smallest tables for a number of digits.  A column's table is entry 0,
+// the Montgomery one, for every digit that is zero, and then each digit's entries 1
+// .. 2^width - 1.  The blocks share the table: a row takes them from the top, with a
+// squaring per bit of a block between two.
 struct RnsDigits {
-  int n, lo, x;
-  __host__ __device__ static RnsDigits of(int ebits, int n) { return {n, ebits / n, ebits % n}; }
+  int n, lo, x, nblk;
+  __host__ __device__ static RnsDigits of(int ebits, int n, int nblk) {
+    const int bits = (ebits + nblk - 1) / nblk;
+    return {n, bits / n, bits % n, nblk};
+  }
+  __host__ __device__ int bits() const { return lo * n + x; }  // of a block
   __host__ __device__ int wide(int t) const { return t < x ? t : x; }  // of the digits below t
   __host__ __device__ int width(int t) const { return lo + (t < x ? 1 : 0); }
   __host__ __device__ int shift(int t) const { return lo * t + wide(t); }

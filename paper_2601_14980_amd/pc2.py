@@ -115,7 +115,8 @@ def _load() -> ctypes.CDLL:
                                     c_size_t, P]),
         "pc2_matvec_create": (c_int, [P, c_size_t, c_uint32, c_uint32, c_size_t, POINTER(P)]),
         "pc2_matvec_info": (c_int, [P, POINTER(c_uint32), POINTER(c_size_t)]),
-        "pc2_matvec_engine": (c_int, [P, POINTER(c_int), POINTER(c_uint32), POINTER(c_size_t)]),
+        "pc2_matvec_engine": (c_int, [P, POINTER(c_int), POINTER(c_uint32), POINTER(c_uint32),
+                                      POINTER(c_size_t)]),
         "pc2_matvec_load": (c_int, [P, P, P]),
         "pc2_matvec_apply": (c_int, [P, P, P, P, c_size_t, P]),
         "pc2_matvec_destroy": (c_int, [P]),
@@ -420,10 +421,11 @@ class MatVec:
         _check(lib.pc2_matvec_info(h, byref(w), byref(nb)), "pc2_matvec_info")
         self.window = w.value
         self.table_bytes = nb.value
-        res, nd = c_int(), c_uint32()
-        _check(lib.pc2_matvec_engine(h, byref(res), byref(nd), byref(nb)), "pc2_matvec_engine")
+        res, nd, blk = c_int(), c_uint32(), c_uint32()
+        _check(lib.pc2_matvec_engine(h, byref(res), byref(nd), byref(blk), byref(nb)),
+               "pc2_matvec_engine")
         self.residues = bool(res.value)
-        self.digits = nd.value
+        self.digits, self.blocks = nd.value, blk.value
         self.staging_bytes = nb.value
 
     def load(self, c: torch.Tensor, stream=None) -> None:

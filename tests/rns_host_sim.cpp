@@ -78,10 +78,10 @@ int sim_from(const uint32_t* N0, int nn, const uint32_t* x0, int nx, int T, int 
 // (0: the compiled ones).
 int sim_bounds(int T, int mt) { return pc2h::make_rns_base(T, mt ? mt : pc2k::rns_mt(T)).ok; }
 
-// A constant's digits (RnsDigits): for each its shift, width, and the table entries
-// of its values 1 and 2^width - 1; returns the entries of a column.
-int sim_digits(int ebits, int n, int32_t* out) {
-  const pc2k::RnsDigits d = pc2k::RnsDigits::of(ebits, n);
+// The digits of a block of a constant (RnsDigits): for each its shift, width, and the
+// table entries of its values 1 and 2^width - 1; returns the entries of a column.
+int sim_digits(int ebits, int n, int nblk, int32_t* out) {
+  const pc2k::RnsDigits d = pc2k::RnsDigits::of(ebits, n, nblk);
   for (int t = 0; t < n; ++t) {
     out[4 * t] = d.shift(t);
     out[4 * t + 1] = d.width(t);

@@ -66,20 +66,24 @@ def test_output_conversion_of_short_moduli(lib, declared, bits):
             assert int.from_bytes(out.tobytes(), "little") == want
 
 
-# every split of every length that a mat-vec plan can take: the digits cover the
-# constant's bits once, and their entries a column's table behind entry 0
+# every split of every length that a mat-vec plan can take: the blocks cover the
+# constant's bits, the digits a block's bits once, and their entries a column's table
+# behind entry 0
 @pytest.mark.parametrize("ebits", range(1, 65))
 def test_matvec_digits(lib, ebits):
-    for n in range(-(-ebits // 12), ebits + 1):
-        out = np.zeros((n, 4), dtype=np.int32)
-        entries = lib.sim_digits(ebits, n, out.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)))
-        shift, at = 0, 1
-        for s, w, first, last in out.tolist():
-            assert s == shift and 1 <= w <= 12
-            assert first == at and last == at + (1 << w) - 2
-            shift, at = shift + w, last + 1
-        assert shift == ebits and at == entries
-        assert max(out[:, 1]) - min(out[:, 1]) <= 1
+    for nblk in range(1, ebits + 1):
+        bits = -(-ebits // nblk)
+        for n in range(-(-bits // 12), bits + 1):
+            out = np.zeros((n, 4), dtype=np.int32)
+            entries = lib.sim_digits(ebits, n, nblk,
+                                     out.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)))
+            shift, at = 0, 1
+            for s, w, first, last in out.tolist():
+                assert s == shift and 1 <= w <= 12
+                assert first == at and last == at + (1 << w) - 2
+                shift, at = shift + w, last + 1
+            assert shift == bits and at == entries
+            assert max(out[:, 1]) - min(out[:, 1]) <= 1
 
 
 # the compiled splits keep every 32-bit sum in range, and splits that would not are
